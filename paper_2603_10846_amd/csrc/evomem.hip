@@ -14,6 +14,7 @@
 #include "k_scan_gemv.h"
 #include "k_scan_mfma.h"
 #include "k_select.h"
+#include "k_exact.h"
 #include "k_rerank_big.h"
 #include "k_reward.h"
 #include "k_startpoint.h"
@@ -430,6 +431,30 @@ int launch_gemv(evomem* h, const Scratch& sc, hipStream_t st, int B, const Level
     return MEM_OK;
 }
 
+// One pass of the exhaustive selection.  Queries share a bank read in groups: of eight when there are more than
+// four, else of the smallest power of two that holds them (an unused slot would cost as much as a query).
+int launch_exact_scan(evomem* h, const Scratch& sc, hipStream_t st, int B, const Level& L) {
+    unsigned char* ws = sc.base;
+    const int64_t oct_units = ((int64_t)L.ntiles * (TILE_ROWS / EXACT_ROWS) + 7) / 8;    // row units per XCD
+    auto launch = [&](auto dt, auto nb) {
+        constexpr int DT = decltype(dt)::value, NB = decltype(nb)::value;
+        const int groups = (B + NB - 1) / NB;
+        int64_t walkers = 2048 / groups < 1 ? 1 : 2048 / groups;                           // per XCD; at most 16,384 workgroups or one per unit
+        if (walkers > oct_units) walkers = oct_units;
+        hipLaunchKernelGGL((k_exact_scan<DT, NB>), dim3((unsigned)(8 * walkers * groups)), dim3(256), 0, st, (const void*)h->store,
+                           (const float*)(ws + sc.w.qf), (const double*)(ws + sc.w.invq64), (uint64_t*)(ws + sc.w.surv),
+                           (uint32_t*)(ws + sc.w.cnt), (double*)(ws + sc.w.exact), sc.exact_stride, h->N, h->nkb, B, groups, L);
+    };
+    with_store_type(h->dtype, [&](auto dt) {
+        if (B == 1) launch(dt, std::integral_constant<int, 1>{});
+        else if (B == 2) launch(dt, std::integral_constant<int, 2>{});
+        else if (B <= 4) launch(dt, std::integral_constant<int, 4>{});
+        else launch(dt, std::integral_constant<int, EXACT_NB>{});
+    });
+    LAUNCHCHK();
+    return MEM_OK;
+}
+
 }  // namespace
 
 extern "C" int mem_plan_levels(int64_t N, int k1, int* stride, int* rho, int* ntiles, int max_levels) {
@@ -471,7 +496,7 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
 
     Plan plan{};
     uint32_t cnt0 = 0;      // valid rows of the sparsest pass (a prefix of its last tile may be all that exists)
-    if (h->N > 0 && !exhaustive) {
+    if (h->N > 0) {
         plan = plan_levels(h->N, k1);
         const Level& L0 = plan.lv[0];
         const int64_t last = level_tile(L0, L0.ntiles - 1) * TILE_ROWS;
@@ -495,24 +520,19 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     // 256 queries: see the kernel).
     const bool fused_tail = h->N > 0 && k1 <= 128 && B > 128 && !exhaustive;
     if (h->N > 0 && exhaustive) {
-        // every entry's similarity is accumulated in fp64; the bank is walked in ranges that fit a list
-        const int keep = keep_of(k1);
-        const int64_t range_rows = (int64_t)((SURV_CAP - keep) / TILE_ROWS) * TILE_ROWS;
-        int parts = 1;
-        while (parts < 64 && B * parts < 512) parts <<= 1;       // few queries: each query's range is shared by many workgroups
-        for (int64_t first = 0; first < h->N; first += range_rows) {
-            const int n_new = (int)(h->N - first < range_rows ? h->N - first : range_rows);
-            hipLaunchKernelGGL(k_exact_fill, dim3(B), dim3(256), 0, st, surv, cnt, (int32_t)first, n_new);
-            LAUNCHCHK();
-            dim3 kgrid((unsigned)B, (unsigned)parts);
-            with_store_type(h->dtype, [&](auto dt) {
-                hipLaunchKernelGGL(k_exact_keys<decltype(dt)::value>, kgrid, dim3(1024), 0, st, (const void*)h->store, (const float*)qf,
-                                   (const double*)invq64, surv, (const uint32_t*)cnt, h->nkb, n_new);
-            });
-            LAUNCHCHK();
-            hipLaunchKernelGGL(k_exact_select, dim3(B), dim3(1024), 0, st, surv, cnt, thr, (const float*)invq, counters, flags, k1, keep);
+        for (int li = 0; li < plan.n; ++li) {
+            const int rc = launch_exact_scan(h, sc, st, B, plan.lv[li]);
+            if (rc != MEM_OK) return rc;
+            hipLaunchKernelGGL(k_exact_select, dim3(B), dim3(1024), 0, st, surv, cnt, exact, exact_stride, k1, keep_of(k1));
             LAUNCHCHK();
         }
+        int parts = EXACT_WALK_PARTS;                            // a part's share of the query's slots holds a pool
+        while (SURV_CAP / parts < k1) parts >>= 1;
+        with_store_type(h->dtype, [&](auto dt) {
+            hipLaunchKernelGGL(k_exact_walk<decltype(dt)::value>, dim3((unsigned)B, (unsigned)parts), dim3(1024), 0, st, (const void*)h->store,
+                               (const float*)qf, (const double*)invq64, surv, cnt, exact, exact_stride, h->N, h->nkb, k1, keep_of(k1));
+        });
+        LAUNCHCHK();
     }
     if (h->N > 0 && !exhaustive) {
         for (int li = 0; li < plan.n; ++li) {

@@ -108,19 +108,6 @@ __device__ __forceinline__ float only_non_negative(const f32x16_t& v) {
     return __uint_as_float((uint32_t)max(max3(t0, t1, t2), max3(t3, t4, bits(15))));
 }
 
-// Inclusive prefix sum over the 64 lanes of a wavefront (all lanes active): shifts within rows of 16
-// lanes, then the row broadcasts.  Lane 63 ends up with the total.
-__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
-    int v = (int)x;
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);   // row_bcast:15 into rows 1 and 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);   // row_bcast:31 into rows 2 and 3
-    return (uint32_t)v;
-}
-
 constexpr int STAGE_BANK_BYTES = TILE_ROWS * 128;
 constexpr int SCAN_LIST_CAP = 2048;     // survivor entries a workgroup can stage per tile
 

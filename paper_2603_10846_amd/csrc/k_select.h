@@ -43,145 +43,170 @@ __device__ __forceinline__ uint32_t wave_or_u32(uint32_t x) {
     return (uint32_t)v;
 }
 
-// After a scan pass, for one query: find the k1-th best survivor key (similarity desc, id asc) by
-// an MSB-first radix select over the packed 64-bit keys, set the next pass's threshold to that
-// similarity minus `margin` (a bound on the scan's fp32 rounding error, so that no true member of
-// the pool can be filtered out; pre-divided by the query's inverse norm because the scan compares
-// before applying it), and compact every key whose similarity reaches that threshold to the head of
-// the list: these seed the next pass and, after the last pass, are the candidates that get re-scored
-// in fp64.  Nothing is sorted here -- slot order is irrelevant to every consumer.
-// Keys live in registers (8 per lane, 1024 lanes); the passes start at the highest bit on which two
-// keys differ; each builds per-wavefront digit histograms in LDS, sums them, and one wavefront
-// picks the digit by a suffix scan.
+// Sum over the workgroup's 16 wavefronts of one value per lane, and the sum over the lanes before this one.
+// `part` has 16 slots; ends without a barrier (the caller's next barrier protects `part`).
+__device__ __forceinline__ uint32_t group_prefix_u32(uint32_t x, uint32_t* part, int wave, int lane, uint32_t& total) {
+    const uint32_t incl = wave_inclusive_sum(x);
+    if (lane == 63) part[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        const uint32_t p = part[w];
+        before += w < wave ? p : 0u;
+        all += p;
+    }
+    total = all;
+    return before + incl - x;
+}
+
+// After a scan pass, for one query: find the k1-th best survivor key (similarity desc, id asc), set the
+// next pass's threshold to that similarity minus `margin` (a bound on the scan's fp32 rounding error, so
+// that no true member of the pool can be filtered out; pre-divided by the query's inverse norm because the
+// scan compares before applying it), and keep every key whose similarity reaches that threshold: these
+// seed the next pass and, after the last pass, are the candidates that get re-scored in fp64.  Nothing is
+// sorted here -- slot order is irrelevant to every consumer.
+// Keys live in registers (8 per lane, 1024 lanes).  The kernel is a chain of barriers and LDS round trips
+// with one workgroup per query, so what counts is how many there are: a digit has 11 bits and starts at the
+// highest bit on which two keys differ (the survivors of a filtering pass lie in a narrow band of
+// similarities, so the leading 12-20 bits of their keys are the same), after which the pivot's bin nearly always holds
+// no more than SEL_SMALL keys and those few are ranked by counting instead of by further digits; the keys that
+// stay are placed by prefix sums, not by one atomic each.  One query over 8192 keys that differ from the
+// top bit on: 10.3 us with 8-bit digits and per-key atomics, 7.4 us now; a filtered list of 2000: 6.6 us, 5.4 us.
 // A list that overflowed during the pass (more than SURV_CAP rows reached the threshold; the surplus was
 // dropped) is counted and the query is flagged: its pool may then miss members.
 // More than keep_max keys inside the margin ("crowded band"; near-duplicate entries do that):
 //   SEL_PASS   (between scan passes) every key of the band is kept -- any of them may belong to the pool;
-//   SEL_FINAL  (after the last pass) likewise, and the function returns true: the caller replaces the
-//              keys' similarities by exactly accumulated ones (rescore_one_query<DT, true>) and selects
-//              again with a margin of two fp32 roundings;
+//   SEL_FINAL  (after the last pass) likewise, and the caller replaces the keys' similarities by exactly
+//              accumulated ones (rescore_one_query<DT, true>) and selects again with a margin of two
+//              fp32 roundings;
 //   SEL_EXACT  (that second selection) a band that is still crowded can only be one of ties within
 //              fp32 resolution: the k1 best keys are kept, lower ids first among equal similarities.
 enum { SEL_PASS = 0, SEL_FINAL = 1, SEL_EXACT = 2 };
-__device__ __forceinline__ bool select_one_query(const int b, uint64_t* surv, uint32_t* cnt,
-                                                 float* thr, const float* invq, uint32_t* counters, uint32_t* flags,
-                                                 int k1, float margin, int may_have_empty, int keep_max, int mode) {
-    __shared__ uint32_t hist[16][256];
-    __shared__ uint32_t tot[256];
-    __shared__ uint64_t pivot_s, or_s[16];
-    __shared__ uint32_t sel_digit, sel_need, sel_single, band_s, nout_s;
+constexpr int SEL_DIGIT = 11, SEL_BINS = 1 << SEL_DIGIT;
+constexpr int SEL_SMALL = 128;
+struct SelectLds {
+    uint32_t hist[SEL_BINS];
+    uint64_t small[SEL_SMALL];
+    uint64_t differ[16], pivot;
+    uint32_t part_a[16], part_b[16], digit, need, count, nsmall;
+};
+struct Selected {
+    uint64_t key[8];     // this lane's keys (0 = none)
+    uint64_t cut;        // a key stays iff it is not 0 and not below this
+    float tau;           // the threshold that this is (similarity units); meaningless with keep_all
+    uint32_t kept;       // how many stay
+    uint32_t slot;       // this lane's first slot among them (its keys take consecutive slots)
+    bool keep_all;       // fewer keys than the pool has members: all stay and there is no threshold
+    bool crowded;
+};
+__device__ __forceinline__ void select_keys(const uint64_t* list, int n, int k1, float margin, bool may_have_empty, int keep_max,
+                                            int mode, SelectLds& sh, Selected& s) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    uint64_t* list = surv + (int64_t)b * SURV_CAP;
-    const uint32_t raw = cnt[b];
-    const int n = raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw;
-    if (raw > (uint32_t)SURV_CAP && tid == 0) { atomicAdd(counters + 1, 1u); flags[b] |= 1u; }
-    if (!may_have_empty && n < k1) {    // fewer rows than the pool size: keep them all, no threshold
-        if (tid == 0) { cnt[b] = (uint32_t)n; thr[b] = -2.0f / invq[b]; }   // finite floor, see k_prep_queries
-        return false;
-    }
-    uint64_t key[8];
+    uint64_t (&key)[8] = s.key;
+    uint64_t ref = 0ull;                              // any one key, see the digits below
 #pragma unroll
     for (int i = 0; i < 8; ++i) { int idx = i * 1024 + tid; key[i] = idx < n ? list[idx] : 0ull; }   // 0 = empty
-    const uint64_t ref = n > 0 ? list[0] : 0ull;      // any one key (or an empty slot), see the radix passes
-    if (tid == 0) { band_s = 0; nout_s = 0; }
-    if (may_have_empty) {               // uniform
-        // A masked sparsest pass leaves the slots of rows the query does not accept empty (key 0): if
-        // fewer than k1 slots are in use, keep those (compacted to the head of the list), no threshold.
-        uint32_t used = 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) used += key[i] != 0;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) used += __shfl_xor(used, o, 64);
-        __syncthreads();
-        if (lane == 0 && used) atomicAdd(&band_s, used);
-        __syncthreads();
-        if (band_s < (uint32_t)k1) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (key[i] != 0) list[atomicAdd(&nout_s, 1u)] = key[i];
-            __syncthreads();
-            if (tid == 0) { cnt[b] = nout_s; thr[b] = -2.0f / invq[b]; }
-            return false;
-        }
-        __syncthreads();
-        if (tid == 0) band_s = 0;
-        __syncthreads();
-    }
-    // Bits that all keys share need no pass: the survivors of a filtering pass lie in a narrow band
-    // of similarities, so the leading 12-20 bits of their keys are the same, and a pass over such
-    // bits would also send every key to one histogram bin (same-address LDS atomics serialise).
-    // (the bits on which some key differs from the list's first key, OR-ed over the workgroup)
-    uint64_t differ = 0ull;
+    if (n > 0) ref = list[0];
+    for (int i = tid; i < SEL_BINS; i += 1024) sh.hist[i] = 0;
+    if (tid == 0) sh.nsmall = 0;
+    uint32_t used = 0;
+    uint64_t differ = 0ull;                           // the bits on which some key differs from the list's first
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-        if (key[i] != 0) differ |= key[i] ^ ref;
+        if (key[i] != 0) { differ |= key[i] ^ ref; ++used; }
     differ = ((uint64_t)wave_or_u32((uint32_t)(differ >> 32)) << 32) | wave_or_u32((uint32_t)differ);
-    if (lane == 63) or_s[wave] = differ;
-    for (int i = tid; i < 16 * 256; i += 1024) (&hist[0][0])[i] = 0;
-    __syncthreads();
+    if (lane == 63) sh.differ[wave] = differ;
+    uint32_t total;
+    const uint32_t first = group_prefix_u32(used, sh.part_a, wave, lane, total);      // (has the barrier)
+    s.crowded = false;
+    s.keep_all = may_have_empty ? total < (uint32_t)k1 : n < k1;      // uniform
+    if (s.keep_all) { s.cut = 1ull; s.tau = 0.f; s.kept = total; s.slot = first; return; }
     differ = 0ull;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) differ |= or_s[w];               // 0 only if there is a single key
-    int hi = differ ? 63 - __builtin_clzll(differ) : 7;           // highest bit on which two keys differ
+    for (int w = 0; w < 16; ++w) differ |= sh.differ[w];               // 0 only if there is a single key
+    int hi = differ ? 63 - __builtin_clzll(differ) : SEL_DIGIT - 1;    // highest bit on which two keys differ
     uint64_t prefix = hi < 63 ? (ref >> (hi + 1)) << (hi + 1) : 0ull, pivot = 0;
     uint32_t need = (uint32_t)k1;
     for (;;) {
-        const int shift = hi >= 7 ? hi - 7 : 0;               // this pass ranks bits hi .. shift
+        const int shift = hi >= SEL_DIGIT - 1 ? hi - (SEL_DIGIT - 1) : 0;   // this round ranks bits hi .. shift
         const uint32_t dmask = (1u << (hi - shift + 1)) - 1u;
+        // bins in descending order of the digit, so that the search for the pivot's bin is a prefix sum
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             if (key[i] != 0 && (hi == 63 || (key[i] >> (hi + 1)) == (prefix >> (hi + 1))))
-                atomicAdd(&hist[wave][(uint32_t)(key[i] >> shift) & dmask], 1u);
+                atomicAdd(&sh.hist[SEL_BINS - 1 - ((uint32_t)(key[i] >> shift) & dmask)], 1u);
         __syncthreads();
-        if (tid < 256) {
-            uint32_t sum = 0;
-#pragma unroll
-            for (int w = 0; w < 16; ++w) { sum += hist[w][tid]; hist[w][tid] = 0; }   // cleared for the next pass
-            tot[tid] = sum;
+        const uint32_t c0 = sh.hist[2 * tid], c1 = sh.hist[2 * tid + 1];
+        sh.hist[2 * tid] = 0; sh.hist[2 * tid + 1] = 0;                      // cleared for the next round
+        uint32_t all;
+        const uint32_t run = group_prefix_u32(c0 + c1, sh.part_b, wave, lane, all);
+        if (run < need && run + c0 + c1 >= need) {                           // exactly one lane
+            const bool second = run + c0 < need;
+            sh.digit = SEL_BINS - 1 - (uint32_t)(2 * tid + second);
+            sh.need = need - run - (second ? c0 : 0u);
+            sh.count = second ? c1 : c0;
         }
         __syncthreads();
-        if (wave == 0) {                // lane l owns digits 4l .. 4l+3; larger digit = better key
-            uint32_t c[4] = {tot[4 * lane], tot[4 * lane + 1], tot[4 * lane + 2], tot[4 * lane + 3]};
-            uint32_t local = c[0] + c[1] + c[2] + c[3], incl = local;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) { uint32_t t = __shfl_down(incl, o, 64); if (lane + o < 64) incl += t; }
-            uint32_t run = incl - local;            // keys with a digit in a higher lane
-#pragma unroll
-            for (int k = 3; k >= 0; --k) {
-                if (run < need && run + c[k] >= need) { sel_digit = 4 * lane + k; sel_need = need - run; sel_single = c[k] == 1; }
-                run += c[k];
-            }
-        }
-        __syncthreads();
-        prefix |= (uint64_t)sel_digit << shift;
-        need = sel_need;
-        if (sel_single || shift == 0) {             // one key left under this prefix: it is the k1-th best
+        prefix |= (uint64_t)sh.digit << shift;
+        need = sh.need;
+        const uint32_t in_bin = sh.count;
+        if (shift == 0) { pivot = prefix; break; }                           // all 64 bits are known
+        if (in_bin <= (uint32_t)SEL_SMALL) {                                 // uniform
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                if (key[i] != 0 && (key[i] >> shift) == (prefix >> shift)) pivot_s = key[i];
+                if (key[i] != 0 && (key[i] >> shift) == (prefix >> shift)) sh.small[atomicAdd(&sh.nsmall, 1u)] = key[i];
             __syncthreads();
-            pivot = pivot_s;
+            if ((uint32_t)tid < in_bin) {
+                const uint64_t mine = sh.small[tid];
+                uint32_t rank = 0;
+#pragma unroll 8
+                for (uint32_t j = 0; j < in_bin; ++j) rank += sh.small[j] > mine;
+                if (rank == need - 1) sh.pivot = mine;                       // keys are distinct
+            }
+            __syncthreads();
+            pivot = sh.pivot;
             break;
         }
         hi = shift - 1;
     }
-    const float tau = key_sim(pivot) - margin;
-    uint64_t cutkey = (uint64_t)f2ord(tau) << 32;   // every key with similarity >= tau compares >= cutkey
-    uint32_t mine = 0;
+    s.tau = key_sim(pivot) - margin;
+    s.cut = (uint64_t)f2ord(s.tau) << 32;           // every key with similarity >= tau compares >= cut
+    for (int again = 0;; ++again) {
+        uint32_t mine = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) mine += key[i] != 0 && key[i] >= cutkey;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
-    if (lane == 0 && mine) atomicAdd(&band_s, mine);
-    __syncthreads();
-    const bool crowded = band_s > (uint32_t)keep_max;   // uniform
-    if (crowded && mode == SEL_EXACT) cutkey = pivot;   // ties within fp32 resolution: exactly the k1 best
+        for (int i = 0; i < 8; ++i) mine += key[i] != 0 && key[i] >= s.cut;
+        s.slot = group_prefix_u32(mine, again ? sh.part_b : sh.part_a, wave, lane, s.kept);
+        if (again || s.kept <= (uint32_t)keep_max) break;                    // uniform
+        s.crowded = true;
+        if (mode != SEL_EXACT) break;
+        s.cut = pivot;                              // ties within fp32 resolution: exactly the k1 best
+    }
+}
+
+// As above, the kept keys going to the head of the query's list.  Returns whether the band is crowded and
+// the caller has to refine it (SEL_FINAL).
+__device__ __forceinline__ bool select_one_query(const int b, uint64_t* surv, uint32_t* cnt,
+                                                 float* thr, const float* invq, uint32_t* counters, uint32_t* flags,
+                                                 int k1, float margin, int may_have_empty, int keep_max, int mode) {
+    __shared__ SelectLds sh;
+    const int tid = threadIdx.x;
+    uint64_t* list = surv + (int64_t)b * SURV_CAP;
+    const uint32_t raw = cnt[b];
+    const int n = raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw;
+    if (raw > (uint32_t)SURV_CAP && tid == 0) { atomicAdd(counters + 1, 1u); flags[b] |= 1u; }
+    Selected s;
+    select_keys(list, n, k1, margin, may_have_empty != 0, keep_max, mode, sh, s);
+    // (every lane has read its keys and cnt: there was a barrier since)
+    uint32_t at = s.slot;
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-        if (key[i] != 0 && key[i] >= cutkey) list[atomicAdd(&nout_s, 1u)] = key[i];
-    __syncthreads();
-    if (tid == 0) { cnt[b] = nout_s; thr[b] = tau / invq[b]; }
-    return crowded && mode == SEL_FINAL;
+        if (s.key[i] != 0 && s.key[i] >= s.cut) list[at++] = s.key[i];
+    if (tid == 0) {
+        cnt[b] = s.kept;
+        thr[b] = (s.keep_all ? -2.0f : s.tau) / invq[b];      // no threshold: a finite floor, see k_prep_queries
+    }
+    return s.crowded && mode == SEL_FINAL;
 }
 
 __global__ __launch_bounds__(1024) void k_select(uint64_t* __restrict__ surv, uint32_t* __restrict__ cnt,
@@ -191,76 +216,86 @@ __global__ __launch_bounds__(1024) void k_select(uint64_t* __restrict__ surv, ui
     select_one_query((int)blockIdx.x, surv, cnt, thr, invq, counters, flags, k1, margin, may_have_empty, keep_max, SEL_PASS);
 }
 
-// Exact similarities of the selected candidates: one wavefront per (query, candidate) re-reads the
-// stored row and accumulates dot product and squared norm in fp64 (products of 16-bit values are
-// exact, so this is the cosine of the stored vectors up to fp64 rounding).
-// REQUANT: instead of storing the fp64 similarity, the candidate's key is rewritten with it (rounded to
-// fp32: resolution 6e-8), for a second selection over a crowded band.
+// Products of one stored row with one query, accumulated in fp64 by 16 neighbouring lanes (lane `sub` of them
+// takes every 16th 16-byte chunk, up to eight loads in flight); every lane gets the sums.  Products of 16-bit
+// values are exact, so dot / sqrt(ssq) is the cosine of the stored vectors up to fp64 rounding.
+template <int DT>
+__device__ __forceinline__ void row_products(const void* store_, const float* q, int32_t id, bool live, int sub, int nkb, double& dot,
+                                             double& ssq) {
+    constexpr int EPC = DT == 0 ? 4 : 8;                 // elements per 16-byte chunk
+    const int nch = nkb * KB / EPC;                      // chunks per row
+    dot = 0.0;
+    ssq = 0.0;
+    for (int c0 = sub; c0 < nch; c0 += 16 * 8) {
+        uint4 pk[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int c = c0 + 16 * u;
+            pk[u] = make_uint4(0, 0, 0, 0);
+            if (live && c < nch) {
+                if (DT == 0) pk[u] = *reinterpret_cast<const uint4*>(static_cast<const float*>(store_) + off32(id, c, nkb));
+                else pk[u] = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(store_) + off16(id, c, nkb));
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int c = c0 + 16 * u;
+            if (c >= nch) break;
+            const uint32_t w[4] = {pk[u].x, pk[u].y, pk[u].z, pk[u].w};
+            if (DT == 0) {
+                const float4 y = *reinterpret_cast<const float4*>(q + c * 4);
+                const float yy[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { double x = __uint_as_float(w[i]); dot += x * (double)yy[i]; ssq += x * x; }
+            } else {
+                const float4 y0 = *reinterpret_cast<const float4*>(q + c * 8), y1 = *reinterpret_cast<const float4*>(q + c * 8 + 4);
+                const float yy[8] = {y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint16_t lo = (uint16_t)(w[i] & 0xffff), hi = (uint16_t)(w[i] >> 16);
+                    const double x0 = DT == 1 ? bf16_to_f(lo) : f16_to_f(lo);
+                    const double x1 = DT == 1 ? bf16_to_f(hi) : f16_to_f(hi);
+                    dot += x0 * (double)yy[2 * i] + x1 * (double)yy[2 * i + 1];
+                    ssq += x0 * x0 + x1 * x1;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) { dot += __shfl_xor(dot, o, 64); ssq += __shfl_xor(ssq, o, 64); }
+}
+
+// The key of a similarity accumulated in fp64, rounded to fp32 (resolution 6e-8); NaN ranks lowest.
+__device__ __forceinline__ uint64_t exact_key(double sim, int32_t id) { return pack_key(sim == sim ? (float)sim : -INFINITY, id); }
+
+// Exact similarities of the selected candidates: 16 lanes per candidate row, so a wavefront works on four rows
+// at a time.  REQUANT: instead of storing the fp64 similarity, the candidate's key is rewritten with it,
+// for a second selection over a crowded band.
 template <int DT, bool REQUANT = false>
 __device__ __forceinline__ void rescore_one_query(const int b, const int part, const int parts,
                                                   const void* store_, const float* qf,
                                                   const double* invq64, std::conditional_t<REQUANT, uint64_t, const uint64_t>* surv,
                                                   const uint32_t* cnt, double* exact,
-                                                  int nkb, int exact_stride, int begin = 0) {
-    // One workgroup per query; 16 lanes per candidate row, so a wavefront works on four rows at a
-    // time and every lane has up to eight 16-byte loads in flight.
+                                                  int nkb, int exact_stride) {
     const int sub = threadIdx.x & 15, grp = threadIdx.x >> 4;   // grp 0..63
     const int n = (int)cnt[b];
     const float* q = qf + (int64_t)b * nkb * KB;
-    constexpr int EPC = DT == 0 ? 4 : 8;                 // elements per 16-byte chunk
-    const int nch = nkb * KB / EPC;                      // chunks per row
     // (`parts` workgroups share a query: workgroup `part` takes the candidate groups part, part + parts, ...)
-    for (int j0 = begin + 64 * part; j0 < n; j0 += 64 * parts) {   // uniform trip count: the shuffles below need all lanes
+    for (int j0 = 64 * part; j0 < n; j0 += 64 * parts) {   // uniform trip count: the shuffles need all lanes
         const int j = j0 + grp;
         const bool live = j < n;
         const int32_t id = live ? key_id(surv[(int64_t)b * SURV_CAP + j]) : 0;
-        double dot = 0.0, ssq = 0.0;
-        for (int c0 = sub; c0 < nch; c0 += 16 * 8) {
-            uint4 pk[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int c = c0 + 16 * u;
-                pk[u] = make_uint4(0, 0, 0, 0);
-                if (live && c < nch) {
-                    if (DT == 0) pk[u] = *reinterpret_cast<const uint4*>(static_cast<const float*>(store_) + off32(id, c, nkb));
-                    else pk[u] = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(store_) + off16(id, c, nkb));
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int c = c0 + 16 * u;
-                if (c >= nch) break;
-                const uint32_t w[4] = {pk[u].x, pk[u].y, pk[u].z, pk[u].w};
-                if (DT == 0) {
-                    const float4 y = *reinterpret_cast<const float4*>(q + c * 4);
-                    const float yy[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) { double x = __uint_as_float(w[i]); dot += x * (double)yy[i]; ssq += x * x; }
-                } else {
-                    const float4 y0 = *reinterpret_cast<const float4*>(q + c * 8), y1 = *reinterpret_cast<const float4*>(q + c * 8 + 4);
-                    const float yy[8] = {y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint16_t lo = (uint16_t)(w[i] & 0xffff), hi = (uint16_t)(w[i] >> 16);
-                        const double x0 = DT == 1 ? bf16_to_f(lo) : f16_to_f(lo);
-                        const double x1 = DT == 1 ? bf16_to_f(hi) : f16_to_f(hi);
-                        dot += x0 * (double)yy[2 * i] + x1 * (double)yy[2 * i + 1];
-                        ssq += x0 * x0 + x1 * x1;
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) { dot += __shfl_xor(dot, o, 64); ssq += __shfl_xor(ssq, o, 64); }
+        double dot, ssq;
+        row_products<DT>(store_, q, id, live, sub, nkb, dot, ssq);
         if (live && sub == 0) {
             const double sim = dot * invq64[b] * (1.0 / sqrt(ssq));
-            if constexpr (REQUANT) surv[(int64_t)b * SURV_CAP + j] = pack_key(sim == sim ? (float)sim : -INFINITY, id);
+            if constexpr (REQUANT) surv[(int64_t)b * SURV_CAP + j] = exact_key(sim, id);
             else exact[(int64_t)b * exact_stride + j] = sim;
         }
     }
 }
 
-// The selection after the last scan pass, with the refinement of a crowded band (see select_one_query).
+// The selection after the last scan pass, with the refinement of a crowded band (see select_keys).
 constexpr float EXACT_KEY_MARGIN = 2.4e-7f;     // two fp32 roundings of a similarity of magnitude <= 1
 template <int DT>
 __device__ __forceinline__ void select_final_one_query(const int b, uint64_t* surv, uint32_t* cnt, float* thr,
@@ -293,35 +328,6 @@ __global__ __launch_bounds__(1024) void k_rescore(const void* __restrict__ store
                                                   const uint32_t* __restrict__ cnt, double* __restrict__ exact,
                                                   int nkb, int exact_stride) {
     rescore_one_query<DT>((int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y, store_, qf, invq64, surv, cnt, exact, nkb, exact_stride);
-}
-
-// ---- exhaustive selection (mem_retrieve_exact): no threshold, no scan, no list that can overflow ----
-// The bank is walked in ranges small enough that the carried candidates plus every row of the range fit
-// a survivor list.  Per range: (1) the range's ids are appended to every query's list, (2) each appended
-// entry gets its key from the similarity accumulated in fp64 (rounded to fp32), (3) the list is cut back to
-// the k1 best keys plus those within two fp32 roundings of the k1-th (or, if that band is crowded, to
-// exactly the k1 best: lower ids first among equal similarities).  The top-k1 of a union is the top-k1 of
-// the parts' top-k1, so after the last range the list holds the pool.
-__global__ __launch_bounds__(256) void k_exact_fill(uint64_t* __restrict__ surv, uint32_t* __restrict__ cnt, int32_t first_id, int n_new) {
-    const int b = (int)blockIdx.x;
-    const uint32_t have = cnt[b];
-    __syncthreads();                                    // every lane has read the old count
-    for (int i = threadIdx.x; i < n_new; i += 256) surv[(int64_t)b * SURV_CAP + have + i] = pack_key(0.f, first_id + i);
-    if (threadIdx.x == 0) cnt[b] = have + (uint32_t)n_new;
-}
-
-template <int DT>
-__global__ __launch_bounds__(1024) void k_exact_keys(const void* __restrict__ store_, const float* __restrict__ qf,
-                                                     const double* __restrict__ invq64, uint64_t* __restrict__ surv,
-                                                     const uint32_t* __restrict__ cnt, int nkb, int n_new) {
-    const int b = (int)blockIdx.x;
-    rescore_one_query<DT, true>(b, (int)blockIdx.y, (int)gridDim.y, store_, qf, invq64, surv, cnt, nullptr, nkb, 0, (int)cnt[b] - n_new);
-}
-
-__global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ surv, uint32_t* __restrict__ cnt, float* __restrict__ thr,
-                                                       const float* __restrict__ invq, uint32_t* __restrict__ counters,
-                                                       uint32_t* __restrict__ flags, int k1, int keep_max) {
-    select_one_query((int)blockIdx.x, surv, cnt, thr, invq, counters, flags, k1, EXACT_KEY_MARGIN, 0, keep_max, SEL_EXACT);
 }
 
 constexpr int RERANK_T = 256;

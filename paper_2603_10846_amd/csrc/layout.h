@@ -77,6 +77,19 @@ __device__ __forceinline__ uint64_t pack_key(float sim, int32_t id) {
 __device__ __forceinline__ int32_t key_id(uint64_t k) { return (int32_t)(0xffffffffu - (uint32_t)k); }
 __device__ __forceinline__ float key_sim(uint64_t k) { return ord2f((uint32_t)(k >> 32)); }
 
+// Inclusive prefix sum over the 64 lanes of a wavefront (all lanes active): shifts within rows of 16
+// lanes, then the row broadcasts.  Lane 63 ends up with the total.
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
+    int v = (int)x;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);   // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);   // row_bcast:31 into rows 2 and 3
+    return (uint32_t)v;
+}
+
 // ---- element conversion, round-to-nearest-even ----
 __device__ __forceinline__ uint16_t f2bf16_rne(float x) {
     uint32_t u = __float_as_uint(x);

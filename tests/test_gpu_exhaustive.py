@@ -1,0 +1,88 @@
+"""Exhaustive selection: group sizes and tile edges of its scan, and the queries whose list overflows in a
+pass (they walk the bank by themselves), against the oracle."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_10846_amd import binding as B
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+DT = {"f32": 0, "bf16": 1, "f16": 2}
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def _unit(rng, n, d):
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    return (x / np.linalg.norm(x, axis=1, keepdims=True)).astype(np.float32)
+
+
+def _exact(bank, q, stage, k1, k2, lam):
+    out = bank.retrieve_exact(_dev(q), stage, k1, k2, lam, want_candidates=True)
+    torch.cuda.synchronize()
+    return dict(zip(("ids", "scores", "cand_ids", "cand_sims"), (t.cpu().numpy() for t in out)))
+
+
+# every group size (1, 2, 4, 8 queries per bank read; the last group partly filled), odd and even numbers of
+# k-blocks, banks that end at, just before and just after a tile, one pass and several, pools up to the largest
+@pytest.mark.parametrize("dtype,N,d,nq,k1", [
+    ("bf16", 257, 64, 1, 8), ("f16", 20000, 192, 2, 256), ("f32", 8449, 136, 3, 33), ("bf16", 30001, 320, 4, 64),
+    ("f16", 8192, 64, 5, 100), ("f32", 20000, 64, 9, 300), ("bf16", 12287, 128, 17, 2048)])
+def test_groups_and_edges(orc, dtype, N, d, nq, k1):
+    rng = np.random.default_rng([31, N, nq])
+    rows = _unit(rng, N, d) * rng.uniform(0.5, 2.0, (N, 1)).astype(np.float32)
+    rows[N - 1] = rows[3]                                            # an exact tie, one copy in the last row
+    q = _unit(rng, nq, d)
+    q[nq - 1] = rows[3]
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    print(f"exhaustive {dtype} N={N} d={d} B={nq} k1={k1}", flush=True)
+    bank = B.MemoryBank(d, dtype, N, max_B=nq, max_k1=k1)
+    bank.append(_dev(rows), _dev(qtab[0]), _dev(qtab[1]))
+    ex = _exact(bank, q, 1, k1, min(8, k1), 0.5)
+    stats = parity.check_retrieve(orc, orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype]), qtab[1], k1, min(8, k1), 0.5, ex)
+    assert stats["boundary_swaps"] == 0 and stats["final_swaps"] == 0
+    assert ex["cand_ids"][nq - 1, 0] == 3 and ex["cand_ids"][nq - 1, 1] == N - 1
+    assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    bank.close()
+
+
+@pytest.mark.parametrize("dtype,k1,nq", [("bf16", 64, 3), ("f32", 300, 2), ("f16", 2048, 9)])
+def test_lost_queries_walk_the_bank(orc, dtype, k1, nq):
+    """Near rows stand only in tiles that the sparser passes leave out, more of them than a list holds: their
+    query's list overflows in the last pass, and its pool is still the oracle's (up to the resolution of an
+    fp32 similarity, by which the selection ranks)."""
+    rng = np.random.default_rng([32, k1])
+    N, d = 40000, 64
+    lib = B.load()
+    st_, rh_, nt_ = (C.c_int * 16)(), (C.c_int * 16)(), (C.c_int * 16)()
+    n = lib.mem_plan_levels(N, k1, st_, rh_, nt_, 16)
+    assert n >= 2
+    tiles = np.arange((N + 255) // 256)
+    rows = _unit(rng, N, d)
+    v = _unit(rng, 1, d)
+    free = np.flatnonzero(np.isin(np.arange(N) // 256, tiles[tiles % st_[n - 2] != 0]))   # rows only the last pass meets
+    near = rng.choice(free, 9000, replace=False)
+    assert near.size > 8192
+    rows[near] = v + 0.3 * _unit(rng, near.size, d) * rng.uniform(0.2, 1.0, (near.size, 1)).astype(np.float32)
+    q = _unit(rng, nq, d)
+    q[1] = v[0]
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    print(f"lost query {dtype} k1={k1}", flush=True)
+    bank = B.MemoryBank(d, dtype, N, max_B=nq, max_k1=k1)
+    bank.append(_dev(rows), _dev(qtab[0]), _dev(qtab[1]))
+    stored, qr = orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype])
+    ids, sims = orc.recall(stored, qr, k1, threads=8)
+    for _ in range(2):                                               # the second call starts from the first one's leftovers
+        ex = _exact(bank, q, 0, k1, 8, 0.5)
+        for b in range(nq):
+            only = sorted(set(ex["cand_ids"][b].tolist()) - set(ids[b].tolist()))
+            if only:
+                assert np.all(orc.sims_of(stored, qr[b], np.array(only, np.int32)) > sims[b, k1 - 1] - 3e-7)
+        parity.check_retrieve(orc, stored, qr, qtab[0], k1, 8, 0.5, ex, ora_recall=(ids, sims))
+        assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    bank.close()
