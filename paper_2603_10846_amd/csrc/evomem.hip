@@ -15,7 +15,7 @@
 #include "k_scan_mfma.h"
 #include "k_select.h"
 #include "k_exact.h"
-#include "k_rerank_big.h"
+#include "k_tail.h"
 #include "k_reward.h"
 #include "k_startpoint.h"
 #include "k_update.h"
@@ -515,24 +515,23 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     if (!gemv) eps += 2e-5f;                             // threshold * norm carried as 16-bit hi/lo pairs
     const float margin = 2.f * eps;
 
-    // Pools of up to 128 with one workgroup per query in the gather (more than 128 queries): the last
-    // selection, the re-scoring and the value filter run as one launch (measured on the 1M x 1024 bank at
-    // 256 queries: see the kernel).
-    const bool fused_tail = h->N > 0 && k1 <= 128 && B > 128 && !exhaustive;
     if (h->N > 0 && exhaustive) {
         for (int li = 0; li < plan.n; ++li) {
             const int rc = launch_exact_scan(h, sc, st, B, plan.lv[li]);
             if (rc != MEM_OK) return rc;
+            if (li == plan.n - 1) break;
             hipLaunchKernelGGL(k_exact_select, dim3(B), dim3(1024), 0, st, surv, cnt, exact, exact_stride, k1, keep_of(k1));
             LAUNCHCHK();
         }
-        int parts = EXACT_WALK_PARTS;                            // a part's share of the query's slots holds a pool
-        while (SURV_CAP / parts < k1) parts >>= 1;
-        with_store_type(h->dtype, [&](auto dt) {
-            hipLaunchKernelGGL(k_exact_walk<decltype(dt)::value>, dim3((unsigned)B, (unsigned)parts), dim3(1024), 0, st, (const void*)h->store,
-                               (const float*)qf, (const double*)invq64, surv, cnt, exact, exact_stride, h->N, h->nkb, k1, keep_of(k1));
-        });
-        LAUNCHCHK();
+        if (plan.n > 1) {                                            // (a single pass never overflows)
+            int parts = EXACT_WALK_PARTS;                            // a part's share of the query's slots holds a pool
+            while (SURV_CAP / parts < k1) parts >>= 1;
+            with_store_type(h->dtype, [&](auto dt) {
+                hipLaunchKernelGGL(k_exact_walk<decltype(dt)::value>, dim3((unsigned)B, (unsigned)parts), dim3(1024), 0, st, (const void*)h->store,
+                                   (const float*)qf, (const double*)invq64, surv, cnt, exact, exact_stride, h->N, h->nkb, k1, keep_of(k1));
+            });
+            LAUNCHCHK();
+        }
     }
     if (h->N > 0 && !exhaustive) {
         for (int li = 0; li < plan.n; ++li) {
@@ -555,63 +554,43 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
                 int64_t rows = (int64_t)L.ntiles * TILE_ROWS;
                 h->prof_rows[h->prof_n++] = rows;
             }
-            if (li == plan.n - 1) {
-                if (fused_tail) break;                              // the last selection runs inside the fused kernel below
-                // the last selection refines a crowded band with exactly accumulated similarities
-                with_store_type(h->dtype, [&](auto dt) {
-                    hipLaunchKernelGGL(k_select_final<decltype(dt)::value>, dim3(B), dim3(1024), 0, st, surv, cnt, thr, (const float*)invq,
-                                       counters, flags, k1, margin, mask.tags != nullptr, keep_of(k1), (const void*)h->store,
-                                       (const float*)qf, (const double*)invq64, h->nkb);
-                });
-            } else {
-                hipLaunchKernelGGL(k_select, dim3(B), dim3(1024), 0, st, surv, cnt, thr, (const float*)invq, counters, flags, k1, margin,
-                                   mask.tags != nullptr, keep_of(k1));
-            }
+            if (li == plan.n - 1) break;                                // the last selection is the tail's
+            hipLaunchKernelGGL(k_select, dim3(B), dim3(1024), 0, st, surv, cnt, thr, (const float*)invq, counters, flags, k1, margin,
+                               mask.tags != nullptr, keep_of(k1));
             LAUNCHCHK();
         }
-        if (fused_tail) {
-            const float* qs = (const float*)(h->q + (int64_t)stage * h->capacity);
-            with_store_type(h->dtype, [&](auto dt) {
-                hipLaunchKernelGGL(k_select_rescore_rerank<decltype(dt)::value>, dim3(B), dim3(1024), 0, st, surv, cnt, thr,
-                                   (const float*)invq, counters, flags, k1, margin, mask.tags != nullptr, keep_of(k1),
-                                   (const void*)h->store, (const float*)qf, (const double*)invq64, exact, h->nkb, exact_stride, qs, k2,
-                                   (double)lambda, out_ids_dev, out_scores_dev, out_cand_ids_dev, out_cand_sims_dev, eg);
-            });
-            LAUNCHCHK();
-            return MEM_OK;
-        }
     }
-    if (h->N > 0) {
-        // a query's candidates are split over several workgroups when there are few queries, so that the
-        // gather occupies the whole device
-        // (measured: 151 -> 102 us at B = 128, d = 4096; no gain at B = 256)
-        int rsplit = 1;
-        while (B <= 128 && rsplit < 8 && B * rsplit < 512) rsplit <<= 1;
-        dim3 rgrid((unsigned)B, (unsigned)rsplit);
-        with_store_type(h->dtype, [&](auto dt) {
-            hipLaunchKernelGGL(k_rescore<decltype(dt)::value>, rgrid, dim3(1024), 0, st, (const void*)h->store, (const float*)qf,
-                               (const double*)invq64, (const uint64_t*)surv, (const uint32_t*)cnt, exact, h->nkb, exact_stride);
-        });
-        LAUNCHCHK();
-    }
-    if (k1 <= 128) {                       // counting ranks is quadratic: measured faster than sorting up to here
-        hipLaunchKernelGGL(k_rerank, dim3(B), dim3(RERANK_T), 0, st, (const uint64_t*)surv, (const uint32_t*)cnt, (const double*)exact,
-                           (const float*)(h->q + (int64_t)stage * h->capacity), k1, k2, (double)lambda, out_ids_dev, out_scores_dev,
-                           out_cand_ids_dev, out_cand_sims_dev, eg, exact_stride);
-    } else {                               // larger pools: sorts instead of counting ranks
-        int cap = 2;
-        while (cap < keep_of(k1)) cap <<= 1;
-        const size_t lds = rerank_big_lds(cap, k1, k2);
+    // Few queries: a query's candidates are shared by several workgroups, as long as that leaves a compute unit to each
+    // and more than 96 KB of rows to gather.  Measured with 1, 2, 4 and 8: one query, 128 x 2 KB 26.5, 23.0, 18.7, 18.1 us;
+    // 64 queries, 64 x 4 KB 32.8, 24.1, 23.6, 38.2; 128 queries, 256 x 8 KB 163, 116, 146, 152; 64 queries, 960 x 2 KB 135, 87, 66,
+    // 74; one query, 32 x 3 KB 14.9, 16.0, 16.3, 16.3.
+    TailArgs ta{};
+    ta.surv = surv; ta.cnt = cnt; ta.counters = counters; ta.flags = flags;
+    ta.arrived = reinterpret_cast<uint32_t*>(qop + (int64_t)(h->dtype == MEM_F32 ? 2 * h->nkb : h->nkb) * Bp * KB);
+    ta.store = h->store; ta.qf = qf; ta.invq64 = invq64; ta.exact = exact; ta.qstage = h->q + (int64_t)stage * h->capacity;
+    ta.out_ids = out_ids_dev; ta.out_scores = out_scores_dev; ta.cand_ids = out_cand_ids_dev; ta.cand_sims = out_cand_sims_dev;
+    ta.lambda = (double)lambda; ta.nkb = h->nkb; ta.exact_stride = exact_stride; ta.k1 = k1; ta.k2 = k2;
+    ta.may_have_empty = mask.tags != nullptr; ta.mode = exhaustive ? SEL_EXACT : SEL_FINAL; ta.margin = exhaustive ? EXACT_KEY_MARGIN : margin;
+    const int64_t gather = (int64_t)k1 * h->nkb * KB * (h->dtype == MEM_F32 ? 4 : 2);
+    int parts = 1;
+    while (parts < 8 && B * parts * 2 <= 256 && gather / parts > 96 * 1024) parts <<= 1;
+    const bool big = k1 > SMALL_K1_MAX;
+    if (big) {
         static bool lds_set[MAX_DEVICES] = {};
         if (!lds_set[h->device]) {
-            HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_rerank_big), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)rerank_big_lds(4096, BIG_K1_MAX, BIG_K1_MAX)));
+            bool ok = true;
+            for (const void* k : {reinterpret_cast<const void*>(k_tail<0, true>), reinterpret_cast<const void*>(k_tail<1, true>), reinterpret_cast<const void*>(k_tail<2, true>)})
+                ok = ok && hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)tail_lds(BIG_K1_MAX)) == hipSuccess;
+            if (!ok) return MEM_EHIP;
             lds_set[h->device] = true;
         }
-        hipLaunchKernelGGL(k_rerank_big, dim3(B), dim3(BIG_T), lds, st, (const uint64_t*)surv, (const uint32_t*)cnt,
-                           (const double*)exact, exact_stride, (const float*)(h->q + (int64_t)stage * h->capacity), k1, k2,
-                           (double)lambda, cap, out_ids_dev, out_scores_dev, out_cand_ids_dev, out_cand_sims_dev, eg);
     }
+    with_store_type(h->dtype, [&](auto dt) {
+        constexpr int DT = decltype(dt)::value;
+        const dim3 grid((unsigned)B, (unsigned)parts), block(TAIL_T);
+        if (big) hipLaunchKernelGGL((k_tail<DT, true>), grid, block, tail_lds(k1), st, ta, eg);
+        else hipLaunchKernelGGL((k_tail<DT, false>), grid, block, tail_lds(k1), st, ta, eg);
+    });
     LAUNCHCHK();
     return MEM_OK;
 }

@@ -8,7 +8,7 @@
 // best).  The top-k1 of a union is the top-k1 of the parts' top-k1, so after the last pass the list holds the
 // pool.  There is no error margin in a cut, and ties break by id as in the pool itself, so masses of equal
 // rows pass a cut no more often than distinct rows do.  A list can still overflow when a pass meets thousands of
-// rows that beat everything in the sparser passes (the bank's order decides); such a query is marked lost, takes
+// rows that beat everything in the sparser passes (the bank's order decides); such a query is lost, takes
 // part in no further pass, and walks the whole bank by itself afterwards (k_exact_walk), range by range with
 // lists that cannot overflow.
 //
@@ -16,13 +16,13 @@
 // entries (411 launches), 0.49 ms now, of which the last pass is 0.38 ms for 2.0 GB: bound by fp64 multiply-adds and
 // conversions as much as by HBM (fetching two steps ahead instead of one changed nothing).
 #pragma once
+#include "k_ingest.h"
 #include "k_select.h"
 
 namespace evk {
 
 constexpr int EXACT_NB = 8;               // queries per bank read, at most
 constexpr int EXACT_ROWS = 64;            // rows a workgroup scores at a time: 16 lanes per row, 4 rows per lane group
-constexpr uint32_t EXACT_LOST = 0xffffffffu;     // count of a query whose list overflowed
 constexpr int EXACT_WALK_PARTS = 64;      // workgroups of a lost query, at most
 
 // Per-query words of the exhaustive selection, in the space of the query's fp64 similarities (which are
@@ -30,16 +30,6 @@ constexpr int EXACT_WALK_PARTS = 64;      // workgroups of a lost query, at most
 __device__ __forceinline__ uint64_t* exact_words(double* exact, int b, int exact_stride) {
     return reinterpret_cast<uint64_t*>(exact + (int64_t)b * exact_stride);
 }
-
-// x + (x of the lane that is N places further round in its row of 16 lanes)
-template <int N>
-__device__ __forceinline__ double add_row_ror(double x) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + N, 0xf, 0xf, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + N, 0xf, 0xf, true);
-    return x + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double row16_sum(double x) { return add_row_ror<1>(add_row_ror<2>(add_row_ror<4>(add_row_ror<8>(x)))); }
 
 // Products of four neighbouring rows r0 .. r0 + 3 of bank tile t with NB queries, accumulated in fp64 by a lane
 // group of 16: a lane takes one 16-byte chunk of each row per step (its offset within a k-block is fixed, so a
@@ -168,27 +158,21 @@ __global__ __launch_bounds__(256, NB > 4 ? 2 : 3) void k_exact_scan(const void* 
     }
 }
 
-// After a pass: the list cut back, the cut of the next pass.
+// Between two passes: the list cut back, the cut of the next pass.  (After the last one the tail selects.)
 __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ surv, uint32_t* __restrict__ cnt, double* __restrict__ exact,
                                                        int exact_stride, int k1, int keep_max) {
     __shared__ SelectLds sh;
     const int b = (int)blockIdx.x, tid = threadIdx.x;
     uint64_t* list = surv + (int64_t)b * SURV_CAP;
     uint64_t* words = exact_words(exact, b, exact_stride);
-    const uint32_t raw = cnt[b];
-    if (raw == EXACT_LOST) return;
-    __syncthreads();                                // every lane has read the old count
-    if (raw > (uint32_t)SURV_CAP) {                 // no key reaches this cut, so the count stays as it is
-        if (tid == 0) { cnt[b] = EXACT_LOST; words[0] = ~0ull; words[1] = 0ull; }
+    Selected s;
+    const uint32_t raw = select_keys(list, cnt + b, k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, sh, s);
+    if (raw > (uint32_t)SURV_CAP) {                 // lost: no key reaches this cut, so the count stays as it is
+        if (tid == 0) words[0] = ~0ull;
         return;
     }
-    Selected s;
-    select_keys(list, (int)raw, k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, sh, s);
-    uint32_t at = s.slot;
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        if (s.key[i] != 0 && s.key[i] >= s.cut) list[at++] = s.key[i];
-    if (tid == 0) { cnt[b] = s.kept; words[0] = s.cut; }
+    store_kept(s, list);
+    if (tid == 0) { cnt[b] = s.kept; words[0] = s.cut; words[1] = 0ull; }
 }
 
 // The lost queries: gridDim.y workgroups each walk a part of the bank, a tile at a time, with a list in LDS of
@@ -204,7 +188,7 @@ __global__ __launch_bounds__(1024) void k_exact_walk(const void* __restrict__ st
                                                      uint32_t* __restrict__ cnt, double* __restrict__ exact, int exact_stride,
                                                      int64_t N, int nkb, int k1, int keep_max) {
     const int b = (int)blockIdx.x, part = (int)blockIdx.y, parts = (int)gridDim.y, tid = threadIdx.x;
-    if (cnt[b] != EXACT_LOST) return;               // uniform over the query's workgroups: written only below, by the last of them
+    if (cnt[b] <= (uint32_t)SURV_CAP) return;       // uniform over the query's workgroups: written only below, by the last of them
     __shared__ uint64_t keys[WALK_CAP];
     __shared__ uint32_t n_s, last_s;
     __shared__ SelectLds sh;
@@ -247,11 +231,10 @@ __global__ __launch_bounds__(1024) void k_exact_walk(const void* __restrict__ st
     if (!last_s) return;                            // uniform
     __threadfence();
     Selected s;
-    select_keys(list, SURV_CAP, k1, EXACT_KEY_MARGIN, true, keep_max, SEL_EXACT, sh, s);
-    uint32_t at = s.slot;
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        if (s.key[i] != 0 && s.key[i] >= s.cut) list[at++] = s.key[i];
+    if (tid == 0) last_s = SURV_CAP;
+    __syncthreads();
+    select_keys(list, &last_s, k1, EXACT_KEY_MARGIN, true, keep_max, SEL_EXACT, sh, s);
+    store_kept(s, list);
     if (tid == 0) cnt[b] = s.kept;
 }
 

@@ -9,10 +9,26 @@ __device__ __forceinline__ float wave_sum_f(float v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+
+// x + (x of the lane that is N places further round in its row of 16 lanes)
+template <int N>
+__device__ __forceinline__ double add_row_ror(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + N, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + N, 0xf, 0xf, true);
+    return x + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double row16_sum(double x) { return add_row_ror<1>(add_row_ror<2>(add_row_ror<4>(add_row_ror<8>(x)))); }
+
+// Sum over the 64 lanes of a wavefront (all lanes active), the same in every lane: within rows of 16 lanes by
+// rotations, then the four rows' sums.
+__device__ __forceinline__ double wave_total_d(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, row16_sum(x));
+    auto row = [&](int lane) __attribute__((always_inline)) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+        return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    };
+    return (row(0) + row(16)) + (row(32) + row(48));
 }
 
 // Memory growth rule of Sec. 3.1: entry first_id + row gets embedding emb[row], rounded to the
@@ -200,8 +216,9 @@ __global__ __launch_bounds__(256) void k_prep_queries(const float* __restrict__ 
         *reinterpret_cast<float4*>(o + 4) = make_float4(v[4], v[5], v[6], v[7]);
     }
     // one all-zero k-block behind the last one: the MFMA scan pairs it with a repeated bank block
-    // when it pads an odd number of k-steps to an even one
-    if (DT != 0 && tid < 8) *reinterpret_cast<uint4*>(qop + ((int64_t)nkb * Bpad + b) * KB + tid * 8) = make_uint4(0, 0, 0, 0);
+    // when it pads an odd number of k-steps to an even one, and after the last pass its words count the
+    // workgroups of the tail
+    if (tid < 8) *reinterpret_cast<uint4*>(qop + ((int64_t)(DT == 0 ? 2 * nkb : nkb) * Bpad + b) * KB + tid * 8) = make_uint4(0, 0, 0, 0);
     red[tid] = ssq;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) { if (tid < s) red[tid] += red[tid + s]; __syncthreads(); }

@@ -78,8 +78,7 @@ __device__ __forceinline__ uint32_t group_prefix_u32(uint32_t x, uint32_t* part,
 // More than keep_max keys inside the margin ("crowded band"; near-duplicate entries do that):
 //   SEL_PASS   (between scan passes) every key of the band is kept -- any of them may belong to the pool;
 //   SEL_FINAL  (after the last pass) likewise, and the caller replaces the keys' similarities by exactly
-//              accumulated ones (rescore_one_query<DT, true>) and selects again with a margin of two
-//              fp32 roundings;
+//              accumulated ones and selects again with a margin of two fp32 roundings;
 //   SEL_EXACT  (that second selection) a band that is still crowded can only be one of ties within
 //              fp32 resolution: the k1 best keys are kept, lower ids first among equal similarities.
 enum { SEL_PASS = 0, SEL_FINAL = 1, SEL_EXACT = 2 };
@@ -100,14 +99,22 @@ struct Selected {
     bool keep_all;       // fewer keys than the pool has members: all stay and there is no threshold
     bool crowded;
 };
-__device__ __forceinline__ void select_keys(const uint64_t* list, int n, int k1, float margin, bool may_have_empty, int keep_max,
-                                            int mode, SelectLds& sh, Selected& s) {
+// Returns the list's count as the scan left it (it may exceed the list's size).  The count and the first quarter of
+// the list, which is what a filtering pass fills, are requested together.
+__device__ __forceinline__ uint32_t select_keys(const uint64_t* list, const uint32_t* count, int k1, float margin, bool may_have_empty,
+                                                int keep_max, int mode, SelectLds& sh, Selected& s) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     uint64_t (&key)[8] = s.key;
-    uint64_t ref = 0ull;                              // any one key, see the digits below
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { int idx = i * 1024 + tid; key[i] = idx < n ? list[idx] : 0ull; }   // 0 = empty
-    if (n > 0) ref = list[0];
+    for (int i = 0; i < 2; ++i) key[i] = list[i * 1024 + tid];
+    uint64_t ref = list[0];                           // any one key, see the digits below
+    const uint32_t raw = *count;
+    const int n = raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw;
+#pragma unroll
+    for (int i = 2; i < 8; ++i) { int idx = i * 1024 + tid; key[i] = idx < n ? list[idx] : 0ull; }   // 0 = empty
+#pragma unroll
+    for (int i = 0; i < 2; ++i) key[i] = i * 1024 + tid < n ? key[i] : 0ull;
+    if (n == 0) ref = 0ull;
     for (int i = tid; i < SEL_BINS; i += 1024) sh.hist[i] = 0;
     if (tid == 0) sh.nsmall = 0;
     uint32_t used = 0;
@@ -121,7 +128,7 @@ __device__ __forceinline__ void select_keys(const uint64_t* list, int n, int k1,
     const uint32_t first = group_prefix_u32(used, sh.part_a, wave, lane, total);      // (has the barrier)
     s.crowded = false;
     s.keep_all = may_have_empty ? total < (uint32_t)k1 : n < k1;      // uniform
-    if (s.keep_all) { s.cut = 1ull; s.tau = 0.f; s.kept = total; s.slot = first; return; }
+    if (s.keep_all) { s.cut = 1ull; s.tau = 0.f; s.kept = total; s.slot = first; return raw; }
     differ = 0ull;
 #pragma unroll
     for (int w = 0; w < 16; ++w) differ |= sh.differ[w];               // 0 only if there is a single key
@@ -182,38 +189,33 @@ __device__ __forceinline__ void select_keys(const uint64_t* list, int n, int k1,
         if (mode != SEL_EXACT) break;
         s.cut = pivot;                              // ties within fp32 resolution: exactly the k1 best
     }
+    return raw;
 }
 
-// As above, the kept keys going to the head of the query's list.  Returns whether the band is crowded and
-// the caller has to refine it (SEL_FINAL).
-__device__ __forceinline__ bool select_one_query(const int b, uint64_t* surv, uint32_t* cnt,
-                                                 float* thr, const float* invq, uint32_t* counters, uint32_t* flags,
-                                                 int k1, float margin, int may_have_empty, int keep_max, int mode) {
-    __shared__ SelectLds sh;
-    const int tid = threadIdx.x;
-    uint64_t* list = surv + (int64_t)b * SURV_CAP;
-    const uint32_t raw = cnt[b];
-    const int n = raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw;
-    if (raw > (uint32_t)SURV_CAP && tid == 0) { atomicAdd(counters + 1, 1u); flags[b] |= 1u; }
-    Selected s;
-    select_keys(list, n, k1, margin, may_have_empty != 0, keep_max, mode, sh, s);
-    // (every lane has read its keys and cnt: there was a barrier since)
+// The kept keys of a selection to the head of a list (the keys were read before a barrier inside the selection).
+__device__ __forceinline__ void store_kept(const Selected& s, uint64_t* list) {
     uint32_t at = s.slot;
 #pragma unroll
     for (int i = 0; i < 8; ++i)
         if (s.key[i] != 0 && s.key[i] >= s.cut) list[at++] = s.key[i];
-    if (tid == 0) {
-        cnt[b] = s.kept;
-        thr[b] = (s.keep_all ? -2.0f : s.tau) / invq[b];      // no threshold: a finite floor, see k_prep_queries
-    }
-    return s.crowded && mode == SEL_FINAL;
 }
 
+// Between two scan passes: one workgroup per query.
 __global__ __launch_bounds__(1024) void k_select(uint64_t* __restrict__ surv, uint32_t* __restrict__ cnt,
                                                  float* __restrict__ thr, const float* __restrict__ invq,
                                                  uint32_t* __restrict__ counters, uint32_t* __restrict__ flags, int k1, float margin,
                                                  int may_have_empty, int keep_max) {
-    select_one_query((int)blockIdx.x, surv, cnt, thr, invq, counters, flags, k1, margin, may_have_empty, keep_max, SEL_PASS);
+    __shared__ SelectLds sh;
+    const int b = (int)blockIdx.x, tid = threadIdx.x;
+    uint64_t* list = surv + (int64_t)b * SURV_CAP;
+    Selected s;
+    const uint32_t raw = select_keys(list, cnt + b, k1, margin, may_have_empty != 0, keep_max, SEL_PASS, sh, s);
+    if (raw > (uint32_t)SURV_CAP && tid == 0) { atomicAdd(counters + 1, 1u); flags[b] |= 1u; }
+    store_kept(s, list);                            // (every lane has also read the count by now)
+    if (tid == 0) {
+        cnt[b] = s.kept;
+        thr[b] = (s.keep_all ? -2.0f : s.tau) / invq[b];      // no threshold: a finite floor, see k_prep_queries
+    }
 }
 
 // Products of one stored row with one query, accumulated in fp64 by 16 neighbouring lanes (lane `sub` of them
@@ -268,69 +270,7 @@ __device__ __forceinline__ void row_products(const void* store_, const float* q,
 // The key of a similarity accumulated in fp64, rounded to fp32 (resolution 6e-8); NaN ranks lowest.
 __device__ __forceinline__ uint64_t exact_key(double sim, int32_t id) { return pack_key(sim == sim ? (float)sim : -INFINITY, id); }
 
-// Exact similarities of the selected candidates: 16 lanes per candidate row, so a wavefront works on four rows
-// at a time.  REQUANT: instead of storing the fp64 similarity, the candidate's key is rewritten with it,
-// for a second selection over a crowded band.
-template <int DT, bool REQUANT = false>
-__device__ __forceinline__ void rescore_one_query(const int b, const int part, const int parts,
-                                                  const void* store_, const float* qf,
-                                                  const double* invq64, std::conditional_t<REQUANT, uint64_t, const uint64_t>* surv,
-                                                  const uint32_t* cnt, double* exact,
-                                                  int nkb, int exact_stride) {
-    const int sub = threadIdx.x & 15, grp = threadIdx.x >> 4;   // grp 0..63
-    const int n = (int)cnt[b];
-    const float* q = qf + (int64_t)b * nkb * KB;
-    // (`parts` workgroups share a query: workgroup `part` takes the candidate groups part, part + parts, ...)
-    for (int j0 = 64 * part; j0 < n; j0 += 64 * parts) {   // uniform trip count: the shuffles need all lanes
-        const int j = j0 + grp;
-        const bool live = j < n;
-        const int32_t id = live ? key_id(surv[(int64_t)b * SURV_CAP + j]) : 0;
-        double dot, ssq;
-        row_products<DT>(store_, q, id, live, sub, nkb, dot, ssq);
-        if (live && sub == 0) {
-            const double sim = dot * invq64[b] * (1.0 / sqrt(ssq));
-            if constexpr (REQUANT) surv[(int64_t)b * SURV_CAP + j] = exact_key(sim, id);
-            else exact[(int64_t)b * exact_stride + j] = sim;
-        }
-    }
-}
-
-// The selection after the last scan pass, with the refinement of a crowded band (see select_keys).
 constexpr float EXACT_KEY_MARGIN = 2.4e-7f;     // two fp32 roundings of a similarity of magnitude <= 1
-template <int DT>
-__device__ __forceinline__ void select_final_one_query(const int b, uint64_t* surv, uint32_t* cnt, float* thr,
-                                                       const float* invq, uint32_t* counters, uint32_t* flags, int k1,
-                                                       float margin, int may_have_empty, int keep_max,
-                                                       const void* store_, const float* qf, const double* invq64, int nkb) {
-    const bool crowded = select_one_query(b, surv, cnt, thr, invq, counters, flags, k1, margin, may_have_empty, keep_max, SEL_FINAL);
-    __syncthreads();
-    if (crowded) {                                  // uniform
-        rescore_one_query<DT, true>(b, 0, 1, store_, qf, invq64, surv, cnt, nullptr, nkb, 0);
-        __syncthreads();
-        select_one_query(b, surv, cnt, thr, invq, counters, flags, k1, EXACT_KEY_MARGIN, may_have_empty, keep_max, SEL_EXACT);
-        __syncthreads();
-    }
-}
-
-template <int DT>
-__global__ __launch_bounds__(1024) void k_select_final(uint64_t* __restrict__ surv, uint32_t* __restrict__ cnt, float* __restrict__ thr,
-                                                       const float* __restrict__ invq, uint32_t* __restrict__ counters,
-                                                       uint32_t* __restrict__ flags, int k1, float margin, int may_have_empty,
-                                                       int keep_max, const void* __restrict__ store_, const float* __restrict__ qf,
-                                                       const double* __restrict__ invq64, int nkb) {
-    select_final_one_query<DT>((int)blockIdx.x, surv, cnt, thr, invq, counters, flags, k1, margin, may_have_empty, keep_max,
-                               store_, qf, invq64, nkb);
-}
-
-template <int DT>
-__global__ __launch_bounds__(1024) void k_rescore(const void* __restrict__ store_, const float* __restrict__ qf,
-                                                  const double* __restrict__ invq64, const uint64_t* __restrict__ surv,
-                                                  const uint32_t* __restrict__ cnt, double* __restrict__ exact,
-                                                  int nkb, int exact_stride) {
-    rescore_one_query<DT>((int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y, store_, qf, invq64, surv, cnt, exact, nkb, exact_stride);
-}
-
-constexpr int RERANK_T = 256;
 
 // One block of the Philox-4x32 counter-based generator with 10 rounds (Salmon et al., SC'11): each
 // round multiplies counter words 0 and 2 by fixed odd constants, crosses the high and low halves
@@ -359,183 +299,5 @@ struct EpsGreedy {
     uint64_t seed, step;
     unsigned char* explored; // [B][k2] or null
 };
-
-// Deterministic sum of one value per pool entry: wavefront butterflies, then the four partial sums of
-// the first 256 lanes added in a fixed order.  `red` has four slots; pool entry i belongs to lane
-// i < SMALL_K1_MAX = 256, so the lanes beyond (the fused kernel runs 1024) hold zeros and store nothing.
-__device__ __forceinline__ double block_sum(double* red, int tid, double x) {
-    static_assert(SMALL_K1_MAX == 4 * 64, "block_sum adds the partial sums of exactly four wavefronts");
-    x = wave_sum_d(x);
-    if ((tid & 63) == 0 && tid < SMALL_K1_MAX) red[tid >> 6] = x;
-    __syncthreads();
-    double r = (red[0] + red[1]) + (red[2] + red[3]);
-    __syncthreads();
-    return r;
-}
-
-// A NaN similarity or score (a zero-norm or non-finite row or query, a NaN in the Q table: inputs
-// for which the results are unspecified) is ranked as -inf, so that the orderings below stay total
-// orders: every rank is taken exactly once and every id that is gathered with is a real one.
-__device__ __forceinline__ double finite_or_lowest(double v) { return v == v ? v : -INFINITY; }
-
-// (v, id) before (w, jd)?  Written without short-circuit operators: inside the counting loops below
-// the arguments come from LDS, and a short-circuit form compiles to a branch per element with the
-// second LDS read behind it, so that every element pays two LDS round trips (measured: 200 cycles
-// per element, 36 us for a 128-entry pool); this form lets the reads of an unrolled group go out together.
-__device__ __forceinline__ bool ranks_before(double v, int32_t id, double w, int32_t jd) {
-    return (bool)((int)(v > w) | ((int)(v == w) & (int)(id < jd)));
-}
-
-// Candidate pool and value filter for one query (Sec. 3.2): order the re-scored candidates by
-// (similarity desc, id asc), keep k1 as the pool C(x); gather the stage's Q values; z-score both
-// over the pool (population deviation, denominator std + 1e-6); score = (1-lambda) z_s + lambda z_q;
-// emit the k2 best by (score desc, id asc).  All in fp64, scores rounded to fp32 on output.
-// The lists are short (at most 512 and 256 entries), so both orderings are done by counting: every
-// thread counts how many entries precede its own (each step reads one LDS entry, broadcast to all
-// lanes) and writes its entry to that rank -- two barriers instead of a sorting network.
-// T: lanes of the workgroup that runs it (256, or 1024 inside the fused kernel below; pool entry i belongs
-// to lane i either way, and the block sums add the same four partial sums in the same order).
-template <int T>
-__device__ __forceinline__ void rerank_one_query(const int b, const uint64_t* surv, const uint32_t* cnt,
-                                                const double* exact, const float* qstage,
-                                                int k1, int k2, double lambda, int32_t* out_ids,
-                                                float* out_scores, int32_t* cand_ids,
-                                                float* cand_sims, EpsGreedy eg, int exact_stride) {
-    __shared__ double v0[KEEP_MAX], v1[SMALL_K1_MAX];
-    __shared__ int32_t i0[KEEP_MAX], i1[SMALL_K1_MAX];
-    __shared__ double red[4];
-    const int tid = threadIdx.x;
-    const int kk = (int)cnt[b];
-    for (int i = tid; i < kk; i += T) {
-        v0[i] = finite_or_lowest(exact[(int64_t)b * exact_stride + i]);
-        i0[i] = key_id(surv[(int64_t)b * SURV_CAP + i]);
-    }
-    __syncthreads();
-    const int k1e = kk < k1 ? kk : k1;
-    // ordering 1: the k1e best by (similarity desc, id asc) -> (v1, i1)
-    // (SPLIT lanes share an entry when the workgroup has lanes to spare: each counts over every
-    // SPLIT-th other entry and the partial counts are added across the neighbouring lanes)
-    constexpr int SPLIT = T >= 1024 ? 4 : 1;
-    for (int i = tid / SPLIT; i < kk; i += T / SPLIT) {           // trip count uniform within a lane group
-        const double v = v0[i];
-        const int32_t id = i0[i];
-        int rank = 0;
-#pragma unroll 8
-        for (int j = tid % SPLIT; j < kk; j += SPLIT) rank += ranks_before(v0[j], i0[j], v, id);
-        if (SPLIT == 4) { rank += __shfl_xor(rank, 1, 64); rank += __shfl_xor(rank, 2, 64); }
-        if (tid % SPLIT == 0 && rank < k1e) { v1[rank] = v; i1[rank] = id; }
-    }
-    __syncthreads();
-    if (cand_ids)
-        for (int i = tid; i < k1; i += T) {
-            cand_ids[(int64_t)b * k1 + i] = i < k1e ? i1[i] : -1;
-            cand_sims[(int64_t)b * k1 + i] = i < k1e ? (float)v1[i] : -INFINITY;
-        }
-    // z-scores over the pool (one pool entry per thread, k1e <= 256)
-    const bool mine = tid < k1e;
-    const double sim = mine ? v1[tid] : 0.0;
-    const int32_t id = mine ? i1[tid] : 0x7fffffff;
-    const double qv = mine ? (double)qstage[id] : 0.0;
-    double score = -INFINITY;
-    if (k1e > 0) {                                                    // uniform
-        const double mean_s = block_sum(red, tid, sim) / k1e;
-        const double mean_q = block_sum(red, tid, qv) / k1e;
-        const double ds = mine ? sim - mean_s : 0.0, dq = mine ? qv - mean_q : 0.0;
-        const double var_s = block_sum(red, tid, ds * ds) / k1e;
-        const double var_q = block_sum(red, tid, dq * dq) / k1e;
-        const double scale_s = 1.0 / (sqrt(var_s) + 1e-6), scale_q = 1.0 / (sqrt(var_q) + 1e-6);
-        if (mine) score = finite_or_lowest((1.0 - lambda) * (ds * scale_s) + lambda * (dq * scale_q));
-    }
-    __syncthreads();
-    // ordering 2: the k2 best by (score desc, id asc); v0/i0 are reused for the scores
-    if (mine) { v0[tid] = score; i0[tid] = id; }
-    __syncthreads();
-    const int k2e = k1e < k2 ? k1e : k2;
-    const bool greedy = eg.threshold == 0 && eg.explored == nullptr;
-    int rank = 0;
-    if (mine) {
-#pragma unroll 8
-        for (int j = 0; j < k1e; ++j) rank += ranks_before(v0[j], i0[j], score, id);
-        if (greedy && rank < k2e) { out_ids[(int64_t)b * k2 + rank] = id; out_scores[(int64_t)b * k2 + rank] = (float)score; }
-    }
-    for (int i = k2e + tid; i < k2; i += T) {
-        out_ids[(int64_t)b * k2 + i] = -1;
-        out_scores[(int64_t)b * k2 + i] = -INFINITY;
-        if (eg.explored) eg.explored[(int64_t)b * k2 + i] = 0;
-    }
-    if (greedy) return;                                               // uniform
-
-    // Epsilon-greedy slot filling (Sec. 3.3).  The whole pool is laid out in greedy order; every
-    // slot's draw is computed by its own lane (the draws depend on the slot number only); then one
-    // lane fills the slots in order, because which members are still free depends on the slots before.
-    __shared__ uint32_t word0[SMALL_K1_MAX], word1[SMALL_K1_MAX];
-    if (mine) { v1[rank] = score; i1[rank] = id; }
-    if (tid < k2e) {
-        const philox_out r = philox4x32_10((uint32_t)eg.step, (uint32_t)(eg.step >> 32), (uint32_t)b, (uint32_t)tid,
-                                           (uint32_t)eg.seed, (uint32_t)(eg.seed >> 32));
-        word0[tid] = r.w0;
-        word1[tid] = r.w1;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        uint64_t taken[SMALL_K1_MAX / 64];                     // bit set = chosen (or past the pool's end)
-#pragma unroll
-        for (int w = 0; w < SMALL_K1_MAX / 64; ++w) {
-            const int lo = w * 64;
-            taken[w] = k1e >= lo + 64 ? 0ull : k1e <= lo ? ~0ull : (~0ull << (k1e - lo));
-        }
-        for (int j = 0; j < k2e; ++j) {
-            const bool explore = (uint64_t)word0[j] < eg.threshold;
-            const uint32_t remaining = (uint32_t)(k1e - j);
-            int want = explore ? (int)(((uint64_t)word1[j] * remaining) >> 32) : 0;   // index among the free members
-            int pos = 0;
-#pragma unroll
-            for (int w = 0; w < SMALL_K1_MAX / 64; ++w) {
-                uint64_t fr = ~taken[w];
-                const int c = __popcll(fr);
-                if (want >= 0 && want < c) {
-                    for (int t = 0; t < want; ++t) fr &= fr - 1;              // drop the `want` lowest free bits
-                    const int bit = __ffsll((long long)fr) - 1;
-                    taken[w] |= 1ull << bit;
-                    pos = w * 64 + bit;
-                    want = -1;
-                } else if (want >= 0) {
-                    want -= c;
-                }
-            }
-            out_ids[(int64_t)b * k2 + j] = i1[pos];
-            out_scores[(int64_t)b * k2 + j] = (float)v1[pos];
-            if (eg.explored) eg.explored[(int64_t)b * k2 + j] = explore ? 1 : 0;
-        }
-    }
-}
-
-
-__global__ __launch_bounds__(RERANK_T) void k_rerank(const uint64_t* __restrict__ surv, const uint32_t* __restrict__ cnt,
-                                                const double* __restrict__ exact, const float* __restrict__ qstage,
-                                                int k1, int k2, double lambda, int32_t* __restrict__ out_ids,
-                                                float* __restrict__ out_scores, int32_t* __restrict__ cand_ids,
-                                                float* __restrict__ cand_sims, EpsGreedy eg, int exact_stride) {
-    rerank_one_query<RERANK_T>((int)blockIdx.x, surv, cnt, exact, qstage, k1, k2, lambda, out_ids, out_scores, cand_ids, cand_sims, eg, exact_stride);
-}
-
-// The last selection, the exact re-scoring and the value filter of one query in one launch (pools of up
-// to 128, one workgroup per query): the three steps hand their results on through the same global
-// buffers as the separate kernels do -- a workgroup's own writes are visible to it after a barrier --
-// so the results are bit for bit those of the three launches, without two launch latencies.
-template <int DT>
-__global__ __launch_bounds__(1024) void k_select_rescore_rerank(
-        uint64_t* __restrict__ surv, uint32_t* __restrict__ cnt, float* __restrict__ thr, const float* __restrict__ invq,
-        uint32_t* __restrict__ counters, uint32_t* __restrict__ flags, int k1, float margin, int may_have_empty, int keep_max,
-        const void* __restrict__ store_, const float* __restrict__ qf, const double* __restrict__ invq64,
-        double* __restrict__ exact, int nkb, int exact_stride,
-        const float* __restrict__ qstage, int k2, double lambda, int32_t* __restrict__ out_ids, float* __restrict__ out_scores,
-        int32_t* __restrict__ cand_ids, float* __restrict__ cand_sims, EpsGreedy eg) {
-    const int b = (int)blockIdx.x;
-    select_final_one_query<DT>(b, surv, cnt, thr, invq, counters, flags, k1, margin, may_have_empty, keep_max, store_, qf, invq64, nkb);
-    rescore_one_query<DT>(b, 0, 1, store_, qf, invq64, surv, cnt, exact, nkb, exact_stride);
-    __syncthreads();
-    rerank_one_query<1024>(b, surv, cnt, exact, qstage, k1, k2, lambda, out_ids, out_scores, cand_ids, cand_sims, eg, exact_stride);
-}
 
 }  // namespace evk

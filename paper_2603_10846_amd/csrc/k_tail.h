@@ -1,0 +1,388 @@
+// Last steps of a retrieve (Sec. 3.2), one launch: the selection after the last scan pass, the exact re-scoring of
+// the candidates it keeps, the candidate pool C(x) and the value filter.
+//
+// One workgroup per query, or `parts` of them: each then makes the same selection (from the same list, so with the same
+// result, and at the same time), re-scores its share of the candidates, and the last one to finish orders the
+// pool.  Nothing waits for another workgroup.  What the separate launches cost was their latencies: one query
+// over 4096 x 768 fp32 rows with a pool of 32 took 6.1 + 5.1 + 5.2 us in three launches, 14.9 in one; 128 queries, d = 4096, a
+// pool of 256: 9.5 + 93 + 36 us, 116 in one; 64 queries, d = 1024, a pool of 960: 6.5 + 35.6 + 68.6 us, 66 in one.
+// What bounds it: about 4 us of barriers and LDS round trips in the selection and 2 to 5 us in the orderings; in
+// between fp64 conversions and multiply-adds, 13 us for 160 rows of 1024 on one compute unit.
+//
+// Re-scoring: 16 lanes per candidate row accumulate in fp64, so that the value filter, which divides by the
+// pool's spread, sees exact similarities.  It is a gather of 128-byte pieces that lie a k-block apart.
+// Ordering: a pool of up to 256 is ordered by counting how many candidates precede each one (four lanes share a
+// candidate); for larger ones counting all pairs is too much work, so the entries are spread over 2048 buckets by
+// value first -- a monotone map, so only entries of one bucket need comparing -- with a bitonic sort as the way out
+// when a bucket holds too many (masses of equal values).
+// z-scores over the pool (population deviation, denominator std + 1e-6), score = (1-lambda) z_s + lambda z_q, the
+// k2 best by (score desc, id asc) or the k2 slots filled epsilon-greedily (Sec. 3.3).  All in fp64, scores rounded
+// to fp32 on output.
+#pragma once
+#include "k_select.h"
+
+namespace evk {
+
+constexpr int TAIL_T = 1024;
+constexpr int TAIL_CROWD = 64;            // entries of one bucket that are still ranked by counting
+
+// LDS besides the static part (dynamic), in this order: v0[cap] f64, v1[k1p] f64, i0[cap] i32, i1[k1p] i32, q0[cap] f32, q1[k1p] f32,
+// then for pools of more than 256 order[sort_cap] u32; cap = keep_of(k1), k1p = k1 rounded up to 64, sort_cap = cap rounded up to a
+// power of two.  The epsilon-greedy draws (two words per slot) take over v0's space.
+__host__ __device__ constexpr int tail_pad64(int x) { return (x + 63) & ~63; }
+__host__ __device__ constexpr int tail_pow2(int x) { int p = 64; while (p < x) p <<= 1; return p; }
+__host__ __device__ constexpr size_t tail_lds(int k1) {
+    return (size_t)keep_of(k1) * 16 + (size_t)tail_pad64(k1) * 16 + (k1 > SMALL_K1_MAX ? (size_t)tail_pow2(keep_of(k1)) * 4 : 0);
+}
+
+// A NaN similarity or score (a zero-norm or non-finite row or query, a NaN in the Q table: inputs
+// for which the results are unspecified) is ranked as -inf, so that the orderings below stay total
+// orders: every rank is taken exactly once and every id that is gathered with is a real one.
+__device__ __forceinline__ double finite_or_lowest(double v) { return v == v ? v : -INFINITY; }
+
+// (v, id) before (w, jd)?  Written without short-circuit operators: inside the counting loops below
+// the arguments come from LDS, and a short-circuit form compiles to a branch per element with the
+// second LDS read behind it, so that every element pays two LDS round trips (measured: 200 cycles
+// per element, 36 us for a 128-entry pool); this form lets the reads of an unrolled group go out together.
+__device__ __forceinline__ bool ranks_before(double v, int32_t id, double w, int32_t jd) {
+    return (bool)((int)(v > w) | ((int)(v == w) & (int)(id < jd)));
+}
+
+// Sums of two values per lane over the workgroup, in a fixed order.
+__device__ __forceinline__ void group_sum2(double (*red)[16], int wave, int lane, double& a, double& b) {
+    a = wave_total_d(a);
+    b = wave_total_d(b);
+    if (lane == 0) { red[0][wave] = a; red[1][wave] = b; }
+    __syncthreads();
+    a = 0.0;
+    b = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) { a += red[0][w]; b += red[1][w]; }
+    __syncthreads();
+}
+
+// Calls emit(i, r) for every entry i of n, r being its rank by (value desc, id asc).  All lanes take part; the
+// inputs were written before a barrier, and emit must not write them.
+template <bool BIG, class Emit>
+__device__ __forceinline__ void rank_entries(const double* val, const int32_t* ids, int n, uint32_t* order, SelectLds& sh,
+                                             double (*red)[16], Emit emit) {
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    if constexpr (!BIG) {
+        // four lanes share an entry: each counts over every fourth other entry
+        for (int i = tid / 4; i < n; i += TAIL_T / 4) {              // trip count uniform within a lane quad
+            const double v = val[i];
+            const int32_t id = ids[i];
+            int rank = 0;
+#pragma unroll 8
+            for (int j = tid % 4; j < n; j += 4) rank += ranks_before(val[j], ids[j], v, id);
+            rank += __shfl_xor(rank, 1, 64);
+            rank += __shfl_xor(rank, 2, 64);
+            if (tid % 4 == 0) emit(i, rank);
+        }
+    } else {
+        constexpr int U = (BIG_K1_MAX + 256 + TAIL_T - 1) / TAIL_T;   // entries per lane
+        // range of the finite values
+        double hi = -INFINITY, lo = INFINITY;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = tid + u * TAIL_T;
+            const double v = i < n ? val[i] : -INFINITY;
+            hi = fmax(hi, v);
+            if (v > -INFINITY) lo = fmin(lo, v);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) { hi = fmax(hi, __shfl_xor(hi, o, 64)); lo = fmin(lo, __shfl_xor(lo, o, 64)); }
+        if (lane == 0) { red[0][wave] = hi; red[1][wave] = lo; }
+        for (int i = tid; i < SEL_BINS; i += TAIL_T) sh.hist[i] = 0;
+        if (tid == 0) sh.count = 0;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < 16; ++w) { hi = fmax(hi, red[0][w]); lo = fmin(lo, red[1][w]); }
+        const double scale = (double)SEL_BINS / (hi - lo);
+        uint32_t bin[U], pos[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = tid + u * TAIL_T;
+            if (i < n) {
+                const double x = (hi - val[i]) * scale;               // grows as the value falls; NaN (no range) goes to the last bucket
+                bin[u] = x < (double)(SEL_BINS - 1) ? (uint32_t)(int)x : (uint32_t)(SEL_BINS - 1);
+                pos[u] = atomicAdd(&sh.hist[bin[u]], 1u);
+            }
+        }
+        __syncthreads();
+        const uint32_t c0 = sh.hist[2 * tid], c1 = sh.hist[2 * tid + 1];
+        if (c0 > TAIL_CROWD || c1 > TAIL_CROWD) sh.count = 1;
+        uint32_t total;
+        const uint32_t start = group_prefix_u32(c0 + c1, sh.part_a, wave, lane, total);     // (has a barrier)
+        sh.hist[2 * tid] = start;
+        sh.hist[2 * tid + 1] = start + c0;
+        const bool crowd = sh.count != 0;                              // uniform
+        __syncthreads();
+        if (!crowd) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = tid + u * TAIL_T;
+                if (i < n) order[sh.hist[bin[u]] + pos[u]] = (uint32_t)i;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = tid + u * TAIL_T;
+                if (i < n) {
+                    const uint32_t first = sh.hist[bin[u]], last = bin[u] + 1 < (uint32_t)SEL_BINS ? sh.hist[bin[u] + 1] : (uint32_t)n;
+                    const double v = val[i];
+                    const int32_t id = ids[i];
+                    uint32_t rank = first;
+                    for (uint32_t t = first; t < last; ++t) {
+                        const uint32_t j = order[t];
+                        rank += ranks_before(val[j], ids[j], v, id);
+                    }
+                    emit(i, (int)rank);
+                }
+            }
+        } else {
+            int cap = 2;
+            while (cap < n) cap <<= 1;
+            for (int i = tid; i < cap; i += TAIL_T) order[i] = (uint32_t)i;
+            __syncthreads();
+            bitonic_desc(order, cap, tid, TAIL_T, [&](uint32_t x, uint32_t y) {
+                const bool lx = (int)x < n, ly = (int)y < n;           // padding sorts last
+                if (!lx || !ly) return !lx && ly;
+                return ranks_before(val[y], ids[y], val[x], ids[x]);
+            });
+            for (int r = tid; r < n; r += TAIL_T) emit((int)order[r], r);
+        }
+    }
+}
+
+// Position of the set bit number `want` (from 0) of x, which has more than `want` of them.
+__device__ __forceinline__ int nth_set_bit(uint64_t x, int want) {
+    int pos = 0;
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) {
+        const int c = __popcll(x & ((1ull << w) - 1ull));
+        const bool up = want >= c;
+        want -= up ? c : 0;
+        pos += up ? w : 0;
+        x >>= up ? w : 0;
+    }
+    return pos;
+}
+
+struct TailArgs {
+    uint64_t* surv;
+    const uint32_t* cnt;
+    uint32_t* counters;
+    uint32_t* flags;
+    uint32_t* arrived;        // per query, zero before the launch
+    const void* store;
+    const float* qf;
+    const double* invq64;
+    double* exact;            // [B][exact_stride]; used when a query has several workgroups
+    const float* qstage;
+    int32_t* out_ids;
+    float* out_scores;
+    int32_t* cand_ids;
+    float* cand_sims;
+    double lambda;
+    int nkb, exact_stride, k1, k2, may_have_empty, mode;
+    float margin;
+};
+
+template <int DT, bool BIG>
+__global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A, EpsGreedy eg) {
+    extern __shared__ __align__(16) unsigned char tail_smem[];
+    __shared__ SelectLds sh;
+    __shared__ double red[2][16];
+    __shared__ uint32_t last_s;
+    const int k1 = A.k1, k2 = A.k2, cap = keep_of(k1), k1p = tail_pad64(k1);
+    double* v0 = reinterpret_cast<double*>(tail_smem);
+    double* v1 = v0 + cap;
+    int32_t* i0 = reinterpret_cast<int32_t*>(v1 + k1p);
+    int32_t* i1 = i0 + cap;
+    float* q0 = reinterpret_cast<float*>(i1 + k1p);                // the stage's values of the entries in i0, i1
+    float* q1 = q0 + cap;
+    uint32_t* order = reinterpret_cast<uint32_t*>(q1 + k1p);      // larger pools only
+    const int b = (int)blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, sub = tid & 15, grp = tid >> 4;
+    int part = (int)blockIdx.y, parts = (int)gridDim.y;
+    uint64_t* list = A.surv + (int64_t)b * SURV_CAP;
+    const float* q = A.qf + (int64_t)b * A.nkb * KB;
+
+    // ---- selection ----
+    Selected s;
+    const uint32_t raw = select_keys(list, A.cnt + b, k1, A.margin, A.may_have_empty != 0, cap, A.mode, sh, s);
+    if (raw > (uint32_t)SURV_CAP && part == 0 && tid == 0) { atomicAdd(A.counters + 1, 1u); A.flags[b] |= 1u; }
+    // The last of the query's workgroups to come here?  All that one workgroup hands to another are the similarities
+    // below, and those are stored and loaded as device-scope atomics, which pass by the caches that differ between
+    // XCDs; so it is enough that a workgroup's stores have been acknowledged before it arrives.  (Device-scope
+    // fences instead write back and invalidate a whole L2 per wavefront: this kernel took 71 us with them for 64
+    // queries in two parts, 24 without.)
+    auto last_to_arrive = [&]() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) last_s = __hip_atomic_fetch_add(A.arrived + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)gridDim.y - 1u;
+        __syncthreads();
+        return last_s != 0;
+    };
+    if (s.crowded && A.mode == SEL_FINAL) {          // uniform, and the same for all of the query's workgroups
+        // every key of the band gets its similarity accumulated in fp64 and the selection is made again; the list
+        // is rewritten in place, so this is for the workgroup that knows that the others have read theirs
+        if (parts > 1 && !last_to_arrive()) return;
+        part = 0;
+        parts = 1;
+        store_kept(s, list);
+        __syncthreads();
+        const int n = (int)s.kept;
+        for (int j0 = 0; j0 < n; j0 += TAIL_T / 16) {               // uniform trip count: the row's lanes add up across lanes
+            const int j = j0 + grp;
+            const bool live = j < n;
+            const int32_t id = live ? key_id(list[j]) : 0;
+            double dot, ssq;
+            row_products<DT>(A.store, q, id, live, sub, A.nkb, dot, ssq);
+            if (live && sub == 0) list[j] = exact_key(dot * A.invq64[b] * (1.0 / sqrt(ssq)), id);
+        }
+        __syncthreads();
+        if (tid == 0) last_s = (uint32_t)n;
+        __syncthreads();
+        select_keys(list, &last_s, k1, EXACT_KEY_MARGIN, A.may_have_empty != 0, cap, SEL_EXACT, sh, s);
+    }
+    {
+        uint32_t at = s.slot;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (s.key[i] != 0 && s.key[i] >= s.cut) i0[at++] = key_id(s.key[i]);
+    }
+    const int kk = (int)s.kept;
+    __syncthreads();
+    // the stage's values of all candidates: requested here, so that the z-scores need not wait for them
+    constexpr int UC = ((BIG ? keep_of(BIG_K1_MAX) : KEEP_MAX) + TAIL_T - 1) / TAIL_T;
+    float qc[UC];
+#pragma unroll
+    for (int u = 0; u < UC; ++u) qc[u] = tid + u * TAIL_T < kk ? A.qstage[i0[tid + u * TAIL_T]] : 0.f;
+
+    // ---- exact similarities of the candidates (of this workgroup's share) ----
+    for (int j0 = 0; j0 * parts < kk; j0 += TAIL_T / 16) {
+        const int j = (j0 + grp) * parts + part;
+        const bool live = j < kk;
+        const int32_t id = live ? i0[j] : 0;
+        double dot, ssq;
+        row_products<DT>(A.store, q, id, live, sub, A.nkb, dot, ssq);
+        if (live && sub == 0) {
+            const double sim = dot * A.invq64[b] * (1.0 / sqrt(ssq));
+            if (parts == 1) v0[j] = finite_or_lowest(sim);
+            else __hip_atomic_store(A.exact + (int64_t)b * A.exact_stride + j, finite_or_lowest(sim), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    if (parts > 1) {
+        if (!last_to_arrive()) return;
+        for (int i = tid; i < kk; i += TAIL_T)
+            v0[i] = __hip_atomic_load(A.exact + (int64_t)b * A.exact_stride + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int u = 0; u < UC; ++u)
+        if (tid + u * TAIL_T < kk) q0[tid + u * TAIL_T] = qc[u];
+    __syncthreads();
+
+    // ---- the pool: the k1e best by (similarity desc, id asc) -> (v1, i1, q1) ----
+    const int k1e = kk < k1 ? kk : k1;
+    rank_entries<BIG>(v0, i0, kk, order, sh, red, [&](int i, int r) __attribute__((always_inline)) {
+        if (r < k1e) { v1[r] = v0[i]; i1[r] = i0[i]; q1[r] = q0[i]; }
+    });
+    __syncthreads();
+    // ---- z-scores over the pool ----
+    constexpr int U = BIG ? (BIG_K1_MAX + TAIL_T - 1) / TAIL_T : 1;   // pool entries per lane
+    double sim[U], qv[U];
+    int32_t pid[U];
+    double sum_s = 0.0, sum_q = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = tid + u * TAIL_T;
+        const bool mine = i < k1e;
+        sim[u] = mine ? v1[i] : 0.0;
+        pid[u] = mine ? i1[i] : 0x7fffffff;
+        qv[u] = mine ? (double)q1[i] : 0.0;
+        sum_s += sim[u];
+        sum_q += qv[u];
+    }
+    if (A.cand_ids)
+        for (int i = tid; i < k1; i += TAIL_T) {
+            A.cand_ids[(int64_t)b * k1 + i] = i < k1e ? i1[i] : -1;
+            A.cand_sims[(int64_t)b * k1 + i] = i < k1e ? (float)v1[i] : -INFINITY;
+        }
+    if (k1e > 0) {                                                    // uniform
+        group_sum2(red, wave, lane, sum_s, sum_q);
+        const double mean_s = sum_s / k1e, mean_q = sum_q / k1e;
+        double var_s = 0.0, var_q = 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool mine = tid + u * TAIL_T < k1e;
+            sim[u] = mine ? sim[u] - mean_s : 0.0;
+            qv[u] = mine ? qv[u] - mean_q : 0.0;
+            var_s += sim[u] * sim[u];
+            var_q += qv[u] * qv[u];
+        }
+        group_sum2(red, wave, lane, var_s, var_q);
+        const double scale_s = 1.0 / (sqrt(var_s / k1e) + 1e-6), scale_q = 1.0 / (sqrt(var_q / k1e) + 1e-6);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {                                 // v0 / i0 are reused for the scores
+            const int i = tid + u * TAIL_T;
+            if (i < k1e) {
+                v0[i] = finite_or_lowest((1.0 - A.lambda) * (sim[u] * scale_s) + A.lambda * (qv[u] * scale_q));
+                i0[i] = pid[u];
+            }
+        }
+    }
+    __syncthreads();
+    // ---- the k2 best by (score desc, id asc) ----
+    const int k2e = k1e < k2 ? k1e : k2;
+    const bool greedy = eg.threshold == 0 && eg.explored == nullptr;
+    int32_t* out_ids = A.out_ids + (int64_t)b * k2;
+    float* out_scores = A.out_scores + (int64_t)b * k2;
+    rank_entries<BIG>(v0, i0, k1e, order, sh, red, [&](int i, int r) __attribute__((always_inline)) {
+        if (greedy) {
+            if (r < k2e) { out_ids[r] = i0[i]; out_scores[r] = (float)v0[i]; }
+        } else {
+            v1[r] = v0[i];
+            i1[r] = i0[i];
+        }
+    });
+    for (int i = k2e + tid; i < k2; i += TAIL_T) {
+        out_ids[i] = -1;
+        out_scores[i] = -INFINITY;
+        if (eg.explored) eg.explored[(int64_t)b * k2 + i] = 0;
+    }
+    if (greedy) return;                                               // uniform
+    // ---- epsilon-greedy slot filling (Sec. 3.3) ----
+    // The whole pool is laid out in greedy order; every slot's draw is computed by its own lane (the draws
+    // depend on the slot number only); then one wavefront fills the slots in order, because which members are
+    // still free depends on the slots before.  Lane w holds the free members 64 w .. 64 w + 63 as a bit mask.
+    uint32_t* word0 = reinterpret_cast<uint32_t*>(v0);                 // v0 holds at least 2 k2 words
+    uint32_t* word1 = word0 + k2;
+    __syncthreads();                                                   // the ordering has read v0
+    for (int j = tid; j < k2e; j += TAIL_T) {
+        const philox_out r = philox4x32_10((uint32_t)eg.step, (uint32_t)(eg.step >> 32), (uint32_t)b, (uint32_t)j,
+                                           (uint32_t)eg.seed, (uint32_t)(eg.seed >> 32));
+        word0[j] = r.w0;
+        word1[j] = r.w1;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    uint64_t is_free = k1e >= 64 * lane + 64 ? ~0ull : k1e <= 64 * lane ? 0ull : (1ull << (k1e - 64 * lane)) - 1ull;
+    for (int j = 0; j < k2e; ++j) {
+        const bool explore = (uint64_t)word0[j] < eg.threshold;
+        const int want = explore ? (int)(((uint64_t)word1[j] * (uint32_t)(k1e - j)) >> 32) : 0;   // index among the free members
+        const int c = __popcll(is_free);
+        const int upto = (int)wave_inclusive_sum((uint32_t)c);
+        const int holder = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto > want));               // the first lane that reaches it
+        if (lane == holder) {
+            const int bit = nth_set_bit(is_free, want - (upto - c));
+            is_free &= ~(1ull << bit);
+            const int at = 64 * lane + bit;
+            out_ids[j] = i1[at];
+            out_scores[j] = (float)v1[at];
+            if (eg.explored) eg.explored[(int64_t)b * k2 + j] = explore ? 1 : 0;
+        }
+    }
+}
+
+}  // namespace evk
