@@ -265,10 +265,29 @@ int mem_shape_rewards(evomem_t* h, int stage, const unsigned char* feasible_dev,
     if (!h || (stage != 0 && stage != 1) || M < 0 || (normalise && !(sigma_min > 0.f)) || !(clip >= 0.f)) return MEM_EINVAL;
     if (M == 0) return MEM_OK;
     if (!feasible_dev || !rewards_out_dev || (stage == 1 && (!latency_dev || !best_latency_dev))) return MEM_EINVAL;
-    hipLaunchKernelGGL(k_shape_rewards, dim3(1), dim3(1024), 0, static_cast<hipStream_t>(hip_stream), stage, feasible_dev,
-                       latency_dev, best_latency_dev, M, normalise, (double)sigma_min, (double)clip, reward_state(h, stage),
-                       rewards_out_dev);
-    LAUNCHCHK();
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    RewardArgs A{feasible_dev, latency_dev, best_latency_dev, M, (double)sigma_min, (double)clip, reward_state(h, stage),
+                 reinterpret_cast<double*>(h->ws + h->w.surv), rewards_out_dev, stage, normalise};
+    if (M <= REWARD_ONE) {
+        hipLaunchKernelGGL(k_shape_rewards, dim3(1), dim3(REWARD_ONE), 0, st, A);
+        LAUNCHCHK();
+        return MEM_OK;
+    }
+    // the blocks' sums lie where the survivor lists of a retrieve lie (calls on a handle are ordered): room for a million blocks
+    const int64_t most = (int64_t)((h->w.exact - h->w.surv) / (2 * sizeof(double)) - REWARD_HEAD) / 2 * REWARD_T;
+    for (int64_t off = 0; off < M; off += most) {
+        A.feasible = feasible_dev + off;
+        if (stage == 1) { A.latency = latency_dev + off; A.best = best_latency_dev + off; }
+        A.out = rewards_out_dev + off;
+        A.M = M - off < most ? M - off : most;
+        const dim3 grid((unsigned)((A.M + REWARD_T - 1) / REWARD_T)), block(REWARD_T);
+        if (normalise) {
+            hipLaunchKernelGGL(k_reward_sums, grid, block, 0, st, A);
+            LAUNCHCHK();
+        }
+        hipLaunchKernelGGL(k_reward_shape, grid, block, 0, st, A);
+        LAUNCHCHK();
+    }
     return MEM_OK;
 }
 

@@ -7,14 +7,22 @@
 //   (r_t - mu_{t-1}) / max(sigma_{t-1}, sigma_min), optionally clipped, with mu, sigma the running
 //   mean and population deviation of the raw rewards BEFORE it; the statistics (count, sum, sum of
 //   squares, fp64) persist in the handle's workspace.
-// The dependence of sample t on all earlier ones is a prefix sum: one workgroup walks the batch in
-// pieces of 1024 samples, scans (r, r^2) within the piece (wavefront shuffles, then the 16 wavefront
-// totals) and carries the totals to the next piece.  All arithmetic in fp64; outputs fp32.
+// The dependence of sample t on all earlier ones is a prefix sum.  A batch of one workgroup's size is one
+// launch; a longer one is two: the first leaves every block's sums of (r, r^2), in the second a block adds
+// the sums of the blocks before it and scans its own samples.  The raw rewards are computed in both -- two fp64
+// logarithms and a tanh per sample are what bounds the kernel, and one workgroup walking the batch in
+// pieces of 1024 did them on one compute unit: 8192 samples 45.3 us, 3.3 + 4.2 us in two launches.
+// All arithmetic in fp64; outputs fp32.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "k_ingest.h"
+
 namespace evk {
+
+constexpr int REWARD_ONE = 1024;          // largest batch of the one-launch form
+constexpr int REWARD_T = 256;             // samples per block of the two-launch form
 
 __device__ __forceinline__ double wave_inclusive_sum_d(double x, int lane) {
 #pragma unroll
@@ -25,50 +33,112 @@ __device__ __forceinline__ double wave_inclusive_sum_d(double x, int lane) {
     return x;
 }
 
-__global__ __launch_bounds__(1024) void k_shape_rewards(int stage, const unsigned char* __restrict__ feasible,
-                                                        const float* __restrict__ latency, const float* __restrict__ best,
-                                                        int64_t M, int normalise, double sigma_min, double clip,
-                                                        double* __restrict__ state, float* __restrict__ out) {
-    __shared__ double wave_s[16], wave_q[16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double n0 = state[0], s0 = state[1], q0 = state[2];          // statistics before the current piece
-    for (int64_t base = 0; base < M; base += 1024) {
-        const int64_t j = base + tid;
-        const bool live = j < M;
-        double raw = 0.0;
-        if (live) {
-            if (!feasible[j]) raw = -1.0;
-            else if (stage == 0) raw = 1.0;
-            else raw = tanh(log((double)best[j]) - log((double)latency[j]));
-        }
-        double r = raw;
-        if (normalise) {                                             // uniform
-            const double is = wave_inclusive_sum_d(raw, lane), iq = wave_inclusive_sum_d(raw * raw, lane);
-            if (lane == 63) { wave_s[wave] = is; wave_q[wave] = iq; }
-            __syncthreads();
-            double before_s = 0.0, before_q = 0.0, piece_s = 0.0, piece_q = 0.0;
+struct RewardArgs {
+    const unsigned char* feasible;
+    const float* latency;
+    const float* best;
+    int64_t M;
+    double sigma_min, clip;
+    double* state;            // count, sum, sum of squares
+    double* sums;             // two-launch form: the statistics before the batch, then two sums per block
+    float* out;
+    int stage, normalise;
+};
+constexpr int REWARD_HEAD = 4;            // doubles in front of the blocks' sums
+
+__device__ __forceinline__ double raw_reward(const RewardArgs& A, int64_t j) {
+    if (!A.feasible[j]) return -1.0;
+    return A.stage == 0 ? 1.0 : tanh(log((double)A.best[j]) - log((double)A.latency[j]));
+}
+
+// Normalised reward of a sample, n samples with the given sums having come before it.
+__device__ __forceinline__ double normalised_reward(const RewardArgs& A, double raw, double n, double sum, double sq) {
+    const double mu = n > 0.0 ? sum / n : 0.0;
+    const double var = n > 0.0 ? sq / n - mu * mu : 0.0;
+    const double sigma = var > 0.0 ? sqrt(var) : 0.0;
+    double r = (raw - mu) / (sigma > A.sigma_min ? sigma : A.sigma_min);
+    if (A.clip > 0.0) r = r > A.clip ? A.clip : (r < -A.clip ? -A.clip : r);
+    return r;
+}
+
+// Sums over the samples of earlier lanes and over the block, for blocks of W wavefronts (all lanes call it).
+template <int W>
+__device__ __forceinline__ void block_prefix2(double (*part)[2], int wave, int lane, double x, double y, double& before_x, double& before_y,
+                                              double& all_x, double& all_y) {
+    const double ix = wave_inclusive_sum_d(x, lane), iy = wave_inclusive_sum_d(y, lane);
+    if (lane == 63) { part[wave][0] = ix; part[wave][1] = iy; }
+    __syncthreads();
+    before_x = ix - x;
+    before_y = iy - y;
+    all_x = 0.0;
+    all_y = 0.0;
 #pragma unroll
-            for (int w = 0; w < 16; ++w) {
-                if (w < wave) { before_s += wave_s[w]; before_q += wave_q[w]; }
-                piece_s += wave_s[w];
-                piece_q += wave_q[w];
-            }
-            __syncthreads();
-            const double n = n0 + (double)tid;                       // samples before this one
-            const double sum = s0 + before_s + (is - raw), sq = q0 + before_q + (iq - raw * raw);
-            const double mu = n > 0.0 ? sum / n : 0.0;
-            const double var = n > 0.0 ? sq / n - mu * mu : 0.0;
-            const double sigma = var > 0.0 ? sqrt(var) : 0.0;
-            r = (raw - mu) / (sigma > sigma_min ? sigma : sigma_min);
-            if (clip > 0.0) r = r > clip ? clip : (r < -clip ? -clip : r);
-            const int64_t left = M - base;
-            n0 += (double)(left < 1024 ? left : 1024);
-            s0 += piece_s;
-            q0 += piece_q;
-        }
-        if (live) out[j] = (float)r;
+    for (int w = 0; w < W; ++w) {
+        if (w < wave) { before_x += part[w][0]; before_y += part[w][1]; }
+        all_x += part[w][0];
+        all_y += part[w][1];
     }
-    if (normalise && tid == 0) { state[0] = n0; state[1] = s0; state[2] = q0; }
+}
+
+__global__ __launch_bounds__(REWARD_ONE) void k_shape_rewards(RewardArgs A) {
+    __shared__ double part[REWARD_ONE / 64][2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool live = tid < A.M;
+    const double raw = live ? raw_reward(A, tid) : 0.0;
+    if (!A.normalise) {                                              // uniform
+        if (live) A.out[tid] = (float)raw;
+        return;
+    }
+    const double n0 = A.state[0], s0 = A.state[1], q0 = A.state[2];
+    double bs, bq, as, aq;
+    block_prefix2<REWARD_ONE / 64>(part, wave, lane, raw, raw * raw, bs, bq, as, aq);    // (has a barrier: the state is read before it)
+    if (live) A.out[tid] = (float)normalised_reward(A, raw, n0 + tid, s0 + bs, q0 + bq);
+    if (tid == 0) { A.state[0] = n0 + (double)A.M; A.state[1] = s0 + as; A.state[2] = q0 + aq; }
+}
+
+// First launch of a longer batch: the blocks' sums, and a copy of the statistics (the second launch replaces them
+// while other blocks still need the old ones).
+__global__ __launch_bounds__(REWARD_T) void k_reward_sums(RewardArgs A) {
+    __shared__ double part[REWARD_T / 64][2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t j = (int64_t)blockIdx.x * REWARD_T + tid;
+    const double raw = j < A.M ? raw_reward(A, j) : 0.0;
+    const double s = wave_total_d(raw), q = wave_total_d(raw * raw);
+    if (lane == 0) { part[wave][0] = s; part[wave][1] = q; }
+    __syncthreads();
+    if (tid < 2) A.sums[REWARD_HEAD + 2 * (int64_t)blockIdx.x + tid] = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+    if (blockIdx.x == 0 && tid < 3) A.sums[tid] = A.state[tid];
+}
+
+__global__ __launch_bounds__(REWARD_T) void k_reward_shape(RewardArgs A) {
+    __shared__ double part[REWARD_T / 64][2], earlier[REWARD_T / 64][2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t j = (int64_t)blockIdx.x * REWARD_T + tid;
+    const bool live = j < A.M;
+    const double raw = live ? raw_reward(A, j) : 0.0;
+    if (!A.normalise) {                                              // uniform
+        if (live) A.out[j] = (float)raw;
+        return;
+    }
+    double s = 0.0, q = 0.0;                                         // sums of the blocks before this one
+    for (int64_t k = tid; k < (int64_t)blockIdx.x; k += REWARD_T) {
+        s += A.sums[REWARD_HEAD + 2 * k];
+        q += A.sums[REWARD_HEAD + 2 * k + 1];
+    }
+    s = wave_total_d(s);
+    q = wave_total_d(q);
+    if (lane == 0) { earlier[wave][0] = s; earlier[wave][1] = q; }
+    double bs, bq, as, aq;
+    block_prefix2<REWARD_T / 64>(part, wave, lane, raw, raw * raw, bs, bq, as, aq);       // (has a barrier)
+    const double n0 = A.sums[0];
+    const double s0 = A.sums[1] + ((earlier[0][0] + earlier[1][0]) + (earlier[2][0] + earlier[3][0]));
+    const double q0 = A.sums[2] + ((earlier[0][1] + earlier[1][1]) + (earlier[2][1] + earlier[3][1]));
+    if (live) A.out[j] = (float)normalised_reward(A, raw, n0 + (double)j, s0 + bs, q0 + bq);
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+        A.state[0] = n0 + (double)A.M;
+        A.state[1] = s0 + as;
+        A.state[2] = q0 + aq;
+    }
 }
 
 }  // namespace evk

@@ -1,0 +1,31 @@
+"""Batch sizes of the reward shaping at the edges of its one-launch and two-launch forms, the statistics
+carried from call to call, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_10846_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("stage", [0, 1])
+def test_batch_sizes(orc, stage):
+    rng = np.random.default_rng(41 + stage)
+    bank = B.MemoryBank(64, "f32", 256, max_B=1, max_k1=1)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    state = None
+    for M in (1, 1023, 1024, 1025, 1, 1280, 1281, 70001, 3):        # one block, block edges, more blocks than a block adds up at once
+        print(f"rewards stage={stage} M={M}", flush=True)
+        feasible = (rng.random(M) < 0.7).astype(np.uint8)
+        latency, best = rng.uniform(0.1, 5.0, M).astype(np.float32), rng.uniform(0.1, 5.0, M).astype(np.float32)
+        want, state = orc.shape_rewards(stage, feasible, latency, best, True, np.float32(0.1), np.float32(2.5), state)
+        got = bank.shape_rewards(stage, dev(feasible), dev(latency), dev(best), True, 0.1, 2.5).cpu().numpy()
+        # fp64 sums in another order, then one rounding to fp32: 1e-6 as the reward test of the parity suite has it
+        assert np.all(np.abs(got - want) <= 1e-6 * np.maximum(1.0, np.abs(want))), M
+        plain = bank.shape_rewards(stage, dev(feasible), dev(latency), dev(best), False).cpu().numpy()
+        raw, _ = orc.shape_rewards(stage, feasible, latency, best, False, 0.1, 0.0, None)
+        assert np.all(np.abs(plain - raw) <= 1e-6)
+    n, mu, sd = bank.reward_stats(stage)
+    assert n == state[0] and abs(mu - state[1] / state[0]) < 1e-9
+    bank.close()
