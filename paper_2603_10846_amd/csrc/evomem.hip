@@ -13,6 +13,7 @@
 #include "k_ingest.h"
 #include "k_scan_gemv.h"
 #include "k_scan_mfma.h"
+#include "k_scan_direct.h"
 #include "k_select.h"
 #include "k_exact.h"
 #include "k_tail.h"
@@ -52,7 +53,7 @@ constexpr Workspace carve(int d, int dtype, int max_B, int max_k1, int bpad = 25
     const int64_t dpad = round_up(d, KB), Bp = round_up(max_B, bpad);
     const size_t sizes[10] = {256, (size_t)Bp * dpad * 4,
                               (size_t)Bp * (dpad + KB) * (dtype == MEM_F32 ? 4 : 2),   // + one all-zero k-block
-                              (size_t)Bp * 4, (size_t)Bp * 8, (size_t)Bp * 4, (size_t)Bp * 4, (size_t)Bp * 4,
+                              (size_t)Bp * 4, (size_t)Bp * 8, (size_t)Bp * 4, (size_t)Bp * CNT_STRIDE * 4, (size_t)Bp * 4,
                               (size_t)Bp * SURV_CAP * 8, (size_t)Bp * keep_of(max_k1) * 8};
     size_t at[11] = {};
     for (int i = 0; i < 10; ++i) at[i + 1] = (size_t)round_up((int64_t)(at[i] + sizes[i]), 256);
@@ -450,6 +451,53 @@ int launch_gemv(evomem* h, const Scratch& sc, hipStream_t st, int B, const Level
     return MEM_OK;
 }
 
+// One sparse pass: 32 or 64 rows and 16 .. 64 queries to a workgroup.
+template <int DT, int MQ, int MR>
+int launch_direct(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, const Mask& mask, int B) {
+    constexpr int lds = direct_lds_bytes<MQ, MR>();
+    auto kern = k_scan_direct<DT, MQ, MR>;
+    if constexpr (lds > 64 * 1024) {
+        static bool lds_set[MAX_DEVICES] = {};
+        if (!lds_set[h->device]) {
+            HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+            lds_set[h->device] = true;
+        }
+    }
+    const int nqt = (B + 16 * MQ - 1) / (16 * MQ), units = L.ntiles * (TILE_ROWS / (16 * MR));
+    unsigned char* ws = sc.base;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * ((units + 7) / 8) * nqt)), dim3(64 * DIRECT_WAVES), lds, st, (const void*)h->store, (const float*)h->invnorm,
+                       (const uint16_t*)(ws + sc.w.qop), (const float*)(ws + sc.w.invq), (const float*)(ws + sc.w.thr),
+                       (uint32_t*)(ws + sc.w.cnt), (uint64_t*)(ws + sc.w.surv), h->N, h->nkb, Bp, nqt, L, mask, B);
+    LAUNCHCHK();
+    return MEM_OK;
+}
+// Rows and queries (tr and tq) of a direct workgroup: 32 rows while that makes enough workgroups of a sparse pass.
+constexpr int direct_tq(int B) { return B <= 16 ? 16 : B <= 32 ? 32 : 64; }
+constexpr int direct_tr(int B) { return B <= 64 ? 32 : 64; }
+// Direct or tile by tile?  Either way a compute unit takes in about 30 GB/s of operands in such a pass (loads in flight
+// are limited by its 32 KB first-level cache), so what decides is how many rows and queries the busiest one reads.  The
+// direct scan pays for its tail (partial sums, counters) on top, hence the quarter.  Measured, direct against by tiles
+// (us; share of the operands the direct scan reads): 32 tiles of 1024 bf16, one query 5.6 / 17.2 (0.17), 64 queries 9.4 / 17.5
+// (0.33), 256 queries 20.8 / 20.0 (0.89); 64 tiles, 64 queries 20.0 / 21.0 (0.67); 128 tiles, 64 queries 34 / 23 (1.2);
+// 45 tiles of 4096 fp16, 128 queries 79 / 66 (0.89); 32 tiles of 1024 fp32, 64 queries 14.8 / 33.6 (0.33).
+bool use_direct(const Level& L, int B, int Bp, int qt) {
+    const int tq = direct_tq(B), tr = direct_tr(B);
+    const int64_t direct = ((int64_t)L.ntiles * (TILE_ROWS / tr) * ((B + tq - 1) / tq) + 255) / 256 * (tr + tq);
+    const int64_t tiles = ((int64_t)L.ntiles * (Bp / qt) + 255) / 256 * (TILE_ROWS + qt);
+    return direct * 4 <= tiles * 3;
+}
+int launch_direct_any(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, const Mask& mask, int B) {
+    int rc = MEM_OK;
+    with_store_type(h->dtype, [&](auto dt) {
+        constexpr int DT = decltype(dt)::value;
+        rc = B <= 16   ? launch_direct<DT, direct_tq(16) / 16, direct_tr(16) / 16>(h, sc, st, Bp, L, mask, B)
+             : B <= 32 ? launch_direct<DT, direct_tq(32) / 16, direct_tr(32) / 16>(h, sc, st, Bp, L, mask, B)
+             : B <= 64 ? launch_direct<DT, direct_tq(64) / 16, direct_tr(64) / 16>(h, sc, st, Bp, L, mask, B)
+                       : launch_direct<DT, direct_tq(256) / 16, direct_tr(256) / 16>(h, sc, st, Bp, L, mask, B);
+    });
+    return rc;
+}
+
 // One pass of the exhaustive selection.  Queries share a bank read in groups: of eight when there are more than
 // four, else of the smallest power of two that holds them (an unused slot would cost as much as a query).
 int launch_exact_scan(evomem* h, const Scratch& sc, hipStream_t st, int B, const Level& L) {
@@ -565,7 +613,8 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
                 // workgroups share the pass and each one's k-loop is shorter
                 int lqt = qt;
                 while (lqt > 32 && (int64_t)L.ntiles * (Bp / lqt) < 128) lqt >>= 1;
-                rc = mask.tags ? launch_mfma_any<true>(h, sc, st, Bp, lqt, L, k1, mask, B) : launch_mfma_any<false>(h, sc, st, Bp, lqt, L, k1, mask, B);
+                if (use_direct(L, B, Bp, lqt)) rc = launch_direct_any(h, sc, st, Bp, L, mask, B);
+                else rc = mask.tags ? launch_mfma_any<true>(h, sc, st, Bp, lqt, L, k1, mask, B) : launch_mfma_any<false>(h, sc, st, Bp, lqt, L, k1, mask, B);
             }
             if (rc != MEM_OK) return rc;
             if (prof) {

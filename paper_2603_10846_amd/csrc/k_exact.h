@@ -151,7 +151,7 @@ __global__ __launch_bounds__(256, NB > 4 ? 2 : 3) void k_exact_scan(const void* 
             if (L.rho == 0) {                       // sparsest pass: every row, at its own position
                 list[tile_j * TILE_ROWS + r0 + i] = key;
             } else if (key >= exact_words(exact, b, exact_stride)[0]) {
-                const uint32_t pos = atomicAdd(cnt + b, 1u);
+                const uint32_t pos = atomicAdd(slot_counter(cnt, b), 1u);
                 if (pos < (uint32_t)SURV_CAP) list[pos] = key;
             }
         }
@@ -166,13 +166,13 @@ __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ su
     uint64_t* list = surv + (int64_t)b * SURV_CAP;
     uint64_t* words = exact_words(exact, b, exact_stride);
     Selected s;
-    const uint32_t raw = select_keys(list, cnt + b, k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, sh, s);
+    const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, sh, s);
     if (raw > (uint32_t)SURV_CAP) {                 // lost: no key reaches this cut, so the count stays as it is
         if (tid == 0) words[0] = ~0ull;
         return;
     }
     store_kept(s, list);
-    if (tid == 0) { cnt[b] = s.kept; words[0] = s.cut; words[1] = 0ull; }
+    if (tid == 0) { *slot_counter(cnt, b) = s.kept; words[0] = s.cut; words[1] = 0ull; }
 }
 
 // The lost queries: gridDim.y workgroups each walk a part of the bank, a tile at a time, with a list in LDS of
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(1024) void k_exact_walk(const void* __restrict__ st
                                                      uint32_t* __restrict__ cnt, double* __restrict__ exact, int exact_stride,
                                                      int64_t N, int nkb, int k1, int keep_max) {
     const int b = (int)blockIdx.x, part = (int)blockIdx.y, parts = (int)gridDim.y, tid = threadIdx.x;
-    if (cnt[b] <= (uint32_t)SURV_CAP) return;       // uniform over the query's workgroups: written only below, by the last of them
+    if (*slot_counter(cnt, b) <= (uint32_t)SURV_CAP) return;       // uniform over the query's workgroups: written only below, by the last of them
     __shared__ uint64_t keys[WALK_CAP];
     __shared__ uint32_t n_s, last_s;
     __shared__ SelectLds sh;
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(1024) void k_exact_walk(const void* __restrict__ st
     __syncthreads();
     select_keys(list, &last_s, k1, EXACT_KEY_MARGIN, true, keep_max, SEL_EXACT, sh, s);
     store_kept(s, list);
-    if (tid == 0) cnt[b] = s.kept;
+    if (tid == 0) *slot_counter(cnt, b) = s.kept;
 }
 
 }  // namespace evk

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256) void k_prep_queries(const float* __restrict__ 
         // dot * invnorm, which lies in [-|q|, |q|]); empty slots get a threshold their all-zero query
         // can never reach.  Finite values keep the scan's arithmetic free of inf - inf.
         thr[b] = live ? (float)(-2.0 / inv) : 1.0f;
-        cnt[b] = live ? cnt0 : 0u;     // rows the sparsest pass will write without counting
+        *slot_counter(cnt, b) = live ? cnt0 : 0u;     // rows the sparsest pass will write without counting
         flags[b] = 0u;                 // per-query status of this retrieve (bit 0: a survivor list overflowed)
     }
 }

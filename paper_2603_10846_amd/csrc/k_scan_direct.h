@@ -1,0 +1,174 @@
+// Similarity scan of a sparse pass (Sec. 3.2, dense recall): few bank tiles, so latency is what counts.
+//
+// The matrix-core scan of k_scan_mfma.h walks a tile's k-blocks one after another in one workgroup, about 1 us per
+// block however few tiles there are: a pass over 32 tiles leaves most compute units idle and takes as long as one
+// tile does.  Here a workgroup takes 16 MR bank rows and 16 MQ queries and its eight wavefronts share the k
+// dimension: each forms the products of its own eighth with v_mfma_f32_16x16x32, operands loaded straight from
+// global memory into registers (both are stored in operand order: a lane's 16 bytes are 8 consecutive elements of
+// its row), several steps' loads in flight, no barrier and no LDS until the partial sums are added once at the end.
+// What bounds it: two memory latencies and, with many queries or long rows, the operands a compute unit can take in
+// (about 30 GB/s each).  First pass over 8192 rows, before and now: one query, d = 1024 bf16 17.2 -> 5.6 us; 64 queries
+// 20.5 -> 9.4; 64 queries, d = 1024 fp32 33.6 -> 14.8; 32 queries, d = 384 fp16 13.4 -> 4.9.
+#pragma once
+#include "k_scan_mfma.h"
+#include "layout.h"
+
+namespace evk {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+
+template <int DT>
+__device__ __forceinline__ f32x4_t mfma16(u32x4_t a, u32x4_t b, f32x4_t c) {
+    if constexpr (DT == 2) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
+constexpr int DIRECT_WAVES = 8;
+// Partial sums [wavefront][query][row]; four spare floats per row of queries put the four lane groups of an
+// accumulator's store (queries 4 apart) on different banks.
+template <int MQ, int MR> constexpr int direct_lds_bytes() { return DIRECT_WAVES * 16 * MQ * (16 * MR + 4) * 4; }
+
+template <int DT, int MQ, int MR>
+__global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* __restrict__ store_, const float* __restrict__ invnorm,
+                                                                   const uint16_t* __restrict__ qop, const float* __restrict__ invq,
+                                                                   const float* __restrict__ thr, uint32_t* __restrict__ cnt,
+                                                                   uint64_t* __restrict__ surv, int64_t N, int nkb, int Bp, int nqt,
+                                                                   Level L, Mask mask, int B) {
+    static_assert(MR == 2 || MR == 4, "32 or 64 rows: a wavefront finishes two queries or one at a time");
+    constexpr int TQ = 16 * MQ, TR = 16 * MR, TRP = TR + 4, W = DIRECT_WAVES;
+    constexpr int DEPTH = DT == 0 ? 2 : 4;                // steps whose loads are in flight together
+    extern __shared__ __align__(16) float direct_part[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, grp = lane >> 4;
+    // The query tiles that share rows are neighbours on one XCD: all but the first find the rows in its L2.
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int q0 = (slot % nqt) * TQ;
+    const int unit = (slot / nqt) * 8 + xcd;
+    if (unit >= L.ntiles * (TILE_ROWS / TR)) return;      // uniform
+    const int tile_j = unit / (TILE_ROWS / TR), r0 = unit % (TILE_ROWS / TR) * TR;
+    const int64_t t = level_tile(L, tile_j);
+
+    // ---- this wavefront's share of the k dimension, in steps of 32 elements ----
+    const int steps = 2 * nkb, s0 = steps * wave / W, s1 = steps * (wave + 1) / W;
+    f32x4_t acc[MQ][MR];
+#pragma unroll
+    for (int a = 0; a < MQ; ++a)
+#pragma unroll
+        for (int b = 0; b < MR; ++b) acc[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // rows 16 apart have the same swizzle, and so have the two halves of a k-block up to one bit
+    const int lane16 = l16 * KB + swz16(grp, l16) * 8;    // a lane's offset in 16 rows of 16-bit elements, first half
+    const int row_elem = (r0 + l16) * KB + grp * 8;       // fp32 stores
+    for (int s = s0; s < s1; s += DEPTH) {                // uniform within the wavefront
+        u32x4_t x[DEPTH][MR][DT == 0 ? 2 : 1], y[DEPTH][MQ][DT == 0 ? 2 : 1];
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) {
+            const int su = s + u < s1 ? s + u : s1 - 1, kb = su >> 1, h = su & 1;   // (past the end: loaded, not used)
+            if constexpr (DT == 0) {
+                const float* blk = static_cast<const float*>(store_) + (t * nkb + kb) * (int64_t)BLOCK_ELEMS + row_elem + h * 32;
+#pragma unroll
+                for (int b = 0; b < MR; ++b)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) x[u][b][i] = *reinterpret_cast<const u32x4_t*>(blk + b * 16 * KB + i * 4);
+                const uint16_t* qb = qop + (((int64_t)kb * 2 + h) * Bp + q0) * KB;
+#pragma unroll
+                for (int a = 0; a < MQ; ++a)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) y[u][a][i] = *reinterpret_cast<const u32x4_t*>(qb + a * 16 * KB + (lane16 ^ (i * 32)));
+            } else {
+                const uint16_t* blk = static_cast<const uint16_t*>(store_) + (t * nkb + kb) * (int64_t)BLOCK_ELEMS + r0 * KB;
+#pragma unroll
+                for (int b = 0; b < MR; ++b) x[u][b][0] = *reinterpret_cast<const u32x4_t*>(blk + b * 16 * KB + (lane16 ^ (h * 32)));
+                const uint16_t* qb = qop + ((int64_t)kb * Bp + q0) * KB;
+#pragma unroll
+                for (int a = 0; a < MQ; ++a) y[u][a][0] = *reinterpret_cast<const u32x4_t*>(qb + a * 16 * KB + (lane16 ^ (h * 32)));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);                // all of them requested before the first is used
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) {
+            if (s + u >= s1) break;                       // uniform
+            if constexpr (DT == 0) {
+                // bf16 hi + lo of the rows (the queries are stored split): hi*hi + hi*lo + lo*hi
+#pragma unroll
+                for (int b = 0; b < MR; ++b) {
+                    u32x4_t hi, lo;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const u32x4_t v = x[u][b][i >> 1];
+                        float ra, rb;
+                        hi[i] = pack_bf16x2_hi(__uint_as_float(v[(i & 1) * 2]), __uint_as_float(v[(i & 1) * 2 + 1]), ra, rb);
+                        lo[i] = cvt_pk_bf16(ra, rb);
+                    }
+#pragma unroll
+                    for (int a = 0; a < MQ; ++a) {
+                        acc[a][b] = mfma16<1>(y[u][a][1], hi, acc[a][b]);
+                        acc[a][b] = mfma16<1>(y[u][a][0], lo, acc[a][b]);
+                        acc[a][b] = mfma16<1>(y[u][a][0], hi, acc[a][b]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int a = 0; a < MQ; ++a)
+#pragma unroll
+                    for (int b = 0; b < MR; ++b) acc[a][b] = mfma16<DT>(y[u][a][0], x[u][b][0], acc[a][b]);
+            }
+        }
+    }
+    // ---- the eight partial sums; then a wavefront finishes 64 / TR queries at a time, a lane per row ----
+    // (queries are the accumulator's rows, 4 grp + register; bank rows its columns, l16)
+#pragma unroll
+    for (int a = 0; a < MQ; ++a)
+#pragma unroll
+        for (int b = 0; b < MR; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) direct_part[(wave * TQ + a * 16 + 4 * grp + r) * TRP + b * 16 + l16] = acc[a][b][r];
+    constexpr int QL = 64 / TR, ITER = (TQ + W * QL - 1) / (W * QL);
+    const int row = lane % TR, ql = lane / TR;
+    const int64_t id = t * TILE_ROWS + r0 + row;
+    const float inve = id < N ? invnorm[id] : 0.f;
+    const uint32_t tag = mask.tags && id < N ? mask.tags[id] : 0u;
+    float v[ITER], th[ITER], inq[ITER];
+    bool keep[ITER], ok[ITER];
+    uint32_t base[ITER];
+#pragma unroll
+    for (int i = 0; i < ITER; ++i) {                      // (requested before the barrier)
+        const int qi = (i * W + wave) * QL + ql, q = q0 + qi;
+        keep[i] = qi < TQ && q < B && id < N;
+        th[i] = thr[keep[i] ? q : 0];
+        inq[i] = invq[keep[i] ? q : 0];
+        ok[i] = keep[i] && (!mask.tags || eligible(tag, mask.allow[q], mask.exclude[q]));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITER; ++i) {
+        const int qi = (i * W + wave) * QL + ql, q = q0 + qi;
+        v[i] = 0.f;
+        if (qi < TQ) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) v[i] += direct_part[(w * TQ + qi) * TRP + row];
+        }
+        v[i] *= inve;
+        if (L.rho == 0) {
+            // sparsest pass: every row is kept, at its own position (0 = empty slot)
+            if (keep[i])
+                surv[(int64_t)q * SURV_CAP + (int64_t)tile_j * TILE_ROWS + r0 + row] = ok[i] ? pack_key(v[i] * inq[i], (int32_t)id) : 0ull;
+        } else {
+            keep[i] = ok[i] && v[i] >= th[i];
+            const uint64_t m = __builtin_amdgcn_ballot_w64(keep[i]);
+            const uint32_t c = QL == 1 ? (uint32_t)__popcll(m) : (uint32_t)__popc((uint32_t)(m >> (32 * ql)));
+            base[i] = 0;
+            if (row == 0 && c != 0) base[i] = atomicAdd(slot_counter(cnt, q), c);
+        }
+    }
+    if (L.rho == 0) return;
+#pragma unroll
+    for (int i = 0; i < ITER; ++i) {
+        const int q = q0 + (i * W + wave) * QL + ql;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(keep[i]);
+        if (m == 0) continue;                             // uniform within the wavefront
+        const uint64_t below = (m >> (TR * ql)) & ((1ull << row) - 1ull);
+        const uint32_t pos = (uint32_t)__shfl((int)base[i], TR * ql, 64) + (uint32_t)__popcll(below);
+        if (keep[i] && pos < (uint32_t)SURV_CAP) surv[(int64_t)q * SURV_CAP + pos] = pack_key(v[i] * inq[i], (int32_t)id);
+    }
+}
+
+}  // namespace evk

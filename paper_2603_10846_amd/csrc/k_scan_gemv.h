@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
             const bool ok = !mask.tags || eligible(tag, mask.allow[b], mask.exclude[b]);
             if (L.rho == 0)      // sparsest pass keeps every row at its own position, no counter (0 = empty slot)
                 surv[(int64_t)b * SURV_CAP + (int64_t)tile_j * TILE_ROWS + (id - t * TILE_ROWS)] = ok ? pack_key(v * invq[b], (int32_t)id) : 0ull;
-            else if (ok && v >= thr[b]) append_survivor(v, invq[b], (int32_t)id, cnt + b, surv + (int64_t)b * SURV_CAP);
+            else if (ok && v >= thr[b]) append_survivor(v, invq[b], (int32_t)id, slot_counter(cnt, b), surv + (int64_t)b * SURV_CAP);
         }
     }
 }

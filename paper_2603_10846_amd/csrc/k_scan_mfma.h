@@ -435,7 +435,7 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
         __syncthreads();
         for (int i = tid; i < QT; i += NT) {
             uint32_t c = cnt_s[i];
-            base_s[i] = c ? atomicAdd(cnt + q0 + i, c) : 0u;
+            base_s[i] = c ? atomicAdd(slot_counter(cnt, q0 + i), c) : 0u;
             cnt_s[i] = 0;
         }
         __syncthreads();
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
                         lkey[slot] = ((uint64_t)__float_as_uint(av) << 32) | (uint32_t)id;
                         lq[slot] = ok ? (uint32_t)ql : 0xffffu;          // the slot was reserved before the check
                     } else if (ok) {   // list full (a very loose threshold): fall back to the direct path
-                        uint32_t pos = atomicAdd(cnt + q0 + ql, 1u);
+                        uint32_t pos = atomicAdd(slot_counter(cnt, q0 + ql), 1u);
                         if (pos < (uint32_t)SURV_CAP) surv[(int64_t)(q0 + ql) * SURV_CAP + pos] = finish_key(av, ql, id, invnorm[id]);
                     }
                     ++slot;

@@ -209,11 +209,11 @@ __global__ __launch_bounds__(1024) void k_select(uint64_t* __restrict__ surv, ui
     const int b = (int)blockIdx.x, tid = threadIdx.x;
     uint64_t* list = surv + (int64_t)b * SURV_CAP;
     Selected s;
-    const uint32_t raw = select_keys(list, cnt + b, k1, margin, may_have_empty != 0, keep_max, SEL_PASS, sh, s);
+    const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, margin, may_have_empty != 0, keep_max, SEL_PASS, sh, s);
     if (raw > (uint32_t)SURV_CAP && tid == 0) { atomicAdd(counters + 1, 1u); flags[b] |= 1u; }
     store_kept(s, list);                            // (every lane has also read the count by now)
     if (tid == 0) {
-        cnt[b] = s.kept;
+        *slot_counter(cnt, b) = s.kept;
         thr[b] = (s.keep_all ? -2.0f : s.tau) / invq[b];      // no threshold: a finite floor, see k_prep_queries
     }
 }
