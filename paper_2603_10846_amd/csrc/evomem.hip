@@ -434,14 +434,19 @@ int launch_mfma_any(evomem* h, const Scratch& sc, hipStream_t st, int Bp, int qt
 template <int NB>
 int launch_gemv(evomem* h, const Scratch& sc, hipStream_t st, int B, const Level& L, const Mask& mask) {
     unsigned char* ws = sc.base;
-    const bool split = L.ntiles < 1024;        // few tiles: four workgroups per tile
-    dim3 grid((unsigned)(split ? 4 * L.ntiles : L.ntiles)), block(256);
+    // Workgroups per tile.  Measured with 16 and with 4 (us): one query, 205 tiles of 768 28.8, 32.2, 476 tiles of 72 16.6, 14.4;
+    // four queries, 52 tiles of 768 16.5, 18.0, 205 tiles of 768 41.4, 36.6.
+    const int wgs = L.ntiles <= (NB <= 2 ? 256 : 64) ? 16 : L.ntiles < 1024 ? 4 : 1;
+    dim3 grid((unsigned)(wgs * L.ntiles)), block(256);
     const float* invq = (const float*)(ws + sc.w.invq);
     const float* thr = (const float*)(ws + sc.w.thr);
     const float* qf = (const float*)(ws + sc.w.qf);
     uint32_t* cnt = (uint32_t*)(ws + sc.w.cnt);
     uint64_t* surv = (uint64_t*)(ws + sc.w.surv);
-    if (split)
+    if (wgs == 16)
+        hipLaunchKernelGGL((k_scan_gemv32<NB, 1>), grid, block, 0, st, (const float*)h->store, (const float*)h->invnorm, qf, invq,
+                           thr, cnt, surv, h->N, h->nkb, B, L, mask);
+    else if (wgs == 4)
         hipLaunchKernelGGL((k_scan_gemv32<NB, 4>), grid, block, 0, st, (const float*)h->store, (const float*)h->invnorm, qf, invq,
                            thr, cnt, surv, h->N, h->nkb, B, L, mask);
     else

@@ -1,5 +1,5 @@
-"""The scan of sparse passes: edges of its query tiles (16, 32, 64), of the bank's tiles, of the k dimension's split over
-eight wavefronts, masks, one pass and several, against the oracle."""
+"""The scans of sparse passes: edges of the query tiles (16, 32, 64; up to 4 queries on fp32 rows), of the bank's tiles, of
+the k dimension's split over eight wavefronts, masks, one pass and several, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,8 @@ DT = {"f32": 0, "bf16": 1, "f16": 2}
 @pytest.mark.parametrize("masked", [False, True])
 @pytest.mark.parametrize("dtype,N,d,nq", [
     ("bf16", 1, 8, 1), ("f16", 255, 64, 16), ("f32", 257, 72, 17), ("bf16", 8192, 320, 32), ("f16", 8193, 200, 33),
-    ("f32", 9001, 520, 64), ("bf16", 16641, 1032, 65), ("f16", 16385, 2056, 7), ("f32", 30011, 136, 9), ("bf16", 30000, 192, 129)])
+    ("f32", 9001, 520, 64), ("bf16", 16641, 1032, 65), ("f16", 16385, 2056, 7), ("f32", 30011, 136, 9), ("bf16", 30000, 192, 129),
+    ("f32", 257, 72, 1), ("f32", 9001, 328, 2), ("f32", 20003, 136, 4)])
 def test_sparse_passes_match_oracle(orc, dtype, N, d, nq, masked):
     rng = np.random.default_rng([41, N, nq])
     rows = _unit(rng, N, d) * rng.uniform(0.5, 2.0, (N, 1)).astype(np.float32)
