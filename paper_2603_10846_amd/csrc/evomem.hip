@@ -793,15 +793,13 @@ extern "C" int mem_update_q(evomem_t* h, const int32_t* ids_dev, int64_t M, int 
     static bool lds_set[MAX_DEVICES] = {};          // the kernel's LDS list can exceed the default 64 KB limit
     if (!lds_set[h->device]) {
         HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_update_q), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (UPD_CHUNK + UPD_PAD) * 8));
+                                   (int)upd_lds(UPD_CHUNK)));
         lds_set[h->device] = true;
     }
     for (int64_t off = 0; off < M; off += UPD_CHUNK) {
         int m = (int)(M - off < UPD_CHUNK ? M - off : UPD_CHUNK);
         const int lg = upd_log2_buckets(m);
-        int npad = 2;                      // a bucket may receive every pair of the launch
-        while (npad < m) npad <<= 1;
-        hipLaunchKernelGGL(k_update_q, dim3(1u << lg), dim3(1024), (size_t)(npad + UPD_PAD) * 8, st, ids_dev + off, rewards_dev + off, m,
+        hipLaunchKernelGGL(k_update_q, dim3(1u << lg), dim3(1024), upd_lds(m), st, ids_dev + off, rewards_dev + off, m,
                            h->q + (int64_t)stage * h->capacity, h->N, alpha, counters, lg);
         LAUNCHCHK();
     }
