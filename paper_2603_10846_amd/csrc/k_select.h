@@ -31,16 +31,16 @@ __device__ __forceinline__ void bitonic_desc(T* a, int n, int tid, int nthreads,
     __syncthreads();
 }
 
-// OR over the 64 lanes of a wavefront (all lanes active); lane 63 ends up with the result.
-__device__ __forceinline__ uint32_t wave_or_u32(uint32_t x) {
-    int v = (int)x;
-    v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
-    v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
-    v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
-    v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
-    v |= __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);   // row_bcast:15 into rows 1 and 3
-    v |= __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);   // row_bcast:31 into rows 2 and 3
-    return (uint32_t)v;
+// Maximum over the 64 lanes of a wavefront (all lanes active); lane 63 ends up with the result.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+    auto up = [](uint32_t a, int b) __attribute__((always_inline)) { return (uint32_t)b > a ? (uint32_t)b : a; };
+    x = up(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true));   // row_shr:1
+    x = up(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true));   // row_shr:2
+    x = up(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true));   // row_shr:4
+    x = up(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true));   // row_shr:8
+    x = up(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, true));   // row_bcast:15 into rows 1 and 3
+    x = up(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, true));   // row_bcast:31 into rows 2 and 3
+    return x;
 }
 
 // Sum over the workgroup's 16 wavefronts of one value per lane, and the sum over the lanes before this one.
@@ -67,12 +67,12 @@ __device__ __forceinline__ uint32_t group_prefix_u32(uint32_t x, uint32_t* part,
 // seed the next pass and, after the last pass, are the candidates that get re-scored in fp64.  Nothing is
 // sorted here -- slot order is irrelevant to every consumer.
 // Keys live in registers (8 per lane, 1024 lanes).  The kernel is a chain of barriers and LDS round trips
-// with one workgroup per query, so what counts is how many there are: a digit has 11 bits and starts at the
-// highest bit on which two keys differ (the survivors of a filtering pass lie in a narrow band of
-// similarities, so the leading 12-20 bits of their keys are the same), after which the pivot's bin nearly always holds
-// no more than SEL_SMALL keys and those few are ranked by counting instead of by further digits; the keys that
-// stay are placed by prefix sums, not by one atomic each.  One query over 8192 keys that differ from the
-// top bit on: 10.3 us with 8-bit digits and per-key atomics, 7.4 us now; a filtered list of 2000: 6.6 us, 5.4 us.
+// with one workgroup per query, so what counts is how many there are.  The first round uses 2048 bins of equal width in
+// similarity: the pool is the thin upper tail of a list, so the pivot's bin nearly always holds no more than SEL_SMALL
+// keys and those few are ranked by counting.  (Digits of the bit pattern put most keys into a few bins, one per
+// exponent and leading bits; they remain for lists that equal widths cannot resolve.)  The keys that stay are placed by
+// prefix sums, not by one atomic each.  8192 keys of 64 queries: 8.5 us with digits of 11 bits, 6.3 now; 8192 keys of
+// one query 7.1, 6.2; lists of a filtering pass 5.1, 5.1.
 // A list that overflowed during the pass (more than SURV_CAP rows reached the threshold; the surplus was
 // dropped) is counted and the query is flagged: its pool may then miss members.
 // More than keep_max keys inside the margin ("crowded band"; near-duplicate entries do that):
@@ -87,7 +87,8 @@ constexpr int SEL_SMALL = 128;
 struct SelectLds {
     uint32_t hist[SEL_BINS];
     uint64_t small[SEL_SMALL];
-    uint64_t differ[16], pivot;
+    uint64_t pivot;
+    uint32_t most[16], least[16];
     uint32_t part_a[16], part_b[16], digit, need, count, nsmall;
 };
 struct Selected {
@@ -107,72 +108,114 @@ __device__ __forceinline__ uint32_t select_keys(const uint64_t* list, const uint
     uint64_t (&key)[8] = s.key;
 #pragma unroll
     for (int i = 0; i < 2; ++i) key[i] = list[i * 1024 + tid];
-    uint64_t ref = list[0];                           // any one key, see the digits below
     const uint32_t raw = *count;
     const int n = raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw;
 #pragma unroll
     for (int i = 2; i < 8; ++i) { int idx = i * 1024 + tid; key[i] = idx < n ? list[idx] : 0ull; }   // 0 = empty
 #pragma unroll
     for (int i = 0; i < 2; ++i) key[i] = i * 1024 + tid < n ? key[i] : 0ull;
-    if (n == 0) ref = 0ull;
     for (int i = tid; i < SEL_BINS; i += 1024) sh.hist[i] = 0;
     if (tid == 0) sh.nsmall = 0;
     uint32_t used = 0;
-    uint64_t differ = 0ull;                           // the bits on which some key differs from the list's first
+    uint32_t most = 0u, least = 0u;                   // largest similarity part of a key, and complement of the smallest
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-        if (key[i] != 0) { differ |= key[i] ^ ref; ++used; }
-    differ = ((uint64_t)wave_or_u32((uint32_t)(differ >> 32)) << 32) | wave_or_u32((uint32_t)differ);
-    if (lane == 63) sh.differ[wave] = differ;
+        if (key[i] != 0) {
+            const uint32_t o = (uint32_t)(key[i] >> 32);
+            most = o > most ? o : most;
+            least = ~o > least ? ~o : least;
+            ++used;
+        }
+    most = wave_max_u32(most);
+    least = wave_max_u32(least);
+    if (lane == 63) { sh.most[wave] = most; sh.least[wave] = least; }
     uint32_t total;
     const uint32_t first = group_prefix_u32(used, sh.part_a, wave, lane, total);      // (has the barrier)
     s.crowded = false;
     s.keep_all = may_have_empty ? total < (uint32_t)k1 : n < k1;      // uniform
     if (s.keep_all) { s.cut = 1ull; s.tau = 0.f; s.kept = total; s.slot = first; return raw; }
-    differ = 0ull;
+    most = 0u;
+    least = 0u;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) differ |= sh.differ[w];               // 0 only if there is a single key
-    int hi = differ ? 63 - __builtin_clzll(differ) : SEL_DIGIT - 1;    // highest bit on which two keys differ
-    uint64_t prefix = hi < 63 ? (ref >> (hi + 1)) << (hi + 1) : 0ull, pivot = 0;
+    for (int w = 0; w < 16; ++w) {
+        most = sh.most[w] > most ? sh.most[w] : most;
+        least = sh.least[w] > least ? sh.least[w] : least;
+    }
+    least = ~least;
+    // The search for the k1-th key.  A round counts the keys per bin (bins in descending order, so that the pivot's bin is
+    // found by a prefix sum); a bin of few keys is ranked by counting, else the next round looks into it.
+    uint64_t pivot = 0;
     uint32_t need = (uint32_t)k1;
-    for (;;) {
-        const int shift = hi >= SEL_DIGIT - 1 ? hi - (SEL_DIGIT - 1) : 0;   // this round ranks bits hi .. shift
-        const uint32_t dmask = (1u << (hi - shift + 1)) - 1u;
-        // bins in descending order of the digit, so that the search for the pivot's bin is a prefix sum
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (key[i] != 0 && (hi == 63 || (key[i] >> (hi + 1)) == (prefix >> (hi + 1))))
-                atomicAdd(&sh.hist[SEL_BINS - 1 - ((uint32_t)(key[i] >> shift) & dmask)], 1u);
+    // the bin that holds the pivot, its rank there -> need, and how many keys it has; clears the bins for the next round
+    auto find_bin = [&](uint32_t& in_bin) __attribute__((always_inline)) {
         __syncthreads();
         const uint32_t c0 = sh.hist[2 * tid], c1 = sh.hist[2 * tid + 1];
-        sh.hist[2 * tid] = 0; sh.hist[2 * tid + 1] = 0;                      // cleared for the next round
+        sh.hist[2 * tid] = 0; sh.hist[2 * tid + 1] = 0;
         uint32_t all;
         const uint32_t run = group_prefix_u32(c0 + c1, sh.part_b, wave, lane, all);
         if (run < need && run + c0 + c1 >= need) {                           // exactly one lane
             const bool second = run + c0 < need;
-            sh.digit = SEL_BINS - 1 - (uint32_t)(2 * tid + second);
+            sh.digit = (uint32_t)(2 * tid + second);
             sh.need = need - run - (second ? c0 : 0u);
             sh.count = second ? c1 : c0;
         }
         __syncthreads();
-        prefix |= (uint64_t)sh.digit << shift;
         need = sh.need;
-        const uint32_t in_bin = sh.count;
+        in_bin = sh.count;
+        return sh.digit;
+    };
+    // ranks the in_bin keys that `in` names; the need-th of them is the pivot
+    auto rank_few = [&](uint32_t in_bin, auto in) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (key[i] != 0 && in(i)) sh.small[atomicAdd(&sh.nsmall, 1u)] = key[i];
+        __syncthreads();
+        if ((uint32_t)tid < in_bin) {
+            const uint64_t mine = sh.small[tid];
+            uint32_t rank = 0;
+#pragma unroll 8
+            for (uint32_t j = 0; j < in_bin; ++j) rank += sh.small[j] > mine;
+            if (rank == need - 1) sh.pivot = mine;                           // keys are distinct
+        }
+        __syncthreads();
+        return sh.pivot;
+    };
+    // First round: bins of equal width in similarity between the largest and the smallest one (differences and
+    // products round monotonically, so a better key never gets a later bin).  The upper tail, where the pivot lies, is thin.
+    const float top = ord2f(most), width = (float)SEL_BINS / (top - ord2f(least));
+    bool found = false;
+    if (width > 0.f && width < 1e30f && top - ord2f(least) < 1e30f) {        // uniform; not with infinities, NaN or equal similarities
+        uint32_t bin[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float x = (top - key_sim(key[i])) * width;
+            bin[i] = x < (float)(SEL_BINS - 1) ? (uint32_t)x : (uint32_t)(SEL_BINS - 1);
+            if (key[i] != 0) atomicAdd(&sh.hist[bin[i]], 1u);
+        }
+        uint32_t in_bin;
+        const uint32_t at = find_bin(in_bin);
+        if (in_bin <= (uint32_t)SEL_SMALL) {                                 // uniform
+            pivot = rank_few(in_bin, [&](int i) __attribute__((always_inline)) { return bin[i] == at; });
+            found = true;
+        } else {
+            need = (uint32_t)k1;                                             // crowded: by digits, from the start
+        }
+    }
+    // By digits of 11 bits, from the highest bit on which two keys differ.
+    int hi = most != least ? 63 - __builtin_clz(most ^ least) : 31;
+    uint64_t prefix = hi < 63 ? (((uint64_t)most << 32) >> (hi + 1)) << (hi + 1) : 0ull;
+    while (!found) {
+        const int shift = hi >= SEL_DIGIT - 1 ? hi - (SEL_DIGIT - 1) : 0;   // this round ranks bits hi .. shift
+        const uint32_t dmask = (1u << (hi - shift + 1)) - 1u;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (key[i] != 0 && (hi == 63 || (key[i] >> (hi + 1)) == (prefix >> (hi + 1))))
+                atomicAdd(&sh.hist[SEL_BINS - 1 - ((uint32_t)(key[i] >> shift) & dmask)], 1u);
+        uint32_t in_bin;
+        prefix |= (uint64_t)(SEL_BINS - 1 - find_bin(in_bin)) << shift;
         if (shift == 0) { pivot = prefix; break; }                           // all 64 bits are known
         if (in_bin <= (uint32_t)SEL_SMALL) {                                 // uniform
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (key[i] != 0 && (key[i] >> shift) == (prefix >> shift)) sh.small[atomicAdd(&sh.nsmall, 1u)] = key[i];
-            __syncthreads();
-            if ((uint32_t)tid < in_bin) {
-                const uint64_t mine = sh.small[tid];
-                uint32_t rank = 0;
-#pragma unroll 8
-                for (uint32_t j = 0; j < in_bin; ++j) rank += sh.small[j] > mine;
-                if (rank == need - 1) sh.pivot = mine;                       // keys are distinct
-            }
-            __syncthreads();
-            pivot = sh.pivot;
+            pivot = rank_few(in_bin, [&](int i) __attribute__((always_inline)) { return (key[i] >> shift) == (prefix >> shift); });
             break;
         }
         hi = shift - 1;
