@@ -596,8 +596,8 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
             LAUNCHCHK();
         }
         if (plan.n > 1) {                                            // (a single pass never overflows)
-            int parts = EXACT_WALK_PARTS;                            // a part's share of the query's slots holds a pool
-            while (SURV_CAP / parts < k1) parts >>= 1;
+            int parts = EXACT_WALK_PARTS;                            // a part's share of the query's slots holds a pool and its guard band
+            while (SURV_CAP / parts < keep_of(k1)) parts >>= 1;
             with_store_type(h->dtype, [&](auto dt) {
                 hipLaunchKernelGGL(k_exact_walk<decltype(dt)::value>, dim3((unsigned)B, (unsigned)parts), dim3(1024), 0, st, (const void*)h->store,
                                    (const float*)qf, (const double*)invq64, surv, cnt, exact, exact_stride, h->N, h->nkb, k1, keep_of(k1));

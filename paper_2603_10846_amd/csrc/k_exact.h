@@ -177,11 +177,12 @@ __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ su
 
 // The lost queries: gridDim.y workgroups each walk a part of the bank, a tile at a time, with a list in LDS of
 // the rows that reach the part's own cut; when the list has no room for another tile it is sorted and cut back
-// to the k1 best, which gives the next cut.  Each leaves its best in a share of the query's survivor slots (at
-// least k1 of them) and the last one to finish selects from the shares.  Queries that are not lost leave at
+// as a pass's list is, which gives the next cut.  Each leaves its best in a share of the query's survivor slots (at
+// least keep_of(k1) of them) and the last one to finish selects from the shares.  Queries that are not lost leave at
 // once.  Over the 1M x 1024 bank one such query takes 1.5 ms on top of the passes and 64 of them 33 ms, fp64
 // arithmetic being the bound (4.5 and 23 ms in all by ranges of 7,680 entries, which every query had to walk).
 constexpr int WALK_CAP = 4096;
+static_assert(keep_of(BIG_K1_MAX) <= WALK_CAP - TILE_ROWS, "a list that was cut back has room for a tile");
 template <int DT>
 __global__ __launch_bounds__(1024) void k_exact_walk(const void* __restrict__ store_, const float* __restrict__ qf,
                                                      const double* __restrict__ invq64, uint64_t* __restrict__ surv,
@@ -217,7 +218,15 @@ __global__ __launch_bounds__(1024) void k_exact_walk(const void* __restrict__ st
             if (tid == 0) n_s = (uint32_t)(n < k1 ? n : k1);
             __syncthreads();
             bitonic_desc(keys, WALK_CAP, tid, 1024, [](uint64_t x, uint64_t y) { return x < y; });
-            if (n >= k1) cut = keys[k1 - 1];
+            if (n >= k1) {                          // as between two passes: the k1 best and what lies within two fp32 roundings of the k1-th,
+                cut = keys[k1 - 1];                 // or exactly the k1 best when that is more than keep_max
+                const uint64_t band = (uint64_t)f2ord(key_sim(cut) - EXACT_KEY_MARGIN) << 32;
+                if (keys[keep_max] < band) {        // uniform
+                    cut = band;
+                    for (int i = k1 + tid; i <= keep_max; i += 1024)
+                        if (keys[i] < band && keys[i - 1] >= band) n_s = (uint32_t)i;
+                }
+            }
         }
     }
     __syncthreads();

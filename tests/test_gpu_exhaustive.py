@@ -86,3 +86,39 @@ def test_lost_queries_walk_the_bank(orc, dtype, k1, nq):
         parity.check_retrieve(orc, stored, qr, qtab[0], k1, 8, 0.5, ex, ora_recall=(ids, sims))
         assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
     bank.close()
+
+
+@pytest.mark.parametrize("k1,nq", [(64, 2), (300, 1), (2048, 3)])
+def test_lost_query_orders_its_boundary_in_fp64(orc, k1, nq):
+    """A lost query whose pool stands in neighbouring tiles, with two dozen rows to every fp32 step of the
+    similarity: the rows that tie with the k1-th in fp32 reach the fp64 re-scoring from the walk too, so the pool is the
+    oracle's without a swap.  (Similarities here differ by 2e-9 on average, fp64 sums over 64 products by 1e-15.)"""
+    rng = np.random.default_rng([33, k1])
+    N, d, n_near = 60000, 64, 9216
+    lib = B.load()
+    st_, rh_, nt_ = (C.c_int * 16)(), (C.c_int * 16)(), (C.c_int * 16)()
+    n = lib.mem_plan_levels(N, k1, st_, rh_, nt_, 16)
+    rows = _unit(rng, N, d)
+    v = _unit(rng, 1, d)[0].astype(np.float64)
+    free = np.flatnonzero((np.arange(N) // 256) % st_[n - 2] != 0)   # rows that only the last pass meets
+    sims = np.sort(1.0 - rng.uniform(0, 2e-5, n_near))[::-1].reshape(-1, 256)
+    sims = np.concatenate([rng.permutation(s) for s in sims])        # best tiles first, any order within a tile
+    side = rng.standard_normal((n_near, d))
+    side -= (side @ v)[:, None] * v
+    side /= np.linalg.norm(side, axis=1, keepdims=True)
+    rows[free[:n_near]] = (sims[:, None] * v + np.sqrt(1 - sims**2)[:, None] * side).astype(np.float32)
+    q = _unit(rng, nq, d)
+    q[0] = v
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    ids, osims = orc.recall(rows, q, k1, threads=8)
+    all_sims = orc.sims_of(rows, q[0], np.arange(N, dtype=np.int32))
+    in_step, in_band = [(all_sims > osims[0, k1 - 1] - w).sum() for w in (3e-8, 3.6e-7)]
+    assert k1 + 5 < in_step and in_band < (512 if k1 <= 256 else k1 + 256)      # the case is what it claims to be
+    print(f"lost query, boundary of k1={k1}: {in_band} rows in the band", flush=True)
+    bank = B.MemoryBank(d, "f32", N, max_B=nq, max_k1=k1)
+    bank.append(_dev(rows), _dev(qtab[0]), _dev(qtab[1]))
+    ex = _exact(bank, q, 0, k1, 8, 0.5)
+    stats = parity.check_retrieve(orc, rows, q, qtab[0], k1, 8, 0.5, ex, ora_recall=(ids, osims))
+    assert stats["boundary_swaps"] == 0 and stats["order_swaps"] == 0 and stats["final_swaps"] == 0, stats
+    assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    bank.close()
