@@ -24,7 +24,7 @@
 
 using namespace evk;
 
-static_assert(MEM_MAX_K1 == evk::BIG_K1_MAX, "header and kernels disagree on the largest pool");
+static_assert(MEM_MAX_K1 == evk::BIG_K1_MAX && MEM_MAX_B == evk::MAX_BATCH, "header and kernels disagree on the largest pool or batch");
 
 namespace {
 
@@ -527,6 +527,24 @@ int launch_exact_scan(evomem* h, const Scratch& sc, hipStream_t st, int B, const
     return MEM_OK;
 }
 
+// What the passes of the exhaustive selection lost (most calls: nothing, and the launch ends at once).
+template <int DT>
+int launch_exact_walk(evomem* h, const Scratch& sc, hipStream_t st, int B, int k1) {
+    auto kern = k_exact_walk<DT>;
+    static bool lds_set[MAX_DEVICES] = {};
+    if (!lds_set[h->device]) {
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, WALK_LDS));
+        lds_set[h->device] = true;
+    }
+    unsigned char* ws = sc.base;
+    const int lists = (int)((sc.w.exact - sc.w.surv) / (SURV_CAP * sizeof(uint64_t)));    // survivor lists in the scratch, at least B
+    hipLaunchKernelGGL(kern, dim3(WALK_GROUPS), dim3(WALK_T), WALK_LDS, st, (const void*)h->store, (const float*)(ws + sc.w.qf),
+                       (const double*)(ws + sc.w.invq64), (uint64_t*)(ws + sc.w.surv), (const uint32_t*)(ws + sc.w.cnt),
+                       (double*)(ws + sc.w.exact), sc.exact_stride, h->N, h->nkb, k1, B, lists);
+    LAUNCHCHK();
+    return MEM_OK;
+}
+
 }  // namespace
 
 extern "C" int mem_plan_levels(int64_t N, int k1, int* stride, int* rho, int* ntiles, int max_levels) {
@@ -596,13 +614,11 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
             LAUNCHCHK();
         }
         if (plan.n > 1) {                                            // (a single pass never overflows)
-            int parts = EXACT_WALK_PARTS;                            // a part's share of the query's slots holds a pool and its guard band
-            while (SURV_CAP / parts < keep_of(k1)) parts >>= 1;
+            int rc = MEM_OK;
             with_store_type(h->dtype, [&](auto dt) {
-                hipLaunchKernelGGL(k_exact_walk<decltype(dt)::value>, dim3((unsigned)B, (unsigned)parts), dim3(1024), 0, st, (const void*)h->store,
-                                   (const float*)qf, (const double*)invq64, surv, cnt, exact, exact_stride, h->N, h->nkb, k1, keep_of(k1));
+                rc = launch_exact_walk<decltype(dt)::value>(h, sc, st, B, k1);
             });
-            LAUNCHCHK();
+            if (rc != MEM_OK) return rc;
         }
     }
     if (h->N > 0 && !exhaustive) {
@@ -643,7 +659,7 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     ta.store = h->store; ta.qf = qf; ta.invq64 = invq64; ta.exact = exact; ta.qstage = h->q + (int64_t)stage * h->capacity;
     ta.out_ids = out_ids_dev; ta.out_scores = out_scores_dev; ta.cand_ids = out_cand_ids_dev; ta.cand_sims = out_cand_sims_dev;
     ta.lambda = (double)lambda; ta.nkb = h->nkb; ta.exact_stride = exact_stride; ta.k1 = k1; ta.k2 = k2;
-    ta.may_have_empty = mask.tags != nullptr; ta.mode = exhaustive ? SEL_EXACT : SEL_FINAL; ta.margin = exhaustive ? EXACT_KEY_MARGIN : margin;
+    ta.may_have_empty = mask.tags != nullptr || exhaustive; ta.mode = exhaustive ? SEL_EXACT : SEL_FINAL; ta.margin = exhaustive ? EXACT_KEY_MARGIN : margin;
     const int64_t gather = (int64_t)k1 * h->nkb * KB * (h->dtype == MEM_F32 ? 4 : 2);
     int parts = 1;
     while (parts < 8 && B * parts * 2 <= 256 && gather / parts > 96 * 1024) parts <<= 1;

@@ -9,8 +9,7 @@
 // pool.  There is no error margin in a cut, and ties break by id as in the pool itself, so masses of equal
 // rows pass a cut no more often than distinct rows do.  A list can still overflow when a pass meets thousands of
 // rows that beat everything in the sparser passes (the bank's order decides); such a query is lost, takes
-// part in no further pass, and walks the whole bank by itself afterwards (k_exact_walk), range by range with
-// lists that cannot overflow.
+// part in no further pass, and walks the whole bank afterwards (k_exact_walk), with lists that cannot overflow.
 //
 // Four queries over 1M x 1024 bf16 entries: 4.37 ms when every query read the bank for itself in ranges of 7,680
 // entries (411 launches), 0.49 ms now, of which the last pass is 0.38 ms for 2.0 GB: bound by fp64 multiply-adds and
@@ -23,10 +22,9 @@ namespace evk {
 
 constexpr int EXACT_NB = 8;               // queries per bank read, at most
 constexpr int EXACT_ROWS = 64;            // rows a workgroup scores at a time: 16 lanes per row, 4 rows per lane group
-constexpr int EXACT_WALK_PARTS = 64;      // workgroups of a lost query, at most
 
 // Per-query words of the exhaustive selection, in the space of the query's fp64 similarities (which are
-// written only after the selection): the cut, and the number of workgroups that have walked their part.
+// written only after the selection): the cut, and the number of parts of the bank that have been walked.
 __device__ __forceinline__ uint64_t* exact_words(double* exact, int b, int exact_stride) {
     return reinterpret_cast<uint64_t*>(exact + (int64_t)b * exact_stride);
 }
@@ -175,76 +173,171 @@ __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ su
     if (tid == 0) { *slot_counter(cnt, b) = s.kept; words[0] = s.cut; words[1] = 0ull; }
 }
 
-// The lost queries: gridDim.y workgroups each walk a part of the bank, a tile at a time, with a list in LDS of
-// the rows that reach the part's own cut; when the list has no room for another tile it is sorted and cut back
-// as a pass's list is, which gives the next cut.  Each leaves its best in a share of the query's survivor slots (at
-// least keep_of(k1) of them) and the last one to finish selects from the shares.  Queries that are not lost leave at
-// once.  Over the 1M x 1024 bank one such query takes 1.5 ms on top of the passes and 64 of them 33 ms, fp64
-// arithmetic being the bound (4.5 and 23 ms in all by ranges of 7,680 entries, which every query had to walk).
-constexpr int WALK_CAP = 4096;
-static_assert(keep_of(BIG_K1_MAX) <= WALK_CAP - TILE_ROWS, "a list that was cut back has room for a tile");
-template <int DT>
-__global__ __launch_bounds__(1024) void k_exact_walk(const void* __restrict__ store_, const float* __restrict__ qf,
-                                                     const double* __restrict__ invq64, uint64_t* __restrict__ surv,
-                                                     uint32_t* __restrict__ cnt, double* __restrict__ exact, int exact_stride,
-                                                     int64_t N, int nkb, int k1, int keep_max) {
-    const int b = (int)blockIdx.x, part = (int)blockIdx.y, parts = (int)gridDim.y, tid = threadIdx.x;
-    if (*slot_counter(cnt, b) <= (uint32_t)SURV_CAP) return;       // uniform over the query's workgroups: written only below, by the last of them
-    __shared__ uint64_t keys[WALK_CAP];
-    __shared__ uint32_t n_s, last_s;
-    __shared__ SelectLds sh;
-    const int share = SURV_CAP / parts, sub = tid & 15, r0 = (tid >> 4) * 4;
-    const int64_t tiles = (N + TILE_ROWS - 1) / TILE_ROWS, first = tiles * part / parts, end = tiles * (part + 1) / parts;
-    const float* const qp[1] = {qf + (int64_t)b * nkb * KB + sub * (DT == 0 ? 4 : 8)};
-    uint64_t* list = surv + (int64_t)b * SURV_CAP;
-    uint64_t cut = 0ull;
-    if (tid == 0) n_s = 0;
+// The lost queries walk the bank together, WALK_NB to a group (one at a time while there are only one or two): a
+// workgroup scores a part of the bank for its group, with a list in LDS per query of the rows that reach the query's
+// cut in this part.  A list without room for another step is sorted and cut back as a pass's list is, which gives the
+// next cut.  Each part leaves what it has (at most keep_of(k1) keys) in its share of the survivor slots, and the last
+// part of a group to finish merges the shares into the head of the queries' lists, zeros behind.  The counts stay
+// as they are, above SURV_CAP, while any workgroup may still look for lost queries; the tail takes such a list as full,
+// with empty slots.
+// The shares lie in the survivor lists of the query slots that this call does not use, as long as those give a query
+// more parts than its own list does: tied to its own 8192 slots a pool of 2048 was walked by four workgroups.
+// 1M x 1024 bf16 bank, ms for the whole call: by ranges of 7,680 entries that every query walked; by workgroups of one
+// query, 8192 / k1 of them at most; now.  One lost query of one, pool 64 4.0, 1.4, 0.88, pool 2048 5.4, 15.0, 1.1; four of
+// four, pool 2048 5.9, 15.3, 1.6; 64 of 64, pool 64 23.2, 24.7, 11.0, pool 2048 24.5, 23.8, 15.9.  fp64 arithmetic is the bound.
+constexpr int WALK_T = 512, WALK_ROWS = WALK_T / 4, WALK_NB = 4, WALK_CAP = 4096;
+constexpr int WALK_GROUPS = 256;          // workgroups of the launch: one per compute unit
+constexpr int WALK_LDS = WALK_NB * WALK_CAP * 8;
+static_assert(keep_of(BIG_K1_MAX) <= WALK_CAP - WALK_T, "a list that was cut back has room for a step and for a load of the merge");
+
+struct WalkLds {
+    uint64_t cut[WALK_NB];
+    uint32_t n[WALK_NB], wave_n[WALK_T / 64], last;
+    uint16_t lost[MAX_BATCH];             // the lost queries
+};
+
+// Sorts a list of n keys and cuts it back: the k1 best and what lies within two fp32 roundings of the k1-th, or exactly
+// the k1 best when that is more than keep_max.  All lanes call it, with the keys written before a barrier; ends with one.
+__device__ __forceinline__ void walk_cut_back(uint64_t* keys, int n, int k1, int keep_max, uint32_t* n_out, uint64_t* cut_out) {
+    const int tid = threadIdx.x;
+    int cap = 2;
+    while (cap < n) cap <<= 1;
+    for (int i = n + tid; i < cap; i += WALK_T) keys[i] = 0ull;                    // sorts last
     __syncthreads();
-    for (int64_t t = first; t < end; ++t) {
-        double dot[4][1], ssq[4];
-        score_four_rows<DT, 1>(store_, qp, t, r0, sub, nkb, dot, ssq);
-        if (sub < 4) {
-            const double dv = sub == 0 ? dot[0][0] : sub == 1 ? dot[1][0] : sub == 2 ? dot[2][0] : dot[3][0];
-            const double sv = sub == 0 ? ssq[0] : sub == 1 ? ssq[1] : sub == 2 ? ssq[2] : ssq[3];
-            const int64_t id = t * TILE_ROWS + r0 + sub;
-            const uint64_t key = exact_key(dv * invq64[b] * (1.0 / sqrt(sv)), (int32_t)id);
-            if (id < N && key >= cut) keys[atomicAdd(&n_s, 1u)] = key;      // there is room for a whole tile
-        }
-        __syncthreads();
-        const int n = (int)n_s;
-        __syncthreads();                            // every lane has read it
-        if (n > WALK_CAP - TILE_ROWS || t + 1 == end) {       // uniform
-            for (int i = n + tid; i < WALK_CAP; i += 1024) keys[i] = 0ull;       // sorts last
-            if (tid == 0) n_s = (uint32_t)(n < k1 ? n : k1);
-            __syncthreads();
-            bitonic_desc(keys, WALK_CAP, tid, 1024, [](uint64_t x, uint64_t y) { return x < y; });
-            if (n >= k1) {                          // as between two passes: the k1 best and what lies within two fp32 roundings of the k1-th,
-                cut = keys[k1 - 1];                 // or exactly the k1 best when that is more than keep_max
-                const uint64_t band = (uint64_t)f2ord(key_sim(cut) - EXACT_KEY_MARGIN) << 32;
-                if (keys[keep_max] < band) {        // uniform
-                    cut = band;
-                    for (int i = k1 + tid; i <= keep_max; i += 1024)
-                        if (keys[i] < band && keys[i - 1] >= band) n_s = (uint32_t)i;
-                }
-            }
-        }
+    bitonic_desc(keys, cap, tid, WALK_T, [](uint64_t x, uint64_t y) { return x < y; });
+    if (n < k1) return;                                                            // uniform, as all that follows
+    const uint64_t pivot = keys[k1 - 1], band = (uint64_t)f2ord(key_sim(pivot) - EXACT_KEY_MARGIN) << 32;
+    if (n <= keep_max || keys[keep_max] < band) {
+        for (int i = k1 + tid; i <= (n < keep_max ? n : keep_max); i += WALK_T)
+            if ((i == n || keys[i] < band) && keys[i - 1] >= band) { *n_out = (uint32_t)i; *cut_out = band; }
+    } else if (tid == 0) {
+        *n_out = (uint32_t)k1;
+        *cut_out = pivot;
     }
     __syncthreads();
-    const int have = (int)n_s;
-    for (int i = tid; i < share; i += 1024) list[part * share + i] = i < have ? keys[i] : 0ull;
-    __threadfence();
-    __syncthreads();
-    uint64_t* words = exact_words(exact, b, exact_stride);
-    if (tid == 0) last_s = atomicAdd(reinterpret_cast<uint32_t*>(words + 1), 1u) == (uint32_t)parts - 1u;
-    __syncthreads();
-    if (!last_s) return;                            // uniform
-    __threadfence();
-    Selected s;
-    if (tid == 0) last_s = SURV_CAP;
-    __syncthreads();
-    select_keys(list, &last_s, k1, EXACT_KEY_MARGIN, true, keep_max, SEL_EXACT, sh, s);
-    store_kept(s, list);
-    if (tid == 0) *slot_counter(cnt, b) = s.kept;
+}
+
+template <int DT, int NB>
+__device__ __forceinline__ void walk_lost(const void* store_, const float* qf, const double* invq64, uint64_t* surv, double* exact,
+                                          int exact_stride, int64_t N, int nkb, int k1, int B, int lists, int nlost, uint64_t* keys, WalkLds& sh) {
+    constexpr int R = 4;
+    const int tid = threadIdx.x, sub = tid & 15, grp = tid >> 4, keep = keep_of(k1);
+    const int groups = (nlost + NB - 1) / NB;
+    const int64_t tiles = (N + TILE_ROWS - 1) / TILE_ROWS, spare = (int64_t)(lists - B) * SURV_CAP / ((int64_t)nlost * keep);
+    const bool own = spare <= SURV_CAP / keep;                // the shares in the query's own list
+    int64_t parts = own ? SURV_CAP / keep : spare;
+    if (parts > WALK_GROUPS / groups) parts = WALK_GROUPS / groups > 1 ? WALK_GROUPS / groups : 1;
+    if (parts > tiles) parts = tiles;
+    static_assert(WALK_GROUPS <= WALK_T, "a load of the merge sees every share");
+    for (int64_t item = blockIdx.x; item < groups * parts; item += gridDim.x) {
+        const int g = (int)(item / parts), part = (int)(item % parts);
+        const int live = nlost - g * NB < NB ? nlost - g * NB : NB;                // queries of this group
+        auto query = [&](int j) __attribute__((always_inline)) { return (int)sh.lost[g * NB + (j < live ? j : live - 1)]; };
+        auto share_of = [&](int j) __attribute__((always_inline)) {
+            return own ? surv + (int64_t)query(j) * SURV_CAP : surv + (int64_t)B * SURV_CAP + (int64_t)(g * NB + j) * parts * keep;
+        };
+        auto start = [&]() __attribute__((always_inline)) {                        // empty lists; a valid cut if a pass left one
+            if (tid < NB) {
+                const uint64_t c = exact_words(exact, query(tid), exact_stride)[0];
+                sh.n[tid] = 0;
+                sh.cut[tid] = c == ~0ull ? 0ull : c;
+            }
+            __syncthreads();
+        };
+        const float* qp[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) qp[j] = qf + (int64_t)query(j) * nkb * KB + sub * (DT == 0 ? 4 : 8);
+        start();
+        const int64_t first = tiles * part / parts * (TILE_ROWS / WALK_ROWS), end = tiles * (part + 1) / parts * (TILE_ROWS / WALK_ROWS);
+        for (int64_t u = first; u < end; ++u) {
+            const int64_t t = u / (TILE_ROWS / WALK_ROWS);
+            const int r0 = (int)(u % (TILE_ROWS / WALK_ROWS)) * WALK_ROWS + grp * R;
+            double dot[R][NB], ssq[R];
+            score_four_rows<DT, NB>(store_, qp, t, r0, sub, nkb, dot, ssq);
+            // lane p of a group of 16 finishes pair (row p % R, query p / R)
+            double dv = 0.0, sv = ssq[0];
+            const int i = sub % R, j = sub / R;
+#pragma unroll
+            for (int k = 1; k < R; ++k) sv = i == k ? ssq[k] : sv;
+#pragma unroll
+            for (int k = 0; k < R * NB; ++k) dv = sub == k ? dot[k % R][k / R] : dv;
+            const int64_t id = t * TILE_ROWS + r0 + i;
+            if (j < live && id < N) {
+                const uint64_t key = exact_key(dv * invq64[query(j)] * (1.0 / sqrt(sv)), (int32_t)id);
+                if (key >= sh.cut[j]) keys[j * WALK_CAP + atomicAdd(&sh.n[j], 1u)] = key;   // there is room for a whole step
+            }
+            __syncthreads();
+            for (int l = 0; l < live; ++l) {                                       // uniform
+                const int n = (int)sh.n[l];
+                if (n > WALK_CAP - WALK_ROWS || u + 1 == end) walk_cut_back(keys + l * WALK_CAP, n, k1, keep, &sh.n[l], &sh.cut[l]);
+            }
+            __syncthreads();                                                       // every lane has read the counts
+        }
+        for (int l = 0; l < live; ++l) {
+            uint64_t* share = share_of(l) + (int64_t)part * keep;
+            const int n = (int)sh.n[l];
+            for (int i = tid; i < keep; i += WALK_T) share[i] = i < n ? keys[l * WALK_CAP + i] : 0ull;
+        }
+        __threadfence();
+        __syncthreads();
+        if (tid == 0) sh.last = atomicAdd(reinterpret_cast<uint32_t*>(exact_words(exact, query(0), exact_stride) + 1), 1u) == (uint32_t)parts - 1u;
+        __syncthreads();
+        if (sh.last) {                                                             // uniform
+            __threadfence();
+            start();
+            for (int l = 0; l < live; ++l) {
+                // best ranks of all shares first; they are sorted, so nothing follows a load that brought no key
+                const uint64_t* shares = share_of(l);
+                const int total = (int)parts * keep;
+                int before = 0;
+                for (int i0 = 0; i0 < total; i0 += WALK_T) {
+                    const int i = i0 + tid;
+                    const uint64_t key = i < total ? shares[(i % (int)parts) * keep + i / (int)parts] : 0ull;
+                    if (key != 0ull && key >= sh.cut[l]) keys[l * WALK_CAP + atomicAdd(&sh.n[l], 1u)] = key;
+                    __syncthreads();
+                    const int n = (int)sh.n[l];
+                    if (n == before) break;                                        // uniform
+                    __syncthreads();                                               // every lane has read the count
+                    if (n > WALK_CAP - WALK_T) walk_cut_back(keys + l * WALK_CAP, n, k1, keep, &sh.n[l], &sh.cut[l]);
+                    before = (int)sh.n[l];
+                    __syncthreads();
+                }
+                walk_cut_back(keys + l * WALK_CAP, (int)sh.n[l], k1, keep, &sh.n[l], &sh.cut[l]);
+                uint64_t* list = surv + (int64_t)query(l) * SURV_CAP;
+                const int n = (int)sh.n[l];
+                for (int i = tid; i < SURV_CAP; i += WALK_T) list[i] = i < n ? keys[l * WALK_CAP + i] : 0ull;
+            }
+        }
+        __syncthreads();                                                           // the lists are used again
+    }
+}
+
+template <int DT>
+__global__ __launch_bounds__(WALK_T) void k_exact_walk(const void* __restrict__ store_, const float* __restrict__ qf,
+                                                       const double* __restrict__ invq64, uint64_t* __restrict__ surv,
+                                                       const uint32_t* __restrict__ cnt, double* __restrict__ exact, int exact_stride,
+                                                       int64_t N, int nkb, int k1, int B, int lists) {
+    extern __shared__ __align__(16) uint64_t walk_keys[];
+    __shared__ WalkLds sh;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    int nlost = 0;
+    for (int b0 = 0; b0 < B; b0 += WALK_T) {
+        const bool lost = b0 + tid < B && *slot_counter(cnt, b0 + tid) > (uint32_t)SURV_CAP;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(lost);
+        if (lane == 0) sh.wave_n[wave] = (uint32_t)__popcll(m);
+        __syncthreads();
+        int at = nlost + __popcll(m & ((1ull << lane) - 1ull));
+#pragma unroll
+        for (int w = 0; w < WALK_T / 64; ++w) {
+            at += w < wave ? (int)sh.wave_n[w] : 0;
+            nlost += (int)sh.wave_n[w];
+        }
+        if (lost) sh.lost[at] = (uint16_t)(b0 + tid);
+        __syncthreads();
+    }
+    if (nlost == 0) return;                                                        // uniform
+    if (nlost <= 2) walk_lost<DT, 1>(store_, qf, invq64, surv, exact, exact_stride, N, nkb, k1, B, lists, nlost, walk_keys, sh);
+    else walk_lost<DT, WALK_NB>(store_, qf, invq64, surv, exact, exact_stride, N, nkb, k1, B, lists, nlost, walk_keys, sh);
 }
 
 }  // namespace evk

@@ -211,7 +211,7 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A, EpsGreedy eg) {
     // ---- selection ----
     Selected s;
     const uint32_t raw = select_keys(list, slot_counter(A.cnt, b), k1, A.margin, A.may_have_empty != 0, cap, A.mode, sh, s);
-    if (raw > (uint32_t)SURV_CAP && part == 0 && tid == 0) { atomicAdd(A.counters + 1, 1u); A.flags[b] |= 1u; }
+    if (raw > (uint32_t)SURV_CAP && A.mode == SEL_FINAL && part == 0 && tid == 0) { atomicAdd(A.counters + 1, 1u); A.flags[b] |= 1u; }
     // The last of the query's workgroups to come here?  All that one workgroup hands to another are the similarities
     // below, and those are stored and loaded as device-scope atomics, which pass by the caches that differ between
     // XCDs; so it is enough that a workgroup's stores have been acknowledged before it arrives.  (Device-scope

@@ -122,3 +122,42 @@ def test_lost_query_orders_its_boundary_in_fp64(orc, k1, nq):
     assert stats["boundary_swaps"] == 0 and stats["order_swaps"] == 0 and stats["final_swaps"] == 0, stats
     assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
     bank.close()
+
+
+# one, two, and groups of three and four (the last group partly filled); shares in unused survivor lists (nq < 256) and in
+# the queries' own (256 of 256); parts that hold a tile each and parts that hold many
+@pytest.mark.parametrize("dtype,k1,nq,nlost,d", [
+    ("bf16", 64, 2, 2, 64), ("f32", 300, 40, 3, 136), ("f16", 2048, 9, 9, 64), ("bf16", 1000, 256, 6, 192), ("f32", 2048, 256, 17, 64), ("f16", 8, 256, 256, 64)])
+def test_lost_queries_share_their_walks(orc, dtype, k1, nq, nlost, d):
+    rng = np.random.default_rng([34, k1, nq])
+    N = 30011
+    lib = B.load()
+    st_, rh_, nt_ = (C.c_int * 16)(), (C.c_int * 16)(), (C.c_int * 16)()
+    n = lib.mem_plan_levels(N, k1, st_, rh_, nt_, 16)
+    rows = _unit(rng, N, d)
+    v = _unit(rng, 1, d)
+    free = np.flatnonzero((np.arange(N) // 256) % st_[n - 2] != 0)   # rows that only the last pass meets
+    near = rng.choice(free, 9500, replace=False)
+    rows[near] = v + 0.3 * _unit(rng, near.size, d) * rng.uniform(0.2, 1.0, (near.size, 1)).astype(np.float32)
+    q = _unit(rng, nq, d)
+    lost = np.sort(rng.permutation(nq)[:nlost])
+    q[lost] = v + 0.05 * _unit(rng, nlost, d)
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    print(f"lost queries {dtype} k1={k1} B={nq} lost={nlost} d={d}", flush=True)
+    bank = B.MemoryBank(d, dtype, N, max_B=nq, max_k1=k1)
+    bank.append(_dev(rows), _dev(qtab[0]), _dev(qtab[1]))
+    stored, qr = orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype])
+    look = np.unique(np.concatenate([lost[:12], lost[-5:], rng.permutation(nq)[:8]])).tolist()
+    ids, sims = orc.recall(stored, np.ascontiguousarray(qr[look]), k1, threads=8)
+    for _ in range(2):                                               # the second call starts from the first one's leftovers
+        ex = _exact(bank, q, 0, k1, 8, 0.5)
+        for row, b in enumerate(look):
+            only = sorted(set(ex["cand_ids"][b].tolist()) - set(ids[row].tolist()))
+            if only:
+                assert np.all(orc.sims_of(stored, qr[b], np.array(only, np.int32)) > sims[row, k1 - 1] - 3e-7)
+        parity.check_retrieve(orc, stored, qr, qtab[0], k1, 8, 0.5, ex, ora_recall=(ids, sims), sample=look)
+        assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    # the ordinary retrieve that uses the same lists afterwards
+    plain = parity.gpu_retrieve(bank, torch, q[:4], 0, k1, 8, 0.5)
+    assert plain["cand_ids"].min() >= 0
+    bank.close()
