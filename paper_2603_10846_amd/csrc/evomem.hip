@@ -65,6 +65,7 @@ struct Scratch {
     unsigned char* base;
     Workspace w;
     int exact_stride;      // fp64 similarities per query
+    int lists() const { return (int)((w.exact - w.surv) / (SURV_CAP * sizeof(uint64_t))); }    // survivor lists, at least one per query
 };
 
 // Limits of mem_retrieve_static and the library's own scratch array for it (see the header).
@@ -537,10 +538,9 @@ int launch_exact_walk(evomem* h, const Scratch& sc, hipStream_t st, int B, int k
         lds_set[h->device] = true;
     }
     unsigned char* ws = sc.base;
-    const int lists = (int)((sc.w.exact - sc.w.surv) / (SURV_CAP * sizeof(uint64_t)));    // survivor lists in the scratch, at least B
     hipLaunchKernelGGL(kern, dim3(WALK_GROUPS), dim3(WALK_T), WALK_LDS, st, (const void*)h->store, (const float*)(ws + sc.w.qf),
                        (const double*)(ws + sc.w.invq64), (uint64_t*)(ws + sc.w.surv), (const uint32_t*)(ws + sc.w.cnt),
-                       (double*)(ws + sc.w.exact), sc.exact_stride, h->N, h->nkb, k1, B, lists);
+                       (double*)(ws + sc.w.exact), sc.exact_stride, h->N, h->nkb, k1, B, sc.lists());
     LAUNCHCHK();
     return MEM_OK;
 }
@@ -654,9 +654,10 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     // 64 queries, 64 x 4 KB 32.8, 24.1, 23.6, 38.2; 128 queries, 256 x 8 KB 163, 116, 146, 152; 64 queries, 960 x 2 KB 135, 87, 66,
     // 74; one query, 32 x 3 KB 14.9, 16.0, 16.3, 16.3.
     TailArgs ta{};
+    ta.eg = eg;
     ta.surv = surv; ta.cnt = cnt; ta.counters = counters; ta.flags = flags;
     ta.arrived = reinterpret_cast<uint32_t*>(qop + (int64_t)(h->dtype == MEM_F32 ? 2 * h->nkb : h->nkb) * Bp * KB);
-    ta.store = h->store; ta.qf = qf; ta.invq64 = invq64; ta.exact = exact; ta.qstage = h->q + (int64_t)stage * h->capacity;
+    ta.store = h->store; ta.qf = qf; ta.invq64 = invq64; ta.exact = exact; ta.spare = sc.lists() >= 2 * B ? surv + (int64_t)B * SURV_CAP : nullptr; ta.qstage = h->q + (int64_t)stage * h->capacity;
     ta.out_ids = out_ids_dev; ta.out_scores = out_scores_dev; ta.cand_ids = out_cand_ids_dev; ta.cand_sims = out_cand_sims_dev;
     ta.lambda = (double)lambda; ta.nkb = h->nkb; ta.exact_stride = exact_stride; ta.k1 = k1; ta.k2 = k2;
     ta.may_have_empty = mask.tags != nullptr || exhaustive; ta.mode = exhaustive ? SEL_EXACT : SEL_FINAL; ta.margin = exhaustive ? EXACT_KEY_MARGIN : margin;
@@ -677,8 +678,8 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     with_store_type(h->dtype, [&](auto dt) {
         constexpr int DT = decltype(dt)::value;
         const dim3 grid((unsigned)B, (unsigned)parts), block(TAIL_T);
-        if (big) hipLaunchKernelGGL((k_tail<DT, true>), grid, block, tail_lds(k1), st, ta, eg);
-        else hipLaunchKernelGGL((k_tail<DT, false>), grid, block, tail_lds(k1), st, ta, eg);
+        if (big) hipLaunchKernelGGL((k_tail<DT, true>), grid, block, tail_lds(k1), st, ta);
+        else hipLaunchKernelGGL((k_tail<DT, false>), grid, block, tail_lds(k1), st, ta);
     });
     LAUNCHCHK();
     return MEM_OK;

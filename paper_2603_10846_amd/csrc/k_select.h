@@ -100,11 +100,10 @@ struct Selected {
     bool keep_all;       // fewer keys than the pool has members: all stay and there is no threshold
     bool crowded;
 };
-// Returns the list's count as the scan left it (it may exceed the list's size).  The count and the first quarter of
-// the list, which is what a filtering pass fills, are requested together.
-__device__ __forceinline__ uint32_t select_keys(const uint64_t* list, const uint32_t* count, int k1, float margin, bool may_have_empty,
-                                                int keep_max, int mode, SelectLds& sh, Selected& s) {
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+// Reads a list into the lanes' registers; returns its count as the scan left it (it may exceed the list's size).  The
+// count and the first quarter of the list, which is what a filtering pass fills, are requested together.
+__device__ __forceinline__ uint32_t load_keys(const uint64_t* list, const uint32_t* count, Selected& s) {
+    const int tid = threadIdx.x;
     uint64_t (&key)[8] = s.key;
 #pragma unroll
     for (int i = 0; i < 2; ++i) key[i] = list[i * 1024 + tid];
@@ -114,6 +113,13 @@ __device__ __forceinline__ uint32_t select_keys(const uint64_t* list, const uint
     for (int i = 2; i < 8; ++i) { int idx = i * 1024 + tid; key[i] = idx < n ? list[idx] : 0ull; }   // 0 = empty
 #pragma unroll
     for (int i = 0; i < 2; ++i) key[i] = i * 1024 + tid < n ? key[i] : 0ull;
+    return raw;
+}
+
+// Selects among the keys in the registers (n of them, or fewer where some are empty).
+__device__ __forceinline__ void select_keys(int n, int k1, float margin, bool may_have_empty, int keep_max, int mode, SelectLds& sh, Selected& s) {
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const uint64_t (&key)[8] = s.key;
     for (int i = tid; i < SEL_BINS; i += 1024) sh.hist[i] = 0;
     if (tid == 0) sh.nsmall = 0;
     uint32_t used = 0;
@@ -133,7 +139,7 @@ __device__ __forceinline__ uint32_t select_keys(const uint64_t* list, const uint
     const uint32_t first = group_prefix_u32(used, sh.part_a, wave, lane, total);      // (has the barrier)
     s.crowded = false;
     s.keep_all = may_have_empty ? total < (uint32_t)k1 : n < k1;      // uniform
-    if (s.keep_all) { s.cut = 1ull; s.tau = 0.f; s.kept = total; s.slot = first; return raw; }
+    if (s.keep_all) { s.cut = 1ull; s.tau = 0.f; s.kept = total; s.slot = first; return; }
     most = 0u;
     least = 0u;
 #pragma unroll
@@ -232,6 +238,11 @@ __device__ __forceinline__ uint32_t select_keys(const uint64_t* list, const uint
         if (mode != SEL_EXACT) break;
         s.cut = pivot;                              // ties within fp32 resolution: exactly the k1 best
     }
+}
+__device__ __forceinline__ uint32_t select_keys(const uint64_t* list, const uint32_t* count, int k1, float margin, bool may_have_empty,
+                                                int keep_max, int mode, SelectLds& sh, Selected& s) {
+    const uint32_t raw = load_keys(list, count, s);
+    select_keys(raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw, k1, margin, may_have_empty, keep_max, mode, sh, s);
     return raw;
 }
 

@@ -25,6 +25,7 @@ namespace evk {
 
 constexpr int TAIL_T = 1024;
 constexpr int TAIL_CROWD = 64;            // entries of one bucket that are still ranked by counting
+constexpr int TAIL_PIECE = 2048;          // ids of a crowded band that are laid out at a time (whole blocks of 512)
 
 // LDS besides the static part (dynamic), in this order: v0[cap] f64, v1[k1p] f64, i0[cap] i32, i1[k1p] i32, q0[cap] f32, q1[k1p] f32,
 // then for pools of more than 256 order[sort_cap] u32; cap = keep_of(k1), k1p = k1 rounded up to 64, sort_cap = cap rounded up to a
@@ -34,6 +35,7 @@ __host__ __device__ constexpr int tail_pow2(int x) { int p = 64; while (p < x) p
 __host__ __device__ constexpr size_t tail_lds(int k1) {
     return (size_t)keep_of(k1) * 16 + (size_t)tail_pad64(k1) * 16 + (k1 > SMALL_K1_MAX ? (size_t)tail_pow2(keep_of(k1)) * 4 : 0);
 }
+static_assert(TAIL_PIECE * 4 <= tail_lds(1), "a piece of a crowded band's ids lies where the candidates will");
 
 // A NaN similarity or score (a zero-norm or non-finite row or query, a NaN in the Q table: inputs
 // for which the results are unspecified) is ranked as -inf, so that the orderings below stay total
@@ -179,6 +181,7 @@ struct TailArgs {
     const float* qf;
     const double* invq64;
     double* exact;            // [B][exact_stride]; used when a query has several workgroups
+    uint64_t* spare;          // B lists of SURV_CAP words that nothing else uses, or null
     const float* qstage;
     int32_t* out_ids;
     float* out_scores;
@@ -187,15 +190,17 @@ struct TailArgs {
     double lambda;
     int nkb, exact_stride, k1, k2, may_have_empty, mode;
     float margin;
+    EpsGreedy eg;
 };
 
 template <int DT, bool BIG>
-__global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A, EpsGreedy eg) {
+__global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs args) {
     extern __shared__ __align__(16) unsigned char tail_smem[];
     __shared__ SelectLds sh;
     __shared__ double red[2][16];
     __shared__ uint32_t last_s;
-    const int k1 = A.k1, k2 = A.k2, cap = keep_of(k1), k1p = tail_pad64(k1);
+    const TailArgs& A = args;
+    const int k1 = A.k1, cap = keep_of(k1), k1p = tail_pad64(k1);
     double* v0 = reinterpret_cast<double*>(tail_smem);
     double* v1 = v0 + cap;
     int32_t* i0 = reinterpret_cast<int32_t*>(v1 + k1p);
@@ -224,65 +229,122 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A, EpsGreedy eg) {
         __syncthreads();
         return last_s != 0;
     };
-    if (s.crowded && A.mode == SEL_FINAL) {          // uniform, and the same for all of the query's workgroups
-        // every key of the band gets its similarity accumulated in fp64 and the selection is made again; the list
-        // is rewritten in place, so this is for the workgroup that knows that the others have read theirs
-        if (parts > 1 && !last_to_arrive()) return;
+    auto stays = [&](int i) __attribute__((always_inline)) { return s.key[i] != 0 && s.key[i] >= s.cut; };
+    // A crowded band (uniform, and the same for all of the query's workgroups): every key of it, up to 8192, gets its
+    // similarity accumulated in fp64 and the selection is made again with those, which are then the candidates' similarities.
+    // The keys' ids stay in registers, so the similarities can take the place of the query's own list, or, if several
+    // workgroups share the work, a list that the call does not use; without one it is left to the workgroup that knows
+    // that the others have read theirs.
+    // 7000 near rows, us for the whole call with the re-keying left to one workgroup and the candidates gathered once more,
+    // and as it is: one query, d = 1024 bf16 681, 160; 64 queries, two of them crowded, d = 4096 fp16 2690, 768; 256 queries (one
+    // workgroup each), d = 1024 bf16 826, 757.
+    const bool crowded = s.crowded && A.mode == SEL_FINAL;
+    if (crowded && parts > 1 && A.spare == nullptr) {
+        if (!last_to_arrive()) return;
         part = 0;
         parts = 1;
-        store_kept(s, list);
-        __syncthreads();
-        const int n = (int)s.kept;
-        for (int j0 = 0; j0 < n; j0 += TAIL_T / 16) {               // uniform trip count: the row's lanes add up across lanes
-            const int j = j0 + grp;
-            const bool live = j < n;
-            const int32_t id = live ? key_id(list[j]) : 0;
-            double dot, ssq;
-            row_products<DT>(A.store, q, id, live, sub, A.nkb, dot, ssq);
-            if (live && sub == 0) list[j] = exact_key(dot * A.invq64[b] * (1.0 / sqrt(ssq)), id);
-        }
-        __syncthreads();
-        if (tid == 0) last_s = (uint32_t)n;
-        __syncthreads();
-        select_keys(list, &last_s, k1, EXACT_KEY_MARGIN, A.may_have_empty != 0, cap, SEL_EXACT, sh, s);
     }
-    {
+    uint64_t* sims = !crowded ? reinterpret_cast<uint64_t*>(A.exact + (int64_t)b * A.exact_stride) : parts > 1 ? A.spare + (int64_t)b * SURV_CAP : list;
+    int32_t* ids = crowded ? reinterpret_cast<int32_t*>(tail_smem) : i0;            // (a crowded band's in pieces)
+    const uint32_t place = s.slot;
+    int32_t mine[8];                                                 // crowded: this lane's ids, -1 = none
+    auto each = [&](auto f) __attribute__((always_inline)) {         // f(i, id, place of the id)
+        uint32_t at = place;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            int32_t id = mine[i];
+            asm volatile("" : "+v"(id));                             // (kept from one use to the next, the eight conditions fill the scalar registers)
+            if (id >= 0) f(i, id, at++);
+        }
+    };
+    int kk = (int)s.kept;
+    auto lay_out = [&](int c0) __attribute__((always_inline)) {      // the ids at places c0 .. c0 + TAIL_PIECE - 1
+        each([&](int, int32_t id, uint32_t at) __attribute__((always_inline)) {
+            if (at - (uint32_t)c0 < (uint32_t)TAIL_PIECE) ids[at - (uint32_t)c0] = id;
+        });
+        __syncthreads();
+    };
+    if (crowded) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) mine[i] = stays(i) ? key_id(s.key[i]) : -1;
+        lay_out(0);
+    } else {
         uint32_t at = s.slot;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-            if (s.key[i] != 0 && s.key[i] >= s.cut) i0[at++] = key_id(s.key[i]);
+            if (stays(i)) ids[at++] = key_id(s.key[i]);
+        __syncthreads();
     }
-    const int kk = (int)s.kept;
-    __syncthreads();
     // the stage's values of all candidates: requested here, so that the z-scores need not wait for them
     constexpr int UC = ((BIG ? keep_of(BIG_K1_MAX) : KEEP_MAX) + TAIL_T - 1) / TAIL_T;
     float qc[UC];
 #pragma unroll
-    for (int u = 0; u < UC; ++u) qc[u] = tid + u * TAIL_T < kk ? A.qstage[i0[tid + u * TAIL_T]] : 0.f;
+    for (int u = 0; u < UC; ++u) qc[u] = !crowded && tid + u * TAIL_T < kk ? A.qstage[i0[tid + u * TAIL_T]] : 0.f;
 
-    // ---- exact similarities of the candidates (of this workgroup's share) ----
-    for (int j0 = 0; j0 * parts < kk; j0 += TAIL_T / 16) {
-        const int j = (j0 + grp) * parts + part;
-        const bool live = j < kk;
-        const int32_t id = live ? i0[j] : 0;
-        double dot, ssq;
-        row_products<DT>(A.store, q, id, live, sub, A.nkb, dot, ssq);
-        if (live && sub == 0) {
-            const double sim = dot * A.invq64[b] * (1.0 / sqrt(ssq));
-            if (parts == 1) v0[j] = finite_or_lowest(sim);
-            else __hip_atomic_store(A.exact + (int64_t)b * A.exact_stride + j, finite_or_lowest(sim), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // ---- exact similarities (of this workgroup's share) ----
+    // A lane's keys lie 1024 entries apart in the list and next to each other here.  Neighbours in a list are often
+    // neighbours in the bank: of a crowded band, rows 2^lg apart are gathered together (5 to 8 % faster than in order).
+    const int lg = !crowded || kk <= 1024 ? 0 : kk <= 2048 ? 1 : kk <= 4096 ? 2 : 3;
+    for (int c0 = 0;;) {                                             // (one piece unless crowded)
+        const int m = !crowded || kk - c0 < TAIL_PIECE ? kk - c0 : TAIL_PIECE;
+        const int span = ((m - 1) | ((64 << lg) - 1)) + 1;           // whole blocks of 64 x 2^lg
+        for (int j0 = 0; j0 * parts < span; j0 += TAIL_T / 16) {     // uniform trip count: the row's lanes add up across lanes
+            const int x = (j0 + grp) * parts + part;
+            const int j = (x & ~((64 << lg) - 1)) | ((x & 63) << lg) | ((x >> 6) & ((1 << lg) - 1));
+            const bool live = j < m;
+            const int32_t id = live ? ids[j] : 0;
+            double dot, ssq;
+            row_products<DT>(A.store, q, id, live, sub, A.nkb, dot, ssq);
+            if (live && sub == 0) {
+                const double sim = finite_or_lowest(dot * A.invq64[b] * (1.0 / sqrt(ssq)));
+                if (!crowded && parts == 1) v0[j] = sim;
+                else __hip_atomic_store(sims + c0 + j, __builtin_bit_cast(uint64_t, sim), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
+        c0 += TAIL_PIECE;
+        if (!crowded || c0 >= kk) break;                             // uniform
+        __syncthreads();
+        lay_out(c0);
     }
-    if (parts > 1) {
-        if (!last_to_arrive()) return;
-        for (int i = tid; i < kk; i += TAIL_T)
-            v0[i] = __hip_atomic_load(A.exact + (int64_t)b * A.exact_stride + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (parts > 1 && !last_to_arrive()) return;
+    auto sim_at = [&](uint32_t at) __attribute__((always_inline)) {
+        return __builtin_bit_cast(double, __hip_atomic_load(sims + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    };
+    if (crowded) {
+        __syncthreads();
 #pragma unroll
-    for (int u = 0; u < UC; ++u)
-        if (tid + u * TAIL_T < kk) q0[tid + u * TAIL_T] = qc[u];
+        for (int i = 0; i < 8; ++i) s.key[i] = 0ull;
+        each([&](int i, int32_t id, uint32_t at) __attribute__((always_inline)) { s.key[i] = exact_key(sim_at(at), id); });
+        select_keys(kk, k1, EXACT_KEY_MARGIN, true, cap, SEL_EXACT, sh, s);
+        kk = (int)s.kept;
+        uint32_t to = s.slot;
+        each([&](int i, int32_t id, uint32_t at) __attribute__((always_inline)) {
+            if (stays(i)) { i0[to] = id; v0[to++] = sim_at(at); }
+        });
+        __syncthreads();
+        for (int i = tid; i < kk; i += TAIL_T) q0[i] = A.qstage[i0[i]];
+    } else {
+        if (parts > 1)
+            for (int i = tid; i < kk; i += TAIL_T) v0[i] = sim_at((uint32_t)i);
+#pragma unroll
+        for (int u = 0; u < UC; ++u)
+            if (tid + u * TAIL_T < kk) q0[tid + u * TAIL_T] = qc[u];
+    }
     __syncthreads();
 
+    // What only the steps from here on need is loaded here: held from the start it fills the scalar registers, and the
+    // selections spill theirs to vector lanes (a pool of 32 over 100 rows: 12.2 us, 11.6 this way).
+    typedef const __attribute__((address_space(4))) TailArgs* LateArgs;
+    LateArgs late = (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(late));
+    const int k2 = late->k2;
+    int32_t* cand_ids = late->cand_ids;
+    float* cand_sims = late->cand_sims;
+    const double lambda = late->lambda;
+    int32_t* out_ids = late->out_ids + (int64_t)b * k2;
+    float* out_scores = late->out_scores + (int64_t)b * k2;
+    const uint64_t threshold = late->eg.threshold;
+    unsigned char* explored = late->eg.explored;
     // ---- the pool: the k1e best by (similarity desc, id asc) -> (v1, i1, q1) ----
     const int k1e = kk < k1 ? kk : k1;
     rank_entries<BIG>(v0, i0, kk, order, sh, red, [&](int i, int r) __attribute__((always_inline)) {
@@ -304,10 +366,10 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A, EpsGreedy eg) {
         sum_s += sim[u];
         sum_q += qv[u];
     }
-    if (A.cand_ids)
+    if (cand_ids)
         for (int i = tid; i < k1; i += TAIL_T) {
-            A.cand_ids[(int64_t)b * k1 + i] = i < k1e ? i1[i] : -1;
-            A.cand_sims[(int64_t)b * k1 + i] = i < k1e ? (float)v1[i] : -INFINITY;
+            cand_ids[(int64_t)b * k1 + i] = i < k1e ? i1[i] : -1;
+            cand_sims[(int64_t)b * k1 + i] = i < k1e ? (float)v1[i] : -INFINITY;
         }
     if (k1e > 0) {                                                    // uniform
         group_sum2(red, wave, lane, sum_s, sum_q);
@@ -327,7 +389,7 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A, EpsGreedy eg) {
         for (int u = 0; u < U; ++u) {                                 // v0 / i0 are reused for the scores
             const int i = tid + u * TAIL_T;
             if (i < k1e) {
-                v0[i] = finite_or_lowest((1.0 - A.lambda) * (sim[u] * scale_s) + A.lambda * (qv[u] * scale_q));
+                v0[i] = finite_or_lowest((1.0 - lambda) * (sim[u] * scale_s) + lambda * (qv[u] * scale_q));
                 i0[i] = pid[u];
             }
         }
@@ -335,9 +397,7 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A, EpsGreedy eg) {
     __syncthreads();
     // ---- the k2 best by (score desc, id asc) ----
     const int k2e = k1e < k2 ? k1e : k2;
-    const bool greedy = eg.threshold == 0 && eg.explored == nullptr;
-    int32_t* out_ids = A.out_ids + (int64_t)b * k2;
-    float* out_scores = A.out_scores + (int64_t)b * k2;
+    const bool greedy = threshold == 0 && explored == nullptr;
     rank_entries<BIG>(v0, i0, k1e, order, sh, red, [&](int i, int r) __attribute__((always_inline)) {
         if (greedy) {
             if (r < k2e) { out_ids[r] = i0[i]; out_scores[r] = (float)v0[i]; }
@@ -349,38 +409,41 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A, EpsGreedy eg) {
     for (int i = k2e + tid; i < k2; i += TAIL_T) {
         out_ids[i] = -1;
         out_scores[i] = -INFINITY;
-        if (eg.explored) eg.explored[(int64_t)b * k2 + i] = 0;
+        if (explored) explored[(int64_t)b * k2 + i] = 0;
     }
     if (greedy) return;                                               // uniform
     // ---- epsilon-greedy slot filling (Sec. 3.3) ----
     // The whole pool is laid out in greedy order; every slot's draw is computed by its own lane (the draws
     // depend on the slot number only); then one wavefront fills the slots in order, because which members are
     // still free depends on the slots before.  Lane w holds the free members 64 w .. 64 w + 63 as a bit mask.
+    int t = (int)threadIdx.x;                                          // (computed anew: what is kept for these lines is spilled by every call)
+    asm volatile("" : "+v"(t));
+    const int tl = t & 63;
     uint32_t* word0 = reinterpret_cast<uint32_t*>(v0);                 // v0 holds at least 2 k2 words
     uint32_t* word1 = word0 + k2;
     __syncthreads();                                                   // the ordering has read v0
-    for (int j = tid; j < k2e; j += TAIL_T) {
-        const philox_out r = philox4x32_10((uint32_t)eg.step, (uint32_t)(eg.step >> 32), (uint32_t)b, (uint32_t)j,
-                                           (uint32_t)eg.seed, (uint32_t)(eg.seed >> 32));
+    for (int j = t; j < k2e; j += TAIL_T) {
+        const philox_out r = philox4x32_10((uint32_t)late->eg.step, (uint32_t)(late->eg.step >> 32), (uint32_t)b, (uint32_t)j,
+                                           (uint32_t)late->eg.seed, (uint32_t)(late->eg.seed >> 32));
         word0[j] = r.w0;
         word1[j] = r.w1;
     }
     __syncthreads();
-    if (wave != 0) return;
-    uint64_t is_free = k1e >= 64 * lane + 64 ? ~0ull : k1e <= 64 * lane ? 0ull : (1ull << (k1e - 64 * lane)) - 1ull;
+    if (t >= 64) return;                                               // uniform within a wavefront
+    uint64_t is_free = k1e >= 64 * tl + 64 ? ~0ull : k1e <= 64 * tl ? 0ull : (1ull << (k1e - 64 * tl)) - 1ull;
     for (int j = 0; j < k2e; ++j) {
-        const bool explore = (uint64_t)word0[j] < eg.threshold;
+        const bool explore = (uint64_t)word0[j] < threshold;
         const int want = explore ? (int)(((uint64_t)word1[j] * (uint32_t)(k1e - j)) >> 32) : 0;   // index among the free members
         const int c = __popcll(is_free);
         const int upto = (int)wave_inclusive_sum((uint32_t)c);
         const int holder = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto > want));               // the first lane that reaches it
-        if (lane == holder) {
+        if (tl == holder) {
             const int bit = nth_set_bit(is_free, want - (upto - c));
             is_free &= ~(1ull << bit);
-            const int at = 64 * lane + bit;
+            const int at = 64 * tl + bit;
             out_ids[j] = i1[at];
             out_scores[j] = (float)v1[at];
-            if (eg.explored) eg.explored[(int64_t)b * k2 + j] = explore ? 1 : 0;
+            if (explored) explored[(int64_t)b * k2 + j] = explore ? 1 : 0;
         }
     }
 }

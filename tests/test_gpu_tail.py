@@ -28,8 +28,66 @@ def test_shared_candidates(orc, dtype, d, nq, k1, near):
     bank = _make_bank(dtype, rows, qtab, max_B=nq, max_k1=k1)
     stored, qr = orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype])
     first = parity.gpu_retrieve(bank, torch, q, 1, k1, 8, 0.5)
-    parity.check_retrieve(orc, stored, qr, qtab[1], k1, 8, 0.5, first)
+    o_ids, o_sims = orc.recall(stored, qr, k1, threads=8)
+    stats = parity.check_retrieve(orc, stored, qr, qtab[1], k1, 8, 0.5, first, ora_recall=(o_ids, o_sims))
+    if near:                                                        # every candidate ties by the bound above: here the bound is an fp32 similarity's resolution
+        band = (orc.sims_of(stored, qr[0], np.arange(6000, dtype=np.int32)) > o_sims[0, k1 - 1] - 2e-5).sum()
+        assert band > (512 if k1 <= 256 else k1 + 256)               # the case is what it claims to be
+        for b in range(nq):
+            only = sorted(set(first["cand_ids"][b].tolist()) - set(o_ids[b].tolist()))
+            assert not only or np.all(orc.sims_of(stored, qr[b], np.array(only, np.int32)) > o_sims[b, k1 - 1] - 3e-7), b
+    else:
+        assert stats["boundary_swaps"] == 0 and stats["final_swaps"] == 0, stats
     again = parity.gpu_retrieve(bank, torch, q, 1, k1, 8, 0.5)
     assert all(np.array_equal(first[k], again[k]) for k in ("ids", "scores", "cand_ids", "cand_sims"))
     assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    bank.close()
+
+
+# The crowded band with one to eight workgroups per query, by rows that differ by a fraction of the scan's margin.  Shared
+# through the survivor lists that a call leaves unused, or, with the built-in scratch's 64 lists and more than 32 queries, by the
+# last workgroup alone; bands of one and of several pieces of ids; the crowded query first, in the middle and last.
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("dtype,d,nq,k1,near,at", [
+    ("f32", 136, 2, 200, 2200, 1), ("bf16", 512, 3, 128, 3000, 0), ("f16", 2040, 33, 250, 5000, 32), ("f32", 1024, 64, 64, 900, 20),
+    ("f32", 520, 1, 256, 7900, 0), ("bf16", 64, 130, 16, 4100, 77), ("f32", 520, 3, 257, 7900, 2), ("bf16", 1536, 2, 960, 6000, 1)])
+def test_crowded_band_is_refined(orc, dtype, d, nq, k1, near, at, static):
+    if static and (nq > 64 or k1 > 256 or d > 2048):
+        pytest.skip("beyond the built-in scratch")
+    rng = np.random.default_rng([72, d, nq, k1])
+    N = 9000
+    v = _unit(rng, 1, d)
+    rows = _unit(rng, N, d)
+    step = np.float32({"f32": 2e-4, "f16": 5e-4, "bf16": 1e-3}[dtype] * (512 / d) ** 0.5)
+    x = v + step * rng.standard_normal((near, d)).astype(np.float32) * rng.uniform(0.2, 1, (near, 1)).astype(np.float32)
+    where = np.sort(rng.permutation(N)[:near])
+    rows[where] = x / np.linalg.norm(x, axis=1, keepdims=True)
+    q = _unit(rng, nq, d)
+    q[at] = v[0] + (np.float32(0.02) * _unit(rng, 1, d)[0] if dtype == "f32" else 0)     # fp32: similarities that spread over the band
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    stored, qr = orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype])
+    ids, sims = orc.recall(stored, qr, k1, threads=8)
+    kth = sims[at, k1 - 1]
+    band = (orc.sims_of(stored, qr[at], np.arange(N, dtype=np.int32)) > kth - 2e-5).sum()
+    print(f"crowded tail {dtype} d={d} B={nq} k1={k1} near={near}: {band} in the band, pool over {sims[at, 0] - kth:.1e}", flush=True)
+    assert band > (512 if k1 <= 256 else k1 + 256)                   # the case is what it claims to be
+    bank = _make_bank(dtype, rows, qtab, max_B=nq, max_k1=k1)
+    for _ in range(2):
+        if static:
+            out = (torch.empty((nq, 8), dtype=torch.int32, device="cuda:0"), torch.empty((nq, 8), device="cuda:0"),
+                   torch.empty((nq, k1), dtype=torch.int32, device="cuda:0"), torch.empty((nq, k1), device="cuda:0"))
+            bank.retrieve_static(torch.from_numpy(q).to("cuda:0"), 1, k1, 8, 0.5, out)
+            torch.cuda.synchronize()
+            got = dict(zip(("ids", "scores", "cand_ids", "cand_sims"), (t.cpu().numpy() for t in out)))
+        else:
+            got = parity.gpu_retrieve(bank, torch, q, 1, k1, 8, 0.5)
+        for b in range(nq):
+            only = sorted(set(got["cand_ids"][b].tolist()) - set(ids[b].tolist()))
+            if only:        # the selection ranks by similarities rounded to fp32 when the band stays crowded: two roundings of 6e-8
+                assert np.all(orc.sims_of(stored, qr[b], np.array(only, np.int32)) > sims[b, k1 - 1] - 3e-7), b
+        stats = parity.check_retrieve(orc, stored, qr, qtab[1], k1, 8, 0.5, got, ora_recall=(ids, sims))
+        if (orc.sims_of(stored, qr[at], np.arange(N, dtype=np.int32)) > kth - 4e-7).sum() <= (512 if k1 <= 256 else k1 + 256):
+            assert stats["boundary_swaps"] == 0, stats                # what ties in fp32 was ordered in fp64
+        assert stats["order_swaps"] == 0 and stats["final_swaps"] == 0, stats
+    assert not bank.retrieve_flags(nq).cpu().numpy().any()
     bank.close()
