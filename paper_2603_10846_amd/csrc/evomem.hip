@@ -275,8 +275,9 @@ int mem_shape_rewards(evomem_t* h, int stage, const unsigned char* feasible_dev,
         LAUNCHCHK();
         return MEM_OK;
     }
-    // the blocks' sums lie where the survivor lists of a retrieve lie (calls on a handle are ordered): room for a million blocks
-    const int64_t most = (int64_t)((h->w.exact - h->w.surv) / (2 * sizeof(double)) - REWARD_HEAD) / 2 * REWARD_T;
+    // the blocks' sums lie where the survivor lists of a retrieve lie (calls on a handle are ordered)
+    static_assert((REWARD_HEAD + 2ll * REWARD_BLOCKS) * sizeof(double) <= 256ll * SURV_CAP * sizeof(uint64_t), "a workspace has at least 256 lists");
+    const int64_t most = normalise ? (int64_t)REWARD_BLOCKS * REWARD_T : (int64_t)1 << 30;
     for (int64_t off = 0; off < M; off += most) {
         A.feasible = feasible_dev + off;
         if (stage == 1) { A.latency = latency_dev + off; A.best = best_latency_dev + off; }

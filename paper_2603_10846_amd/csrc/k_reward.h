@@ -23,6 +23,10 @@ namespace evk {
 
 constexpr int REWARD_ONE = 1024;          // largest batch of the one-launch form
 constexpr int REWARD_T = 256;             // samples per block of the two-launch form
+// Blocks of a pair of launches, at most: every block adds up the sums of all before it, so a pair's work has a part that
+// grows with the square of its blocks.  Normalised, 4 M samples 147 -> 133 us, 16.7 M 1267 -> 531, 67 M 17.5 -> 2.2 ms (a batch in one
+// pair before; pairs of 2048 blocks take 15 to 20 % longer than these).
+constexpr int REWARD_BLOCKS = 8192;
 
 __device__ __forceinline__ double wave_inclusive_sum_d(double x, int lane) {
 #pragma unroll
