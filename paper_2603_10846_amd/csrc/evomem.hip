@@ -270,7 +270,7 @@ int mem_shape_rewards(evomem_t* h, int stage, const unsigned char* feasible_dev,
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     RewardArgs A{feasible_dev, latency_dev, best_latency_dev, M, (double)sigma_min, (double)clip, reward_state(h, stage),
                  reinterpret_cast<double*>(h->ws + h->w.surv), rewards_out_dev, stage, normalise};
-    if (M <= REWARD_ONE) {
+    if (M <= reward_one_launch(stage, normalise)) {
         hipLaunchKernelGGL(k_shape_rewards, dim3(1), dim3(REWARD_ONE), 0, st, A);
         LAUNCHCHK();
         return MEM_OK;

@@ -7,7 +7,7 @@
 //   (r_t - mu_{t-1}) / max(sigma_{t-1}, sigma_min), optionally clipped, with mu, sigma the running
 //   mean and population deviation of the raw rewards BEFORE it; the statistics (count, sum, sum of
 //   squares, fp64) persist in the handle's workspace.
-// The dependence of sample t on all earlier ones is a prefix sum.  A batch of one workgroup's size is one
+// The dependence of sample t on all earlier ones is a prefix sum.  A batch of little more than one workgroup's size is one
 // launch; a longer one is two: the first leaves every block's sums of (r, r^2), in the second a block adds
 // the sums of the blocks before it and scans its own samples.  The raw rewards are computed in both -- two fp64
 // logarithms and a tanh per sample are what bounds the kernel, and one workgroup walking the batch in
@@ -21,7 +21,11 @@
 
 namespace evk {
 
-constexpr int REWARD_ONE = 1024;          // largest batch of the one-launch form
+constexpr int REWARD_ONE = 1024;          // samples per piece of the one-launch form
+// Largest batch of the one-launch form.  A second launch costs the host about 3.5 us, a second piece what its samples cost
+// (one launch / two, us a call): stage 1, 1025 samples 10.1 / 11.5, 1536 11.0 / 11.7, 2000 12.8 / 11.5; stage 0 (no logarithms), 1025
+// 8.9 / 12.0, 3000 10.7 / 11.8, 4096 13.2 / 12.1; unnormalised rewards of a longer batch need one launch over all blocks in any case.
+__host__ constexpr int64_t reward_one_launch(int stage, int normalise) { return !normalise ? REWARD_ONE : stage == 0 ? 3 * REWARD_ONE : REWARD_ONE + REWARD_ONE / 2; }
 constexpr int REWARD_T = 256;             // samples per block of the two-launch form
 // Blocks of a pair of launches, at most: every block adds up the sums of all before it, so a pair's work has a part that
 // grows with the square of its blocks.  Normalised, 4 M samples 147 -> 133 us, 16.7 M 1267 -> 531, 67 M 17.5 -> 2.2 ms (a batch in one
@@ -84,20 +88,28 @@ __device__ __forceinline__ void block_prefix2(double (*part)[2], int wave, int l
     }
 }
 
+// One workgroup walks the batch in pieces of 1024 samples.
 __global__ __launch_bounds__(REWARD_ONE) void k_shape_rewards(RewardArgs A) {
-    __shared__ double part[REWARD_ONE / 64][2];
+    __shared__ double part[2][REWARD_ONE / 64][2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool live = tid < A.M;
-    const double raw = live ? raw_reward(A, tid) : 0.0;
-    if (!A.normalise) {                                              // uniform
-        if (live) A.out[tid] = (float)raw;
-        return;
+    double n0 = 0.0, s0 = 0.0, q0 = 0.0;                             // the statistics before the piece
+    if (A.normalise) { n0 = A.state[0]; s0 = A.state[1]; q0 = A.state[2]; }
+    for (int64_t base = 0; base < A.M; base += REWARD_ONE) {
+        const int64_t j = base + tid;
+        const bool live = j < A.M;
+        const double raw = live ? raw_reward(A, j) : 0.0;
+        if (!A.normalise) {                                          // uniform
+            if (live) A.out[j] = (float)raw;
+            continue;
+        }
+        double bs, bq, as, aq;
+        block_prefix2<REWARD_ONE / 64>(part[(base / REWARD_ONE) & 1], wave, lane, raw, raw * raw, bs, bq, as, aq);    // (has a barrier)
+        if (live) A.out[j] = (float)normalised_reward(A, raw, n0 + tid, s0 + bs, q0 + bq);
+        n0 += (double)(A.M - base < REWARD_ONE ? A.M - base : REWARD_ONE);
+        s0 += as;
+        q0 += aq;
     }
-    const double n0 = A.state[0], s0 = A.state[1], q0 = A.state[2];
-    double bs, bq, as, aq;
-    block_prefix2<REWARD_ONE / 64>(part, wave, lane, raw, raw * raw, bs, bq, as, aq);    // (has a barrier: the state is read before it)
-    if (live) A.out[tid] = (float)normalised_reward(A, raw, n0 + tid, s0 + bs, q0 + bq);
-    if (tid == 0) { A.state[0] = n0 + (double)A.M; A.state[1] = s0 + as; A.state[2] = q0 + aq; }
+    if (A.normalise && tid == 0) { A.state[0] = n0; A.state[1] = s0; A.state[2] = q0; }
 }
 
 // First launch of a longer batch: the blocks' sums, and a copy of the statistics (the second launch replaces them

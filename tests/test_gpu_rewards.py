@@ -49,3 +49,26 @@ def test_long_batches_are_split(orc, stage):
         n, mu, sd = bank.reward_stats(stage)
         assert n == state[0] and abs(mu - state[1] / state[0]) < 1e-9
     bank.close()
+
+
+@pytest.mark.parametrize("stage", [0, 1])
+def test_pieces_of_one_launch(orc, stage):
+    """One to three pieces of 1024 in one launch, the last one full, nearly empty or nearly full, and the first batch beyond."""
+    rng = np.random.default_rng(45 + stage)
+    bank = B.MemoryBank(64, "f32", 256, max_B=1, max_k1=1)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    state = None
+    for M in (1024, 1025, 1087, 1535, 1536, 1537, 2047, 2048, 2049, 3072, 3073):
+        print(f"rewards stage={stage} M={M}", flush=True)
+        feasible = (rng.random(M) < 0.7).astype(np.uint8)
+        latency, best = rng.uniform(0.1, 5.0, M).astype(np.float32), rng.uniform(0.1, 5.0, M).astype(np.float32)
+        for normalise in (True, False):
+            want, after = orc.shape_rewards(stage, feasible, latency, best, normalise, np.float32(0.1), np.float32(2.5), state)
+            got = bank.shape_rewards(stage, dev(feasible), dev(latency), dev(best), normalise, 0.1, 2.5).cpu().numpy()
+            # fp64 sums in another order, then one rounding to fp32
+            assert np.all(np.abs(got - want) <= 1e-6 * np.maximum(1.0, np.abs(want))), (M, normalise)
+            if normalise:
+                state = after
+        n, mu, sd = bank.reward_stats(stage)
+        assert n == state[0] and abs(mu - state[1] / state[0]) < 1e-9
+    bank.close()
