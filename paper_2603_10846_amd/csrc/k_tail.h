@@ -25,7 +25,7 @@ namespace evk {
 
 constexpr int TAIL_T = 1024;
 constexpr int TAIL_CROWD = 64;            // entries of one bucket that are still ranked by counting
-constexpr int TAIL_PIECE = 2048;          // ids of a crowded band that are laid out at a time (whole blocks of 512)
+constexpr int TAIL_PIECE = keep_of(BIG_K1_MAX);   // ids of a crowded band that are laid out at a time
 
 // LDS besides the static part (dynamic), in this order: v0[cap] f64, v1[k1p] f64, i0[cap] i32, i1[k1p] i32, q0[cap] f32, q1[k1p] f32,
 // then for pools of more than 256 order[sort_cap] u32; cap = keep_of(k1), k1p = k1 rounded up to 64, sort_cap = cap rounded up to a
@@ -193,13 +193,22 @@ struct TailArgs {
     EpsGreedy eg;
 };
 
+// The arguments of a kernel whose only parameter is a TailArgs, to be loaded where they are used.  Held from the start, what the
+// later steps need fills the scalar registers, and the selections spill theirs to vector lanes (150 reads of spilled
+// scalars in the code, 42 this way: a pool of 32 over 100 rows takes 10.9 us instead of 11.2 to 12.2).
+typedef const __attribute__((address_space(4))) TailArgs* TailArgsPtr;
+__device__ __forceinline__ TailArgsPtr tail_args_from_here() {
+    TailArgsPtr p = (TailArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 template <int DT, bool BIG>
-__global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs args) {
+__global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     extern __shared__ __align__(16) unsigned char tail_smem[];
     __shared__ SelectLds sh;
     __shared__ double red[2][16];
     __shared__ uint32_t last_s;
-    const TailArgs& A = args;
     const int k1 = A.k1, cap = keep_of(k1), k1p = tail_pad64(k1);
     double* v0 = reinterpret_cast<double*>(tail_smem);
     double* v1 = v0 + cap;
@@ -211,12 +220,13 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs args) {
     const int b = (int)blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, sub = tid & 15, grp = tid >> 4;
     int part = (int)blockIdx.y, parts = (int)gridDim.y;
     uint64_t* list = A.surv + (int64_t)b * SURV_CAP;
-    const float* q = A.qf + (int64_t)b * A.nkb * KB;
 
     // ---- selection ----
     Selected s;
     const uint32_t raw = select_keys(list, slot_counter(A.cnt, b), k1, A.margin, A.may_have_empty != 0, cap, A.mode, sh, s);
-    if (raw > (uint32_t)SURV_CAP && A.mode == SEL_FINAL && part == 0 && tid == 0) { atomicAdd(A.counters + 1, 1u); A.flags[b] |= 1u; }
+    const TailArgsPtr mid = tail_args_from_here();
+    const float* q = mid->qf + (int64_t)b * mid->nkb * KB;
+    if (raw > (uint32_t)SURV_CAP && mid->mode == SEL_FINAL && part == 0 && tid == 0) { atomicAdd(mid->counters + 1, 1u); mid->flags[b] |= 1u; }
     // The last of the query's workgroups to come here?  All that one workgroup hands to another are the similarities
     // below, and those are stored and loaded as device-scope atomics, which pass by the caches that differ between
     // XCDs; so it is enough that a workgroup's stores have been acknowledged before it arrives.  (Device-scope
@@ -225,7 +235,7 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs args) {
     auto last_to_arrive = [&]() __attribute__((always_inline)) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) last_s = __hip_atomic_fetch_add(A.arrived + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)gridDim.y - 1u;
+        if (tid == 0) last_s = __hip_atomic_fetch_add(mid->arrived + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)gridDim.y - 1u;
         __syncthreads();
         return last_s != 0;
     };
@@ -237,36 +247,44 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs args) {
     // that the others have read theirs.
     // 7000 near rows, us for the whole call with the re-keying left to one workgroup and the candidates gathered once more,
     // and as it is: one query, d = 1024 bf16 681, 160; 64 queries, two of them crowded, d = 4096 fp16 2690, 768; 256 queries (one
-    // workgroup each), d = 1024 bf16 826, 757.
-    const bool crowded = s.crowded && A.mode == SEL_FINAL;
-    if (crowded && parts > 1 && A.spare == nullptr) {
+    // workgroup each), d = 1024 bf16 826, 737; one query, d = 128 bf16 (one workgroup, short rows) 194, 200.
+    const bool crowded = s.crowded && mid->mode == SEL_FINAL;
+    if (crowded && parts > 1 && mid->spare == nullptr) {
         if (!last_to_arrive()) return;
         part = 0;
         parts = 1;
     }
-    uint64_t* sims = !crowded ? reinterpret_cast<uint64_t*>(A.exact + (int64_t)b * A.exact_stride) : parts > 1 ? A.spare + (int64_t)b * SURV_CAP : list;
+    uint64_t* sims = !crowded ? reinterpret_cast<uint64_t*>(mid->exact + (int64_t)b * mid->exact_stride) : parts > 1 ? mid->spare + (int64_t)b * SURV_CAP : list;
     int32_t* ids = crowded ? reinterpret_cast<int32_t*>(tail_smem) : i0;            // (a crowded band's in pieces)
-    const uint32_t place = s.slot;
-    int32_t mine[8];                                                 // crowded: this lane's ids, -1 = none
-    auto each = [&](auto f) __attribute__((always_inline)) {         // f(i, id, place of the id)
-        uint32_t at = place;
+    // Crowded: this lane's ids (-1 = none) and their places, two to a word, in the list's order as far as a wavefront's keys go.
+    // Neighbours in a list are often neighbours in the bank; in the order of `slot` rows gathered together lie 1024 entries
+    // apart (5 to 8 % slower).
+    int32_t mine[8];
+    uint32_t places[4];
+    int kk = (int)s.kept;
+    auto lay_out = [&](int c0) __attribute__((always_inline)) {      // the ids at places c0 .. c0 + TAIL_PIECE - 1
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             int32_t id = mine[i];
-            asm volatile("" : "+v"(id));                             // (kept from one use to the next, the eight conditions fill the scalar registers)
-            if (id >= 0) f(i, id, at++);
+            asm volatile("" : "+v"(id));                             // (kept from one piece to the next, the eight conditions fill the scalar registers)
+            const uint32_t at = (places[i / 2] >> (16 * (i % 2)) & 0xffffu) - (uint32_t)c0;
+            if (id >= 0 && at < (uint32_t)TAIL_PIECE) ids[at] = id;
         }
-    };
-    int kk = (int)s.kept;
-    auto lay_out = [&](int c0) __attribute__((always_inline)) {      // the ids at places c0 .. c0 + TAIL_PIECE - 1
-        each([&](int, int32_t id, uint32_t at) __attribute__((always_inline)) {
-            if (at - (uint32_t)c0 < (uint32_t)TAIL_PIECE) ids[at - (uint32_t)c0] = id;
-        });
         __syncthreads();
     };
     if (crowded) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) mine[i] = stays(i) ? key_id(s.key[i]) : -1;
+        uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.slot);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint64_t in = __builtin_amdgcn_ballot_w64(mine[i] >= 0);
+            const uint32_t at = first + __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));   // at most SURV_CAP
+            places[i / 2] = i % 2 ? places[i / 2] | at << 16 : at;
+            first += (uint32_t)__popcll(in);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(places[i]));
         lay_out(0);
     } else {
         uint32_t at = s.slot;
@@ -279,24 +297,19 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs args) {
     constexpr int UC = ((BIG ? keep_of(BIG_K1_MAX) : KEEP_MAX) + TAIL_T - 1) / TAIL_T;
     float qc[UC];
 #pragma unroll
-    for (int u = 0; u < UC; ++u) qc[u] = !crowded && tid + u * TAIL_T < kk ? A.qstage[i0[tid + u * TAIL_T]] : 0.f;
+    for (int u = 0; u < UC; ++u) qc[u] = !crowded && tid + u * TAIL_T < kk ? mid->qstage[i0[tid + u * TAIL_T]] : 0.f;
 
     // ---- exact similarities (of this workgroup's share) ----
-    // A lane's keys lie 1024 entries apart in the list and next to each other here.  Neighbours in a list are often
-    // neighbours in the bank: of a crowded band, rows 2^lg apart are gathered together (5 to 8 % faster than in order).
-    const int lg = !crowded || kk <= 1024 ? 0 : kk <= 2048 ? 1 : kk <= 4096 ? 2 : 3;
     for (int c0 = 0;;) {                                             // (one piece unless crowded)
         const int m = !crowded || kk - c0 < TAIL_PIECE ? kk - c0 : TAIL_PIECE;
-        const int span = ((m - 1) | ((64 << lg) - 1)) + 1;           // whole blocks of 64 x 2^lg
-        for (int j0 = 0; j0 * parts < span; j0 += TAIL_T / 16) {     // uniform trip count: the row's lanes add up across lanes
-            const int x = (j0 + grp) * parts + part;
-            const int j = (x & ~((64 << lg) - 1)) | ((x & 63) << lg) | ((x >> 6) & ((1 << lg) - 1));
+        for (int j0 = 0; j0 * parts < m; j0 += TAIL_T / 16) {        // uniform trip count: the row's lanes add up across lanes
+            const int j = (j0 + grp) * parts + part;
             const bool live = j < m;
             const int32_t id = live ? ids[j] : 0;
             double dot, ssq;
-            row_products<DT>(A.store, q, id, live, sub, A.nkb, dot, ssq);
+            row_products<DT>(mid->store, q, id, live, sub, mid->nkb, dot, ssq);
             if (live && sub == 0) {
-                const double sim = finite_or_lowest(dot * A.invq64[b] * (1.0 / sqrt(ssq)));
+                const double sim = finite_or_lowest(dot * mid->invq64[b] * (1.0 / sqrt(ssq)));
                 if (!crowded && parts == 1) v0[j] = sim;
                 else __hip_atomic_store(sims + c0 + j, __builtin_bit_cast(uint64_t, sim), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -312,17 +325,19 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs args) {
     };
     if (crowded) {
         __syncthreads();
+        double sim[8];                                               // (all requested at once: behind a condition each it is a round trip each)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) s.key[i] = 0ull;
-        each([&](int i, int32_t id, uint32_t at) __attribute__((always_inline)) { s.key[i] = exact_key(sim_at(at), id); });
+        for (int i = 0; i < 8; ++i) sim[i] = sim_at(mine[i] >= 0 ? places[i / 2] >> (16 * (i % 2)) & 0xffffu : 0u);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s.key[i] = mine[i] >= 0 ? exact_key(sim[i], mine[i]) : 0ull;
         select_keys(kk, k1, EXACT_KEY_MARGIN, true, cap, SEL_EXACT, sh, s);
         kk = (int)s.kept;
-        uint32_t to = s.slot;
-        each([&](int i, int32_t id, uint32_t at) __attribute__((always_inline)) {
-            if (stays(i)) { i0[to] = id; v0[to++] = sim_at(at); }
-        });
+        uint32_t at = s.slot;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (stays(i)) { i0[at] = mine[i]; v0[at++] = sim[i]; }
         __syncthreads();
-        for (int i = tid; i < kk; i += TAIL_T) q0[i] = A.qstage[i0[i]];
+        for (int i = tid; i < kk; i += TAIL_T) q0[i] = mid->qstage[i0[i]];
     } else {
         if (parts > 1)
             for (int i = tid; i < kk; i += TAIL_T) v0[i] = sim_at((uint32_t)i);
@@ -332,11 +347,7 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs args) {
     }
     __syncthreads();
 
-    // What only the steps from here on need is loaded here: held from the start it fills the scalar registers, and the
-    // selections spill theirs to vector lanes (a pool of 32 over 100 rows: 12.2 us, 11.6 this way).
-    typedef const __attribute__((address_space(4))) TailArgs* LateArgs;
-    LateArgs late = (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(late));
+    const TailArgsPtr late = tail_args_from_here();
     const int k2 = late->k2;
     int32_t* cand_ids = late->cand_ids;
     float* cand_sims = late->cand_sims;
