@@ -109,8 +109,8 @@ def other_configs(torch, binding, synth, clustered_bank, clustered_w):
     ex_ms = time_calls(torch, lambda: clustered_bank.retrieve_exact(q4, synth.DRAFT, w4.k1, w4.k2, w4.lam), 5, warm=2)
     res.append({"workload": "clustered bank, mem_retrieve_exact, B=4", "B": 4, "retrieve_ms": round(ex_ms, 3),
                 "queries_per_s": round(4 / (ex_ms * 1e-3), 1),
-                "store_GBps": round(4 * clustered_bank.size() * w4.d * 2 / (ex_ms * 1e-3) / 1e9, 1),
-                "note": "reads the bank once per query"})
+                "store_GBps": round(clustered_bank.size() * w4.d * 2 / (ex_ms * 1e-3) / 1e9, 1),
+                "note": "reads the bank once per group of up to eight queries"})
     # mid: fp32 rows
     w = synth.MID
     bank = binding.MemoryBank(w.d, w.dtype, w.N, max_B=w.B, max_k1=w.k1)

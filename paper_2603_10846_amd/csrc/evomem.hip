@@ -481,9 +481,9 @@ int launch_direct(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Le
 // Rows and queries (tr and tq) of a direct workgroup: 32 rows while that makes enough workgroups of a sparse pass.
 constexpr int direct_tq(int B) { return B <= 16 ? 16 : B <= 32 ? 32 : 64; }
 constexpr int direct_tr(int B) { return B <= 64 ? 32 : 64; }
-// Direct or tile by tile?  Either way a compute unit takes in about 30 GB/s of operands in such a pass (loads in flight
-// are limited by its 32 KB first-level cache), so what decides is how many rows and queries the busiest one reads.  The
-// direct scan pays for its tail (partial sums, counters) on top, hence the quarter.  Measured, direct against by tiles
+// Direct or tile by tile?  Either way a compute unit was seen to take in 20 to 30 GB/s of operands in such a pass (mid-size
+// fp32 bank, 64 queries: 393 KB in 12.8 us, as 128-byte requests of 420 cycles, some forty in flight on average), so
+// what decides is how many rows and queries the busiest one reads.  The direct scan pays for its tail (partial sums, counters) on top, hence the quarter.  Measured, direct against by tiles
 // (us; share of the operands the direct scan reads): 32 tiles of 1024 bf16, one query 5.6 / 17.2 (0.17), 64 queries 9.4 / 17.5
 // (0.33), 256 queries 20.8 / 20.0 (0.89); 64 tiles, 64 queries 20.0 / 21.0 (0.67); 128 tiles, 64 queries 34 / 23 (1.2);
 // 45 tiles of 4096 fp16, 128 queries 79 / 66 (0.89); 32 tiles of 1024 fp32, 64 queries 14.8 / 33.6 (0.33).

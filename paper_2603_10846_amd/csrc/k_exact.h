@@ -11,9 +11,9 @@
 // rows that beat everything in the sparser passes (the bank's order decides); such a query is lost, takes
 // part in no further pass, and walks the whole bank afterwards (k_exact_walk), with lists that cannot overflow.
 //
-// Four queries over 1M x 1024 bf16 entries: 4.37 ms when every query read the bank for itself in ranges of 7,680
-// entries (411 launches), 0.49 ms now, of which the last pass is 0.38 ms for 2.0 GB: bound by fp64 multiply-adds and
-// conversions as much as by HBM (fetching two steps ahead instead of one changed nothing).
+// Four queries over 1M x 1024 bf16 entries: 4.4 ms when every query read the bank for itself in ranges of 7,680
+// entries (411 launches), 0.47 ms now, of which the last pass is 0.41 ms for 2.0 GB: bound by fp64 multiply-adds and
+// conversions as much as by HBM (fetching two steps ahead instead of one changed nothing; one query takes 0.33 ms).
 #pragma once
 #include "k_ingest.h"
 #include "k_select.h"

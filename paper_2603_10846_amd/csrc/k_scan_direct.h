@@ -6,8 +6,8 @@
 // dimension: each forms the products of its own eighth with v_mfma_f32_16x16x32, operands loaded straight from
 // global memory into registers (both are stored in operand order: a lane's 16 bytes are 8 consecutive elements of
 // its row), several steps' loads in flight, no barrier and no LDS until the partial sums are added once at the end.
-// What bounds it: two memory latencies and, with many queries or long rows, the operands a compute unit can take in
-// (about 30 GB/s each).  First pass over 8192 rows, before and now: one query, d = 1024 bf16 17.2 -> 5.6 us; 64 queries
+// What bounds it: two memory latencies and, with many queries or long rows, the operands a compute unit takes in
+// (20 to 30 GB/s).  First pass over 8192 rows, before and now: one query, d = 1024 bf16 17.2 -> 5.6 us; 64 queries
 // 20.5 -> 9.4; 64 queries, d = 1024 fp32 33.6 -> 14.8; 32 queries, d = 384 fp16 13.4 -> 4.9.
 #pragma once
 #include "k_scan_mfma.h"

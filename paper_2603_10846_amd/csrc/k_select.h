@@ -1,4 +1,4 @@
-// Selection kernels: survivor lists -> candidate pool -> value filter (Sec. 3.2).
+// Selection over survivor lists (Sec. 3.2, dense recall), and what it shares with the kernels that follow it.
 #pragma once
 #include <type_traits>
 

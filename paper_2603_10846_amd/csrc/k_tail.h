@@ -4,8 +4,8 @@
 // One workgroup per query, or `parts` of them: each then makes the same selection (from the same list, so with the same
 // result, and at the same time), re-scores its share of the candidates, and the last one to finish orders the
 // pool.  Nothing waits for another workgroup.  What the separate launches cost was their latencies: one query
-// over 4096 x 768 fp32 rows with a pool of 32 took 6.1 + 5.1 + 5.2 us in three launches, 14.9 in one; 128 queries, d = 4096, a
-// pool of 256: 9.5 + 93 + 36 us, 116 in one; 64 queries, d = 1024, a pool of 960: 6.5 + 35.6 + 68.6 us, 66 in one.
+// over 4096 x 768 fp32 rows with a pool of 32 took 6.1 + 5.1 + 5.2 us in three launches, 13.5 in one; 128 queries, d = 4096, a
+// pool of 256: 9.5 + 93 + 36 us, 119 in one; 64 queries, d = 1024, a pool of 960: 6.5 + 35.6 + 68.6 us, 66 in one.
 // What bounds it: about 4 us of barriers and LDS round trips in the selection and 2 to 5 us in the orderings; in
 // between fp64 conversions and multiply-adds, 13 us for 160 rows of 1024 on one compute unit.
 //
@@ -229,9 +229,10 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     if (raw > (uint32_t)SURV_CAP && mid->mode == SEL_FINAL && part == 0 && tid == 0) { atomicAdd(mid->counters + 1, 1u); mid->flags[b] |= 1u; }
     // The last of the query's workgroups to come here?  All that one workgroup hands to another are the similarities
     // below, and those are stored and loaded as device-scope atomics, which pass by the caches that differ between
-    // XCDs; so it is enough that a workgroup's stores have been acknowledged before it arrives.  (Device-scope
-    // fences instead write back and invalidate a whole L2 per wavefront: this kernel took 71 us with them for 64
-    // queries in two parts, 24 without.)
+    // XCDs; so it is enough that a workgroup's stores have been acknowledged before it arrives.  That is this chip's
+    // order, not the language's.  (Device-scope fences instead write back and invalidate a whole L2 per wavefront: this
+    // kernel took 71 us with them for 64 queries in two parts, 24 without; an acquire-release arrival by one lane per
+    // workgroup costs 3 us of a 42 us call for 64 queries in four parts, a pool of 960.)
     auto last_to_arrive = [&]() __attribute__((always_inline)) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
