@@ -47,13 +47,13 @@ def test_shared_candidates(orc, dtype, d, nq, k1, near):
 # The crowded band with one to eight workgroups per query, by rows that differ by a fraction of the scan's margin.  Shared
 # through the survivor lists that a call leaves unused, or, with the built-in scratch's 64 lists and more than 32 queries, by the
 # last workgroup alone; bands of one and of several pieces of ids; the crowded query first, in the middle and last.
-@pytest.mark.parametrize("static", [False, True])
-@pytest.mark.parametrize("dtype,d,nq,k1,near,at", [
+CROWDED = [
     ("f32", 136, 2, 200, 2200, 1), ("bf16", 512, 3, 128, 3000, 0), ("f16", 2040, 33, 250, 5000, 32), ("f32", 1024, 64, 64, 900, 20),
-    ("f32", 520, 1, 256, 7900, 0), ("bf16", 64, 130, 16, 4100, 77), ("f32", 520, 3, 257, 7900, 2), ("bf16", 1536, 2, 960, 6000, 1)])
+    ("f32", 520, 1, 256, 7900, 0), ("bf16", 64, 130, 16, 4100, 77), ("f32", 520, 3, 257, 7900, 2), ("bf16", 1536, 2, 960, 6000, 1)]
+
+
+@pytest.mark.parametrize("dtype,d,nq,k1,near,at,static", [c + (False,) for c in CROWDED] + [c + (True,) for c in CROWDED if c[2] <= 64 and c[3] <= 256])
 def test_crowded_band_is_refined(orc, dtype, d, nq, k1, near, at, static):
-    if static and (nq > 64 or k1 > 256 or d > 2048):
-        pytest.skip("beyond the built-in scratch")
     rng = np.random.default_rng([72, d, nq, k1])
     N = 9000
     v = _unit(rng, 1, d)
