@@ -374,7 +374,7 @@ Plan plan_levels(int64_t N, int k1) {
 
 template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true>
 int launch_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, int k1, const Mask& mask, int B) {
-    constexpr int QT = 32 * MQ * WQ;
+    constexpr int QT = 16 * MQ * WQ;
     constexpr int lds = scan_mfma_lds_bytes<QT, MASKED>();
     auto kern = k_scan_mfma<DT, MQ, WQ, MR, WR, MASKED, STREAM>;
     static int resident[MAX_DEVICES] = {};          // workgroups of this kernel the whole device holds at once
@@ -413,17 +413,17 @@ int launch_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Leve
 template <int DT, bool MASKED>
 int launch_mfma_dt(evomem* h, const Scratch& sc, hipStream_t st, int Bp, int qt, const Level& L, int k1, const Mask& mask, int B) {
     switch (qt) {
-        case 32: return launch_mfma<DT, 1, 1, 2, 4, MASKED>(h, sc, st, Bp, L, k1, mask, B);
+        case 32: return launch_mfma<DT, 2, 1, 4, 4, MASKED>(h, sc, st, Bp, L, k1, mask, B);
         case 64:
             // fp32 stores: 8 wavefronts, so that one wavefront's hi/lo split (vector ALU) overlaps the
-            // MFMAs of the other one on its SIMD (measured 0.054 -> 0.047 ms on the 65,536 x 1024 bank)
-            if constexpr (DT == 0) return launch_mfma<DT, 1, 2, 2, 4, MASKED>(h, sc, st, Bp, L, k1, mask, B);
-            else return launch_mfma<DT, 2, 1, 2, 4, MASKED>(h, sc, st, Bp, L, k1, mask, B);
-        case 128: return launch_mfma<DT, 2, 2, 2, 4, MASKED>(h, sc, st, Bp, L, k1, mask, B);   // 8 wavefronts, 64 x 64 each
+            // MFMAs of the other one on its SIMD (0.054 -> 0.047 ms on the 65,536 x 1024 bank, with 32x32x16 instructions)
+            if constexpr (DT == 0) return launch_mfma<DT, 2, 2, 4, 4, MASKED>(h, sc, st, Bp, L, k1, mask, B);
+            else return launch_mfma<DT, 4, 1, 4, 4, MASKED>(h, sc, st, Bp, L, k1, mask, B);
+        case 128: return launch_mfma<DT, 4, 2, 4, 4, MASKED>(h, sc, st, Bp, L, k1, mask, B);   // 8 wavefronts, 64 x 64 each
         default:                                                                               // 8 wavefronts, 128 x 64 each
             // several query tiles share every bank tile through L2: no streaming hint on the bank loads then
-            return Bp > qt ? launch_mfma<DT, 4, 2, 2, 4, MASKED, false>(h, sc, st, Bp, L, k1, mask, B)
-                           : launch_mfma<DT, 4, 2, 2, 4, MASKED, true>(h, sc, st, Bp, L, k1, mask, B);
+            return Bp > qt ? launch_mfma<DT, 8, 2, 4, 4, MASKED, false>(h, sc, st, Bp, L, k1, mask, B)
+                           : launch_mfma<DT, 8, 2, 4, 4, MASKED, true>(h, sc, st, Bp, L, k1, mask, B);
     }
 }
 template <bool MASKED>

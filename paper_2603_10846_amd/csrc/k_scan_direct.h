@@ -15,14 +15,6 @@
 
 namespace evk {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
-template <int DT>
-__device__ __forceinline__ f32x4_t mfma16(u32x4_t a, u32x4_t b, f32x4_t c) {
-    if constexpr (DT == 2) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
-    else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-}
-
 constexpr int DIRECT_WAVES = 8;
 // Partial sums [wavefront][query][row]; four spare floats per row of queries put the four lane groups of an
 // accumulator's store (queries 4 apart) on different banks.

@@ -6,13 +6,21 @@
 // Persistent workgroups of 4 or 8 wavefronts; each owns QT queries and walks over 256-row bank
 // tiles.  Per k-block the bank tile's 32 KB block (already in LDS operand order in HBM, see
 // layout.h) and the queries' block are staged in LDS (two stages) and consumed by
-// v_mfma_f32_32x32x16 (bf16 or f16 operands, fp32 accumulation).  Global loads run two k-blocks
+// v_mfma_f32_16x16x32 (bf16 or f16 operands, fp32 accumulation).  Bank loads run two k-blocks
 // ahead of the MFMAs through two register sets, and the (tile, k-block) sequence is flattened, so
 // the loads of the next tile are already in flight while a tile's epilogue runs.  Queries are the
-// rows of the accumulator tile and bank rows its columns: a lane holds one bank row per 32x32 block.
-// Within a k-block the four k-steps are a hand-written software pipeline (see compute()): operand
-// fragments are read from LDS one k-step ahead, the LDS stores and global loads of the following
+// rows of the accumulator tile and bank rows its columns: a lane holds one bank row per 16x16 block.
+// Within a k-block the two k-steps are a hand-written software pipeline (see compute()): operand
+// fragments are read from LDS a few query blocks ahead, the LDS stores and global loads of the following
 // k-blocks issue between the MFMAs, and there is one workgroup barrier per k-block.
+//
+// What bounds it with 256 queries and more: power.  Under this load the shader clock falls to 1.6 - 2.0 GHz (2.4 without), so
+// what counts is the energy per k-block, and what the parts take adds up whether or not they overlap.  Fed from LDS alone, in a
+// loop of its own, 256 x 256 x 64 takes 1.35 us with 32x32x16 instructions and 1.15 with 16x16x32 ones, which move half as many
+// accumulator bytes per product (1590 and 1820 TFLOP/s); 32 KB of queries from L2 add 0.1 us, 32 KB of bank rows from HBM 0.5.
+// Hence 16x16x32, queries loaded straight to LDS, and one rotation of the k-loop for workgroups that share bank tiles.  Whole
+// calls: 4M x 1536 bf16, 1024 queries 12.36 -> 11.21 ms, 1M x 1024 bf16, 256 queries 623 -> 603 us, 128 queries of 4096 fp16 over
+// 1.1M rows 1988 -> 1951 us; densest pass of 262,144 x 1024 fp32, 256 queries (registers no longer spilled) 354 -> 297 us.
 //
 // fp32 stores: each value is split on the fly into bf16 hi + bf16 lo and the product is
 // hi*hi + hi*lo + lo*hi (three MFMAs, relative error of a product about 2^-16); this only has to
@@ -32,17 +40,29 @@ namespace evk {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
-typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 
 template <int DT>
-__device__ __forceinline__ f32x16_t mfma32(u32x4_t a, u32x4_t b, f32x16_t c) {
-    if constexpr (DT == 2) {
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
-    } else {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-    }
+__device__ __forceinline__ f32x4_t mfma16(u32x4_t a, u32x4_t b, f32x4_t c) {
+    if constexpr (DT == 2) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
+// acc += a * b in acc's own registers.  Given the choice the compiler lets the result wander to other registers, and with
+// every register taken by accumulators that ends in spills inside the k-loop.  It does not see that a matrix instruction is
+// in flight, so before anything but another one reads acc there has to be a settle().
+template <int DT>
+__device__ __forceinline__ void mfma16_in_place(f32x4_t& acc, u32x4_t a, u32x4_t b) {
+    if constexpr (DT == 2) asm("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+    else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+// Wait states that cover the last matrix instruction issued (eight passes at most, 18 wait states with the instruction itself).
+__device__ __forceinline__ void mfma_settle() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // Two fp32 values rounded to bf16 (round to nearest even) and packed, a first: one v_cvt_pk_bf16_f32.
@@ -62,15 +82,19 @@ __device__ __forceinline__ uint32_t pack_bf16x2_hi(float a, float b, float& ra, 
     return h;
 }
 
-// Per-lane choice of one of the 16 registers of an accumulator block: register r = 4 * hi + lo of each
+// The accumulators of four blocks, as the 16 registers that a lane's survivors are looked for in together.
+struct AccGroup { float v[16]; };
+
+// Per-lane choice of one of the 16 registers of a group: register r = 4 * hi + lo of each
 // lane's own (lo, hi), given as lane masks (lo == 1, lo == 3, lo >= 2, hi == 1, hi == 3, hi >= 2).  A
 // two-level tree of 15 v_cndmask (registers cannot be indexed per lane).  Written as instructions because
 // the compiler turns the equivalent C++ selects over elements of an accumulator vector into a
 // dynamically indexed vector access, which it expands to a 16-way chain.  The two wait states at the
 // top are the ones gfx950 needs between a vector compare writing a mask and a vector instruction reading
 // it; the compiler does not add them for instructions it cannot see, and one pair serves all 15.
-__device__ __forceinline__ float lane_select16(const f32x16_t& v, uint64_t lo1, uint64_t lo3, uint64_t lo23,
+__device__ __forceinline__ float lane_select16(const AccGroup& g, uint64_t lo1, uint64_t lo3, uint64_t lo23,
                                                uint64_t hi1, uint64_t hi3, uint64_t hi23) {
+    const float (&v)[16] = g.v;
     float g0, g1, g2, g3, t;
     asm("s_nop 1\n\t"
         "v_cndmask_b32_e64 %[g0], %[a0], %[a1], %[lo1]\n\t"
@@ -96,12 +120,12 @@ __device__ __forceinline__ float lane_select16(const f32x16_t& v, uint64_t lo1, 
     return g0;
 }
 
-// The one non-negative value among the 16 registers of an accumulator block, for lanes that have exactly
+// The one non-negative value among the 16 registers of a group, for lanes that have exactly
 // one: as signed integers, every value with the sign bit set is below every value without it, so the
 // integer maximum of the bit patterns is that value, bit for bit (8 three-operand maxima; no compare
 // masks and no per-lane register choice).
-__device__ __forceinline__ float only_non_negative(const f32x16_t& v) {
-    auto bits = [&](int r) __attribute__((always_inline)) { return (int)__float_as_uint(v[r]); };
+__device__ __forceinline__ float only_non_negative(const AccGroup& g) {
+    auto bits = [&](int r) __attribute__((always_inline)) { return (int)__float_as_uint(g.v[r]); };
     auto max3 = [](int a, int b, int c) __attribute__((always_inline)) { return max(max(a, b), c); };
     const int t0 = max3(bits(0), bits(1), bits(2)), t1 = max3(bits(3), bits(4), bits(5)), t2 = max3(bits(6), bits(7), bits(8));
     const int t3 = max3(bits(9), bits(10), bits(11)), t4 = max3(bits(12), bits(13), bits(14));
@@ -118,31 +142,38 @@ template <int QT, bool MASKED = false> constexpr int scan_mfma_lds_bytes() {
     return 2 * (STAGE_BANK_BYTES + QT * 128) + QT * 16 + SCAN_LIST_CAP * 12 + 16 + (MASKED ? QT * 8 : 0);
 }
 
-// DT: 0 fp32 store (bf16 split), 1 bf16, 2 f16.  Wave grid WQ x WR, each wave MQ x MR blocks of 32x32.
+// DT: 0 fp32 store (bf16 split), 1 bf16, 2 f16.  Wave grid WQ x WR, each wave MQ x MR blocks of 16x16.
 // gridDim.x is a multiple of 8 * (Bp / QT).
 // MASKED: typed / masked retrieval -- a row is kept for a query only if the query accepts its tag.
 // STREAM: bank rows are loaded with the non-temporal hint (layout.h).  Right whenever a bank tile is read
 // by one workgroup only; with several query tiles per bank tile (more than 256 queries) the later readers
 // are meant to find the tile in L2, and the hint costs 7 % there (measured: 1185 -> 1105 TFLOP/s at 1024 queries).
 template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true>
-__global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restrict__ store_, const float* __restrict__ invnorm,
+__global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __restrict__ store_, const float* __restrict__ invnorm,
                                                    const uint16_t* __restrict__ qop, const float* __restrict__ invq,
                                                    const float* __restrict__ thr, uint32_t* __restrict__ cnt,
                                                    uint64_t* __restrict__ surv, int64_t N, int nkb, int Bp,
                                                    Level L, int flush_every, Mask mask, int B) {
-    static_assert((WQ * WR == 4 || WQ * WR == 8) && MR * WR == 8, "4 or 8 waves, 256 bank rows per workgroup");
+    static_assert((WQ * WR == 4 || WQ * WR == 8) && MR * WR == 16, "4 or 8 waves, 256 bank rows per workgroup");
+    static_assert(MQ == 2 || MQ == 4 || MQ == 8, "whole groups of query blocks");
     constexpr int NT = 64 * WQ * WR;                   // lanes per workgroup
-    constexpr int QT = 32 * MQ * WQ;
+    constexpr int QT = 16 * MQ * WQ;
     constexpr int BCH = 2048 / NT;                     // 16-byte bank chunks per lane per stage
     constexpr int QCH = QT * 8 / NT;                   // 16-byte query chunks per lane per stage
-    constexpr int STAGE_BYTES = STAGE_BANK_BYTES + QT * 128;
+    constexpr int QUERY_AT = 2 * STAGE_BANK_BYTES;     // the two stages of query blocks lie behind those of bank blocks
+    // Query blocks go straight to LDS in the largest variant, whose registers are all taken; the few pieces of a smaller query tile
+    // pass through registers, which look a step further ahead (whole masked call, 32 queries, 300,007 x 384 fp16: 94.8 us, 96.9
+    // straight to LDS).
+    constexpr bool Q_DIRECT = QT == 256;
+    // an AccGroup: GB query blocks of BB row blocks, 16 registers (4 * (GB * row block + query block) + register)
+    constexpr int GB = MQ < 4 ? MQ : 4, BB = 4 / GB, GROUPS = MQ / GB, RGROUPS = MR / BB;
     // 16-bit float type of the MFMA operands (bf16 also for fp32 stores, which are split into bf16)
     auto enc16 = [](float x) __attribute__((always_inline)) { return DT == 2 ? f2f16_rne(x) : f2bf16_rne(x); };
     auto dec16 = [](uint16_t h) __attribute__((always_inline)) { return DT == 2 ? f16_to_f(h) : bf16_to_f(h); };
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wq = wave / WR, wr = wave % WR;
-    const int half = lane >> 5, l32 = lane & 31;
+    const int l16 = lane & 15, grp = lane >> 4;
     // Outside the k-loop (tile start, epilogue) lane coordinates are formed afresh: the wavefront's
     // position from scalar registers, the lane index from the lane counter seeded with a zero the
     // compiler cannot see through.  A per-lane value kept from the kernel's start would live on the
@@ -168,13 +199,13 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
     if (first_j >= L.ntiles) return;
     const int my_tiles = (L.ntiles - first_j + stride_j - 1) / stride_j;
 
-    auto sbank = [&](int s) __attribute__((always_inline)) { return smem + s * STAGE_BYTES; };
-    auto sq = [&](int s) __attribute__((always_inline)) { return smem + s * STAGE_BYTES + STAGE_BANK_BYTES; };
-    uint32_t* thp_s = reinterpret_cast<uint32_t*>(smem + 2 * STAGE_BYTES);   // thresholds as (hi | lo << 16), 16-bit floats
+    auto sbank = [&](int s) __attribute__((always_inline)) { return smem + s * STAGE_BANK_BYTES; };
+    auto sq = [&](int s) __attribute__((always_inline)) { return smem + QUERY_AT + s * QT * 128; };
+    uint32_t* thp_s = reinterpret_cast<uint32_t*>(smem + 2 * (STAGE_BANK_BYTES + QT * 128));   // thresholds as (hi | lo << 16), 16-bit floats
     float* invq_s = reinterpret_cast<float*>(thp_s + QT);
     uint32_t* cnt_s = reinterpret_cast<uint32_t*>(invq_s + QT);
     uint32_t* base_s = cnt_s + QT;
-    constexpr uint32_t LKEY_OFF = 2 * STAGE_BYTES + QT * 16, LQ_OFF = LKEY_OFF + SCAN_LIST_CAP * 8;   // the list's two arrays
+    constexpr uint32_t LKEY_OFF = 2 * (STAGE_BANK_BYTES + QT * 128) + QT * 16, LQ_OFF = LKEY_OFF + SCAN_LIST_CAP * 8;   // the list's two arrays
     uint64_t* lkey = reinterpret_cast<uint64_t*>(smem + LKEY_OFF);
     uint32_t* lq = reinterpret_cast<uint32_t*>(smem + LQ_OFF);
     uint32_t* total_s = lq + SCAN_LIST_CAP;
@@ -195,20 +226,22 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
 
     // Accumulators: (re)initialised at the start of every tile by MFMAs with a zero C operand.
     // (An explicit re-zeroing inside the tile loop makes the compiler keep two copies of them.)
-    f32x16_t acc[MQ][MR];
+    f32x4_t acc[MQ][MR];
 
     // Steps per tile, made even so that the two register sets / LDS stages are in the same phase at
     // every tile boundary: an odd count gets one dummy step that multiplies the tile's last bank
     // block with an all-zero query block (the query operand holds one such block at index nkb).
     const int real_steps = DT == 0 ? nkb * 2 : nkb;
     const int nsteps = real_steps + (real_steps & 1);
-    u32x4_t gbA[BCH], gbB[BCH], gqA[QCH], gqB[QCH];
+    u32x4_t gbA[BCH], gbB[BCH], gqA[QCH], gqB[QCH];       // (gq: unless Q_DIRECT)
 
     // Bank and query loads run two steps ahead of the MFMAs.
-    // Each workgroup starts its k-loop at a different k-block (the order of the k-blocks does not
+    // Each tile walker starts its k-loop at a different k-block (the order of the k-blocks does not
     // matter for a dot product): workgroups run in near lock-step over tiles that are 2^n bytes
     // apart, and without the rotation they would all pull from the same few HBM channels at once.
-    const int rot = (int)((blockIdx.x * 7u) % (unsigned)real_steps);
+    // Workgroups that share a walker's tiles start at the same one, so that each of them finds in L2 what the first
+    // one fetched (L2 misses of a pass over 1M x 1536 with 1024 queries: 104 M lines when they did not, 52 M; 2.52 -> 2.46 ms).
+    const int rot = (int)(((unsigned)first_j * 7u) % (unsigned)real_steps);
     auto rotated = [&](int step) __attribute__((always_inline)) {   // logical step -> k-step actually loaded
         if (step >= real_steps) return step;                          // the dummy step stays last
         int k = step + rot;
@@ -287,21 +320,33 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
 #pragma unroll
             for (int i = 0; i < BCH; ++i) *reinterpret_cast<u32x4_t*>(sbank(s) + (i * NT + tid) * 16) = gb[i];
         }
+        if constexpr (!Q_DIRECT) {
 #pragma unroll
-        for (int i = 0; i < QCH; ++i) *reinterpret_cast<u32x4_t*>(sq(s) + (i * NT + tid) * 16) = gq[i];
+            for (int i = 0; i < QCH; ++i) *reinterpret_cast<u32x4_t*>(sq(s) + (i * NT + tid) * 16) = gq[i];
+        }
     };
-    // Operand addresses.  Row (block*32 + l32) of an operand tile, logical chunk c = 2*k4 + half:
-    // byte offset = block*4096 + l32*128 + ((c ^ f(l32)) * 16), the swizzle depending on l32 only.
-    // The k-step enters through bits 5..6 only, so the address for k-step k4 is the one for k-step 0
-    // with (k4 << 5) xor-ed in: one per-lane offset per operand (the wave's first block folded in)
-    // serves every block, both stages and all k-steps; the rest is a compile-time constant.
-    const uint32_t off0 = l32 * 128 + swz16(half, l32) * 16;
-    const uint32_t offA0 = off0 + STAGE_BANK_BYTES + wq * MQ * 4096, offB0 = off0 + wr * MR * 4096;
-    uint32_t offA[4], offB[4];
-#pragma unroll
-    for (int k4 = 0; k4 < 4; ++k4) { offA[k4] = offA0 ^ (k4 << 5); offB[k4] = offB0 ^ (k4 << 5); }
-    auto frag = [&](int s, uint32_t off, int block) __attribute__((always_inline)) {
-        return *reinterpret_cast<const u32x4_t*>(smem + off + (s * STAGE_BYTES + block * 4096));
+    // Q_DIRECT: query blocks go from global memory straight to LDS (a lane's 16 bytes land at M0 + 16 * lane, and the
+    // block's image in memory is its image in LDS), without registers and LDS stores.  The compiler does not see
+    // these loads: what waits for them is the explicit count before the step's barrier.
+    const uint32_t lds_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+    const uint32_t piece_at = (uint32_t)tid * 16u;
+    auto qload_to_lds = [&](const uint16_t* qb, int s, int i) __attribute__((always_inline)) {
+        const uint32_t to = lds_at + (uint32_t)(QUERY_AT + s * QT * 128 + i * NT * 16) + (uint32_t)__builtin_amdgcn_readfirstlane(wave) * 1024u;
+        const uint64_t from = (uint64_t)(qb + i * NT * 8);                 // (uniform; said so to the compiler)
+        const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(from >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)from);
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(piece_at), "s"(base) : "memory");
+    };
+    // Operand addresses.  Row (block*16 + l16) of an operand tile, logical chunk c = 4*h + grp of k-step h:
+    // byte offset = block*2048 + l16*128 + ((c ^ f(l16)) * 16), the swizzle depending on l16 only.
+    // The k-step enters through bit 6 only, so one per-lane offset per operand (the wave's first block folded in)
+    // serves every block, both stages and both k-steps; the rest is a compile-time constant.
+    const uint32_t off0 = l16 * 128 + swz16(grp, l16) * 16;
+    const uint32_t offA0 = off0 + QUERY_AT + wq * MQ * 2048, offB0 = off0 + wr * MR * 2048;
+    auto frag_a = [&](int s, uint32_t off, int block) __attribute__((always_inline)) {
+        return *reinterpret_cast<const u32x4_t*>(smem + off + (s * QT * 128 + block * 2048));
+    };
+    auto frag_b = [&](int s, uint32_t off, int block) __attribute__((always_inline)) {
+        return *reinterpret_cast<const u32x4_t*>(smem + off + (s * STAGE_BANK_BYTES + block * 2048));
     };
     // One step: the MFMAs on LDS stage s, and meanwhile the operands of the next step (registers gb, gq,
     // loaded two steps ago) go to stage s ^ 1 and the same registers take the loads of the step three
@@ -316,97 +361,133 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
     int tile_now = 0;
     auto load_invnorm = [&](int ti) __attribute__((always_inline)) {
         const int64_t t = level_tile(L, first_j + (ti < my_tiles ? ti : my_tiles - 1) * stride_j);
-        const int row0 = (wr_u * MR) * 32 + (fresh_lane() & 31);
+        const int row0 = (wr_u * MR) * 16 + (fresh_lane() & 15);
 #pragma unroll
         for (int b = 0; b < MR; ++b) {
-            const int64_t id = t * TILE_ROWS + row0 + b * 32;
+            const int64_t id = t * TILE_ROWS + row0 + b * 16;
             inv_n[b] = invnorm[id < N ? id : N - 1];
         }
     };
 
-    u32x4_t af[MQ], bfr[2][MR];   // operand fragments of the 16-bit path, carried from step to step
+    // Operand fragments of the 16-bit path, carried from step to step.  A step has 2 MQ slots (k-step h, query block a); the
+    // query fragment of slot g lies in af[g % RA], requested RA slots ahead.
+    constexpr int RA = MQ < 4 ? MQ : 4, SLOTS = 2 * MQ, BARRIER = 3 * MQ / 2;
+    u32x4_t af[RA], bfr[2][MR];
     auto compute = [&](int s, u32x4_t (&gb)[BCH], u32x4_t (&gq)[QCH], auto fetch_next) __attribute__((always_inline)) {
         if constexpr (DT == 0) {
+            // hi (chunks 0..3) and lo (4..7) of 32 elements: one k-step of three products
+            if constexpr (Q_DIRECT) {
+                const uint16_t* nq = gnext_q();                             // the next step's; stage s ^ 1 is free
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                u32x4_t ah[MQ], al[MQ], bh[MR], bl[MR];
-#pragma unroll
-                for (int a = 0; a < MQ; ++a) { ah[a] = frag(s, offA[ks], a); al[a] = frag(s, offA[2 + ks], a); }
-#pragma unroll
-                for (int b = 0; b < MR; ++b) { bh[b] = frag(s, offB[ks], b); bl[b] = frag(s, offB[2 + ks], b); }
-#pragma unroll
-                for (int a = 0; a < MQ; ++a)
-#pragma unroll
-                    for (int b = 0; b < MR; ++b) {
-                        acc[a][b] = mfma32<1>(al[a], bh[b], acc[a][b]);
-                        acc[a][b] = mfma32<1>(ah[a], bl[b], acc[a][b]);
-                        acc[a][b] = mfma32<1>(ah[a], bh[b], acc[a][b]);
-                    }
+                for (int i = 0; i < QCH; ++i) qload_to_lds(nq, s ^ 1, i);
                 __builtin_amdgcn_sched_barrier(0);
-                if (ks == 0) {
+            }
+            u32x4_t bh[MR], bl[MR];
+            u32x4_t al = frag_a(s, offA0 ^ 64, 0);
+#pragma unroll
+            for (int b = 0; b < MR; ++b) bh[b] = frag_b(s, offB0, b);
+            u32x4_t ah = frag_a(s, offA0, 0);
+#pragma unroll
+            for (int b = 0; b < MR; ++b) bl[b] = frag_b(s, offB0 ^ 64, b);
+#pragma unroll
+            for (int a = 0; a < MQ; ++a) {
+                u32x4_t al1 = al, ah1 = ah;
+                if (MQ < 8 && a + 1 < MQ) { al1 = frag_a(s, offA0 ^ 64, a + 1); ah1 = frag_a(s, offA0, a + 1); }
+#pragma unroll
+                for (int b = 0; b < MR; ++b) mfma16_in_place<1>(acc[a][b], al, bh[b]);     // (MR of them apart: no one waits for the one before)
+#pragma unroll
+                for (int b = 0; b < MR; ++b) mfma16_in_place<1>(acc[a][b], ah, bl[b]);
+#pragma unroll
+                for (int b = 0; b < MR; ++b) mfma16_in_place<1>(acc[a][b], ah, bh[b]);
+                if (MQ == 8 && a + 1 < MQ) { al1 = frag_a(s, offA0 ^ 64, a + 1); ah1 = frag_a(s, offA0, a + 1); }   // (no registers to have them earlier)
+                al = al1;
+                ah = ah1;
+                if (a == MQ / 2 - 1) {
+                    __builtin_amdgcn_sched_barrier(0);
                     lstore(s ^ 1, gb, gq);
-                    gload_q(gq);
+                    if constexpr (!Q_DIRECT) gload_q(gq);
                     gload(gb);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);
         } else {
-            // A software pipeline written out by hand, one slot per query block a of a k-step:
-            //   the MFMAs of block a (MR of them), then the LDS read of block a's fragment for the next
-            //   k-step into the registers those MFMAs have just read, then one piece of the side work.
-            // The bank fragments are used by every slot and are double buffered instead.  So every
-            // fragment is requested at least MR * (MQ - 1) MFMAs before its first use and a wavefront
-            // can keep the matrix pipe busy by itself; the LDS stores (k-steps 1 and 2) and the global
-            // loads (k-step 3) issue in the shadow of the MFMAs instead of forming a period without any.
+            // A software pipeline written out by hand, one slot per query block a of a k-step: the MFMAs of block a
+            // (MR of them), then the LDS read of the fragment RA slots ahead into the registers those MFMAs have just
+            // read, then one piece of the side work.  The bank fragments are used by every slot of a k-step and are
+            // double buffered instead.  The LDS stores (second and third quarter of the slots) and the global loads
+            // (last quarter) issue in the shadow of the MFMAs instead of forming a period without any.
             // The scheduler is fenced per slot to keep this order (left alone it hoists the reads).
-            // On entry af and bfr[0] hold the fragments of k-step 0, fetched by the previous step or, for
+            // On entry af and bfr[0] hold the step's first fragments, fetched by the previous step or, for
             // the first step of a tile, by the tile loop (the last step of a tile fetches nothing: the
             // fragments would only occupy registers that the tile epilogue needs).
             constexpr bool FETCH = decltype(fetch_next)::value;
             const uint16_t* nq = gnext_q();
             const uint16_t* nb = gnext_b();
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const int cur = ks & 1;
-                const uint32_t oa = offA0 ^ (((ks + 1) & 3) << 5), ob = offB0 ^ (((ks + 1) & 3) << 5);
-                // The step's only barrier: every wavefront has stored its share of stage s ^ 1 (k-steps
-                // 1 and 2) and has received all it reads from stage s (the fragments of k-step 3 were
-                // requested during k-step 2).  After it, k-step 3 still has its operands in registers,
-                // and its slots fetch the first fragments of the next step from stage s ^ 1, so the
-                // matrix pipe does not wait for LDS after the barrier.
-                if (ks == 3) __syncthreads();
-                if (ks < 3 || FETCH) {
+            for (int g = 0; g < SLOTS; ++g) {
+                const int h = g / MQ, a = g % MQ;
+                // The step's only barrier: every wavefront has stored its share of stage s ^ 1 and has received all
+                // it reads from stage s.  The query block of the next step has arrived in LDS too: of what this
+                // wavefront requested in the previous step only the bank pieces came after it.  After the barrier
+                // the last quarter's slots still have their operands in registers or requested, and fetch the first
+                // fragments of the next step from stage s ^ 1, so the matrix pipe does not wait for LDS.
+                if (g == BARRIER) {
+                    if constexpr (Q_DIRECT) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(BCH) : "memory");
+                    __syncthreads();
+                    if constexpr (Q_DIRECT) {                               // stage s is free: the query block two steps ahead
 #pragma unroll
-                    for (int b = 0; b < MR; ++b) bfr[cur ^ 1][b] = frag(ks < 3 ? s : s ^ 1, ob, b);
-                }
-#pragma unroll
-                for (int a = 0; a < MQ; ++a) {
-#pragma unroll
-                    for (int b = 0; b < MR; ++b) acc[a][b] = mfma32<DT>(af[a], bfr[cur][b], acc[a][b]);
-                    if (ks < 3 || FETCH) af[a] = frag(ks < 3 ? s : s ^ 1, oa, a);
-                    if (ks == 1) {
-#pragma unroll
-                        for (int i = a * QCH / MQ; i < (a + 1) * QCH / MQ; ++i)
-                            *reinterpret_cast<u32x4_t*>(sq(s ^ 1) + (i * NT + tid) * 16) = gq[i];
-                    }
-                    if (ks == 2) {
-#pragma unroll
-                        for (int i = a * BCH / MQ; i < (a + 1) * BCH / MQ; ++i)
-                            *reinterpret_cast<u32x4_t*>(sbank(s ^ 1) + (i * NT + tid) * 16) = gb[i];
-                    }
-                    // the registers stored during k-step 1 (query pieces) are reloaded during k-step 2,
-                    // those stored during k-step 2 (bank pieces) during k-step 3, a few per slot
-                    if (ks == 2) {
-#pragma unroll
-                        for (int i = a * QCH / MQ; i < (a + 1) * QCH / MQ; ++i) gq[i] = gpiece(nq, i);
-                    }
-                    if (ks == 3) {
-#pragma unroll
-                        for (int i = a * BCH / MQ; i < (a + 1) * BCH / MQ; ++i) gb[i] = gpiece_bank(nb, i);
-                        if (!FETCH && a == MQ - 1) load_invnorm(tile_now + 1);
+                        for (int i = 0; i < QCH; ++i) qload_to_lds(nq, s, i);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                // bank fragments: those of k-step 1 over the first slots, those of the next step behind the barrier
+                constexpr int BPS = (2 * MR + MQ - 1) / MQ;               // per slot
+                if (g < MQ / 2) {
+#pragma unroll
+                    for (int b = g * BPS; b < (g + 1) * BPS && b < MR; ++b) bfr[1][b] = frag_b(s, offB0 ^ 64, b);
+                }
+                if (FETCH && g >= BARRIER) {
+                    // query fragments whose registers were free before stage s ^ 1 could be read
+                    if (g == BARRIER) {
+#pragma unroll
+                        for (int f = SLOTS - RA; f < BARRIER; ++f) af[f % RA] = frag_a(s ^ 1, offA0, f + RA - SLOTS);
+                    }
+#pragma unroll
+                    for (int b = (g - BARRIER) * BPS; b < (g - BARRIER + 1) * BPS && b < MR; ++b) bfr[0][b] = frag_b(s ^ 1, offB0, b);
+                }
+#pragma unroll
+                for (int b = 0; b < MR; ++b) mfma16_in_place<DT>(acc[a][b], af[g % RA], bfr[h][b]);
+                if (g + RA < SLOTS) {
+                    const int f = g + RA;
+                    af[g % RA] = frag_a(s, f >= MQ ? offA0 ^ 64 : offA0, f % MQ);
+                } else if (FETCH && g >= BARRIER) {
+                    af[g % RA] = frag_a(s ^ 1, offA0, g + RA - SLOTS);
+                }
+                // the bank pieces: stored over the second and third quarter of the slots, reloaded over the last
+                constexpr int Q1 = MQ / 2;                                  // slots of a quarter
+                if (g >= Q1 && g < BARRIER) {
+#pragma unroll
+                    for (int i = (g - Q1) * BCH / (2 * Q1); i < (g - Q1 + 1) * BCH / (2 * Q1); ++i)
+                        *reinterpret_cast<u32x4_t*>(sbank(s ^ 1) + (i * NT + tid) * 16) = gb[i];
+                }
+                if constexpr (!Q_DIRECT) {                                  // stored over the second quarter, reloaded over the third
+                    if (g >= Q1 && g < MQ) {
+#pragma unroll
+                        for (int i = (g - Q1) * QCH / Q1; i < (g - Q1 + 1) * QCH / Q1; ++i)
+                            *reinterpret_cast<u32x4_t*>(sq(s ^ 1) + (i * NT + tid) * 16) = gq[i];
+                    }
+                    if (g >= MQ && g < BARRIER) {
+#pragma unroll
+                        for (int i = (g - MQ) * QCH / Q1; i < (g - MQ + 1) * QCH / Q1; ++i) gq[i] = gpiece(nq, i);
+                    }
+                }
+                if (g >= BARRIER) {
+#pragma unroll
+                    for (int i = (g - BARRIER) * BCH / Q1; i < (g - BARRIER + 1) * BCH / Q1; ++i) gb[i] = gpiece_bank(nb, i);
+                    if (!FETCH && g == SLOTS - 1) load_invnorm(tile_now + 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
@@ -461,12 +542,15 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
                 }
             }
         }
+        // Nothing of this is in flight when the k-loop goes on (a wait that the compiler knows of): a register that it has to take
+        // for a load's target would otherwise be waited for at the top of every step, and with it every load before it.
+        __builtin_amdgcn_s_waitcnt(0x0f70);                    // vmcnt(0)
         __syncthreads();
         if (tid == 0) *total_s = 0;
         __syncthreads();
     };
 
-    // Start of a tile.  The accumulators are not zeroed but initialised, by one MFMA per 32x32 block,
+    // Start of a tile.  The accumulators are not zeroed but initialised, by one MFMA per block,
     // with  - threshold[query] * norm[row] : the filter  score * invnorm >= threshold  is
     // score - threshold * norm >= 0, so after the k-loop the epilogue only has to look at signs.
     // The operands are a 3-term extension, query side (th, th, tl), bank side -(nh, nl, nh), with
@@ -476,28 +560,28 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
     // Norm operands of the tile about to start, from the inverse norms requested a tile earlier.
     uint32_t bx[MR], by[MR];
     auto tile_prepare = [&]() __attribute__((always_inline)) {
-        const int half = fresh_lane() >> 5;
+        const bool none = fresh_lane() >= 16;                      // only the first chunk of the extension is used
 #pragma unroll
         for (int b = 0; b < MR; ++b) {
             const float norm = __builtin_amdgcn_rcpf(inv_n[b]);   // finish_key() forms it the same way
             const uint16_t nh = enc16(norm), nl = enc16(norm - dec16(nh));
             const uint32_t mh = nh ^ 0x8000u, ml = nl ^ 0x8000u;
-            bx[b] = half ? 0u : (mh | (ml << 16));
-            by[b] = half ? 0u : mh;
+            bx[b] = none ? 0u : (mh | (ml << 16));
+            by[b] = none ? 0u : mh;
         }
     };
     auto tile_init = [&](int ti) __attribute__((always_inline)) {
         const bool use_thr = L.rho != 0;
-        const int ln = fresh_lane(), half = ln >> 5, l32 = ln & 31;
+        const int ln = fresh_lane();
 #pragma unroll
         for (int a = 0; a < MQ; ++a) {
-            const uint32_t tp = use_thr ? thp_s[(wq_u * MQ + a) * 32 + l32] : 0u;
-            const u32x4_t aext = {half ? 0u : ((tp & 0xffffu) | (tp << 16)), half ? 0u : (tp >> 16), 0u, 0u};
+            const uint32_t tp = use_thr && ln < 16 ? thp_s[(wq_u * MQ + a) * 16 + (ln & 15)] : 0u;
+            const u32x4_t aext = {(tp & 0xffffu) | (tp << 16), tp >> 16, 0u, 0u};
 #pragma unroll
             for (int b = 0; b < MR; ++b) {
                 const u32x4_t bext = {bx[b], by[b], 0u, 0u};
-                const f32x16_t z = {0.f};
-                acc[a][b] = mfma32<DT == 0 ? 1 : DT>(aext, bext, z);
+                const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+                acc[a][b] = mfma16<DT == 0 ? 1 : DT>(aext, bext, z);
             }
         }
     };
@@ -511,8 +595,8 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
             // this pass, so no counter is needed (the count was preset to the pass's valid rows).
 #pragma unroll
             for (int b = 0; b < MR; ++b) {
-                const int ln = fresh_lane(), half = ln >> 5, l32 = ln & 31;
-                const int rt = (wr_u * MR + b) * 32 + l32;
+                const int ln = fresh_lane();
+                const int rt = (wr_u * MR + b) * 16 + (ln & 15);
                 const int64_t id = t * TILE_ROWS + rt;
                 if (id < N) {
                     const float inve = invnorm[id];
@@ -524,8 +608,8 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
                         int opq = 0;
                         asm volatile("" : "+v"(opq));
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int ql = (wq_u * MQ + a) * 32 + 4 * (half + opq) + 8 * (r >> 2) + (r & 3);
+                        for (int r = 0; r < 4; ++r) {
+                            const int ql = (wq_u * MQ + a) * 16 + 4 * ((ln >> 4) + opq) + r;
                             const bool ok = !MASKED || eligible(tag, allow_s[ql], exclude_s[ql]);
                             surv[(int64_t)(q0 + ql) * SURV_CAP + pos] = ok ? pack_key(acc[a][b][r] * inve * invq_s[ql], (int32_t)id) : 0ull;   // 0 = empty slot
                         }
@@ -539,21 +623,31 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
             // and all at the same time, instead of one dependent device-wide atomic per survivor.
             // The accumulators hold  score - threshold * norm  (see tile_init): survivors are the
             // non-negative values.
-            // Pass 1.  Per block and lane a 16-bit mask of the non-negative accumulators, built from the
-            // sign bits with one funnel shift per register (no test for "no survivor in this block"
-            // first: at the survivor rates of the dense passes nearly every block has some).
-            uint32_t msk[MQ * MR];
+            // Pass 1.  Per group and lane a 16-bit mask of the non-negative accumulators, built from the
+            // sign bits with one funnel shift per register (no test for "no survivor here"
+            // first: at the survivor rates of the dense passes nearly every wavefront has some).
+            auto group = [&](int g, int bg) __attribute__((always_inline)) {
+                AccGroup v;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v.v[r] = acc[g * GB + (r >> 2) % GB][bg * BB + (r >> 2) / GB][r & 3];
+                return v;
+            };
+            uint32_t msk[GROUPS * RGROUPS];
             uint32_t mine = 0;
 #pragma unroll
-            for (int b = 0; b < MR; ++b) {
-                const bool valid = t * TILE_ROWS + (wr_u * MR + b) * 32 + (fresh_lane() & 31) < N;
+            for (int bg = 0; bg < RGROUPS; ++bg) {
+                uint32_t valid = 0;
 #pragma unroll
-                for (int a = 0; a < MQ; ++a) {
+                for (int i = 0; i < BB; ++i)
+                    valid |= t * TILE_ROWS + (wr_u * MR + bg * BB + i) * 16 + (fresh_lane() & 15) < N ? ((1u << (4 * GB)) - 1u) << (4 * GB * i) : 0u;
+#pragma unroll
+                for (int g = 0; g < GROUPS; ++g) {
                     uint32_t neg = 0;                                    // sign bits, register 15 first
+                    const AccGroup v = group(g, bg);
 #pragma unroll
-                    for (int r = 15; r >= 0; --r) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[a][b][r]), 31);
-                    const uint32_t m = valid ? (~neg & 0xffffu) : 0u;
-                    msk[a * MR + b] = m;
+                    for (int r = 15; r >= 0; --r) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(v.v[r]), 31);
+                    const uint32_t m = ~neg & valid;
+                    msk[g * RGROUPS + bg] = m;
                     mine += __popc(m);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -567,19 +661,19 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
                 // Pass 2, survivors only, all lanes in parallel: each lane takes the first set bit of its
                 // own mask, fetches that accumulator register with a two-level select (registers cannot
                 // be indexed per lane) and stages (value, row id, query); the key is finished when the
-                // list is flushed.  The first round over the blocks is straight-line code, so that the
-                // blocks' instructions interleave; lanes that hold a second survivor of one block (few)
+                // list is flushed.  The first round over the groups is straight-line code, so that the
+                // groups' instructions interleave; lanes that hold a second survivor of one group (few)
                 // are served by a loop afterwards.
-                auto pick = [&](int a, int b, int r) __attribute__((always_inline)) {
+                auto pick = [&](int g, int bg, int r) __attribute__((always_inline)) {
                     const int lo = r & 3, hi = (r >> 2) & 3;
-                    return lane_select16(acc[a][b], __builtin_amdgcn_ballot_w64(lo == 1), __builtin_amdgcn_ballot_w64(lo == 3),
+                    return lane_select16(group(g, bg), __builtin_amdgcn_ballot_w64(lo == 1), __builtin_amdgcn_ballot_w64(lo == 3),
                                          __builtin_amdgcn_ballot_w64(lo >= 2), __builtin_amdgcn_ballot_w64(hi == 1),
                                          __builtin_amdgcn_ballot_w64(hi == 3), __builtin_amdgcn_ballot_w64(hi >= 2));
                 };
-                auto stage_one = [&](int a, int b, int r, float av) __attribute__((always_inline)) {   // lanes with a survivor
-                    const int ln = fresh_lane(), half = ln >> 5, l32 = ln & 31;
-                    const int32_t id = (int32_t)(t * TILE_ROWS + (wr_u * MR + b) * 32 + l32);
-                    const int ql = (wq_u * MQ + a) * 32 + 4 * half + 8 * ((r >> 2) & 3) + (r & 3);
+                auto stage_one = [&](int g, int bg, int r, float av) __attribute__((always_inline)) {   // lanes with a survivor
+                    const int ln = fresh_lane();
+                    const int32_t id = (int32_t)(t * TILE_ROWS + (wr_u * MR + bg * BB + ((r >> 2) & 3) / GB) * 16 + (ln & 15));
+                    const int ql = (wq_u * MQ + g * GB + ((r >> 2) & 3) % GB) * 16 + 4 * (ln >> 4) + (r & 3);
                     bool ok = true;
                     if constexpr (MASKED) ok = eligible(mask.tags[id], allow_s[ql], exclude_s[ql]);
                     if (slot < (uint32_t)SCAN_LIST_CAP) {
@@ -592,30 +686,32 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
                     ++slot;
                 };
                 // First round, the common case kept free of inner branches: lanes with exactly one survivor in
-                // a block stage it; lanes with more are left to the loop below, and so is everything when the
+                // a group stage it; lanes with more are left to the loop below, and so is everything when the
                 // wavefront's reservation does not fit the list (then no lane needs a room check here).
                 uint32_t rest = 0;
                 const bool fits = (uint32_t)__builtin_amdgcn_readlane((int)wave_base, 63) + (uint32_t)__builtin_amdgcn_readlane((int)incl, 63)
                                   <= (uint32_t)SCAN_LIST_CAP;                                  // uniform
+                // (a group of two row blocks: the rows past the bank's end must not be a group's maximum)
+                const bool whole = (t + 1) * TILE_ROWS <= N;                                   // uniform
                 const int ln0 = fresh_lane();
-                const int32_t id0 = (int32_t)(t * TILE_ROWS + wr_u * MR * 32 + (ln0 & 31));   // this lane's row in block b = 0
-                int qla[MQ];                                                                   // this lane's first query in block a
+                const int32_t id0 = (int32_t)(t * TILE_ROWS + wr_u * MR * 16 + (ln0 & 15));   // this lane's row in block b = 0
+                int qla[GROUPS];                                                               // this lane's first query in group g
 #pragma unroll
-                for (int a = 0; a < MQ; ++a) qla[a] = (wq_u * MQ + a) * 32 + 4 * (ln0 >> 5);
+                for (int g = 0; g < GROUPS; ++g) qla[g] = (wq_u * MQ + g * GB) * 16 + 4 * (ln0 >> 4);
                 // running LDS addresses of the lane's next list entry (key array, query array)
                 unsigned char* pk = smem + LKEY_OFF + slot * 8u;
                 unsigned char* pq = smem + LQ_OFF + slot * 4u;
 #pragma unroll
-                for (int b = 0; b < MR; ++b)
+                for (int bg = 0; bg < RGROUPS; ++bg)
 #pragma unroll
-                    for (int a = 0; a < MQ; ++a) {
-                        const uint32_t m = msk[a * MR + b];
-                        const bool take = fits && __popc(m) == 1;
+                    for (int g = 0; g < GROUPS; ++g) {
+                        const uint32_t m = msk[g * RGROUPS + bg];
+                        const bool take = fits && __popc(m) == 1 && (BB == 1 || whole);
                         if (take) {
                             const int r = __builtin_ctz(m);
-                            const float av = only_non_negative(acc[a][b]);
-                            const int32_t id = id0 + b * 32;
-                            const int ql = qla[a] + r + (r & 12);            // register r holds query 8 * (r >> 2) + (r & 3) of the block
+                            const float av = only_non_negative(group(g, bg));
+                            const int32_t id = id0 + bg * BB * 16 + (BB > 1 ? (r >> 3) * 16 : 0);
+                            const int ql = qla[g] + (BB > 1 ? (r & 7) + 3 * (r & 4) : r + 3 * (r & 12));    // 16 * query block + register
                             bool ok = true;
                             if constexpr (MASKED) ok = eligible(mask.tags[id], allow_s[ql], exclude_s[ql]);
                             *reinterpret_cast<uint64_t*>(pk) = ((uint64_t)__float_as_uint(av) << 32) | (uint32_t)id;
@@ -624,20 +720,20 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
                             pq += 4;
                         }
                         const uint32_t left = take ? 0u : m;
-                        msk[a * MR + b] = left;
+                        msk[g * RGROUPS + bg] = left;
                         rest |= left;
                     }
                 slot = (uint32_t)(pq - (smem + LQ_OFF)) >> 2;
                 if (__builtin_amdgcn_ballot_w64(rest != 0) != 0) {
 #pragma unroll
-                    for (int b = 0; b < MR; ++b)
+                    for (int bg = 0; bg < RGROUPS; ++bg)
 #pragma unroll
-                        for (int a = 0; a < MQ; ++a) {
-                            uint32_t m = msk[a * MR + b];
+                        for (int g = 0; g < GROUPS; ++g) {
+                            uint32_t m = msk[g * RGROUPS + bg];
                             while (__builtin_amdgcn_ballot_w64(m != 0) != 0) {
                                 const int r = __builtin_ctz(m | 0x10000u);
-                                const float av = pick(a, b, r);
-                                if (m) stage_one(a, b, r, av);
+                                const float av = pick(g, bg, r);
+                                if (m) stage_one(g, bg, r, av);
                                 m &= m - 1;
                             }
                         }
@@ -656,15 +752,28 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
     // ---- pipeline over the flattened (tile, k-block) sequence; g counts steps over all tiles ----
     auto phase = [&](int s, u32x4_t (&gb)[BCH], u32x4_t (&gq)[QCH], auto fetch_next) __attribute__((always_inline)) {
         compute(s, gb, gq, fetch_next);
-        if constexpr (DT == 0) __syncthreads();
+        if constexpr (DT == 0) {
+            if constexpr (Q_DIRECT) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(BCH) : "memory");   // the query block: only the bank pieces came after it
+            __syncthreads();
+        }
     };
-    gload_q(gqA);
+    if constexpr (Q_DIRECT) {
+#pragma unroll
+        for (int s = 0; s < (DT == 0 ? 1 : 2); ++s) {
+            const uint16_t* qb = gnext_q();
+#pragma unroll
+            for (int i = 0; i < QCH; ++i) qload_to_lds(qb, s, i);
+        }
+    } else {
+        gload_q(gqA);
+    }
     gload(gbA);
-    gload_q(gqB);
+    if constexpr (!Q_DIRECT) gload_q(gqB);
     gload(gbB);
     lstore(0, gbA, gqA);
-    gload_q(gqA);
+    if constexpr (!Q_DIRECT) gload_q(gqA);
     gload(gbA);
+    if constexpr (Q_DIRECT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     load_invnorm(0);
     tile_prepare();
@@ -674,9 +783,9 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
         if constexpr (DT == 0) load_invnorm(ti + 1);
         if constexpr (DT != 0) {
 #pragma unroll
-            for (int a = 0; a < MQ; ++a) af[a] = frag(0, offA0, a);
+            for (int a = 0; a < RA; ++a) af[a] = frag_a(0, offA0, a);
 #pragma unroll
-            for (int b = 0; b < MR; ++b) bfr[0][b] = frag(0, offB0, b);
+            for (int b = 0; b < MR; ++b) bfr[0][b] = frag_b(0, offB0, b);
         }
         for (int st = 0; st < nsteps - 2; st += 2) {
             phase(0, gbB, gqB, std::true_type{});
@@ -684,9 +793,11 @@ __global__ __launch_bounds__(64 * WQ * WR) void k_scan_mfma(const void* __restri
         }
         phase(0, gbB, gqB, std::true_type{});
         phase(1, gbA, gqA, std::false_type{});
+        mfma_settle();
         epilogue(ti);
         tile_prepare();
     }
+    if constexpr (Q_DIRECT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // query blocks past the end still land in this workgroup's LDS
 }
 
 }  // namespace evk
