@@ -651,9 +651,9 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
         }
     }
     // Few queries: a query's candidates are shared by several workgroups, as long as that leaves a compute unit to each
-    // and more than 96 KB of rows to gather.  Measured with 1, 2, 4 and 8: one query, 128 x 2 KB 26.5, 23.0, 18.7, 18.1 us;
-    // 64 queries, 64 x 4 KB 32.8, 24.1, 23.6, 38.2; 128 queries, 256 x 8 KB 163, 116, 146, 152; 64 queries, 960 x 2 KB 135, 87, 66,
-    // 74; one query, 32 x 3 KB 14.9, 16.0, 16.3, 16.3.
+    // and more than 96 KB of rows to gather.  Measured with 1, 2, 4 and 8: one query, 128 x 2 KB 20.0, 17.9, 15.2, 14.4 us;
+    // 64 queries, 64 x 4 KB 17.1, 15.2, 14.8, 20.7; 128 queries, 256 x 8 KB 110, 80, 92, 110; 64 queries, 960 x 2 KB 93, 68, 54,
+    // 62; one query, 32 x 3 KB 10.9, 12.4, 12.0, 12.0.
     TailArgs ta{};
     ta.eg = eg;
     ta.surv = surv; ta.cnt = cnt; ta.counters = counters; ta.flags = flags;
@@ -666,12 +666,15 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     int parts = 1;
     while (parts < 8 && B * parts * 2 <= 256 && gather / parts > 96 * 1024) parts <<= 1;
     const bool big = k1 > SMALL_K1_MAX;
-    if (big) {
+    const size_t lds = tail_lds(k1) + (size_t)h->nkb * KB * 4;        // and the query
+    static_assert(tail_lds(BIG_K1_MAX) + 16384 * 4 + TAIL_STATIC_LDS <= 160 * 1024, "the largest pool with the longest rows");
+    if (lds + TAIL_STATIC_LDS > 64 * 1024) {
         static bool lds_set[MAX_DEVICES] = {};
         if (!lds_set[h->device]) {
             bool ok = true;
-            for (const void* k : {reinterpret_cast<const void*>(k_tail<0, true>), reinterpret_cast<const void*>(k_tail<1, true>), reinterpret_cast<const void*>(k_tail<2, true>)})
-                ok = ok && hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)tail_lds(BIG_K1_MAX)) == hipSuccess;
+            for (const void* k : {reinterpret_cast<const void*>(k_tail<0, true>), reinterpret_cast<const void*>(k_tail<1, true>), reinterpret_cast<const void*>(k_tail<2, true>),
+                                  reinterpret_cast<const void*>(k_tail<0, false>), reinterpret_cast<const void*>(k_tail<1, false>), reinterpret_cast<const void*>(k_tail<2, false>)})
+                ok = ok && hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(tail_lds(BIG_K1_MAX) + 16384 * 4)) == hipSuccess;
             if (!ok) return MEM_EHIP;
             lds_set[h->device] = true;
         }
@@ -679,8 +682,8 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     with_store_type(h->dtype, [&](auto dt) {
         constexpr int DT = decltype(dt)::value;
         const dim3 grid((unsigned)B, (unsigned)parts), block(TAIL_T);
-        if (big) hipLaunchKernelGGL((k_tail<DT, true>), grid, block, tail_lds(k1), st, ta);
-        else hipLaunchKernelGGL((k_tail<DT, false>), grid, block, tail_lds(k1), st, ta);
+        if (big) hipLaunchKernelGGL((k_tail<DT, true>), grid, block, lds, st, ta);
+        else hipLaunchKernelGGL((k_tail<DT, false>), grid, block, lds, st, ta);
     });
     LAUNCHCHK();
     return MEM_OK;

@@ -107,17 +107,22 @@ __device__ __forceinline__ uint32_t load_keys(const uint64_t* list, const uint32
     uint64_t (&key)[8] = s.key;
 #pragma unroll
     for (int i = 0; i < 2; ++i) key[i] = list[i * 1024 + tid];
-    const uint32_t raw = *count;
+    const uint32_t raw = (uint32_t)__builtin_amdgcn_readfirstlane((int)*count);
     const int n = raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw;
 #pragma unroll
-    for (int i = 2; i < 8; ++i) { int idx = i * 1024 + tid; key[i] = idx < n ? list[idx] : 0ull; }   // 0 = empty
+    for (int i = 2; i < 8; ++i) key[i] = 0ull;                        // 0 = empty
+#pragma unroll
+    for (int i = 2; i < 8; ++i)
+        if (i * 1024 < n) { int idx = i * 1024 + tid; key[i] = idx < n ? list[idx] : 0ull; }
 #pragma unroll
     for (int i = 0; i < 2; ++i) key[i] = i * 1024 + tid < n ? key[i] : 0ull;
     return raw;
 }
 
-// Selects among the keys in the registers (n of them, or fewer where some are empty).
-__device__ __forceinline__ void select_keys(int n, int k1, float margin, bool may_have_empty, int keep_max, int mode, SelectLds& sh, Selected& s) {
+// Selects among the keys in the registers (n of them, or fewer where some are empty; only the first `slots` places of the list
+// they were read from may hold one: what lies past them is skipped, a list is seldom full).
+__device__ __forceinline__ void select_keys(int n, int slots, int k1, float margin, bool may_have_empty, int keep_max, int mode, SelectLds& sh,
+                                            Selected& s) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const uint64_t (&key)[8] = s.key;
     for (int i = tid; i < SEL_BINS; i += 1024) sh.hist[i] = 0;
@@ -125,21 +130,28 @@ __device__ __forceinline__ void select_keys(int n, int k1, float margin, bool ma
     uint32_t used = 0;
     uint32_t most = 0u, least = 0u;                   // largest similarity part of a key, and complement of the smallest
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 8; ++i) {
+        if (i * 1024 >= slots) continue;                                 // uniform
         if (key[i] != 0) {
             const uint32_t o = (uint32_t)(key[i] >> 32);
             most = o > most ? o : most;
             least = ~o > least ? ~o : least;
             ++used;
         }
+    }
     most = wave_max_u32(most);
     least = wave_max_u32(least);
     if (lane == 63) { sh.most[wave] = most; sh.least[wave] = least; }
-    uint32_t total;
-    const uint32_t first = group_prefix_u32(used, sh.part_a, wave, lane, total);      // (has the barrier)
     s.crowded = false;
-    s.keep_all = may_have_empty ? total < (uint32_t)k1 : n < k1;      // uniform
-    if (s.keep_all) { s.cut = 1ull; s.tau = 0.f; s.kept = total; s.slot = first; return; }
+    s.keep_all = false;
+    if (may_have_empty || n < k1) {                                       // uniform
+        uint32_t total;
+        const uint32_t first = group_prefix_u32(used, sh.part_a, wave, lane, total);      // (has the barrier)
+        s.keep_all = may_have_empty ? total < (uint32_t)k1 : true;
+        if (s.keep_all) { s.cut = 1ull; s.tau = 0.f; s.kept = total; s.slot = first; return; }
+    } else {
+        __syncthreads();
+    }
     most = 0u;
     least = 0u;
 #pragma unroll
@@ -174,7 +186,7 @@ __device__ __forceinline__ void select_keys(int n, int k1, float margin, bool ma
     auto rank_few = [&](uint32_t in_bin, auto in) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-            if (key[i] != 0 && in(i)) sh.small[atomicAdd(&sh.nsmall, 1u)] = key[i];
+            if (i * 1024 < slots && key[i] != 0 && in(i)) sh.small[atomicAdd(&sh.nsmall, 1u)] = key[i];
         __syncthreads();
         if ((uint32_t)tid < in_bin) {
             const uint64_t mine = sh.small[tid];
@@ -194,6 +206,8 @@ __device__ __forceinline__ void select_keys(int n, int k1, float margin, bool ma
         uint32_t bin[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
+            bin[i] = 0;
+            if (i * 1024 >= slots) continue;                             // uniform
             const float x = (top - key_sim(key[i])) * width;
             bin[i] = x < (float)(SEL_BINS - 1) ? (uint32_t)x : (uint32_t)(SEL_BINS - 1);
             if (key[i] != 0) atomicAdd(&sh.hist[bin[i]], 1u);
@@ -215,7 +229,7 @@ __device__ __forceinline__ void select_keys(int n, int k1, float margin, bool ma
         const uint32_t dmask = (1u << (hi - shift + 1)) - 1u;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-            if (key[i] != 0 && (hi == 63 || (key[i] >> (hi + 1)) == (prefix >> (hi + 1))))
+            if (i * 1024 < slots && key[i] != 0 && (hi == 63 || (key[i] >> (hi + 1)) == (prefix >> (hi + 1))))
                 atomicAdd(&sh.hist[SEL_BINS - 1 - ((uint32_t)(key[i] >> shift) & dmask)], 1u);
         uint32_t in_bin;
         prefix |= (uint64_t)(SEL_BINS - 1 - find_bin(in_bin)) << shift;
@@ -231,7 +245,8 @@ __device__ __forceinline__ void select_keys(int n, int k1, float margin, bool ma
     for (int again = 0;; ++again) {
         uint32_t mine = 0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) mine += key[i] != 0 && key[i] >= s.cut;
+        for (int i = 0; i < 8; ++i)
+            if (i * 1024 < slots) mine += key[i] != 0 && key[i] >= s.cut;
         s.slot = group_prefix_u32(mine, again ? sh.part_b : sh.part_a, wave, lane, s.kept);
         if (again || s.kept <= (uint32_t)keep_max) break;                    // uniform
         s.crowded = true;
@@ -242,7 +257,8 @@ __device__ __forceinline__ void select_keys(int n, int k1, float margin, bool ma
 __device__ __forceinline__ uint32_t select_keys(const uint64_t* list, const uint32_t* count, int k1, float margin, bool may_have_empty,
                                                 int keep_max, int mode, SelectLds& sh, Selected& s) {
     const uint32_t raw = load_keys(list, count, s);
-    select_keys(raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw, k1, margin, may_have_empty, keep_max, mode, sh, s);
+    const int n = raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw;
+    select_keys(n, n, k1, margin, may_have_empty, keep_max, mode, sh, s);
     return raw;
 }
 
@@ -272,53 +288,70 @@ __global__ __launch_bounds__(1024) void k_select(uint64_t* __restrict__ surv, ui
     }
 }
 
-// Products of one stored row with one query, accumulated in fp64 by 16 neighbouring lanes (lane `sub` of them
-// takes every 16th 16-byte chunk, up to eight loads in flight); every lane gets the sums.  Products of 16-bit
-// values are exact, so dot / sqrt(ssq) is the cosine of the stored vectors up to fp64 rounding.
+// A query in LDS as row_products reads it: four elements to an entry, the two halves of a 16-bit store's chunks of eight in planes of
+// their own (a wavefront's reads are then 16 bytes apart).  All lanes call it; a barrier has to follow.
 template <int DT>
-__device__ __forceinline__ void row_products(const void* store_, const float* q, int32_t id, bool live, int sub, int nkb, double& dot,
-                                             double& ssq) {
-    constexpr int EPC = DT == 0 ? 4 : 8;                 // elements per 16-byte chunk
+__device__ __forceinline__ void query_to_lds(float4* yq, const float* q, int nkb, int nthreads) {
+    constexpr int PLANES = DT == 0 ? 1 : 2;
+    const int n4 = nkb * KB / 4;
+    for (int f = (int)threadIdx.x; f < n4; f += nthreads) yq[(f % PLANES) * (n4 / PLANES) + f / PLANES] = reinterpret_cast<const float4*>(q)[f];
+}
+
+// Products of R stored rows with one query, accumulated in fp64 by G neighbouring lanes (lane `sub` of them takes every G-th 16-byte
+// chunk; eight loads in flight); every lane gets the sums.  Products of 16-bit values are exact, so dot / sqrt(ssq) is the
+// cosine of the stored vectors up to fp64 rounding.  The query comes from LDS: read from memory where it is used, each of its
+// chunks was a round trip of its own, since the loop's exit checks keep the compiler from requesting them together (64 queries, 66
+// rows of 1024 fp32 each over four workgroups: 10.6 us of the kernel's 22).
+template <int DT, int G, int R>
+__device__ __forceinline__ void row_products(const void* store_, const float4* yq, const int32_t (&id)[R], int sub, int nkb, double (&dot)[R],
+                                             double (&ssq)[R]) {
+    constexpr int EPC = DT == 0 ? 4 : 8, U = 8 / R;      // elements per 16-byte chunk; chunks of a row in flight
     const int nch = nkb * KB / EPC;                      // chunks per row
-    dot = 0.0;
-    ssq = 0.0;
-    for (int c0 = sub; c0 < nch; c0 += 16 * 8) {
-        uint4 pk[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int c = c0 + 16 * u;
-            pk[u] = make_uint4(0, 0, 0, 0);
-            if (live && c < nch) {
-                if (DT == 0) pk[u] = *reinterpret_cast<const uint4*>(static_cast<const float*>(store_) + off32(id, c, nkb));
-                else pk[u] = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(store_) + off16(id, c, nkb));
+    for (int r = 0; r < R; ++r) { dot[r] = 0.0; ssq[r] = 0.0; }
+    for (int first = 0; first < nch; first += G * U) {   // uniform
+        uint4 pk[R][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = first + sub + G * u < nch ? first + sub + G * u : nch - 1;     // past the end: the last chunk, dropped below
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (DT == 0) pk[r][u] = *reinterpret_cast<const uint4*>(static_cast<const float*>(store_) + off32(id[r], c, nkb));
+                else pk[r][u] = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(store_) + off16(id[r], c, nkb));
             }
         }
+        __builtin_amdgcn_sched_barrier(0);               // all of them requested before the first is used
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int c = c0 + 16 * u;
-            if (c >= nch) break;
-            const uint32_t w[4] = {pk[u].x, pk[u].y, pk[u].z, pk[u].w};
-            if (DT == 0) {
-                const float4 y = *reinterpret_cast<const float4*>(q + c * 4);
-                const float yy[4] = {y.x, y.y, y.z, y.w};
+        for (int u = 0; u < U; ++u) {
+            if (first + G * u >= nch) break;             // uniform
+            const bool in = first + sub + G * u < nch;
+            const int c = in ? first + sub + G * u : nch - 1;
+            const float4 y0 = yq[c], y1 = DT == 0 ? y0 : yq[nch + c];
+            const float yy[8] = {y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { double x = __uint_as_float(w[i]); dot += x * (double)yy[i]; ssq += x * x; }
-            } else {
-                const float4 y0 = *reinterpret_cast<const float4*>(q + c * 8), y1 = *reinterpret_cast<const float4*>(q + c * 8 + 4);
-                const float yy[8] = {y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w};
+            for (int r = 0; r < R; ++r) {
+                const uint32_t w[4] = {in ? pk[r][u].x : 0u, in ? pk[r][u].y : 0u, in ? pk[r][u].z : 0u, in ? pk[r][u].w : 0u};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint16_t lo = (uint16_t)(w[i] & 0xffff), hi = (uint16_t)(w[i] >> 16);
-                    const double x0 = DT == 1 ? bf16_to_f(lo) : f16_to_f(lo);
-                    const double x1 = DT == 1 ? bf16_to_f(hi) : f16_to_f(hi);
-                    dot += x0 * (double)yy[2 * i] + x1 * (double)yy[2 * i + 1];
-                    ssq += x0 * x0 + x1 * x1;
+                for (int e = 0; e < EPC; ++e) {
+                    double x;
+                    if (DT == 0) x = __uint_as_float(w[e & 3]);
+                    else {
+                        const uint16_t h = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+                        x = DT == 1 ? bf16_to_f(h) : f16_to_f(h);
+                    }
+                    dot[r] += x * (double)yy[e];
+                    ssq[r] += x * x;
                 }
             }
         }
     }
 #pragma unroll
-    for (int o = 8; o > 0; o >>= 1) { dot += __shfl_xor(dot, o, 64); ssq += __shfl_xor(ssq, o, 64); }
+    for (int r = 0; r < R; ++r) {
+        dot[r] = row16_sum(dot[r]);
+        ssq[r] = row16_sum(ssq[r]);
+#pragma unroll
+        for (int o = 16; o < G; o <<= 1) { dot[r] += __shfl_xor(dot[r], o, 64); ssq[r] += __shfl_xor(ssq[r], o, 64); }
+    }
 }
 
 // The key of a similarity accumulated in fp64, rounded to fp32 (resolution 6e-8); NaN ranks lowest.

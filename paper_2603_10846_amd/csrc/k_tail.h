@@ -3,14 +3,17 @@
 //
 // One workgroup per query, or `parts` of them: each then makes the same selection (from the same list, so with the same
 // result, and at the same time), re-scores its share of the candidates, and the last one to finish orders the
-// pool.  Nothing waits for another workgroup.  What the separate launches cost was their latencies: one query
-// over 4096 x 768 fp32 rows with a pool of 32 took 6.1 + 5.1 + 5.2 us in three launches, 13.5 in one; 128 queries, d = 4096, a
-// pool of 256: 9.5 + 93 + 36 us, 119 in one; 64 queries, d = 1024, a pool of 960: 6.5 + 35.6 + 68.6 us, 66 in one.
-// What bounds it: about 4 us of barriers and LDS round trips in the selection and 2 to 5 us in the orderings; in
-// between fp64 conversions and multiply-adds, 13 us for 160 rows of 1024 on one compute unit.
+// pool.  Nothing waits for another workgroup.  Against separate launches: one query
+// over 4096 x 768 fp32 rows with a pool of 32 took 6.1 + 5.1 + 5.2 us in three launches, 10.7 in one.
+// What bounds it: about 4 us of barriers and LDS round trips in the selection, 1 us to lay out the candidates, 2 to 5 us in the
+// orderings and z-scores; in between the rows, which come at 6.8 TB/s when there are many (128 queries, a pool of 256 of 8 KB: 46 us).
 //
-// Re-scoring: 16 lanes per candidate row accumulate in fp64, so that the value filter, which divides by the
-// pool's spread, sees exact similarities.  It is a gather of 128-byte pieces that lie a k-block apart.
+// Re-scoring: 16 to 64 lanes per candidate row accumulate in fp64, so that the value filter, which divides by the
+// pool's spread, sees exact similarities.  It is a gather of 128-byte pieces that lie a k-block apart; the query lies in
+// LDS, requested before the selection.  With the query's chunks read from memory where they are used (a round trip each), always 16
+// lanes to a row and sums over the workgroup for the z-scores: one query, 32 x 3 KB 13.5 us, 10.7 now; 64 queries, 64 x 4 KB 24.4, 14.0; one
+// query, 128 x 2 KB 19.1, 15.0; 256 queries, 128 x 2 KB 41, 28; 1024 queries, 128 x 3 KB 206, 120; 128 queries, 256 x 8 KB 119, 80;
+// 64 queries, 960 x 2 KB 66, 55.  (Two workgroups of 64 registers a lane to a compute unit then, one of 128 now.)
 // Ordering: a pool of up to 256 is ordered by counting how many candidates precede each one (four lanes share a
 // candidate); for larger ones counting all pairs is too much work, so the entries are spread over 2048 buckets by
 // value first -- a monotone map, so only entries of one bucket need comparing -- with a bitonic sort as the way out
@@ -35,6 +38,7 @@ __host__ __device__ constexpr int tail_pow2(int x) { int p = 64; while (p < x) p
 __host__ __device__ constexpr size_t tail_lds(int k1) {
     return (size_t)keep_of(k1) * 16 + (size_t)tail_pad64(k1) * 16 + (k1 > SMALL_K1_MAX ? (size_t)tail_pow2(keep_of(k1)) * 4 : 0);
 }
+constexpr size_t TAIL_STATIC_LDS = sizeof(SelectLds) + 2 * 16 * 8 + 64;          // besides these, the query's d floats (rounded up to a k-block)
 static_assert(TAIL_PIECE * 4 <= tail_lds(1), "a piece of a crowded band's ids lies where the candidates will");
 
 // A NaN similarity or score (a zero-norm or non-finite row or query, a NaN in the Q table: inputs
@@ -195,7 +199,7 @@ struct TailArgs {
 
 // The arguments of a kernel whose only parameter is a TailArgs, to be loaded where they are used.  Held from the start, what the
 // later steps need fills the scalar registers, and the selections spill theirs to vector lanes (150 reads of spilled
-// scalars in the code, 42 this way: a pool of 32 over 100 rows takes 10.9 us instead of 11.2 to 12.2).
+// scalars in the code, 42 this way when it was measured: a pool of 32 over 100 rows 10.9 us instead of 11.2 to 12.2).
 typedef const __attribute__((address_space(4))) TailArgs* TailArgsPtr;
 __device__ __forceinline__ TailArgsPtr tail_args_from_here() {
     TailArgsPtr p = (TailArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
@@ -217,15 +221,16 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     float* q0 = reinterpret_cast<float*>(i1 + k1p);                // the stage's values of the entries in i0, i1
     float* q1 = q0 + cap;
     uint32_t* order = reinterpret_cast<uint32_t*>(q1 + k1p);      // larger pools only
-    const int b = (int)blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, sub = tid & 15, grp = tid >> 4;
+    const int b = (int)blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    float4* yq = reinterpret_cast<float4*>(tail_smem + tail_lds(k1));                      // the query
     int part = (int)blockIdx.y, parts = (int)gridDim.y;
     uint64_t* list = A.surv + (int64_t)b * SURV_CAP;
 
+    query_to_lds<DT>(yq, A.qf + (int64_t)b * A.nkb * KB, A.nkb, TAIL_T);                   // (barriers follow)
     // ---- selection ----
     Selected s;
     const uint32_t raw = select_keys(list, slot_counter(A.cnt, b), k1, A.margin, A.may_have_empty != 0, cap, A.mode, sh, s);
     const TailArgsPtr mid = tail_args_from_here();
-    const float* q = mid->qf + (int64_t)b * mid->nkb * KB;
     if (raw > (uint32_t)SURV_CAP && mid->mode == SEL_FINAL && part == 0 && tid == 0) { atomicAdd(mid->counters + 1, 1u); mid->flags[b] |= 1u; }
     // The last of the query's workgroups to come here?  All that one workgroup hands to another are the similarities
     // below, and those are stored and loaded as device-scope atomics, which pass by the caches that differ between
@@ -247,8 +252,9 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     // workgroups share the work, a list that the call does not use; without one it is left to the workgroup that knows
     // that the others have read theirs.
     // 7000 near rows, us for the whole call with the re-keying left to one workgroup and the candidates gathered once more,
-    // and as it is: one query, d = 1024 bf16 681, 160; 64 queries, two of them crowded, d = 4096 fp16 2690, 768; 256 queries (one
-    // workgroup each), d = 1024 bf16 826, 737; one query, d = 128 bf16 (one workgroup, short rows) 194, 200.
+    // and shared: one query, d = 1024 bf16 681, 160; 64 queries, two of them crowded, d = 4096 fp16 2690, 768; 256 queries (one
+    // workgroup each), d = 1024 bf16 826, 737; one query, d = 128 bf16 (one workgroup, short rows) 194, 200.  (Rows scored as they
+    // are now: this kernel 109 -> 81 us for one query, 196 -> 134 for 64 with two crowded, d = 1024 bf16.)
     const bool crowded = s.crowded && mid->mode == SEL_FINAL;
     if (crowded && parts > 1 && mid->spare == nullptr) {
         if (!last_to_arrive()) return;
@@ -301,20 +307,40 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     for (int u = 0; u < UC; ++u) qc[u] = !crowded && tid + u * TAIL_T < kk ? mid->qstage[i0[tid + u * TAIL_T]] : 0.f;
 
     // ---- exact similarities (of this workgroup's share) ----
+    // Lanes per row: as many as leave no lane group without a row (16 at least); with more rows than groups of 16, two rows to a group,
+    // which share the query's reads and conversions.
     for (int c0 = 0;;) {                                             // (one piece unless crowded)
         const int m = !crowded || kk - c0 < TAIL_PIECE ? kk - c0 : TAIL_PIECE;
-        for (int j0 = 0; j0 * parts < m; j0 += TAIL_T / 16) {        // uniform trip count: the row's lanes add up across lanes
-            const int j = (j0 + grp) * parts + part;
-            const bool live = j < m;
-            const int32_t id = live ? ids[j] : 0;
-            double dot, ssq;
-            row_products<DT>(mid->store, q, id, live, sub, mid->nkb, dot, ssq);
-            if (live && sub == 0) {
-                const double sim = finite_or_lowest(dot * mid->invq64[b] * (1.0 / sqrt(ssq)));
-                if (!crowded && parts == 1) v0[j] = sim;
-                else __hip_atomic_store(sims + c0 + j, __builtin_bit_cast(uint64_t, sim), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int share = (m - part + parts - 1) / parts;            // rows of this workgroup
+        auto score = [&](auto lanes, auto rows) __attribute__((always_inline)) {
+            constexpr int G = decltype(lanes)::value, R = decltype(rows)::value, GROUPS = TAIL_T / G;
+            const int sub = tid % G, grp = tid / G;
+            for (int j0 = 0; j0 < share; j0 += GROUPS * R) {         // uniform
+                if (j0 + (wave * 64 / G) * R >= share) break;        // uniform within a wavefront, whose lanes add up across
+                int32_t id[R];
+                double dot[R], ssq[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int i = j0 + grp * R + r;
+                    id[r] = ids[(i < share ? i : 0) * parts + part];
+                }
+                row_products<DT, G, R>(mid->store, yq, id, sub, mid->nkb, dot, ssq);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int i = j0 + grp * R + r, j = i * parts + part;
+                    if (i < share && sub == 0) {
+                        const double sim = finite_or_lowest(dot[r] * mid->invq64[b] * (1.0 / sqrt(ssq[r])));
+                        if (!crowded && parts == 1) v0[j] = sim;
+                        else __hip_atomic_store(sims + c0 + j, __builtin_bit_cast(uint64_t, sim), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
             }
-        }
+        };
+        using std::integral_constant;
+        if (share <= TAIL_T / 64) score(integral_constant<int, 64>{}, integral_constant<int, 1>{});
+        else if (share <= TAIL_T / 32) score(integral_constant<int, 32>{}, integral_constant<int, 1>{});
+        else if (share <= TAIL_T / 16) score(integral_constant<int, 16>{}, integral_constant<int, 1>{});
+        else score(integral_constant<int, 16>{}, integral_constant<int, 2>{});
         c0 += TAIL_PIECE;
         if (!crowded || c0 >= kk) break;                             // uniform
         __syncthreads();
@@ -331,7 +357,7 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
         for (int i = 0; i < 8; ++i) sim[i] = sim_at(mine[i] >= 0 ? places[i / 2] >> (16 * (i % 2)) & 0xffffu : 0u);
 #pragma unroll
         for (int i = 0; i < 8; ++i) s.key[i] = mine[i] >= 0 ? exact_key(sim[i], mine[i]) : 0ull;
-        select_keys(kk, k1, EXACT_KEY_MARGIN, true, cap, SEL_EXACT, sh, s);
+        select_keys(kk, SURV_CAP, k1, EXACT_KEY_MARGIN, true, cap, SEL_EXACT, sh, s);
         kk = (int)s.kept;
         uint32_t at = s.slot;
 #pragma unroll
@@ -364,45 +390,72 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     });
     __syncthreads();
     // ---- z-scores over the pool ----
-    constexpr int U = BIG ? (BIG_K1_MAX + TAIL_T - 1) / TAIL_T : 1;   // pool entries per lane
-    double sim[U], qv[U];
-    int32_t pid[U];
-    double sum_s = 0.0, sum_q = 0.0;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int i = tid + u * TAIL_T;
-        const bool mine = i < k1e;
-        sim[u] = mine ? v1[i] : 0.0;
-        pid[u] = mine ? i1[i] : 0x7fffffff;
-        qv[u] = mine ? (double)q1[i] : 0.0;
-        sum_s += sim[u];
-        sum_q += qv[u];
-    }
     if (cand_ids)
         for (int i = tid; i < k1; i += TAIL_T) {
             cand_ids[(int64_t)b * k1 + i] = i < k1e ? i1[i] : -1;
             cand_sims[(int64_t)b * k1 + i] = i < k1e ? (float)v1[i] : -INFINITY;
         }
     if (k1e > 0) {                                                    // uniform
-        group_sum2(red, wave, lane, sum_s, sum_q);
-        const double mean_s = sum_s / k1e, mean_q = sum_q / k1e;
-        double var_s = 0.0, var_q = 0.0;
+        if constexpr (!BIG) {
+            // Every wavefront that holds a member adds up the whole pool for itself: no barrier (with sums over the workgroup, four
+            // of them, this took 2.5 us, 1.2 now).
+            constexpr int U = SMALL_K1_MAX / 64;
+            if (wave * 64 < k1e) {
+                double sim[U], qv[U], sum_s = 0.0, sum_q = 0.0, var_s = 0.0, var_q = 0.0;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool mine = tid + u * TAIL_T < k1e;
-            sim[u] = mine ? sim[u] - mean_s : 0.0;
-            qv[u] = mine ? qv[u] - mean_q : 0.0;
-            var_s += sim[u] * sim[u];
-            var_q += qv[u] * qv[u];
-        }
-        group_sum2(red, wave, lane, var_s, var_q);
-        const double scale_s = 1.0 / (sqrt(var_s / k1e) + 1e-6), scale_q = 1.0 / (sqrt(var_q / k1e) + 1e-6);
+                for (int u = 0; u < U; ++u) {
+                    const int i = lane + 64 * u;
+                    sim[u] = i < k1e ? v1[i] : 0.0;
+                    qv[u] = i < k1e ? (double)q1[i] : 0.0;
+                    sum_s += sim[u];
+                    sum_q += qv[u];
+                }
+                const double mean_s = wave_total_d(sum_s) / k1e, mean_q = wave_total_d(sum_q) / k1e;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {                                 // v0 / i0 are reused for the scores
-            const int i = tid + u * TAIL_T;
-            if (i < k1e) {
-                v0[i] = finite_or_lowest((1.0 - lambda) * (sim[u] * scale_s) + lambda * (qv[u] * scale_q));
-                i0[i] = pid[u];
+                for (int u = 0; u < U; ++u) {
+                    const bool mine = lane + 64 * u < k1e;
+                    sim[u] = mine ? sim[u] - mean_s : 0.0;
+                    qv[u] = mine ? qv[u] - mean_q : 0.0;
+                    var_s += sim[u] * sim[u];
+                    var_q += qv[u] * qv[u];
+                }
+                const double scale_s = 1.0 / (sqrt(wave_total_d(var_s) / k1e) + 1e-6), scale_q = 1.0 / (sqrt(wave_total_d(var_q) / k1e) + 1e-6);
+                if (tid < k1e) {                                      // v0 / i0 are reused for the scores
+                    v0[tid] = finite_or_lowest((1.0 - lambda) * ((v1[tid] - mean_s) * scale_s) + lambda * (((double)q1[tid] - mean_q) * scale_q));
+                    i0[tid] = i1[tid];
+                }
+            }
+        } else {
+            constexpr int U = (BIG_K1_MAX + TAIL_T - 1) / TAIL_T;     // pool entries per lane
+            double sim[U], qv[U], sum_s = 0.0, sum_q = 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = tid + u * TAIL_T;
+                sim[u] = i < k1e ? v1[i] : 0.0;
+                qv[u] = i < k1e ? (double)q1[i] : 0.0;
+                sum_s += sim[u];
+                sum_q += qv[u];
+            }
+            group_sum2(red, wave, lane, sum_s, sum_q);
+            const double mean_s = sum_s / k1e, mean_q = sum_q / k1e;
+            double var_s = 0.0, var_q = 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool mine = tid + u * TAIL_T < k1e;
+                sim[u] = mine ? sim[u] - mean_s : 0.0;
+                qv[u] = mine ? qv[u] - mean_q : 0.0;
+                var_s += sim[u] * sim[u];
+                var_q += qv[u] * qv[u];
+            }
+            group_sum2(red, wave, lane, var_s, var_q);
+            const double scale_s = 1.0 / (sqrt(var_s / k1e) + 1e-6), scale_q = 1.0 / (sqrt(var_q / k1e) + 1e-6);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {                             // v0 / i0 are reused for the scores
+                const int i = tid + u * TAIL_T;
+                if (i < k1e) {
+                    v0[i] = finite_or_lowest((1.0 - lambda) * (sim[u] * scale_s) + lambda * (qv[u] * scale_q));
+                    i0[i] = i1[i];
+                }
             }
         }
     }

@@ -91,3 +91,24 @@ def test_crowded_band_is_refined(orc, dtype, d, nq, k1, near, at, static):
         assert stats["order_swaps"] == 0 and stats["final_swaps"] == 0, stats
     assert not bank.retrieve_flags(nq).cpu().numpy().any()
     bank.close()
+
+
+# Edges of what a workgroup's rows and lanes are: pools of 16, 32 and 64 rows and one more (64, 32 and 16 lanes to a row, then two
+# rows to a lane group), rows shorter than a lane group's reach and of every remainder, the longest rows with the largest pool,
+# and lists whose lengths lie around multiples of the 1024 keys a selection takes at a time.
+@pytest.mark.parametrize("dtype,N,d,nq,k1", [
+    ("f32", 1023, 8, 1, 1), ("f32", 1025, 72, 2, 16), ("bf16", 2048, 8, 3, 17), ("f16", 2049, 136, 1, 32), ("bf16", 3073, 200, 2, 33),
+    ("f32", 4096, 328, 1, 64), ("f16", 5121, 520, 130, 65), ("bf16", 6143, 1032, 2, 129), ("f16", 8191, 2056, 1, 256), ("f32", 7169, 520, 1, 257),
+    ("bf16", 2500, 16384, 1, 2048), ("f32", 1100, 16384, 2, 40), ("f16", 900, 72, 300, 100), ("f32", 40, 64, 3, 64)])
+def test_rows_and_lanes_of_the_scoring(orc, dtype, N, d, nq, k1):
+    rng = np.random.default_rng([73, N, d])
+    rows = _unit(rng, N, d) * rng.uniform(0.5, 2.0, (N, 1)).astype(np.float32)
+    q = _unit(rng, nq, d)
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    print(f"scoring {dtype} N={N} d={d} B={nq} k1={k1}", flush=True)
+    bank = _make_bank(dtype, rows, qtab, max_B=nq, max_k1=k1)
+    k2 = min(k1, 8)
+    got = parity.gpu_retrieve(bank, torch, q, 1, k1, k2, 0.5)
+    parity.check_retrieve(orc, orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype]), qtab[1], k1, k2, 0.5, got)
+    assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    bank.close()
