@@ -434,7 +434,7 @@ int launch_mfma_any(evomem* h, const Scratch& sc, hipStream_t st, int Bp, int qt
 }
 
 template <int NB>
-int launch_gemv(evomem* h, const Scratch& sc, hipStream_t st, int B, const Level& L, const Mask& mask) {
+int launch_gemv(evomem* h, const Scratch& sc, hipStream_t st, int B, const Level& L, const Mask& mask, const PrepArgs* prep) {
     unsigned char* ws = sc.base;
     // Workgroups per tile.  Measured with 16 and with 4 (us): one query, 205 tiles of 768 28.8, 32.2, 476 tiles of 72 16.6, 14.4;
     // four queries, 52 tiles of 768 16.5, 18.0, 205 tiles of 768 41.4, 36.6.
@@ -445,24 +445,30 @@ int launch_gemv(evomem* h, const Scratch& sc, hipStream_t st, int B, const Level
     const float* qf = (const float*)(ws + sc.w.qf);
     uint32_t* cnt = (uint32_t*)(ws + sc.w.cnt);
     uint64_t* surv = (uint64_t*)(ws + sc.w.surv);
+    if (prep) {                                                     // the first pass: at most 32 tiles
+        hipLaunchKernelGGL((k_scan_gemv32<NB, 1, true>), dim3((unsigned)(16 * L.ntiles + prep->Bpad)), block, 0, st, (const float*)h->store,
+                           (const float*)h->invnorm, qf, invq, thr, cnt, surv, h->N, h->nkb, B, L, mask, *prep);
+        LAUNCHCHK();
+        return MEM_OK;
+    }
     if (wgs == 16)
         hipLaunchKernelGGL((k_scan_gemv32<NB, 1>), grid, block, 0, st, (const float*)h->store, (const float*)h->invnorm, qf, invq,
-                           thr, cnt, surv, h->N, h->nkb, B, L, mask);
+                           thr, cnt, surv, h->N, h->nkb, B, L, mask, PrepArgs{});
     else if (wgs == 4)
         hipLaunchKernelGGL((k_scan_gemv32<NB, 4>), grid, block, 0, st, (const float*)h->store, (const float*)h->invnorm, qf, invq,
-                           thr, cnt, surv, h->N, h->nkb, B, L, mask);
+                           thr, cnt, surv, h->N, h->nkb, B, L, mask, PrepArgs{});
     else
         hipLaunchKernelGGL((k_scan_gemv32<NB, 16>), grid, block, 0, st, (const float*)h->store, (const float*)h->invnorm, qf, invq,
-                           thr, cnt, surv, h->N, h->nkb, B, L, mask);
+                           thr, cnt, surv, h->N, h->nkb, B, L, mask, PrepArgs{});
     LAUNCHCHK();
     return MEM_OK;
 }
 
 // One sparse pass: 32 or 64 rows and 16 .. 64 queries to a workgroup.
-template <int DT, int MQ, int MR>
-int launch_direct(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, const Mask& mask, int B) {
-    constexpr int lds = direct_lds_bytes<MQ, MR>();
-    auto kern = k_scan_direct<DT, MQ, MR>;
+template <int DT, int MQ, int MR, bool FIRST>
+int launch_direct(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, const Mask& mask, int B, const PrepArgs* prep) {
+    constexpr int lds = direct_lds_bytes<MQ, MR, FIRST>();
+    auto kern = k_scan_direct<DT, MQ, MR, FIRST>;
     if constexpr (lds > 64 * 1024) {
         static bool lds_set[MAX_DEVICES] = {};
         if (!lds_set[h->device]) {
@@ -472,9 +478,9 @@ int launch_direct(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Le
     }
     const int nqt = (B + 16 * MQ - 1) / (16 * MQ), units = L.ntiles * (TILE_ROWS / (16 * MR));
     unsigned char* ws = sc.base;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * ((units + 7) / 8) * nqt)), dim3(64 * DIRECT_WAVES), lds, st, (const void*)h->store, (const float*)h->invnorm,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * ((units + 7) / 8) * nqt + (FIRST ? Bp : 0))), dim3(64 * DIRECT_WAVES), lds, st, (const void*)h->store, (const float*)h->invnorm,
                        (const uint16_t*)(ws + sc.w.qop), (const float*)(ws + sc.w.invq), (const float*)(ws + sc.w.thr),
-                       (uint32_t*)(ws + sc.w.cnt), (uint64_t*)(ws + sc.w.surv), h->N, h->nkb, Bp, nqt, L, mask, B);
+                       (uint32_t*)(ws + sc.w.cnt), (uint64_t*)(ws + sc.w.surv), h->N, h->nkb, Bp, nqt, L, mask, B, prep ? *prep : PrepArgs{});
     LAUNCHCHK();
     return MEM_OK;
 }
@@ -493,14 +499,15 @@ bool use_direct(const Level& L, int B, int Bp, int qt) {
     const int64_t tiles = ((int64_t)L.ntiles * (Bp / qt) + 255) / 256 * (TILE_ROWS + qt);
     return direct * 4 <= tiles * 3;
 }
-int launch_direct_any(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, const Mask& mask, int B) {
+int launch_direct_any(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, const Mask& mask, int B, const PrepArgs* first) {
     int rc = MEM_OK;
     with_store_type(h->dtype, [&](auto dt) {
         constexpr int DT = decltype(dt)::value;
-        rc = B <= 16   ? launch_direct<DT, direct_tq(16) / 16, direct_tr(16) / 16>(h, sc, st, Bp, L, mask, B)
-             : B <= 32 ? launch_direct<DT, direct_tq(32) / 16, direct_tr(32) / 16>(h, sc, st, Bp, L, mask, B)
-             : B <= 64 ? launch_direct<DT, direct_tq(64) / 16, direct_tr(64) / 16>(h, sc, st, Bp, L, mask, B)
-                       : launch_direct<DT, direct_tq(256) / 16, direct_tr(256) / 16>(h, sc, st, Bp, L, mask, B);
+        rc = B <= 16   ? (first ? launch_direct<DT, direct_tq(16) / 16, direct_tr(16) / 16, true>(h, sc, st, Bp, L, mask, B, first)
+                                : launch_direct<DT, direct_tq(16) / 16, direct_tr(16) / 16, false>(h, sc, st, Bp, L, mask, B, nullptr))
+             : B <= 32 ? launch_direct<DT, direct_tq(32) / 16, direct_tr(32) / 16, false>(h, sc, st, Bp, L, mask, B, nullptr)
+             : B <= 64 ? launch_direct<DT, direct_tq(64) / 16, direct_tr(64) / 16, false>(h, sc, st, Bp, L, mask, B, nullptr)
+                       : launch_direct<DT, direct_tq(256) / 16, direct_tr(256) / 16, false>(h, sc, st, Bp, L, mask, B, nullptr);
     });
     return rc;
 }
@@ -594,11 +601,24 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
         const int64_t in_last = h->N - last < TILE_ROWS ? h->N - last : TILE_ROWS;
         cnt0 = (uint32_t)((int64_t)(L0.ntiles - 1) * TILE_ROWS + in_last);
     }
-    with_store_type(h->dtype, [&](auto dt) {
-        hipLaunchKernelGGL(k_prep_queries<decltype(dt)::value>, dim3(Bp), dim3(256), 0, st, queries_dev, B, Bp, h->d, h->nkb, qf, qop,
-                           invq, invq64, thr, cnt, flags, cnt0);
-    });
-    LAUNCHCHK();
+    // a sparse pass has few bank tiles: give each workgroup fewer queries, so that more
+    // workgroups share the pass and each one's k-loop is shorter
+    auto tile_of = [&](const Level& L) {
+        int lqt = qt;
+        while (lqt > 32 && (int64_t)L.ntiles * (Bp / lqt) < 128) lqt >>= 1;
+        return lqt;
+    };
+    auto direct = [&](const Level& L) { return !gemv && use_direct(L, B, Bp, tile_of(L)); };
+    const PrepArgs prep{queries_dev, qf, qop, invq, invq64, thr, cnt, flags, cnt0, B, Bp, h->d, h->nkb, ((uintptr_t)queries_dev & 15) == 0};
+    // The queries are prepared in the launch of the first pass where that pass reads them as given: for few queries.  With more, what a
+    // workgroup converts of them costs what the launch saves.  Whole calls, us, in a launch of their own and fused: one query,
+    // 4096 x 768 fp32 22.1, 19.0; seven, 30,011 x 200 fp16 33.2, 30.7; one, 1M x 1024 bf16 359.9, 355.8; 32, 300,007 x 384 fp16
+    // masked 92.6, 92.7; 64, 65,536 x 1024 fp32 83.5, 84.0; 64, 262,144 x 1024 bf16 235.6, 238.1.
+    const bool fused = plan.n > 0 && !exhaustive && prep.aligned && (gemv || (B <= 16 && direct(plan.lv[0])));
+    if (!fused) {
+        with_store_type(h->dtype, [&](auto dt) { hipLaunchKernelGGL(k_prep_queries<decltype(dt)::value>, dim3(Bp), dim3(256), 0, st, prep); });
+        LAUNCHCHK();
+    }
 
     // rounding margin of the scan's fp32 similarities
     float eps = (float)(h->nkb * KB) * 5.97e-8f + 1e-6f;
@@ -628,15 +648,13 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
             const bool prof = h->prof_on && h->prof_n < MAX_PROFILE;
             if (prof) HIPCHK(hipEventRecord(h->ev[2 * h->prof_n], st));
             int rc;
+            const PrepArgs* first = fused && li == 0 ? &prep : nullptr;
             if (gemv) {
-                rc = B == 1 ? launch_gemv<1>(h, sc, st, B, L, mask) : B == 2 ? launch_gemv<2>(h, sc, st, B, L, mask) : launch_gemv<4>(h, sc, st, B, L, mask);
+                rc = B == 1 ? launch_gemv<1>(h, sc, st, B, L, mask, first) : B == 2 ? launch_gemv<2>(h, sc, st, B, L, mask, first) : launch_gemv<4>(h, sc, st, B, L, mask, first);
+            } else if (direct(L)) {
+                rc = launch_direct_any(h, sc, st, Bp, L, mask, B, first);
             } else {
-                // a sparse pass has few bank tiles: give each workgroup fewer queries, so that more
-                // workgroups share the pass and each one's k-loop is shorter
-                int lqt = qt;
-                while (lqt > 32 && (int64_t)L.ntiles * (Bp / lqt) < 128) lqt >>= 1;
-                if (use_direct(L, B, Bp, lqt)) rc = launch_direct_any(h, sc, st, Bp, L, mask, B);
-                else rc = mask.tags ? launch_mfma_any<true>(h, sc, st, Bp, lqt, L, k1, mask, B) : launch_mfma_any<false>(h, sc, st, Bp, lqt, L, k1, mask, B);
+                rc = mask.tags ? launch_mfma_any<true>(h, sc, st, Bp, tile_of(L), L, k1, mask, B) : launch_mfma_any<false>(h, sc, st, Bp, tile_of(L), L, k1, mask, B);
             }
             if (rc != MEM_OK) return rc;
             if (prof) {

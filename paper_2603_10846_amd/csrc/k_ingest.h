@@ -164,20 +164,49 @@ __global__ __launch_bounds__(256) void k_read_probe(const uint4* __restrict__ p,
 // plus its inverse norm (fp32 and fp64).  Also resets the per-query threshold and presets the
 // survivor count to the number of rows of the sparsest scan pass, which keeps every row.
 // One workgroup per padded query slot; slots >= B become all-zero queries that never pass a filter.
-template <int DT>
-__global__ __launch_bounds__(256) void k_prep_queries(const float* __restrict__ q, int B, int Bpad, int d, int nkb,
-                                                      float* __restrict__ qf, uint16_t* __restrict__ qop,
-                                                      float* __restrict__ invq, double* __restrict__ invq64,
-                                                      float* __restrict__ thr, uint32_t* __restrict__ cnt,
-                                                      uint32_t* __restrict__ flags, uint32_t cnt0) {
-    int b = blockIdx.x, tid = threadIdx.x;
-    int dpad = nkb * KB;
-    __shared__ double red[256];
-    double ssq = 0.0;
-    for (int c8 = tid; c8 < nkb * 8; c8 += 256) {
-        float v[8];
+//
+// It takes as long as a launch does (3 to 5 us), and the first scan pass needs of it only what a workgroup can make of the
+// queries itself.  So where that pass has variants that read the queries as given (FIRST in k_scan_direct.h and k_scan_gemv.h)
+// these workgroups ride in its launch, and what they write is for the launches after it.
+struct PrepArgs {
+    const float* q;                // [B][d]
+    float* qf;
+    uint16_t* qop;
+    float* invq;
+    double* invq64;
+    float* thr;
+    uint32_t* cnt;
+    uint32_t* flags;
+    uint32_t cnt0;
+    int B, Bpad, d, nkb;
+    int aligned;                   // the queries lie at a multiple of 16 bytes (their rows are multiples of 32 bytes)
+};
+// Eight consecutive elements of a query as given, from element e0 (a multiple of 8) on; zeros past its end.
+template <bool ALIGNED>
+__device__ __forceinline__ void load_query8(const float* row, int e0, int d, float (&v)[8]) {
+    const bool in = e0 < d;                                     // d is a multiple of 8
+    const float* p = row + (in ? e0 : 0);
+    if constexpr (ALIGNED) {
+        const float4 x = *reinterpret_cast<const float4*>(p), y = *reinterpret_cast<const float4*>(p + 4);
+        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
+    } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = (b < B && c8 * 8 + i < d) ? q[(int64_t)b * d + c8 * 8 + i] : 0.f;
+        for (int i = 0; i < 8; ++i) v[i] = p[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = in ? v[i] : 0.f;
+}
+// All NT lanes of a workgroup call it; red has a word per wavefront.
+template <int DT, int NT>
+__device__ __forceinline__ void prep_query(const PrepArgs& A, int b, double* red) {
+    const int tid = threadIdx.x, dpad = A.nkb * KB, nkb = A.nkb, Bpad = A.Bpad, B = A.B;
+    uint16_t* qop = A.qop;
+    double ssq = 0.0;
+    for (int c8 = tid; c8 < nkb * 8; c8 += NT) {
+        float v[8];
+        const float* row = A.q + (int64_t)(b < B ? b : 0) * A.d;
+        if (A.aligned) load_query8<true>(row, c8 * 8, b < B ? A.d : 0, v);
+        else load_query8<false>(row, c8 * 8, b < B ? A.d : 0, v);
         int kb = c8 >> 3, c = c8 & 7;
         if (DT == 0) {
             // fp32 store: keep the value; operand = bf16 hi + bf16 lo
@@ -211,7 +240,7 @@ __global__ __launch_bounds__(256) void k_prep_queries(const float* __restrict__ 
             pk.z = h[4] | ((uint32_t)h[5] << 16); pk.w = h[6] | ((uint32_t)h[7] << 16);
             *reinterpret_cast<uint4*>(qop + ((int64_t)kb * Bpad + b) * KB + swz16(c, b & 255) * 8) = pk;
         }
-        float* o = qf + (int64_t)b * dpad + c8 * 8;
+        float* o = A.qf + (int64_t)b * dpad + c8 * 8;
         *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
         *reinterpret_cast<float4*>(o + 4) = make_float4(v[4], v[5], v[6], v[7]);
     }
@@ -219,21 +248,29 @@ __global__ __launch_bounds__(256) void k_prep_queries(const float* __restrict__ 
     // when it pads an odd number of k-steps to an even one, and after the last pass its words count the
     // workgroups of the tail
     if (tid < 8) *reinterpret_cast<uint4*>(qop + ((int64_t)(DT == 0 ? 2 * nkb : nkb) * Bpad + b) * KB + tid * 8) = make_uint4(0, 0, 0, 0);
-    red[tid] = ssq;
+    ssq = wave_total_d(ssq);
+    if ((tid & 63) == 0) red[tid >> 6] = ssq;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) { if (tid < s) red[tid] += red[tid + s]; __syncthreads(); }
     if (tid == 0) {
         bool live = b < B;
-        double inv = live ? 1.0 / sqrt(red[0]) : 0.0;
-        invq64[b] = inv;
-        invq[b] = (float)inv;
+        ssq = 0.0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) ssq += red[w];
+        double inv = live ? 1.0 / sqrt(ssq) : 0.0;
+        A.invq64[b] = inv;
+        A.invq[b] = (float)inv;
         // "No threshold yet" is a finite floor below every reachable value (the scan compares
         // dot * invnorm, which lies in [-|q|, |q|]); empty slots get a threshold their all-zero query
         // can never reach.  Finite values keep the scan's arithmetic free of inf - inf.
-        thr[b] = live ? (float)(-2.0 / inv) : 1.0f;
-        *slot_counter(cnt, b) = live ? cnt0 : 0u;     // rows the sparsest pass will write without counting
-        flags[b] = 0u;                 // per-query status of this retrieve (bit 0: a survivor list overflowed)
+        A.thr[b] = live ? (float)(-2.0 / inv) : 1.0f;
+        *slot_counter(A.cnt, b) = live ? A.cnt0 : 0u;     // rows the sparsest pass will write without counting
+        A.flags[b] = 0u;                 // per-query status of this retrieve (bit 0: a survivor list overflowed)
     }
+}
+template <int DT>
+__global__ __launch_bounds__(256) void k_prep_queries(PrepArgs A) {
+    __shared__ double red[4];
+    prep_query<DT, 256>(A, (int)blockIdx.x, red);
 }
 
 }  // namespace evk

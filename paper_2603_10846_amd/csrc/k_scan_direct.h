@@ -7,8 +7,9 @@
 // global memory into registers (both are stored in operand order: a lane's 16 bytes are 8 consecutive elements of
 // its row), several steps' loads in flight, no barrier and no LDS until the partial sums are added once at the end.
 // What bounds it: two memory latencies and, with many queries or long rows, the operands a compute unit takes in
-// (20 to 30 GB/s).  First pass over 8192 rows, before and now: one query, d = 1024 bf16 17.2 -> 5.6 us; 64 queries
-// 20.5 -> 9.4; 64 queries, d = 1024 fp32 33.6 -> 14.8; 32 queries, d = 384 fp16 13.4 -> 4.9.
+// (20 to 30 GB/s).  First pass over 8192 rows, by tiles and so: one query, d = 1024 bf16 17.2 -> 5.6 us; 64 queries
+// 20.5 -> 9.4; 64 queries, d = 1024 fp32 33.6 -> 14.8; 32 queries, d = 384 fp16 13.4 -> 4.9.  With up to 16 queries that pass
+// prepares them as well (seven queries, 7680 x 200 fp16: 4.2 + 4.0 us in two launches, 4.3 in one).
 #pragma once
 #include "k_scan_mfma.h"
 #include "layout.h"
@@ -18,19 +19,31 @@ namespace evk {
 constexpr int DIRECT_WAVES = 8;
 // Partial sums [wavefront][query][row]; four spare floats per row of queries put the four lane groups of an
 // accumulator's store (queries 4 apart) on different banks.
-template <int MQ, int MR> constexpr int direct_lds_bytes() { return DIRECT_WAVES * 16 * MQ * (16 * MR + 4) * 4; }
+// FIRST: the wavefronts' sums of the queries' squares behind them.
+template <int MQ, int MR, bool FIRST = false> constexpr int direct_lds_bytes() { return DIRECT_WAVES * 16 * MQ * (16 * MR + 4 + (FIRST ? 1 : 0)) * 4; }
 
-template <int DT, int MQ, int MR>
+// FIRST: the sparsest pass, with the queries as given (fp32 rows at a multiple of 16 bytes): a lane rounds and splits what it
+// needs of them, and adds up its part of their squares; the workgroups behind the scan's prepare the queries for the launches after
+// this one.
+template <int DT, int MQ, int MR, bool FIRST>
 __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* __restrict__ store_, const float* __restrict__ invnorm,
                                                                    const uint16_t* __restrict__ qop, const float* __restrict__ invq,
                                                                    const float* __restrict__ thr, uint32_t* __restrict__ cnt,
                                                                    uint64_t* __restrict__ surv, int64_t N, int nkb, int Bp, int nqt,
-                                                                   Level L, Mask mask, int B) {
+                                                                   Level L, Mask mask, int B, PrepArgs prep) {
+    static_assert(!FIRST || MQ == 1, "few queries");
     static_assert(MR == 2 || MR == 4, "32 or 64 rows: a wavefront finishes two queries or one at a time");
     constexpr int TQ = 16 * MQ, TR = 16 * MR, TRP = TR + 4, W = DIRECT_WAVES;
     constexpr int DEPTH = DT == 0 ? 2 : 4;                // steps whose loads are in flight together
     extern __shared__ __align__(16) float direct_part[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, grp = lane >> 4;
+    if constexpr (FIRST) {
+        const int nscan = 8 * ((L.ntiles * (TILE_ROWS / TR) + 7) / 8) * nqt;
+        if ((int)blockIdx.x >= nscan) {                   // uniform
+            prep_query<DT, 64 * W>(prep, (int)blockIdx.x - nscan, reinterpret_cast<double*>(direct_part));
+            return;
+        }
+    }
     // The query tiles that share rows are neighbours on one XCD: all but the first find the rows in its L2.
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int q0 = (slot % nqt) * TQ;
@@ -49,8 +62,18 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
     // rows 16 apart have the same swizzle, and so have the two halves of a k-block up to one bit
     const int lane16 = l16 * KB + swz16(grp, l16) * 8;    // a lane's offset in 16 rows of 16-bit elements, first half
     const int row_elem = (r0 + l16) * KB + grp * 8;       // fp32 stores
+    float qsq[MQ];
+    const float* qrow[MQ];
+    if constexpr (FIRST) {
+#pragma unroll
+        for (int a = 0; a < MQ; ++a) {
+            const int q = q0 + a * 16 + l16;
+            qsq[a] = 0.f;
+            qrow[a] = prep.q + (int64_t)(q < B ? q : B - 1) * prep.d;    // (a query past the end: computed, not kept)
+        }
+    }
     for (int s = s0; s < s1; s += DEPTH) {                // uniform within the wavefront
-        u32x4_t x[DEPTH][MR][DT == 0 ? 2 : 1], y[DEPTH][MQ][DT == 0 ? 2 : 1];
+        u32x4_t x[DEPTH][MR][DT == 0 ? 2 : 1], y[DEPTH][MQ][DT == 0 || FIRST ? 2 : 1];
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) {
             const int su = s + u < s1 ? s + u : s1 - 1, kb = su >> 1, h = su & 1;   // (past the end: loaded, not used)
@@ -62,7 +85,7 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
                     for (int i = 0; i < 2; ++i) x[u][b][i] = *reinterpret_cast<const u32x4_t*>(blk + b * 16 * KB + i * 4);
                 const uint16_t* qb = qop + (((int64_t)kb * 2 + h) * Bp + q0) * KB;
 #pragma unroll
-                for (int a = 0; a < MQ; ++a)
+                for (int a = 0; a < MQ && !FIRST; ++a)
 #pragma unroll
                     for (int i = 0; i < 2; ++i) y[u][a][i] = *reinterpret_cast<const u32x4_t*>(qb + a * 16 * KB + (lane16 ^ (i * 32)));
             } else {
@@ -71,13 +94,45 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
                 for (int b = 0; b < MR; ++b) x[u][b][0] = *reinterpret_cast<const u32x4_t*>(blk + b * 16 * KB + (lane16 ^ (h * 32)));
                 const uint16_t* qb = qop + ((int64_t)kb * Bp + q0) * KB;
 #pragma unroll
-                for (int a = 0; a < MQ; ++a) y[u][a][0] = *reinterpret_cast<const u32x4_t*>(qb + a * 16 * KB + (lane16 ^ (h * 32)));
+                for (int a = 0; a < MQ && !FIRST; ++a) y[u][a][0] = *reinterpret_cast<const u32x4_t*>(qb + a * 16 * KB + (lane16 ^ (h * 32)));
+            }
+            if constexpr (FIRST) {
+                const int e = su * 32 + grp * 8;
+#pragma unroll
+                for (int a = 0; a < MQ; ++a)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) y[u][a][i] = *reinterpret_cast<const u32x4_t*>(qrow[a] + (e < prep.d ? e + i * 4 : 0));
             }
         }
         __builtin_amdgcn_sched_barrier(0);                // all of them requested before the first is used
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) {
             if (s + u >= s1) break;                       // uniform
+            if constexpr (FIRST) {                        // eight fp32 elements -> operands, as k_prep_queries makes them
+                const bool in = (s + u) * 32 + grp * 8 < prep.d;
+#pragma unroll
+                for (int a = 0; a < MQ; ++a) {
+                    u32x4_t hi, lo;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const u32x4_t v = y[u][a][i >> 1];
+                        const float f0 = in ? __uint_as_float(v[(i & 1) * 2]) : 0.f, f1 = in ? __uint_as_float(v[(i & 1) * 2 + 1]) : 0.f;
+                        if constexpr (DT == 0) {
+                            float ra, rb;
+                            hi[i] = pack_bf16x2_hi(f0, f1, ra, rb);
+                            lo[i] = cvt_pk_bf16(ra, rb);
+                            qsq[a] = fmaf(f0, f0, fmaf(f1, f1, qsq[a]));
+                        } else {
+                            hi[i] = DT == 1 ? cvt_pk_bf16(f0, f1) : (f2f16_rne(f0) | ((uint32_t)f2f16_rne(f1) << 16));
+                            const uint16_t h0 = (uint16_t)hi[i], h1 = (uint16_t)(hi[i] >> 16);
+                            const float g0 = DT == 1 ? bf16_to_f(h0) : f16_to_f(h0), g1 = DT == 1 ? bf16_to_f(h1) : f16_to_f(h1);
+                            qsq[a] = fmaf(g0, g0, fmaf(g1, g1, qsq[a]));
+                        }
+                    }
+                    y[u][a][0] = hi;
+                    if constexpr (DT == 0) y[u][a][1] = lo;
+                }
+            }
             if constexpr (DT == 0) {
                 // bf16 hi + lo of the rows (the queries are stored split): hi*hi + hi*lo + lo*hi
 #pragma unroll
@@ -113,6 +168,15 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
         for (int b = 0; b < MR; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r) direct_part[(wave * TQ + a * 16 + 4 * grp + r) * TRP + b * 16 + l16] = acc[a][b][r];
+    float* qsq_part = direct_part + W * TQ * TRP;         // [wavefront][query]
+    if constexpr (FIRST) {
+#pragma unroll
+        for (int a = 0; a < MQ; ++a) {
+            float v = qsq[a];
+            v += __shfl_xor(v, 16, 64); v += __shfl_xor(v, 32, 64);
+            if (grp == 0) qsq_part[wave * TQ + a * 16 + l16] = v;
+        }
+    }
     constexpr int QL = 64 / TR, ITER = (TQ + W * QL - 1) / (W * QL);
     const int row = lane % TR, ql = lane / TR;
     const int64_t id = t * TILE_ROWS + r0 + row;
@@ -125,8 +189,8 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
     for (int i = 0; i < ITER; ++i) {                      // (requested before the barrier)
         const int qi = (i * W + wave) * QL + ql, q = q0 + qi;
         keep[i] = qi < TQ && q < B && id < N;
-        th[i] = thr[keep[i] ? q : 0];
-        inq[i] = invq[keep[i] ? q : 0];
+        th[i] = FIRST ? 0.f : thr[keep[i] ? q : 0];
+        inq[i] = FIRST ? 0.f : invq[keep[i] ? q : 0];
         ok[i] = keep[i] && (!mask.tags || eligible(tag, mask.allow[q], mask.exclude[q]));
     }
     __syncthreads();
@@ -139,7 +203,15 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
             for (int w = 0; w < W; ++w) v[i] += direct_part[(w * TQ + qi) * TRP + row];
         }
         v[i] *= inve;
-        if (L.rho == 0) {
+        if constexpr (FIRST) {
+            float qs = 0.f;
+            if (qi < TQ) {
+#pragma unroll
+                for (int w = 0; w < W; ++w) qs += qsq_part[w * TQ + qi];
+            }
+            inq[i] = 1.f / sqrtf(qs);
+        }
+        if (FIRST || L.rho == 0) {
             // sparsest pass: every row is kept, at its own position (0 = empty slot)
             if (keep[i])
                 surv[(int64_t)q * SURV_CAP + (int64_t)tile_j * TILE_ROWS + r0 + row] = ok[i] ? pack_key(v[i] * inq[i], (int32_t)id) : 0ull;
@@ -151,7 +223,7 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
             if (row == 0 && c != 0) base[i] = atomicAdd(slot_counter(cnt, q), c);
         }
     }
-    if (L.rho == 0) return;
+    if (FIRST || L.rho == 0) return;
 #pragma unroll
     for (int i = 0; i < ITER; ++i) {
         const int q = q0 + (i * W + wave) * QL + ql;

@@ -20,6 +20,7 @@
 // tiles sixteen workgroups share one, and each requests four k-blocks at a time, so that the pass takes a quarter of
 // the memory round trips: 16 tiles of 768 at one query 10.8 -> 7.1 us, 16 tiles of 3072 33.7 -> 15.6.
 #pragma once
+#include "k_ingest.h"
 #include "layout.h"
 
 namespace evk {
@@ -32,13 +33,24 @@ __device__ __forceinline__ void append_survivor(float v, float invq_b, int32_t i
 
 // fp32 stores: CH = 16 chunks of 4 elements per 256-byte segment.
 // RG: groups of 16 rows a workgroup scans (16 = a whole tile; 4 = a quarter, gridDim.x = 4 * tiles; 1 = a sixteenth).
-template <int NB, int RG>
+// FIRST: the sparsest pass, with the queries as given (at a multiple of 16 bytes): the workgroups behind the scan's prepare them
+// for the launches after this one.
+template <int NB, int RG, bool FIRST = false>
 __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ store,
                                                      const float* __restrict__ invnorm,
                                                      const float* __restrict__ qf, const float* __restrict__ invq,
                                                      const float* __restrict__ thr, uint32_t* __restrict__ cnt,
                                                      uint64_t* __restrict__ surv, int64_t N, int nkb, int B,
-                                                     Level L, Mask mask) {
+                                                     Level L, Mask mask, PrepArgs prep) {
+    if constexpr (FIRST) {
+        static_assert(RG == 1, "a sparse pass");
+        const int nscan = L.ntiles * 16;
+        if ((int)blockIdx.x >= nscan) {                      // uniform
+            __shared__ double red[4];
+            prep_query<0, 256>(prep, (int)blockIdx.x - nscan, red);
+            return;
+        }
+    }
     const int tid = threadIdx.x, c = tid & 15, rbase = tid >> 4;   // rbase 0..15
     constexpr int PARTS = 16 / RG;
     const int tile_j = (int)blockIdx.x / PARTS, g0 = ((int)blockIdx.x % PARTS) * RG;   // first row group
@@ -49,6 +61,9 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
     for (int i = 0; i < RG; ++i)
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[i][b] = 0.f;
+    float qq[NB];                                            // FIRST: squares of this lane's part of the queries
+#pragma unroll
+    for (int b = 0; b < NB; ++b) qq[b] = 0.f;
     const float* blk = store + t * nkb * (int64_t)BLOCK_ELEMS + (g0 * 16 + rbase) * KB + c * 4;
     constexpr int KU = RG == 1 ? 4 : 1;                      // k-blocks whose loads are in flight together
     for (int kb = 0; kb < nkb; kb += KU, blk += KU * BLOCK_ELEMS) {
@@ -59,8 +74,15 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
 #pragma unroll
             for (int i = 0; i < RG; ++i) x[k][i] = stream_load_float4(blk + (k - over) * (int64_t)BLOCK_ELEMS + i * 16 * KB);
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
-                qv[k][b] = *reinterpret_cast<const float4*>(qf + (int64_t)(b < B ? b : 0) * dpad + (kb + k - over) * KB + c * 4);
+            for (int b = 0; b < NB; ++b) {
+                if constexpr (FIRST) {
+                    const int e = (kb + k - over) * KB + c * 4;
+                    const float4 x = *reinterpret_cast<const float4*>(prep.q + (int64_t)(b < B ? b : 0) * prep.d + (e < prep.d ? e : 0));
+                    qv[k][b] = e < prep.d ? x : make_float4(0.f, 0.f, 0.f, 0.f);
+                } else {
+                    qv[k][b] = *reinterpret_cast<const float4*>(qf + (int64_t)(b < B ? b : 0) * dpad + (kb + k - over) * KB + c * 4);
+                }
+            }
         }
         if constexpr (KU > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -69,6 +91,11 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
 #pragma unroll
             for (int b = 0; b < NB; ++b)
                 if (KU > 1) qv[k][b] = kb + k < nkb ? qv[k][b] : make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (FIRST) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    qq[b] = fmaf(qv[k][b].x, qv[k][b].x, fmaf(qv[k][b].y, qv[k][b].y, fmaf(qv[k][b].z, qv[k][b].z, fmaf(qv[k][b].w, qv[k][b].w, qq[b]))));
+            }
 #pragma unroll
             for (int i = 0; i < RG; ++i)
 #pragma unroll
@@ -88,6 +115,14 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
             v += __shfl_xor(v, 1, 64); v += __shfl_xor(v, 2, 64); v += __shfl_xor(v, 4, 64); v += __shfl_xor(v, 8, 64);
             acc[i][b] = v;
         }
+    if constexpr (FIRST) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            float v = qq[b];
+            v += __shfl_xor(v, 1, 64); v += __shfl_xor(v, 2, 64); v += __shfl_xor(v, 4, 64); v += __shfl_xor(v, 8, 64);
+            qq[b] = 1.f / sqrtf(v);
+        }
+    }
 #pragma unroll
     for (int i = 0; i < RG; ++i) {
         if (c != i) continue;
@@ -100,8 +135,8 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
             if (b >= B) break;
             float v = acc[i][b] * inve;
             const bool ok = !mask.tags || eligible(tag, mask.allow[b], mask.exclude[b]);
-            if (L.rho == 0)      // sparsest pass keeps every row at its own position, no counter (0 = empty slot)
-                surv[(int64_t)b * SURV_CAP + (int64_t)tile_j * TILE_ROWS + (id - t * TILE_ROWS)] = ok ? pack_key(v * invq[b], (int32_t)id) : 0ull;
+            if (FIRST || L.rho == 0)      // sparsest pass keeps every row at its own position, no counter (0 = empty slot)
+                surv[(int64_t)b * SURV_CAP + (int64_t)tile_j * TILE_ROWS + (id - t * TILE_ROWS)] = ok ? pack_key(v * (FIRST ? qq[b] : invq[b]), (int32_t)id) : 0ull;
             else if (ok && v >= thr[b]) append_survivor(v, invq[b], (int32_t)id, slot_counter(cnt, b), surv + (int64_t)b * SURV_CAP);
         }
     }

@@ -38,3 +38,31 @@ def test_sparse_passes_match_oracle(orc, dtype, N, d, nq, masked):
         assert stats["boundary_swaps"] == 0 and stats["final_swaps"] == 0
     assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
     bank.close()
+
+
+@pytest.mark.parametrize("dtype,N,d,nq", [
+    ("f32", 300, 8, 1), ("f32", 9001, 328, 3), ("f32", 8191, 136, 4), ("f32", 5000, 72, 5), ("bf16", 257, 8, 1), ("bf16", 12000, 200, 16),
+    ("f16", 8193, 136, 7), ("f16", 70, 1032, 15), ("bf16", 9000, 64, 17)])
+def test_queries_at_any_address(orc, dtype, N, d, nq):
+    """Few queries at a multiple of 16 bytes are read as given by the first pass, which prepares them for the others on the
+    way; at another address a launch of its own does.  Both give the oracle's result."""
+    rng = np.random.default_rng([47, N, nq])
+    rows = _unit(rng, N, d)
+    q = _unit(rng, nq, d) * rng.uniform(0.1, 9.0, (nq, 1)).astype(np.float32)
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    k1 = min(N, 64)
+    print(f"addresses {dtype} N={N} d={d} B={nq}", flush=True)
+    bank = _make_bank(dtype, rows, qtab, max_B=nq, max_k1=k1)
+    room = torch.zeros(nq * d + 1, device="cuda:0")
+    room[1:] = torch.from_numpy(q).to("cuda:0").view(-1)
+    odd = room[1:].view(nq, d)
+    assert odd.data_ptr() % 16 == 4
+    results = []
+    for queries in (torch.from_numpy(q).to("cuda:0"), odd):
+        ids, scores, cand, sims = bank.retrieve(queries, 1, k1, 8, 0.5, want_candidates=True)
+        got = {"ids": ids.cpu().numpy(), "scores": scores.cpu().numpy(), "cand_ids": cand.cpu().numpy(), "cand_sims": sims.cpu().numpy()}
+        parity.check_retrieve(orc, orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype]), qtab[1], k1, 8, 0.5, got)
+        results.append(got)
+    assert all(np.array_equal(results[0][k], results[1][k]) for k in results[0])
+    assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    bank.close()
