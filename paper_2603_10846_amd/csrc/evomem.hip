@@ -346,10 +346,10 @@ namespace {
 // kept in a fixed array so that a retrieve allocates nothing on the host either)
 constexpr int MAX_LEVELS = 24;
 struct Plan { int n; Level lv[MAX_LEVELS]; };
-Plan plan_levels(int64_t N, int k1) {
+Plan plan_levels(int64_t N, int k1, int cap) {
     const int nt = (int)((N + TILE_ROWS - 1) / TILE_ROWS);
-    const int cap_tiles = SURV_CAP / TILE_ROWS;
-    int ratio = SURV_CAP / (4 * k1);
+    const int cap_tiles = cap / TILE_ROWS;
+    int ratio = cap / (4 * k1);
     if (ratio > 16) ratio = 16;
     if (ratio < 2) ratio = 2;
     int strides[MAX_LEVELS] = {1}, ns = 1;
@@ -364,6 +364,7 @@ Plan plan_levels(int64_t N, int k1) {
     for (int i = ns - 1; i >= 0; --i) {
         Level L;
         L.stride = strides[i];
+        L.cap = cap;
         const int U = (nt + L.stride - 1) / L.stride;
         if (i == ns - 1) { L.rho = 0; L.ntiles = U; }
         else { L.rho = strides[i + 1] / strides[i]; L.ntiles = U - (U + L.rho - 1) / L.rho; }
@@ -557,7 +558,7 @@ int launch_exact_walk(evomem* h, const Scratch& sc, hipStream_t st, int B, int k
 
 extern "C" int mem_plan_levels(int64_t N, int k1, int* stride, int* rho, int* ntiles, int max_levels) {
     if (N < 1 || N > 2147483647ll - 256 || k1 < 1 || k1 > MEM_MAX_K1 || !stride || !rho || !ntiles || max_levels < 1) return -1;
-    const Plan p = plan_levels(N, k1);
+    const Plan p = plan_levels(N, k1, SURV_CAP);
     for (int i = 0; i < p.n && i < max_levels; ++i) { stride[i] = p.lv[i].stride; rho[i] = p.lv[i].rho; ntiles[i] = p.lv[i].ntiles; }
     return p.n;
 }
@@ -592,10 +593,16 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     h->last_B = B;
     uint32_t* counters = (uint32_t*)(ws + sc.w.counters);
 
+    // A pool of more than 256 leaves a list of 8192 little room for what a denser pass brings (a list is meant to be filled to a
+    // quarter), and the passes become many: 1024 tiles with a pool of 960 take six.  While three quarters of the lists would lie idle,
+    // a query gets two of them: three passes (64 queries, 262,144 x 1024 bf16, whole call 235.6 -> 203.0 us).  Smaller pools would
+    // save no pass that is worth a selection over twice the keys.
+    const bool two = k1 > SMALL_K1_MAX && !exhaustive && sc.lists() >= 4 * B;
+    const int cap = two ? 2 * SURV_CAP : SURV_CAP;
     Plan plan{};
     uint32_t cnt0 = 0;      // valid rows of the sparsest pass (a prefix of its last tile may be all that exists)
     if (h->N > 0) {
-        plan = plan_levels(h->N, k1);
+        plan = plan_levels(h->N, k1, cap);
         const Level& L0 = plan.lv[0];
         const int64_t last = level_tile(L0, L0.ntiles - 1) * TILE_ROWS;
         const int64_t in_last = h->N - last < TILE_ROWS ? h->N - last : TILE_ROWS;
@@ -663,7 +670,7 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
                 h->prof_rows[h->prof_n++] = rows;
             }
             if (li == plan.n - 1) break;                                // the last selection is the tail's
-            hipLaunchKernelGGL(k_select, dim3(B), dim3(1024), 0, st, surv, cnt, thr, (const float*)invq, counters, flags, k1, margin,
+            hipLaunchKernelGGL(two ? k_select<16> : k_select<8>, dim3(B), dim3(1024), 0, st, surv, cnt, thr, (const float*)invq, counters, flags, k1, margin,
                                mask.tags != nullptr, keep_of(k1));
             LAUNCHCHK();
         }
@@ -676,7 +683,7 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     ta.eg = eg;
     ta.surv = surv; ta.cnt = cnt; ta.counters = counters; ta.flags = flags;
     ta.arrived = reinterpret_cast<uint32_t*>(qop + (int64_t)(h->dtype == MEM_F32 ? 2 * h->nkb : h->nkb) * Bp * KB);
-    ta.store = h->store; ta.qf = qf; ta.invq64 = invq64; ta.exact = exact; ta.spare = sc.lists() >= 2 * B ? surv + (int64_t)B * SURV_CAP : nullptr; ta.qstage = h->q + (int64_t)stage * h->capacity;
+    ta.store = h->store; ta.qf = qf; ta.invq64 = invq64; ta.exact = exact; ta.spare = (int64_t)sc.lists() * SURV_CAP >= 2ll * B * cap ? surv + (int64_t)B * cap : nullptr; ta.qstage = h->q + (int64_t)stage * h->capacity;
     ta.out_ids = out_ids_dev; ta.out_scores = out_scores_dev; ta.cand_ids = out_cand_ids_dev; ta.cand_sims = out_cand_sims_dev;
     ta.lambda = (double)lambda; ta.nkb = h->nkb; ta.exact_stride = exact_stride; ta.k1 = k1; ta.k2 = k2;
     ta.may_have_empty = mask.tags != nullptr || exhaustive; ta.mode = exhaustive ? SEL_EXACT : SEL_FINAL; ta.margin = exhaustive ? EXACT_KEY_MARGIN : margin;
@@ -691,6 +698,7 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
         if (!lds_set[h->device]) {
             bool ok = true;
             for (const void* k : {reinterpret_cast<const void*>(k_tail<0, true>), reinterpret_cast<const void*>(k_tail<1, true>), reinterpret_cast<const void*>(k_tail<2, true>),
+                                  reinterpret_cast<const void*>(k_tail<0, true, 16>), reinterpret_cast<const void*>(k_tail<1, true, 16>), reinterpret_cast<const void*>(k_tail<2, true, 16>),
                                   reinterpret_cast<const void*>(k_tail<0, false>), reinterpret_cast<const void*>(k_tail<1, false>), reinterpret_cast<const void*>(k_tail<2, false>)})
                 ok = ok && hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(tail_lds(BIG_K1_MAX) + 16384 * 4)) == hipSuccess;
             if (!ok) return MEM_EHIP;
@@ -700,7 +708,8 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     with_store_type(h->dtype, [&](auto dt) {
         constexpr int DT = decltype(dt)::value;
         const dim3 grid((unsigned)B, (unsigned)parts), block(TAIL_T);
-        if (big) hipLaunchKernelGGL((k_tail<DT, true>), grid, block, lds, st, ta);
+        if (two) hipLaunchKernelGGL((k_tail<DT, true, 16>), grid, block, lds, st, ta);
+        else if (big) hipLaunchKernelGGL((k_tail<DT, true>), grid, block, lds, st, ta);
         else hipLaunchKernelGGL((k_tail<DT, false>), grid, block, lds, st, ta);
     });
     LAUNCHCHK();

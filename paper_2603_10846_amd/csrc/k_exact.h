@@ -163,7 +163,7 @@ __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ su
     const int b = (int)blockIdx.x, tid = threadIdx.x;
     uint64_t* list = surv + (int64_t)b * SURV_CAP;
     uint64_t* words = exact_words(exact, b, exact_stride);
-    Selected s;
+    Selected<SURV_CAP / 1024> s;
     const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, sh, s);
     if (raw > (uint32_t)SURV_CAP) {                 // lost: no key reaches this cut, so the count stays as it is
         if (tid == 0) words[0] = ~0ull;

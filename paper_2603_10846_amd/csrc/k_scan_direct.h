@@ -214,7 +214,7 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
         if (FIRST || L.rho == 0) {
             // sparsest pass: every row is kept, at its own position (0 = empty slot)
             if (keep[i])
-                surv[(int64_t)q * SURV_CAP + (int64_t)tile_j * TILE_ROWS + r0 + row] = ok[i] ? pack_key(v[i] * inq[i], (int32_t)id) : 0ull;
+                surv[(int64_t)q * L.cap + (int64_t)tile_j * TILE_ROWS + r0 + row] = ok[i] ? pack_key(v[i] * inq[i], (int32_t)id) : 0ull;
         } else {
             keep[i] = ok[i] && v[i] >= th[i];
             const uint64_t m = __builtin_amdgcn_ballot_w64(keep[i]);
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
         if (m == 0) continue;                             // uniform within the wavefront
         const uint64_t below = (m >> (TR * ql)) & ((1ull << row) - 1ull);
         const uint32_t pos = (uint32_t)__shfl((int)base[i], TR * ql, 64) + (uint32_t)__popcll(below);
-        if (keep[i] && pos < (uint32_t)SURV_CAP) surv[(int64_t)q * SURV_CAP + pos] = pack_key(v[i] * inq[i], (int32_t)id);
+        if (keep[i] && pos < (uint32_t)L.cap) surv[(int64_t)q * L.cap + pos] = pack_key(v[i] * inq[i], (int32_t)id);
     }
 }
 

@@ -26,9 +26,9 @@
 namespace evk {
 
 __device__ __forceinline__ void append_survivor(float v, float invq_b, int32_t id, uint32_t* cnt_b,
-                                                uint64_t* surv_b) {
+                                                uint64_t* surv_b, int cap) {
     uint32_t pos = atomicAdd(cnt_b, 1u);           // integer slot counter; order is fixed later by sorting
-    if (pos < (uint32_t)SURV_CAP) surv_b[pos] = pack_key(v * invq_b, id);
+    if (pos < (uint32_t)cap) surv_b[pos] = pack_key(v * invq_b, id);
 }
 
 // fp32 stores: CH = 16 chunks of 4 elements per 256-byte segment.
@@ -136,8 +136,8 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
             float v = acc[i][b] * inve;
             const bool ok = !mask.tags || eligible(tag, mask.allow[b], mask.exclude[b]);
             if (FIRST || L.rho == 0)      // sparsest pass keeps every row at its own position, no counter (0 = empty slot)
-                surv[(int64_t)b * SURV_CAP + (int64_t)tile_j * TILE_ROWS + (id - t * TILE_ROWS)] = ok ? pack_key(v * (FIRST ? qq[b] : invq[b]), (int32_t)id) : 0ull;
-            else if (ok && v >= thr[b]) append_survivor(v, invq[b], (int32_t)id, slot_counter(cnt, b), surv + (int64_t)b * SURV_CAP);
+                surv[(int64_t)b * L.cap + (int64_t)tile_j * TILE_ROWS + (id - t * TILE_ROWS)] = ok ? pack_key(v * (FIRST ? qq[b] : invq[b]), (int32_t)id) : 0ull;
+            else if (ok && v >= thr[b]) append_survivor(v, invq[b], (int32_t)id, slot_counter(cnt, b), surv + (int64_t)b * L.cap, L.cap);
         }
     }
 }

@@ -536,8 +536,8 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 if (e < total && !(MASKED && (lq[e] & 0xffffu) == 0xffffu)) {
                     const uint32_t ql = lq[e] & 0xffffu, rank = lq[e] >> 16;
                     const uint32_t pos = base_s[ql] + rank;
-                    if (pos < (uint32_t)SURV_CAP)
-                        surv[(int64_t)(q0 + ql) * SURV_CAP + pos] =
+                    if (pos < (uint32_t)L.cap)
+                        surv[(int64_t)(q0 + ql) * L.cap + pos] =
                             finish_key(__uint_as_float((uint32_t)(ent[k] >> 32)), (int)ql, (int32_t)(uint32_t)ent[k], inv[k]);
                 }
             }
@@ -611,7 +611,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                         for (int r = 0; r < 4; ++r) {
                             const int ql = (wq_u * MQ + a) * 16 + 4 * ((ln >> 4) + opq) + r;
                             const bool ok = !MASKED || eligible(tag, allow_s[ql], exclude_s[ql]);
-                            surv[(int64_t)(q0 + ql) * SURV_CAP + pos] = ok ? pack_key(acc[a][b][r] * inve * invq_s[ql], (int32_t)id) : 0ull;   // 0 = empty slot
+                            surv[(int64_t)(q0 + ql) * L.cap + pos] = ok ? pack_key(acc[a][b][r] * inve * invq_s[ql], (int32_t)id) : 0ull;   // 0 = empty slot
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -681,7 +681,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                         lq[slot] = ok ? (uint32_t)ql : 0xffffu;          // the slot was reserved before the check
                     } else if (ok) {   // list full (a very loose threshold): fall back to the direct path
                         uint32_t pos = atomicAdd(slot_counter(cnt, q0 + ql), 1u);
-                        if (pos < (uint32_t)SURV_CAP) surv[(int64_t)(q0 + ql) * SURV_CAP + pos] = finish_key(av, ql, id, invnorm[id]);
+                        if (pos < (uint32_t)L.cap) surv[(int64_t)(q0 + ql) * L.cap + pos] = finish_key(av, ql, id, invnorm[id]);
                     }
                     ++slot;
                 };

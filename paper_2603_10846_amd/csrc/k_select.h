@@ -91,8 +91,9 @@ struct SelectLds {
     uint32_t most[16], least[16];
     uint32_t part_a[16], part_b[16], digit, need, count, nsmall;
 };
+template <int K>         // keys per lane: 8 for a list of 8192, 16 for two
 struct Selected {
-    uint64_t key[8];     // this lane's keys (0 = none)
+    uint64_t key[K];     // this lane's keys (0 = none)
     uint64_t cut;        // a key stays iff it is not 0 and not below this
     float tau;           // the threshold that this is (similarity units); meaningless with keep_all
     uint32_t kept;       // how many stay
@@ -102,17 +103,18 @@ struct Selected {
 };
 // Reads a list into the lanes' registers; returns its count as the scan left it (it may exceed the list's size).  The
 // count and the first quarter of the list, which is what a filtering pass fills, are requested together.
-__device__ __forceinline__ uint32_t load_keys(const uint64_t* list, const uint32_t* count, Selected& s) {
+template <int K>
+__device__ __forceinline__ uint32_t load_keys(const uint64_t* list, const uint32_t* count, Selected<K>& s) {
     const int tid = threadIdx.x;
-    uint64_t (&key)[8] = s.key;
+    uint64_t (&key)[K] = s.key;
 #pragma unroll
     for (int i = 0; i < 2; ++i) key[i] = list[i * 1024 + tid];
     const uint32_t raw = (uint32_t)__builtin_amdgcn_readfirstlane((int)*count);
-    const int n = raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw;
+    const int n = raw > (uint32_t)(K * 1024) ? K * 1024 : (int)raw;
 #pragma unroll
-    for (int i = 2; i < 8; ++i) key[i] = 0ull;                        // 0 = empty
+    for (int i = 2; i < K; ++i) key[i] = 0ull;                        // 0 = empty
 #pragma unroll
-    for (int i = 2; i < 8; ++i)
+    for (int i = 2; i < K; ++i)
         if (i * 1024 < n) { int idx = i * 1024 + tid; key[i] = idx < n ? list[idx] : 0ull; }
 #pragma unroll
     for (int i = 0; i < 2; ++i) key[i] = i * 1024 + tid < n ? key[i] : 0ull;
@@ -121,16 +123,17 @@ __device__ __forceinline__ uint32_t load_keys(const uint64_t* list, const uint32
 
 // Selects among the keys in the registers (n of them, or fewer where some are empty; only the first `slots` places of the list
 // they were read from may hold one: what lies past them is skipped, a list is seldom full).
+template <int K>
 __device__ __forceinline__ void select_keys(int n, int slots, int k1, float margin, bool may_have_empty, int keep_max, int mode, SelectLds& sh,
-                                            Selected& s) {
+                                            Selected<K>& s) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const uint64_t (&key)[8] = s.key;
+    const uint64_t (&key)[K] = s.key;
     for (int i = tid; i < SEL_BINS; i += 1024) sh.hist[i] = 0;
     if (tid == 0) sh.nsmall = 0;
     uint32_t used = 0;
     uint32_t most = 0u, least = 0u;                   // largest similarity part of a key, and complement of the smallest
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < K; ++i) {
         if (i * 1024 >= slots) continue;                                 // uniform
         if (key[i] != 0) {
             const uint32_t o = (uint32_t)(key[i] >> 32);
@@ -185,7 +188,7 @@ __device__ __forceinline__ void select_keys(int n, int slots, int k1, float marg
     // ranks the in_bin keys that `in` names; the need-th of them is the pivot
     auto rank_few = [&](uint32_t in_bin, auto in) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < K; ++i)
             if (i * 1024 < slots && key[i] != 0 && in(i)) sh.small[atomicAdd(&sh.nsmall, 1u)] = key[i];
         __syncthreads();
         if ((uint32_t)tid < in_bin) {
@@ -203,9 +206,9 @@ __device__ __forceinline__ void select_keys(int n, int slots, int k1, float marg
     const float top = ord2f(most), width = (float)SEL_BINS / (top - ord2f(least));
     bool found = false;
     if (width > 0.f && width < 1e30f && top - ord2f(least) < 1e30f) {        // uniform; not with infinities, NaN or equal similarities
-        uint32_t bin[8];
+        uint32_t bin[K];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < K; ++i) {
             bin[i] = 0;
             if (i * 1024 >= slots) continue;                             // uniform
             const float x = (top - key_sim(key[i])) * width;
@@ -228,7 +231,7 @@ __device__ __forceinline__ void select_keys(int n, int slots, int k1, float marg
         const int shift = hi >= SEL_DIGIT - 1 ? hi - (SEL_DIGIT - 1) : 0;   // this round ranks bits hi .. shift
         const uint32_t dmask = (1u << (hi - shift + 1)) - 1u;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < K; ++i)
             if (i * 1024 < slots && key[i] != 0 && (hi == 63 || (key[i] >> (hi + 1)) == (prefix >> (hi + 1))))
                 atomicAdd(&sh.hist[SEL_BINS - 1 - ((uint32_t)(key[i] >> shift) & dmask)], 1u);
         uint32_t in_bin;
@@ -245,7 +248,7 @@ __device__ __forceinline__ void select_keys(int n, int slots, int k1, float marg
     for (int again = 0;; ++again) {
         uint32_t mine = 0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < K; ++i)
             if (i * 1024 < slots) mine += key[i] != 0 && key[i] >= s.cut;
         s.slot = group_prefix_u32(mine, again ? sh.part_b : sh.part_a, wave, lane, s.kept);
         if (again || s.kept <= (uint32_t)keep_max) break;                    // uniform
@@ -254,33 +257,36 @@ __device__ __forceinline__ void select_keys(int n, int slots, int k1, float marg
         s.cut = pivot;                              // ties within fp32 resolution: exactly the k1 best
     }
 }
+template <int K>
 __device__ __forceinline__ uint32_t select_keys(const uint64_t* list, const uint32_t* count, int k1, float margin, bool may_have_empty,
-                                                int keep_max, int mode, SelectLds& sh, Selected& s) {
+                                                int keep_max, int mode, SelectLds& sh, Selected<K>& s) {
     const uint32_t raw = load_keys(list, count, s);
-    const int n = raw > (uint32_t)SURV_CAP ? SURV_CAP : (int)raw;
+    const int n = raw > (uint32_t)(K * 1024) ? K * 1024 : (int)raw;
     select_keys(n, n, k1, margin, may_have_empty, keep_max, mode, sh, s);
     return raw;
 }
 
 // The kept keys of a selection to the head of a list (the keys were read before a barrier inside the selection).
-__device__ __forceinline__ void store_kept(const Selected& s, uint64_t* list) {
+template <int K>
+__device__ __forceinline__ void store_kept(const Selected<K>& s, uint64_t* list) {
     uint32_t at = s.slot;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < K; ++i)
         if (s.key[i] != 0 && s.key[i] >= s.cut) list[at++] = s.key[i];
 }
 
 // Between two scan passes: one workgroup per query.
+template <int K>
 __global__ __launch_bounds__(1024) void k_select(uint64_t* __restrict__ surv, uint32_t* __restrict__ cnt,
                                                  float* __restrict__ thr, const float* __restrict__ invq,
                                                  uint32_t* __restrict__ counters, uint32_t* __restrict__ flags, int k1, float margin,
                                                  int may_have_empty, int keep_max) {
     __shared__ SelectLds sh;
     const int b = (int)blockIdx.x, tid = threadIdx.x;
-    uint64_t* list = surv + (int64_t)b * SURV_CAP;
-    Selected s;
+    uint64_t* list = surv + (int64_t)b * (K * 1024);
+    Selected<K> s;
     const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, margin, may_have_empty != 0, keep_max, SEL_PASS, sh, s);
-    if (raw > (uint32_t)SURV_CAP && tid == 0) { atomicAdd(counters + 1, 1u); flags[b] |= 1u; }
+    if (raw > (uint32_t)(K * 1024) && tid == 0) { atomicAdd(counters + 1, 1u); flags[b] |= 1u; }
     store_kept(s, list);                            // (every lane has also read the count by now)
     if (tid == 0) {
         *slot_counter(cnt, b) = s.kept;

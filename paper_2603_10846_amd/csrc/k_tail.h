@@ -185,7 +185,7 @@ struct TailArgs {
     const float* qf;
     const double* invq64;
     double* exact;            // [B][exact_stride]; used when a query has several workgroups
-    uint64_t* spare;          // B lists of SURV_CAP words that nothing else uses, or null
+    uint64_t* spare;          // B lists as long as surv's that nothing else uses, or null
     const float* qstage;
     int32_t* out_ids;
     float* out_scores;
@@ -207,8 +207,10 @@ __device__ __forceinline__ TailArgsPtr tail_args_from_here() {
     return p;
 }
 
-template <int DT, bool BIG>
+// K: keys of a query's list per lane (8 or 16).
+template <int DT, bool BIG, int K = SURV_CAP / TAIL_T>
 __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
+    constexpr int CAP = K * TAIL_T;
     extern __shared__ __align__(16) unsigned char tail_smem[];
     __shared__ SelectLds sh;
     __shared__ double red[2][16];
@@ -224,14 +226,14 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     const int b = (int)blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     float4* yq = reinterpret_cast<float4*>(tail_smem + tail_lds(k1));                      // the query
     int part = (int)blockIdx.y, parts = (int)gridDim.y;
-    uint64_t* list = A.surv + (int64_t)b * SURV_CAP;
+    uint64_t* list = A.surv + (int64_t)b * CAP;
 
     query_to_lds<DT>(yq, A.qf + (int64_t)b * A.nkb * KB, A.nkb, TAIL_T);                   // (barriers follow)
     // ---- selection ----
-    Selected s;
+    Selected<K> s;
     const uint32_t raw = select_keys(list, slot_counter(A.cnt, b), k1, A.margin, A.may_have_empty != 0, cap, A.mode, sh, s);
     const TailArgsPtr mid = tail_args_from_here();
-    if (raw > (uint32_t)SURV_CAP && mid->mode == SEL_FINAL && part == 0 && tid == 0) { atomicAdd(mid->counters + 1, 1u); mid->flags[b] |= 1u; }
+    if (raw > (uint32_t)CAP && mid->mode == SEL_FINAL && part == 0 && tid == 0) { atomicAdd(mid->counters + 1, 1u); mid->flags[b] |= 1u; }
     // The last of the query's workgroups to come here?  All that one workgroup hands to another are the similarities
     // below, and those are stored and loaded as device-scope atomics, which pass by the caches that differ between
     // XCDs; so it is enough that a workgroup's stores have been acknowledged before it arrives.  That is this chip's
@@ -246,7 +248,7 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
         return last_s != 0;
     };
     auto stays = [&](int i) __attribute__((always_inline)) { return s.key[i] != 0 && s.key[i] >= s.cut; };
-    // A crowded band (uniform, and the same for all of the query's workgroups): every key of it, up to 8192, gets its
+    // A crowded band (uniform, and the same for all of the query's workgroups): every key of it, up to the list's size, gets its
     // similarity accumulated in fp64 and the selection is made again with those, which are then the candidates' similarities.
     // The keys' ids stay in registers, so the similarities can take the place of the query's own list, or, if several
     // workgroups share the work, a list that the call does not use; without one it is left to the workgroup that knows
@@ -261,17 +263,17 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
         part = 0;
         parts = 1;
     }
-    uint64_t* sims = !crowded ? reinterpret_cast<uint64_t*>(mid->exact + (int64_t)b * mid->exact_stride) : parts > 1 ? mid->spare + (int64_t)b * SURV_CAP : list;
+    uint64_t* sims = !crowded ? reinterpret_cast<uint64_t*>(mid->exact + (int64_t)b * mid->exact_stride) : parts > 1 ? mid->spare + (int64_t)b * CAP : list;
     int32_t* ids = crowded ? reinterpret_cast<int32_t*>(tail_smem) : i0;            // (a crowded band's in pieces)
     // Crowded: this lane's ids (-1 = none) and their places, two to a word, in the list's order as far as a wavefront's keys go.
     // Neighbours in a list are often neighbours in the bank; in the order of `slot` rows gathered together lie 1024 entries
     // apart (5 to 8 % slower).
-    int32_t mine[8];
-    uint32_t places[4];
+    int32_t mine[K];
+    uint32_t places[K / 2];
     int kk = (int)s.kept;
     auto lay_out = [&](int c0) __attribute__((always_inline)) {      // the ids at places c0 .. c0 + TAIL_PIECE - 1
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < K; ++i) {
             int32_t id = mine[i];
             asm volatile("" : "+v"(id));                             // (kept from one piece to the next, the eight conditions fill the scalar registers)
             const uint32_t at = (places[i / 2] >> (16 * (i % 2)) & 0xffffu) - (uint32_t)c0;
@@ -281,22 +283,22 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     };
     if (crowded) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) mine[i] = stays(i) ? key_id(s.key[i]) : -1;
+        for (int i = 0; i < K; ++i) mine[i] = stays(i) ? key_id(s.key[i]) : -1;
         uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.slot);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < K; ++i) {
             const uint64_t in = __builtin_amdgcn_ballot_w64(mine[i] >= 0);
-            const uint32_t at = first + __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));   // at most SURV_CAP
+            const uint32_t at = first + __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));   // at most CAP
             places[i / 2] = i % 2 ? places[i / 2] | at << 16 : at;
             first += (uint32_t)__popcll(in);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(places[i]));
+        for (int i = 0; i < K / 2; ++i) asm volatile("" : "+v"(places[i]));
         lay_out(0);
     } else {
         uint32_t at = s.slot;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < K; ++i)
             if (stays(i)) ids[at++] = key_id(s.key[i]);
         __syncthreads();
     }
@@ -352,16 +354,16 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     };
     if (crowded) {
         __syncthreads();
-        double sim[8];                                               // (all requested at once: behind a condition each it is a round trip each)
+        double sim[K];                                               // (all requested at once: behind a condition each it is a round trip each)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) sim[i] = sim_at(mine[i] >= 0 ? places[i / 2] >> (16 * (i % 2)) & 0xffffu : 0u);
+        for (int i = 0; i < K; ++i) sim[i] = sim_at(mine[i] >= 0 ? places[i / 2] >> (16 * (i % 2)) & 0xffffu : 0u);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) s.key[i] = mine[i] >= 0 ? exact_key(sim[i], mine[i]) : 0ull;
-        select_keys(kk, SURV_CAP, k1, EXACT_KEY_MARGIN, true, cap, SEL_EXACT, sh, s);
+        for (int i = 0; i < K; ++i) s.key[i] = mine[i] >= 0 ? exact_key(sim[i], mine[i]) : 0ull;
+        select_keys(kk, CAP, k1, EXACT_KEY_MARGIN, true, cap, SEL_EXACT, sh, s);
         kk = (int)s.kept;
         uint32_t at = s.slot;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < K; ++i)
             if (stays(i)) { i0[at] = mine[i]; v0[at++] = sim[i]; }
         __syncthreads();
         for (int i = tid; i < kk; i += TAIL_T) q0[i] = mid->qstage[i0[i]];

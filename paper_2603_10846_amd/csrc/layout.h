@@ -19,7 +19,7 @@ namespace evk {
 constexpr int TILE_ROWS = 256;            // bank rows per tile
 constexpr int KB = 64;                    // elements per k-block
 constexpr int BLOCK_ELEMS = TILE_ROWS * KB;
-constexpr int SURV_CAP = 8192;            // survivor slots per query
+constexpr int SURV_CAP = 8192;            // survivor slots of a list; a query's list is one of them, or two neighbours (Level::cap)
 constexpr int KEEP_MAX = 512;             // padded size of the selected list (k1 + guard band) for pools up to 256
 constexpr int BIG_K1_MAX = 2048;          // largest pool
 constexpr int MAX_BATCH = 4096;           // queries per call
@@ -130,6 +130,7 @@ struct Level {
     int stride;     // tile stride S of this level
     int rho;        // parent stride / S  (0 for the sparsest level)
     int ntiles;     // tiles this level scans
+    int cap;        // survivor slots per query
 };
 // Typed / masked retrieval (Sec. 3.2: the bank holds items of several types; Sec. 4.3: entries that
 // stem from held-out operators are excluded).  Every entry carries a 32-bit tag: type = tag & 0xff
