@@ -110,7 +110,7 @@ def other_configs(torch, binding, synth, clustered_bank, clustered_w):
     res.append({"workload": "clustered bank, mem_retrieve_exact, B=4", "B": 4, "retrieve_ms": round(ex_ms, 3),
                 "queries_per_s": round(4 / (ex_ms * 1e-3), 1),
                 "store_GBps": round(clustered_bank.size() * w4.d * 2 / (ex_ms * 1e-3) / 1e9, 1),
-                "note": "reads the bank once per group of up to eight queries"})
+                "note": "reads the bank once for up to eight queries, or 32 where the denser passes run on the matrix cores"})
     # mid: fp32 rows
     w = synth.MID
     bank = binding.MemoryBank(w.d, w.dtype, w.N, max_B=w.B, max_k1=w.k1)

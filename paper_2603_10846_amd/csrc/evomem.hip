@@ -373,11 +373,11 @@ Plan plan_levels(int64_t N, int k1, int cap) {
     return p;
 }
 
-template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true>
+template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true, bool EXACT = false>
 int launch_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, int k1, const Mask& mask, int B) {
     constexpr int QT = 16 * MQ * WQ;
     constexpr int lds = scan_mfma_lds_bytes<QT, MASKED>();
-    auto kern = k_scan_mfma<DT, MQ, WQ, MR, WR, MASKED, STREAM>;
+    auto kern = k_scan_mfma<DT, MQ, WQ, MR, WR, MASKED, STREAM, EXACT>;
     static int resident[MAX_DEVICES] = {};          // workgroups of this kernel the whole device holds at once
     if (!resident[h->device]) {
         HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
@@ -406,7 +406,8 @@ int launch_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Leve
     unsigned char* ws = sc.base;
     hipLaunchKernelGGL(kern, grid, block, lds, st, (const void*)h->store, (const float*)h->invnorm,
                        (const uint16_t*)(ws + sc.w.qop), (const float*)(ws + sc.w.invq), (const float*)(ws + sc.w.thr),
-                       (uint32_t*)(ws + sc.w.cnt), (uint64_t*)(ws + sc.w.surv), h->N, h->nkb, Bp, L, flush_every, mask, B);
+                       (uint32_t*)(ws + sc.w.cnt), (uint64_t*)(ws + sc.w.surv), h->N, h->nkb, Bp, L, flush_every, mask, B,
+                       ExactPass{(const float*)(ws + sc.w.qf), (const double*)(ws + sc.w.invq64), (double*)(ws + sc.w.exact), sc.exact_stride});
     LAUNCHCHK();
     return MEM_OK;
 }
@@ -537,6 +538,31 @@ int launch_exact_scan(evomem* h, const Scratch& sc, hipStream_t st, int B, const
     return MEM_OK;
 }
 
+// A denser pass of it on the matrix cores (32 queries to a tile): the ordinary scan finds the rows that may reach a query's cut,
+// and those few are scored in fp64.  Scoring every row in fp64 costs by the query, and a group of queries reads the bank once.
+// Whole calls, us, in fp64 and so: 1M x 1024 bf16, one query 394, 390; 2 430, 381; 4 485, 390; 8 682, 416; 16 1245, 444; 64 4552, 793;
+// 390,000 x 1024 fp32, 4 339, 341; 5 365, 341; 16 621, 400; 60,000 x 768 bf16 (220 tiles), 4 58.8, 60.7; 5 70.8, 62.4; 16 92.8, 67.4.
+// The fewer the queries the more fp64 waits for memory too, and the more the idle workgroups of a last round of tiles count: 300,000 x
+// 4096 fp16 (1098 tiles, 4.3 to a workgroup), 4 512, 549; 8 732, 611; 16 1310, 723; 100,000 (366, 1.4), 8 283, 336; 16 468, 413; 1M x 256
+// fp16 (3662, 14.3), 4 184, 138.  So two to four want many tiles and rounds of nine tenths, five to eight one round or rounds of four fifths.
+bool use_exact_mfma(int dtype, const Level& L, int B) {
+    const int64_t n = L.ntiles, places = (n + 255) / 256 * 256;
+    if (L.rho == 0 || B == 1) return false;
+    if (B <= 4) return dtype != MEM_F32 && n >= 1024 && places * 9 <= n * 10;
+    if (B <= EXACT_NB && n > 256 && places * 4 > n * 5) return false;
+    return n * ((B + 31) / 32) >= 128;
+}
+int launch_exact_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, int k1, int B) {
+    int rc = MEM_OK;
+    const Mask none{nullptr, nullptr, nullptr};
+    with_store_type(h->dtype, [&](auto dt) {
+        constexpr int DT = decltype(dt)::value;
+        rc = B > 32 ? launch_mfma<DT, 2, 1, 4, 4, false, false, true>(h, sc, st, Bp, L, k1, none, B)
+                    : launch_mfma<DT, 2, 1, 4, 4, false, true, true>(h, sc, st, Bp, L, k1, none, B);
+    });
+    return rc;
+}
+
 // What the passes of the exhaustive selection lost (most calls: nothing, and the launch ends at once).
 template <int DT>
 int launch_exact_walk(evomem* h, const Scratch& sc, hipStream_t st, int B, int k1) {
@@ -635,10 +661,12 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
 
     if (h->N > 0 && exhaustive) {
         for (int li = 0; li < plan.n; ++li) {
-            const int rc = launch_exact_scan(h, sc, st, B, plan.lv[li]);
+            const Level& L = plan.lv[li];
+            const int rc = use_exact_mfma(h->dtype, L, B) ? launch_exact_mfma(h, sc, st, Bp, L, k1, B) : launch_exact_scan(h, sc, st, B, L);
             if (rc != MEM_OK) return rc;
             if (li == plan.n - 1) break;
-            hipLaunchKernelGGL(k_exact_select, dim3(B), dim3(1024), 0, st, surv, cnt, exact, exact_stride, k1, keep_of(k1));
+            hipLaunchKernelGGL(k_exact_select, dim3(B), dim3(1024), 0, st, surv, cnt, exact, exact_stride, k1, keep_of(k1), thr, (const float*)invq,
+                               use_exact_mfma(h->dtype, plan.lv[plan.n - 1], B) ? margin : 0.f, h->dtype);
             LAUNCHCHK();
         }
         if (plan.n > 1) {                                            // (a single pass never overflows)

@@ -1,7 +1,7 @@
 // Exhaustive selection (mem_retrieve_exact): the pool from similarities accumulated in fp64, whatever the
 // bank holds.
 //
-// The bank is read once per group of up to EXACT_NB queries, in the passes of the ordinary plan: the sparsest
+// The bank is read once per group of up to EXACT_NB queries (32 in a pass on the matrix cores), in the passes of the ordinary plan: the sparsest
 // pass keeps every row, each denser one the rows whose key -- the fp64 similarity rounded to fp32, lower ids
 // first among equals -- reaches the query's cut, and after every pass the list is cut back to the k1 best
 // keys plus those within two fp32 roundings of the k1-th (or, if that band is crowded, to exactly the k1
@@ -11,9 +11,11 @@
 // rows that beat everything in the sparser passes (the bank's order decides); such a query is lost, takes
 // part in no further pass, and walks the whole bank afterwards (k_exact_walk), with lists that cannot overflow.
 //
-// Four queries over 1M x 1024 bf16 entries: 4.4 ms when every query read the bank for itself in ranges of 7,680
-// entries (411 launches), 0.47 ms now, of which the last pass is 0.41 ms for 2.0 GB: bound by fp64 multiply-adds and
-// conversions as much as by HBM (fetching two steps ahead instead of one changed nothing; one query takes 0.33 ms).
+// Scoring every row of a denser pass in fp64 is bound by multiply-adds and conversions as much as by HBM (1M x 1024 bf16, four
+// queries, last pass: 0.41 ms for 2.0 GB, one query 0.33; fetching two steps ahead instead of one changed nothing) and costs by the
+// query.  Where it pays (use_exact_mfma in evomem.hip), such a pass runs on the matrix cores instead: their scan, with a
+// threshold below the query's cut by the margin of its rounding, finds the rows that may reach the cut, and only those are scored in
+// fp64, so lists and cuts are the same.  Whole call with 4 and 16 queries: 485 -> 390 us, 1245 -> 444 us.
 #pragma once
 #include "k_ingest.h"
 #include "k_select.h"
@@ -27,6 +29,21 @@ constexpr int EXACT_ROWS = 64;            // rows a workgroup scores at a time: 
 // written only after the selection): the cut, and the number of parts of the bank that have been walked.
 __device__ __forceinline__ uint64_t* exact_words(double* exact, int b, int exact_stride) {
     return reinterpret_cast<uint64_t*>(exact + (int64_t)b * exact_stride);
+}
+
+// What a denser pass on the matrix cores needs besides an ordinary one (k_scan_mfma with EXACT).
+struct ExactPass {
+    const float* qf;
+    const double* invq64;
+    double* words;            // see exact_words
+    int stride;
+};
+
+// Norms of rows and queries that the matrix cores' filter is good for: its thresholds are pairs of 16-bit floats.  Of fp16 a pair
+// resolves 2^-25 at best, which at a norm of 2^-8 is 8e-6 of it (the margin allows 2e-5), and ends at 2^16; bf16 (also for fp32 rows) has
+// fp32's range, in which products of norms are kept from the ends.  NaN does not fit.
+__device__ __forceinline__ bool exact_norm_fits(float norm, int dtype) {
+    return dtype == 2 ? norm >= 0x1p-8f && norm <= 0x1p15f : norm >= 0x1p-50f && norm <= 0x1p50f;
 }
 
 // Products of four neighbouring rows r0 .. r0 + 3 of bank tile t with NB queries, accumulated in fp64 by a lane
@@ -158,7 +175,8 @@ __global__ __launch_bounds__(256, NB > 4 ? 2 : 3) void k_exact_scan(const void* 
 
 // Between two passes: the list cut back, the cut of the next pass.  (After the last one the tail selects.)
 __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ surv, uint32_t* __restrict__ cnt, double* __restrict__ exact,
-                                                       int exact_stride, int k1, int keep_max) {
+                                                       int exact_stride, int k1, int keep_max, float* __restrict__ thr,
+                                                       const float* __restrict__ invq, float margin, int dtype) {
     __shared__ SelectLds sh;
     const int b = (int)blockIdx.x, tid = threadIdx.x;
     uint64_t* list = surv + (int64_t)b * SURV_CAP;
@@ -166,11 +184,17 @@ __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ su
     Selected<SURV_CAP / 1024> s;
     const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, sh, s);
     if (raw > (uint32_t)SURV_CAP) {                 // lost: no key reaches this cut, so the count stays as it is
-        if (tid == 0) words[0] = ~0ull;
+        if (tid == 0) { words[0] = ~0ull; thr[b] = 2.0f / invq[b]; }            // (beyond any row: a similarity is at most 1)
         return;
     }
     store_kept(s, list);
-    if (tid == 0) { *slot_counter(cnt, b) = s.kept; words[0] = s.cut; words[1] = 0ull; }
+    if (tid == 0) {
+        // (a query that a pass on the matrix cores cannot filter for is lost to it, and walks the bank)
+        *slot_counter(cnt, b) = margin > 0.f && !exact_norm_fits(1.0f / invq[b], dtype) ? (uint32_t)SURV_CAP + 1u : s.kept;
+        words[0] = s.cut;
+        words[1] = 0ull;
+        thr[b] = (s.keep_all ? -2.0f : key_sim(s.cut) - margin) / invq[b];      // for a pass on the matrix cores (margin 0: there is none)
+    }
 }
 
 // The lost queries walk the bank together, WALK_NB to a group (one at a time while there are only one or two): a

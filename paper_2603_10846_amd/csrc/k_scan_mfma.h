@@ -30,9 +30,13 @@
 // block), so after the k-loop a score passes iff its accumulator is non-negative; the epilogue
 // collects sign bits, stages the rare survivors in an LDS list and flushes it every few tiles.
 // The sparsest pass has no threshold and writes every row's key to the row's own position.
+//
+// EXACT: a denser pass of the exhaustive selection (k_exact.h).  The filter is the same, what it stages is scored in fp64 before it
+// goes to a list, and a query whose rows find no room to be staged is lost, as one whose list overflows is.
 #pragma once
 #include <type_traits>
 
+#include "k_exact.h"
 #include "k_scan_gemv.h"
 #include "layout.h"
 
@@ -144,16 +148,17 @@ template <int QT, bool MASKED = false> constexpr int scan_mfma_lds_bytes() {
 
 // DT: 0 fp32 store (bf16 split), 1 bf16, 2 f16.  Wave grid WQ x WR, each wave MQ x MR blocks of 16x16.
 // gridDim.x is a multiple of 8 * (Bp / QT).
+// EXACT: see above; not MASKED, never the sparsest pass, 32 queries to a tile.
 // MASKED: typed / masked retrieval -- a row is kept for a query only if the query accepts its tag.
 // STREAM: bank rows are loaded with the non-temporal hint (layout.h).  Right whenever a bank tile is read
 // by one workgroup only; with several query tiles per bank tile (more than 256 queries) the later readers
 // are meant to find the tile in L2, and the hint costs 7 % there (measured: 1185 -> 1105 TFLOP/s at 1024 queries).
-template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true>
+template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true, bool EXACT = false>
 __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __restrict__ store_, const float* __restrict__ invnorm,
                                                    const uint16_t* __restrict__ qop, const float* __restrict__ invq,
                                                    const float* __restrict__ thr, uint32_t* __restrict__ cnt,
                                                    uint64_t* __restrict__ surv, int64_t N, int nkb, int Bp,
-                                                   Level L, int flush_every, Mask mask, int B) {
+                                                   Level L, int flush_every, Mask mask, int B, ExactPass exact) {
     static_assert((WQ * WR == 4 || WQ * WR == 8) && MR * WR == 16, "4 or 8 waves, 256 bank rows per workgroup");
     static_assert(MQ == 2 || MQ == 4 || MQ == 8, "whole groups of query blocks");
     constexpr int NT = 64 * WQ * WR;                   // lanes per workgroup
@@ -550,6 +555,64 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         __syncthreads();
     };
 
+    // EXACT: the staged rows are scored again in fp64, 16 lanes to a row, and those whose key reaches the query's cut go to its list.
+    // About k1 * rho rows per query and pass come here, some 4 us for sixteen of 2 KB, and none is kept for the masses of near-ties
+    // that only the margin lets through (100,000 copies in 1M x 1024, four queries: 0.86 ms a call, 0.50 with the pass in fp64).
+    auto flush_exact = [&]() __attribute__((always_inline)) {
+        constexpr int EPC = DT == 0 ? 4 : 8, U = 8;            // elements per 16-byte chunk; chunks in flight
+        const uint32_t total = *total_s < (uint32_t)SCAN_LIST_CAP ? *total_s : (uint32_t)SCAN_LIST_CAP;
+        const int sub = tid & 15, nch = nkb * KB / EPC;
+        for (uint32_t e = (uint32_t)tid >> 4; e < total; e += NT / 16) {      // (uniform within a lane group)
+            const int32_t id = (int32_t)(uint32_t)lkey[e];
+            const int b = q0 + (int)lq[e];
+            if (b >= B) continue;                              // (rows without a norm reach any threshold, the padding's too)
+            const float4* y = reinterpret_cast<const float4*>(exact.qf + (int64_t)b * (nkb * KB));
+            const double inv = exact.invq64[b];                // (asked for with the row, not behind it)
+            const uint64_t cut = exact_words(exact.words, b, exact.stride)[0];
+            double dot = 0.0, ssq = 0.0;
+            for (int c0 = sub; c0 < nch; c0 += 16 * U) {
+                u32x4_t x[U];
+                float4 yv[U][EPC / 4];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int c = c0 + 16 * u < nch ? c0 + 16 * u : sub;      // past the end: loaded, not used
+                    if constexpr (DT == 0) x[u] = *reinterpret_cast<const u32x4_t*>(static_cast<const float*>(store_) + off32(id, c, nkb));
+                    else x[u] = *reinterpret_cast<const u32x4_t*>(static_cast<const uint16_t*>(store_) + off16(id, c, nkb));
+#pragma unroll
+                    for (int i = 0; i < EPC / 4; ++i) yv[u][i] = y[c * (EPC / 4) + i];
+                }
+                __builtin_amdgcn_sched_barrier(0);             // all of them requested before the first is used
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (c0 + 16 * u >= nch) break;
+#pragma unroll
+                    for (int k = 0; k < EPC; ++k) {
+                        double xd;
+                        if constexpr (DT == 0) xd = __uint_as_float(x[u][k]);
+                        else xd = dec16((uint16_t)(x[u][k >> 1] >> (16 * (k & 1))));
+                        const float4 yk = yv[u][k >> 2];
+                        const double yd = (k & 3) == 0 ? yk.x : (k & 3) == 1 ? yk.y : (k & 3) == 2 ? yk.z : yk.w;
+                        dot += xd * yd;
+                        ssq += xd * xd;
+                    }
+                }
+            }
+            dot = row16_sum(dot);
+            ssq = row16_sum(ssq);
+            if (sub == 0) {
+                const uint64_t key = exact_key(dot * inv * (1.0 / sqrt(ssq)), id);
+                if (key >= cut) {
+                    const uint32_t pos = atomicAdd(slot_counter(cnt, b), 1u);
+                    if (pos < (uint32_t)L.cap) surv[(int64_t)b * L.cap + pos] = key;
+                }
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);                    // vmcnt(0), as above
+        __syncthreads();
+        if (tid == 0) *total_s = 0;
+        __syncthreads();
+    };
+
     // Start of a tile.  The accumulators are not zeroed but initialised, by one MFMA per block,
     // with  - threshold[query] * norm[row] : the filter  score * invnorm >= threshold  is
     // score - threshold * norm >= 0, so after the k-loop the epilogue only has to look at signs.
@@ -558,7 +621,8 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     // the residuals are ~2^-16 relative, inside the margin).  The sparsest pass has no threshold: its
     // query-side extension is zero and the accumulators start at zero.
     // Norm operands of the tile about to start, from the inverse norms requested a tile earlier.
-    uint32_t bx[MR], by[MR];
+    // EXACT: rows whose norm the threshold's operands cannot carry to the margin's precision are scored in fp64 whatever comes out here.
+    uint32_t bx[MR], by[MR], forced = 0;
     auto tile_prepare = [&]() __attribute__((always_inline)) {
         const bool none = fresh_lane() >= 16;                      // only the first chunk of the extension is used
 #pragma unroll
@@ -566,6 +630,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             const float norm = __builtin_amdgcn_rcpf(inv_n[b]);   // finish_key() forms it the same way
             const uint16_t nh = enc16(norm), nl = enc16(norm - dec16(nh));
             const uint32_t mh = nh ^ 0x8000u, ml = nl ^ 0x8000u;
+            if constexpr (EXACT) forced = (b == 0 ? 0u : forced) | (exact_norm_fits(norm, DT) ? 0u : ((1u << (4 * GB)) - 1u) << (4 * GB * b));
             bx[b] = none ? 0u : (mh | (ml << 16));
             by[b] = none ? 0u : mh;
         }
@@ -646,7 +711,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     const AccGroup v = group(g, bg);
 #pragma unroll
                     for (int r = 15; r >= 0; --r) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(v.v[r]), 31);
-                    const uint32_t m = ~neg & valid;
+                    const uint32_t m = (EXACT ? ~neg | forced >> (4 * GB * BB * bg) : ~neg) & valid;
                     msk[g * RGROUPS + bg] = m;
                     mine += __popc(m);
                 }
@@ -679,6 +744,8 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     if (slot < (uint32_t)SCAN_LIST_CAP) {
                         lkey[slot] = ((uint64_t)__float_as_uint(av) << 32) | (uint32_t)id;
                         lq[slot] = ok ? (uint32_t)ql : 0xffffu;          // the slot was reserved before the check
+                    } else if constexpr (EXACT) {   // list full: the query is lost, and walks the bank
+                        if (q0 + ql < B) atomicMax(slot_counter(cnt, q0 + ql), (uint32_t)L.cap + 1u);
                     } else if (ok) {   // list full (a very loose threshold): fall back to the direct path
                         uint32_t pos = atomicAdd(slot_counter(cnt, q0 + ql), 1u);
                         if (pos < (uint32_t)L.cap) surv[(int64_t)(q0 + ql) * L.cap + pos] = finish_key(av, ql, id, invnorm[id]);
@@ -742,7 +809,10 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             // The list is carried from tile to tile and written out every `flush_every` tiles (the host
             // sizes that from the expected number of survivors per tile; a surplus takes the direct
             // path above) and once at the end, so the device-wide round trip is paid every few tiles.
-            if (ti % flush_every == flush_every - 1 || ti == my_tiles - 1) {     // uniform
+            if constexpr (EXACT) {                             // (no wavefront gets to the next tile's epilogue before all have looked)
+                __syncthreads();
+                if (*total_s > (uint32_t)SCAN_LIST_CAP / 4 || ti == my_tiles - 1) flush_exact();      // uniform
+            } else if (ti % flush_every == flush_every - 1 || ti == my_tiles - 1) {          // uniform
                 __syncthreads();
                 flush();
             }

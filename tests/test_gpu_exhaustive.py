@@ -161,3 +161,83 @@ def test_lost_queries_share_their_walks(orc, dtype, k1, nq, nlost, d):
     plain = parity.gpu_retrieve(bank, torch, q[:4], 0, k1, 8, 0.5)
     assert plain["cand_ids"].min() >= 0
     bank.close()
+
+
+# denser passes on the matrix cores: one and several query tiles, partly filled; odd and even k-blocks, rows that end inside a
+# tile, rows without a norm, one denser pass and many, pools up to the largest
+@pytest.mark.parametrize("dtype,N,d,nq,k1", [
+    ("bf16", 330003, 64, 2, 64), ("f16", 50177, 136, 7, 300), ("f32", 50003, 72, 5, 64), ("bf16", 50432, 320, 33, 128), ("f32", 45001, 200, 40, 33),
+    ("f16", 60000, 64, 70, 2048)])
+def test_denser_passes_on_the_matrix_cores(orc, dtype, N, d, nq, k1):
+    rng = np.random.default_rng([35, N, nq])
+    rows = _unit(rng, N, d) * rng.uniform(0.5, 2.0, (N, 1)).astype(np.float32)
+    rows[N - 1] = rows[3]                                            # an exact tie, one copy in the last row
+    rows[N // 2: N // 2 + 500] = 0.0
+    q = _unit(rng, nq, d)
+    q[nq - 1] = rows[3]
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    print(f"exhaustive, matrix cores {dtype} N={N} d={d} B={nq} k1={k1}", flush=True)
+    bank = B.MemoryBank(d, dtype, N, max_B=nq, max_k1=k1)
+    bank.append(_dev(rows), _dev(qtab[0]), _dev(qtab[1]))
+    kept = np.r_[0:N // 2, N // 2 + 500:N]                           # the oracle sees the rows that have a similarity
+    ex = _exact(bank, q, 1, k1, min(8, k1), 0.5)
+    assert np.isin(ex["cand_ids"], kept).all()
+    to = np.full(N, -1, np.int32)
+    to[kept] = np.arange(kept.size, dtype=np.int32)
+    ex["cand_ids"], ex["ids"] = to[ex["cand_ids"]], to[ex["ids"]]
+    stats = parity.check_retrieve(orc, orc.round_to_store(rows[kept], DT[dtype]), orc.round_to_store(q, DT[dtype]), qtab[1][kept], k1, min(8, k1), 0.5, ex)
+    assert stats["boundary_swaps"] == 0 and stats["final_swaps"] == 0
+    assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    bank.close()
+
+
+@pytest.mark.parametrize("nq,copies", [(5, 16000), (32, 40000), (40, 40000)])
+def test_masses_of_copies_pass_the_matrix_cores(orc, nq, copies):
+    """Copies reach every threshold of the fast scan: few enough to a tile they are dropped by their fp64 keys, and where a
+    workgroup's list has no room for a tile's their queries are lost and walk the bank."""
+    rng = np.random.default_rng([36, nq])
+    N, d, k1 = 50000, 128, 64
+    v = _unit(rng, 1, d)
+    order = rng.permutation(N)
+    rows = np.concatenate([np.repeat(v, copies, axis=0), _unit(rng, N - copies, d)])[order]
+    q = np.repeat(v, nq, axis=0)
+    q[1::2] = _unit(rng, len(q[1::2]), d)
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    print(f"exhaustive, copies B={nq}", flush=True)
+    bank = B.MemoryBank(d, "bf16", N, max_B=nq, max_k1=k1)
+    bank.append(_dev(rows), _dev(qtab[0]), _dev(qtab[1]))
+    lowest = np.flatnonzero(order < copies)[:k1]
+    stored, qr = orc.round_to_store(rows, 1), orc.round_to_store(q, 1)
+    for _ in range(2):
+        ex = _exact(bank, q, 0, k1, 8, 0.5)
+        assert (ex["cand_ids"][::2] == lowest).all()
+        if nq > 1:
+            look = [1, nq // 2 | 1, nq - 1]
+            ids, _ = orc.recall(stored, np.ascontiguousarray(qr[look]), k1, threads=8)
+            assert all(set(ex["cand_ids"][b].tolist()) == set(ids[i].tolist()) for i, b in enumerate(look))
+        assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    bank.close()
+
+
+@pytest.mark.parametrize("dtype,nq,row_scale,query_scale", [
+    ("f16", 7, 2.0 ** -14, 1.0), ("f16", 5, 3000.0, 1.0), ("f16", 8, 1.0, 2.0 ** -14), ("f16", 6, 1.0, 4000.0), ("bf16", 9, 1e-18, 1e3), ("f32", 6, 1e-17, 1.0),
+    ("f32", 5, 1.0, 1e17)])
+def test_norms_beyond_the_threshold_operands(orc, dtype, nq, row_scale, query_scale):
+    """Rows and queries whose norms a pair of 16-bit floats does not resolve: the fast scan leaves them to fp64."""
+    rng = np.random.default_rng([37, nq])
+    N, d, k1 = 50000, 1024, 64
+    unit = np.float32(16)                                            # elements of a half, far from the ends of fp16
+    rows = (_unit(rng, N, d) * unit).astype(np.float32)
+    q = _unit(rng, nq, d) * unit
+    rows[::400] += q[rng.integers(0, nq, 125)]                       # in a pool, so that a lost one shows
+    rows[::40] *= row_scale
+    q = (q * query_scale).astype(np.float32)
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    print(f"exhaustive, norms {dtype} B={nq} rows x {row_scale} queries x {query_scale}", flush=True)
+    bank = B.MemoryBank(d, dtype, N, max_B=nq, max_k1=k1)
+    bank.append(_dev(rows), _dev(qtab[0]), _dev(qtab[1]))
+    ex = _exact(bank, q, 0, k1, 8, 0.5)
+    stored, qr = orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype])
+    stats = parity.check_retrieve(orc, stored, qr, qtab[0], k1, 8, 0.5, ex)
+    assert stats["boundary_swaps"] == 0 and stats["final_swaps"] == 0
+    bank.close()
