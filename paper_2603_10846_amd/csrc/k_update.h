@@ -56,15 +56,18 @@ __global__ __launch_bounds__(1024) void k_update_q(const int32_t* __restrict__ i
     uint32_t bad = 0;
     // all of this lane's ids are requested before the first is looked at (the list insertions
     // below are memory operations the loads cannot be moved across, so a plain loop would pay
-    // one memory round trip per id)
+    // one memory round trip per id); a launch of few ids asks for no more than it has (16 loads a lane whatever M: whole calls of one
+    // query over 4096 x 768 19.35 us, 18.8 so; 64 queries over 65,536 x 1024 85.0, 84.3)
     int32_t mine[UPD_CHUNK / 1024];
 #pragma unroll
     for (int u = 0; u < UPD_CHUNK / 1024; ++u) {
+        if (u * 1024 >= M) break;                            // uniform
         const int i = tid + u * 1024;
         mine[u] = ids[i < M ? i : 0];
     }
 #pragma unroll
     for (int u = 0; u < UPD_CHUNK / 1024; ++u) {
+        if (u * 1024 >= M) break;                            // uniform
         const int i = tid + u * 1024;
         if (i >= M) continue;
         const int32_t id = mine[u];
