@@ -208,7 +208,7 @@ __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ su
 // more parts than its own list does: tied to its own 8192 slots a pool of 2048 was walked by four workgroups.
 // 1M x 1024 bf16 bank, ms for the whole call: by ranges of 7,680 entries that every query walked; by workgroups of one
 // query, 8192 / k1 of them at most; now.  One lost query of one, pool 64 4.0, 1.4, 0.88, pool 2048 5.4, 15.0, 1.1; four of
-// four, pool 2048 5.9, 15.3, 1.6; 64 of 64, pool 64 23.2, 24.7, 11.0, pool 2048 24.5, 23.8, 15.9.  fp64 arithmetic is the bound.
+// four, pool 2048 5.9, 15.3, 1.6; 64 of 64, pool 64 23.2, 24.7, 8.1, pool 2048 24.5, 23.8, 15.9.  fp64 arithmetic is the bound.
 constexpr int WALK_T = 512, WALK_ROWS = WALK_T / 4, WALK_NB = 4, WALK_CAP = 4096;
 constexpr int WALK_GROUPS = 256;          // workgroups of the launch: one per compute unit
 constexpr int WALK_LDS = WALK_NB * WALK_CAP * 8;
