@@ -545,9 +545,14 @@ int launch_exact_scan(evomem* h, const Scratch& sc, hipStream_t st, int B, const
 // The fewer the queries the more fp64 waits for memory too, and the more the idle workgroups of a last round of tiles count: 300,000 x
 // 4096 fp16 (1098 tiles, 4.3 to a workgroup), 4 512, 549; 8 732, 611; 16 1310, 723; 100,000 (366, 1.4), 8 283, 336; 16 468, 413; 1M x 256
 // fp16 (3662, 14.3), 4 184, 138.  So two to four want many tiles and rounds of nine tenths, five to eight one round or rounds of four fifths.
-bool use_exact_mfma(int dtype, const Level& L, int B) {
+// A staged row costs 1.8 times what it costs in a pass that scores a group of eight, 2.6 times for four, and the scan itself half to
+// three quarters of such a pass, so what a pass is expected to stage (k1 * rho rows a query) may be a fifth or a seventeenth of the rows
+// times groups; large pools over short passes stay in fp64.
+bool use_exact_mfma(int dtype, const Level& L, int B, int k1) {
     const int64_t n = L.ntiles, places = (n + 255) / 256 * 256;
     if (L.rho == 0 || B == 1) return false;
+    const int64_t staged = (int64_t)k1 * L.rho * B, scored = n * TILE_ROWS * ((B + EXACT_NB - 1) / EXACT_NB);
+    if (staged * (B <= 4 ? 17 : 5) > scored) return false;
     if (B <= 4) return dtype != MEM_F32 && n >= 1024 && places * 9 <= n * 10;
     if (B <= EXACT_NB && n > 256 && places * 4 > n * 5) return false;
     return n * ((B + 31) / 32) >= 128;
@@ -660,13 +665,15 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     const float margin = 2.f * eps;
 
     if (h->N > 0 && exhaustive) {
+        bool mfma_ahead = false;
+        for (int li = 0; li < plan.n; ++li) mfma_ahead = mfma_ahead || use_exact_mfma(h->dtype, plan.lv[li], B, k1);
         for (int li = 0; li < plan.n; ++li) {
             const Level& L = plan.lv[li];
-            const int rc = use_exact_mfma(h->dtype, L, B) ? launch_exact_mfma(h, sc, st, Bp, L, k1, B) : launch_exact_scan(h, sc, st, B, L);
+            const int rc = use_exact_mfma(h->dtype, L, B, k1) ? launch_exact_mfma(h, sc, st, Bp, L, k1, B) : launch_exact_scan(h, sc, st, B, L);
             if (rc != MEM_OK) return rc;
             if (li == plan.n - 1) break;
             hipLaunchKernelGGL(k_exact_select, dim3(B), dim3(1024), 0, st, surv, cnt, exact, exact_stride, k1, keep_of(k1), thr, (const float*)invq,
-                               use_exact_mfma(h->dtype, plan.lv[plan.n - 1], B) ? margin : 0.f, h->dtype);
+                               mfma_ahead ? margin : 0.f, h->dtype);
             LAUNCHCHK();
         }
         if (plan.n > 1) {                                            // (a single pass never overflows)

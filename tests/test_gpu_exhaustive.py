@@ -166,7 +166,7 @@ def test_lost_queries_share_their_walks(orc, dtype, k1, nq, nlost, d):
 # denser passes on the matrix cores: one and several query tiles, partly filled; odd and even k-blocks, rows that end inside a
 # tile, rows without a norm, one denser pass and many, pools up to the largest
 @pytest.mark.parametrize("dtype,N,d,nq,k1", [
-    ("bf16", 330003, 64, 2, 64), ("f16", 50177, 136, 7, 300), ("f32", 50003, 72, 5, 64), ("bf16", 50432, 320, 33, 128), ("f32", 45001, 200, 40, 33),
+    ("bf16", 330003, 64, 2, 64), ("f16", 50177, 136, 7, 128), ("f32", 50003, 72, 5, 64), ("bf16", 50432, 320, 33, 128), ("f32", 45001, 200, 40, 33),
     ("f16", 60000, 64, 70, 2048)])
 def test_denser_passes_on_the_matrix_cores(orc, dtype, N, d, nq, k1):
     rng = np.random.default_rng([35, N, nq])
