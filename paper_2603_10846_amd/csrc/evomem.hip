@@ -547,7 +547,8 @@ int launch_exact_scan(evomem* h, const Scratch& sc, hipStream_t st, int B, const
 // fp16 (3662, 14.3), 4 184, 138.  So two to four want many tiles and rounds of nine tenths, five to eight one round or rounds of four fifths.
 // A staged row costs 1.8 times what it costs in a pass that scores a group of eight, 2.6 times for four, and the scan itself half to
 // three quarters of such a pass, so what a pass is expected to stage (k1 * rho rows a query) may be a fifth or a seventeenth of the rows
-// times groups; large pools over short passes stay in fp64.
+// times groups; large pools over short passes stay in fp64.  1024 bf16, all in fp64 and so, us: 500,000 rows, pool of 600, 5 queries 416, 346, 16
+// 661, 394; pool of 2048, 5 544, 490; 200,000 rows, pool of 600, 16 319, 263; 100,000 rows: the same, no pass qualifies.
 bool use_exact_mfma(int dtype, const Level& L, int B, int k1) {
     const int64_t n = L.ntiles, places = (n + 255) / 256 * 256;
     if (L.rho == 0 || B == 1) return false;
