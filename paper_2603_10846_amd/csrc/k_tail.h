@@ -310,7 +310,12 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
 
     // ---- exact similarities (of this workgroup's share) ----
     // Lanes per row: as many as leave no lane group without a row (16 at least); with more rows than groups of 16, two rows to a group,
-    // which share the query's reads and conversions.
+    // which share the query's reads and conversions.  The order of a row's sums follows from it, and copies of a row have to tie exactly:
+    // so one number for the whole query, by the largest share of its workgroups, whatever this one's is, and in a crowded band by a whole
+    // piece's.  (Sums in one order for every number of lanes, 64 / G partial sums to a lane, would do too but take registers that are not
+    // there: 256 queries, 128 x 2 KB 29 -> 38 us, 1024 queries, 128 x 3 KB 124 -> 157; with 32 lanes and two rows in place of 16 a
+    // crowded band of 7000 81 -> 91.)
+    const int most = ((crowded ? TAIL_PIECE : kk) + parts - 1) / parts;
     for (int c0 = 0;;) {                                             // (one piece unless crowded)
         const int m = !crowded || kk - c0 < TAIL_PIECE ? kk - c0 : TAIL_PIECE;
         const int share = (m - part + parts - 1) / parts;            // rows of this workgroup
@@ -339,9 +344,9 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
             }
         };
         using std::integral_constant;
-        if (share <= TAIL_T / 64) score(integral_constant<int, 64>{}, integral_constant<int, 1>{});
-        else if (share <= TAIL_T / 32) score(integral_constant<int, 32>{}, integral_constant<int, 1>{});
-        else if (share <= TAIL_T / 16) score(integral_constant<int, 16>{}, integral_constant<int, 1>{});
+        if (most <= TAIL_T / 64) score(integral_constant<int, 64>{}, integral_constant<int, 1>{});
+        else if (most <= TAIL_T / 32) score(integral_constant<int, 32>{}, integral_constant<int, 1>{});
+        else if (most <= TAIL_T / 16) score(integral_constant<int, 16>{}, integral_constant<int, 1>{});
         else score(integral_constant<int, 16>{}, integral_constant<int, 2>{});
         c0 += TAIL_PIECE;
         if (!crowded || c0 >= kk) break;                             // uniform

@@ -112,3 +112,55 @@ def test_rows_and_lanes_of_the_scoring(orc, dtype, N, d, nq, k1):
     parity.check_retrieve(orc, orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype]), qtab[1], k1, k2, 0.5, got)
     assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
     bank.close()
+
+
+# Copies of a row have the same similarity bit for bit, whichever workgroup scored them and however many rows it had: fp32 rows,
+# whose products round in fp64.  66 and 130 candidates over four workgroups are 17 and 16, 33 and 32 rows to one, so that they share out
+# their lanes differently; the cut lies between two copies.
+@pytest.mark.parametrize("d,nq,k1", [(1024, 64, 65), (1032, 64, 129), (2056, 30, 65)])
+def test_copies_tie_across_workgroups(orc, d, nq, k1):
+    rng = np.random.default_rng([74, d, k1])
+    N, distinct = 6000, (k1 + 1) // 2
+    v = _unit(rng, 1, d)
+    rows = _unit(rng, N, d)
+    where = rng.permutation(N)[:2 * distinct].reshape(distinct, 2)
+    x = v + _unit(rng, distinct, d) * np.linspace(0.1, 0.9, distinct, dtype=np.float32)[:, None]
+    rows[where[:, 0]] = rows[where[:, 1]] = x * rng.uniform(0.5, 2.0, (distinct, 1)).astype(np.float32)
+    q = (v + 0.05 * _unit(rng, nq, d)).astype(np.float32)
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    print(f"copies d={d} B={nq} k1={k1}", flush=True)
+    bank = _make_bank("f32", rows, qtab, max_B=2 * nq, max_k1=k1)
+    got = parity.gpu_retrieve(bank, torch, q, 1, k1, 8, 0.5)
+    stats = parity.check_retrieve(orc, rows, q, qtab[1], k1, 8, 0.5, got)
+    assert stats["boundary_swaps"] == 0 and stats["order_swaps"] == 0 and stats["final_swaps"] == 0, stats
+    for b in (0, nq // 2, nq - 1):                                   # a query's pool does not depend on the queries it comes with
+        alone = parity.gpu_retrieve(bank, torch, q[b:b + 1], 1, k1, 8, 0.5)
+        assert np.array_equal(alone["ids"][0], got["ids"][b]) and np.array_equal(alone["cand_ids"][0], got["cand_ids"][b]), b
+    bank.close()
+
+
+# A crowded band of copies that ends in a short piece of ids (2304 to a piece).
+@pytest.mark.parametrize("nq,k1,near", [(64, 256, 2310), (6, 960, 2324), (130, 100, 2318)])
+def test_copies_tie_across_pieces_of_a_crowded_band(orc, nq, k1, near):
+    rng = np.random.default_rng([75, nq, k1])
+    N, d = 9000, 1024
+    v = _unit(rng, 1, d)
+    rows = _unit(rng, N, d)
+    x = v + np.float32(1.4e-4) * rng.standard_normal((near // 2, d)).astype(np.float32) * rng.uniform(0.2, 1, (near // 2, 1)).astype(np.float32)
+    where = rng.permutation(N)[:near].reshape(near // 2, 2)
+    rows[where[:, 0]] = rows[where[:, 1]] = x / np.linalg.norm(x, axis=1, keepdims=True)
+    q = (v + np.float32(0.01) * _unit(rng, nq, d)).astype(np.float32)
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    ids, sims = orc.recall(rows, q, k1, threads=8)
+    spread = max(sims[b, k1 - 1] - orc.sims_of(rows, q[b], where.reshape(-1).astype(np.int32)).min() for b in range(nq))
+    print(f"crowded copies B={nq} k1={k1} near={near}: down to {spread:.1e} below the pool", flush=True)
+    assert spread < 1.2e-4                                           # every one of them lies within the scan's margin: the case is what it claims to be
+    bank = _make_bank("f32", rows, qtab, max_B=2 * nq, max_k1=k1)
+    got = parity.gpu_retrieve(bank, torch, q, 1, k1, 8, 0.5)
+    parity.check_retrieve(orc, rows, q, qtab[1], k1, 8, 0.5, got, ora_recall=(ids, sims))
+    twin = dict(zip(where[:, 0].tolist(), where[:, 1].tolist())) | dict(zip(where[:, 1].tolist(), where[:, 0].tolist()))
+    for b in range(nq):                                              # the pool is cut at equal fp32 roundings by id, so a copy's lower id is in it if the other is
+        at = {int(i): j for j, i in enumerate(got["cand_ids"][b])}
+        for i, j in at.items():
+            assert i < twin[i] or at.get(twin[i], k1) < j, (b, i, twin[i])
+    bank.close()
