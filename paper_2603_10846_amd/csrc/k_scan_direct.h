@@ -19,8 +19,8 @@ namespace evk {
 constexpr int DIRECT_WAVES = 8;
 // Partial sums [wavefront][query][row]; four spare floats per row of queries put the four lane groups of an
 // accumulator's store (queries 4 apart) on different banks.
-// FIRST: the wavefronts' sums of the queries' squares behind them.
-template <int MQ, int MR, bool FIRST = false> constexpr int direct_lds_bytes() { return DIRECT_WAVES * 16 * MQ * (16 * MR + 4 + (FIRST ? 1 : 0)) * 4; }
+// FIRST: the wavefronts' sums of the queries' squares (fp64) behind them.
+template <int MQ, int MR, bool FIRST = false> constexpr int direct_lds_bytes() { return DIRECT_WAVES * 16 * MQ * (16 * MR + 4 + (FIRST ? 2 : 0)) * 4; }
 
 // FIRST: the sparsest pass, with the queries as given (fp32 rows at a multiple of 16 bytes): a lane rounds and splits what it
 // needs of them, and adds up its part of their squares; the workgroups behind the scan's prepare the queries for the launches after
@@ -62,13 +62,13 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
     // rows 16 apart have the same swizzle, and so have the two halves of a k-block up to one bit
     const int lane16 = l16 * KB + swz16(grp, l16) * 8;    // a lane's offset in 16 rows of 16-bit elements, first half
     const int row_elem = (r0 + l16) * KB + grp * 8;       // fp32 stores
-    float qsq[MQ];
+    double qsq[MQ];                                       // (in fp64: a query's squares need not fit a float)
     const float* qrow[MQ];
     if constexpr (FIRST) {
 #pragma unroll
         for (int a = 0; a < MQ; ++a) {
             const int q = q0 + a * 16 + l16;
-            qsq[a] = 0.f;
+            qsq[a] = 0.0;
             qrow[a] = prep.q + (int64_t)(q < B ? q : B - 1) * prep.d;    // (a query past the end: computed, not kept)
         }
     }
@@ -121,12 +121,13 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
                             float ra, rb;
                             hi[i] = pack_bf16x2_hi(f0, f1, ra, rb);
                             lo[i] = cvt_pk_bf16(ra, rb);
-                            qsq[a] = fmaf(f0, f0, fmaf(f1, f1, qsq[a]));
+                            const double g0 = f0, g1 = f1;
+                            qsq[a] += g0 * g0 + g1 * g1;
                         } else {
                             hi[i] = DT == 1 ? cvt_pk_bf16(f0, f1) : (f2f16_rne(f0) | ((uint32_t)f2f16_rne(f1) << 16));
                             const uint16_t h0 = (uint16_t)hi[i], h1 = (uint16_t)(hi[i] >> 16);
-                            const float g0 = DT == 1 ? bf16_to_f(h0) : f16_to_f(h0), g1 = DT == 1 ? bf16_to_f(h1) : f16_to_f(h1);
-                            qsq[a] = fmaf(g0, g0, fmaf(g1, g1, qsq[a]));
+                            const double g0 = DT == 1 ? bf16_to_f(h0) : f16_to_f(h0), g1 = DT == 1 ? bf16_to_f(h1) : f16_to_f(h1);
+                            qsq[a] += g0 * g0 + g1 * g1;
                         }
                     }
                     y[u][a][0] = hi;
@@ -168,11 +169,11 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
         for (int b = 0; b < MR; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r) direct_part[(wave * TQ + a * 16 + 4 * grp + r) * TRP + b * 16 + l16] = acc[a][b][r];
-    float* qsq_part = direct_part + W * TQ * TRP;         // [wavefront][query]
+    double* qsq_part = reinterpret_cast<double*>(direct_part + W * TQ * TRP);             // [wavefront][query]
     if constexpr (FIRST) {
 #pragma unroll
         for (int a = 0; a < MQ; ++a) {
-            float v = qsq[a];
+            double v = qsq[a];
             v += __shfl_xor(v, 16, 64); v += __shfl_xor(v, 32, 64);
             if (grp == 0) qsq_part[wave * TQ + a * 16 + l16] = v;
         }
@@ -204,12 +205,12 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
         }
         v[i] *= inve;
         if constexpr (FIRST) {
-            float qs = 0.f;
+            double qs = 0.0;
             if (qi < TQ) {
 #pragma unroll
                 for (int w = 0; w < W; ++w) qs += qsq_part[w * TQ + qi];
             }
-            inq[i] = 1.f / sqrtf(qs);
+            inq[i] = (float)rsqrt_d(qs);
         }
         if (FIRST || L.rho == 0) {
             // sparsest pass: every row is kept, at its own position (0 = empty slot)

@@ -61,9 +61,9 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
     for (int i = 0; i < RG; ++i)
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[i][b] = 0.f;
-    float qq[NB];                                            // FIRST: squares of this lane's part of the queries
+    double qq[NB];                                           // FIRST: squares of this lane's part of the queries (they need not fit a float)
 #pragma unroll
-    for (int b = 0; b < NB; ++b) qq[b] = 0.f;
+    for (int b = 0; b < NB; ++b) qq[b] = 0.0;
     const float* blk = store + t * nkb * (int64_t)BLOCK_ELEMS + (g0 * 16 + rbase) * KB + c * 4;
     constexpr int KU = RG == 1 ? 4 : 1;                      // k-blocks whose loads are in flight together
     for (int kb = 0; kb < nkb; kb += KU, blk += KU * BLOCK_ELEMS) {
@@ -93,8 +93,11 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
                 if (KU > 1) qv[k][b] = kb + k < nkb ? qv[k][b] : make_float4(0.f, 0.f, 0.f, 0.f);
             if constexpr (FIRST) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    qq[b] = fmaf(qv[k][b].x, qv[k][b].x, fmaf(qv[k][b].y, qv[k][b].y, fmaf(qv[k][b].z, qv[k][b].z, fmaf(qv[k][b].w, qv[k][b].w, qq[b]))));
+                for (int b = 0; b < NB; ++b) {
+                    const double y[4] = {qv[k][b].x, qv[k][b].y, qv[k][b].z, qv[k][b].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) qq[b] += y[e] * y[e];
+                }
             }
 #pragma unroll
             for (int i = 0; i < RG; ++i)
@@ -115,13 +118,10 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
             v += __shfl_xor(v, 1, 64); v += __shfl_xor(v, 2, 64); v += __shfl_xor(v, 4, 64); v += __shfl_xor(v, 8, 64);
             acc[i][b] = v;
         }
+    float inq[NB];
     if constexpr (FIRST) {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            float v = qq[b];
-            v += __shfl_xor(v, 1, 64); v += __shfl_xor(v, 2, 64); v += __shfl_xor(v, 4, 64); v += __shfl_xor(v, 8, 64);
-            qq[b] = 1.f / sqrtf(v);
-        }
+        for (int b = 0; b < NB; ++b) inq[b] = (float)rsqrt_d(row16_sum(qq[b]));
     }
 #pragma unroll
     for (int i = 0; i < RG; ++i) {
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256) void k_scan_gemv32(const float* __restrict__ s
             float v = acc[i][b] * inve;
             const bool ok = !mask.tags || eligible(tag, mask.allow[b], mask.exclude[b]);
             if (FIRST || L.rho == 0)      // sparsest pass keeps every row at its own position, no counter (0 = empty slot)
-                surv[(int64_t)b * L.cap + (int64_t)tile_j * TILE_ROWS + (id - t * TILE_ROWS)] = ok ? pack_key(v * (FIRST ? qq[b] : invq[b]), (int32_t)id) : 0ull;
+                surv[(int64_t)b * L.cap + (int64_t)tile_j * TILE_ROWS + (id - t * TILE_ROWS)] = ok ? pack_key(v * (FIRST ? inq[b] : invq[b]), (int32_t)id) : 0ull;
             else if (ok && v >= thr[b]) append_survivor(v, invq[b], (int32_t)id, slot_counter(cnt, b), surv + (int64_t)b * L.cap, L.cap);
         }
     }

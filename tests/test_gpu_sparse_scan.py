@@ -66,3 +66,25 @@ def test_queries_at_any_address(orc, dtype, N, d, nq):
     assert all(np.array_equal(results[0][k], results[1][k]) for k in results[0])
     assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
     bank.close()
+
+
+@pytest.mark.parametrize("scale", [1e-24, 1e-20, 1e22])
+@pytest.mark.parametrize("dtype,N,d,nq", [("f32", 20000, 72, 1), ("f32", 60000, 328, 4), ("f32", 20000, 136, 7), ("bf16", 20000, 64, 1), ("bf16", 60000, 200, 16)])
+def test_queries_of_any_norm(orc, dtype, N, d, nq, scale):
+    """Queries whose squares a float does not hold, over banks of several passes: a similarity does not depend on the query's norm."""
+    rng = np.random.default_rng([48, N, nq])
+    rows = _unit(rng, N, d)
+    q = (_unit(rng, nq, d) * rng.uniform(0.5, 2.0, (nq, 1)) * scale).astype(np.float32)
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    print(f"norms {dtype} N={N} d={d} B={nq} scale={scale}", flush=True)
+    bank = _make_bank(dtype, rows, qtab, max_B=nq, max_k1=64)
+    stored, qr = orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype])
+    room = torch.zeros(nq * d + 1, device="cuda:0")
+    room[1:] = torch.from_numpy(q).to("cuda:0").view(-1)
+    for queries in (torch.from_numpy(q).to("cuda:0"), room[1:].view(nq, d)):
+        ids, scores, cand, sims = bank.retrieve(queries, 1, 64, 8, 0.5, want_candidates=True)
+        got = {"ids": ids.cpu().numpy(), "scores": scores.cpu().numpy(), "cand_ids": cand.cpu().numpy(), "cand_sims": sims.cpu().numpy()}
+        stats = parity.check_retrieve(orc, stored, qr, qtab[1], 64, 8, 0.5, got)
+        assert stats["boundary_swaps"] == 0 and stats["final_swaps"] == 0
+        assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    bank.close()
