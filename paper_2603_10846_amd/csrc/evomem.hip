@@ -674,7 +674,7 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
             if (rc != MEM_OK) return rc;
             if (li == plan.n - 1) break;
             hipLaunchKernelGGL(k_exact_select, dim3(B), dim3(1024), 0, st, surv, cnt, exact, exact_stride, k1, keep_of(k1), thr, (const float*)invq,
-                               mfma_ahead ? margin : 0.f, h->dtype);
+                               (const double*)invq64, mfma_ahead ? margin : 0.f);
             LAUNCHCHK();
         }
         if (plan.n > 1) {                                            // (a single pass never overflows)

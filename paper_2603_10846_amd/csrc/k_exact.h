@@ -39,12 +39,9 @@ struct ExactPass {
     int stride;
 };
 
-// Norms of rows and queries that the matrix cores' filter is good for: its thresholds are pairs of 16-bit floats.  Of fp16 a pair
-// resolves 2^-25 at best, which at a norm of 2^-8 is 8e-6 of it (the margin allows 2e-5), and ends at 2^16; bf16 (also for fp32 rows) has
-// fp32's range, in which products of norms are kept from the ends.  NaN does not fit.
-__device__ __forceinline__ bool exact_norm_fits(float norm, int dtype) {
-    return dtype == 2 ? norm >= 0x1p-8f && norm <= 0x1p15f : norm >= 0x1p-50f && norm <= 0x1p50f;
-}
+// Norms of rows and queries that the matrix cores' filter is good for: its thresholds are pairs of bf16, which have fp32's range and 2^-16
+// of precision; products of norms are kept from the ends.  All norms that fp16 rows can have fit; zero, infinity and NaN do not.
+__device__ __forceinline__ bool exact_norm_fits(float norm) { return norm >= 0x1p-50f && norm <= 0x1p50f; }
 
 // Products of four neighbouring rows r0 .. r0 + 3 of bank tile t with NB queries, accumulated in fp64 by a lane
 // group of 16: a lane takes one 16-byte chunk of each row per step (its offset within a k-block is fixed, so a
@@ -174,26 +171,35 @@ __global__ __launch_bounds__(256, NB > 4 ? 2 : 3) void k_exact_scan(const void* 
 }
 
 // Between two passes: the list cut back, the cut of the next pass.  (After the last one the tail selects.)
+// margin: of the threshold for a pass on the matrix cores; 0 if there is none ahead.  A query that such a pass cannot filter for is lost to
+// it: its norm does not fit, or its cut lies at the rows without a norm.
+// A query without a norm has no similarity to any row: its pool are the first rows of the bank, and no pass has to look for them.
 __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ surv, uint32_t* __restrict__ cnt, double* __restrict__ exact,
                                                        int exact_stride, int k1, int keep_max, float* __restrict__ thr,
-                                                       const float* __restrict__ invq, float margin, int dtype) {
+                                                       const float* __restrict__ invq, const double* __restrict__ invq64, float margin) {
     __shared__ SelectLds sh;
     const int b = (int)blockIdx.x, tid = threadIdx.x;
     uint64_t* list = surv + (int64_t)b * SURV_CAP;
     uint64_t* words = exact_words(exact, b, exact_stride);
+    const double inv64 = invq64[b];                 // (asked for with the list)
     Selected<SURV_CAP / 1024> s;
     const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, sh, s);
+    if (!(inv64 > 0.0 && inv64 < (double)INFINITY)) {                       // uniform
+        for (int i = tid; i < k1; i += 1024) list[i] = pack_key(-INFINITY, i);  // (with more than one pass the bank holds more rows than a pool)
+        if (tid == 0) { *slot_counter(cnt, b) = (uint32_t)k1; words[0] = ~0ull; words[1] = 0ull; }
+        return;
+    }
     if (raw > (uint32_t)SURV_CAP) {                 // lost: no key reaches this cut, so the count stays as it is
-        if (tid == 0) { words[0] = ~0ull; thr[b] = 2.0f / invq[b]; }            // (beyond any row: a similarity is at most 1)
+        if (tid == 0) words[0] = ~0ull;
         return;
     }
     store_kept(s, list);
     if (tid == 0) {
-        // (a query that a pass on the matrix cores cannot filter for is lost to it, and walks the bank)
-        *slot_counter(cnt, b) = margin > 0.f && !exact_norm_fits(1.0f / invq[b], dtype) ? (uint32_t)SURV_CAP + 1u : s.kept;
+        const bool filtered = exact_norm_fits(1.0f / invq[b]) && key_sim(s.cut) >= -1.5f;
+        *slot_counter(cnt, b) = margin > 0.f && !filtered ? (uint32_t)SURV_CAP + 1u : s.kept;
         words[0] = s.cut;
         words[1] = 0ull;
-        thr[b] = (s.keep_all ? -2.0f : key_sim(s.cut) - margin) / invq[b];      // for a pass on the matrix cores (margin 0: there is none)
+        thr[b] = (key_sim(s.cut) - margin) / invq[b];
     }
 }
 

@@ -32,7 +32,8 @@
 // The sparsest pass has no threshold and writes every row's key to the row's own position.
 //
 // EXACT: a denser pass of the exhaustive selection (k_exact.h).  The filter is the same, what it stages is scored in fp64 before it
-// goes to a list, and a query whose rows find no room to be staged is lost, as one whose list overflows is.
+// goes to a list, and a query whose rows find no room to be staged is lost, as one whose list overflows is.  Padding queries and queries
+// that are lost stage nothing, and neither do zero rows, which are below every cut.
 #pragma once
 #include <type_traits>
 
@@ -172,9 +173,11 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     constexpr bool Q_DIRECT = QT == 256;
     // an AccGroup: GB query blocks of BB row blocks, 16 registers (4 * (GB * row block + query block) + register)
     constexpr int GB = MQ < 4 ? MQ : 4, BB = 4 / GB, GROUPS = MQ / GB, RGROUPS = MR / BB;
-    // 16-bit float type of the MFMA operands (bf16 also for fp32 stores, which are split into bf16)
-    auto enc16 = [](float x) __attribute__((always_inline)) { return DT == 2 ? f2f16_rne(x) : f2bf16_rne(x); };
-    auto dec16 = [](uint16_t h) __attribute__((always_inline)) { return DT == 2 ? f16_to_f(h) : bf16_to_f(h); };
+    // 16-bit float type of the operands that carry thresholds and norms: the store's (bf16 also for fp32 stores, which are split into
+    // bf16).  EXACT: always bf16, whose pairs are good to the margin over the whole range of norms that an fp16 row can have.
+    constexpr int TT = DT == 2 && !EXACT ? 2 : 1;
+    auto enc16 = [](float x) __attribute__((always_inline)) { return TT == 2 ? f2f16_rne(x) : f2bf16_rne(x); };
+    auto dec16 = [](uint16_t h) __attribute__((always_inline)) { return TT == 2 ? f16_to_f(h) : bf16_to_f(h); };
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wq = wave / WR, wr = wave % WR;
@@ -216,6 +219,17 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     uint32_t* total_s = lq + SCAN_LIST_CAP;
     uint32_t* allow_s = total_s + 4;                    // masked variant only
     uint32_t* exclude_s = allow_s + QT;
+    if constexpr (EXACT) {
+        // The queries of the tile that rows are looked for, a bit each: not the padding, not the lost, not those that no row can reach.
+        static_assert(QT == 32 && MQ == 2 && MR == 4, "a bit per query, 16 bits per pair of row blocks");
+        if (wave == 0) {
+            const int b = q0 + (lane & 31), in = b < B ? b : 0;
+            const uint32_t count = *slot_counter(cnt, in);
+            const uint64_t cut = exact_words(exact.words, in, exact.stride)[0];
+            const uint64_t m = __builtin_amdgcn_ballot_w64(b < B && count <= (uint32_t)L.cap && cut != ~0ull);
+            if (lane == 0) total_s[1] = (uint32_t)m;
+        }
+    }
     for (int i = tid; i < QT; i += NT) {
         const float th = thr[q0 + i];
         const uint16_t hi = enc16(th), lo = enc16(th - dec16(hi));
@@ -228,6 +242,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         }
     }
     if (tid == 0) *total_s = 0;
+    uint32_t live = ~0u;                                // EXACT: see there
 
     // Accumulators: (re)initialised at the start of every tile by MFMAs with a zero C operand.
     // (An explicit re-zeroing inside the tile loop makes the compiler keep two copies of them.)
@@ -565,7 +580,6 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         for (uint32_t e = (uint32_t)tid >> 4; e < total; e += NT / 16) {      // (uniform within a lane group)
             const int32_t id = (int32_t)(uint32_t)lkey[e];
             const int b = q0 + (int)lq[e];
-            if (b >= B) continue;                              // (rows without a norm reach any threshold, the padding's too)
             const float4* y = reinterpret_cast<const float4*>(exact.qf + (int64_t)b * (nkb * KB));
             const double inv = exact.invq64[b];                // (asked for with the row, not behind it)
             const uint64_t cut = exact_words(exact.words, b, exact.stride)[0];
@@ -589,7 +603,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     for (int k = 0; k < EPC; ++k) {
                         double xd;
                         if constexpr (DT == 0) xd = __uint_as_float(x[u][k]);
-                        else xd = dec16((uint16_t)(x[u][k >> 1] >> (16 * (k & 1))));
+                        else xd = DT == 1 ? bf16_to_f((uint16_t)(x[u][k >> 1] >> (16 * (k & 1)))) : f16_to_f((uint16_t)(x[u][k >> 1] >> (16 * (k & 1))));
                         const float4 yk = yv[u][k >> 2];
                         const double yd = (k & 3) == 0 ? yk.x : (k & 3) == 1 ? yk.y : (k & 3) == 2 ? yk.z : yk.w;
                         dot += xd * yd;
@@ -621,8 +635,9 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     // the residuals are ~2^-16 relative, inside the margin).  The sparsest pass has no threshold: its
     // query-side extension is zero and the accumulators start at zero.
     // Norm operands of the tile about to start, from the inverse norms requested a tile earlier.
-    // EXACT: rows whose norm the threshold's operands cannot carry to the margin's precision are scored in fp64 whatever comes out here.
-    uint32_t bx[MR], by[MR], forced = 0;
+    // EXACT: rows whose norm these operands cannot carry, a bit per block.  Bits 0 .. 3: they are staged whatever comes out here; bits 4 .. 7:
+    // zero rows, which are not; bits 8 .. 11: rows with an infinite inverse norm, zero or not (the epilogue looks).
+    uint32_t bx[MR], by[MR], odd = 0;
     auto tile_prepare = [&]() __attribute__((always_inline)) {
         const bool none = fresh_lane() >= 16;                      // only the first chunk of the extension is used
 #pragma unroll
@@ -630,7 +645,9 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             const float norm = __builtin_amdgcn_rcpf(inv_n[b]);   // finish_key() forms it the same way
             const uint16_t nh = enc16(norm), nl = enc16(norm - dec16(nh));
             const uint32_t mh = nh ^ 0x8000u, ml = nl ^ 0x8000u;
-            if constexpr (EXACT) forced = (b == 0 ? 0u : forced) | (exact_norm_fits(norm, DT) ? 0u : ((1u << (4 * GB)) - 1u) << (4 * GB * b));
+            if constexpr (EXACT) {
+                odd = (b == 0 ? 0u : odd) | (exact_norm_fits(norm) ? 0u : inv_n[b] == INFINITY ? 0x110u << b : 1u << b);
+            }
             bx[b] = none ? 0u : (mh | (ml << 16));
             by[b] = none ? 0u : mh;
         }
@@ -646,7 +663,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             for (int b = 0; b < MR; ++b) {
                 const u32x4_t bext = {bx[b], by[b], 0u, 0u};
                 const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
-                acc[a][b] = mfma16<DT == 0 ? 1 : DT>(aext, bext, z);
+                acc[a][b] = mfma16<TT>(aext, bext, z);
             }
         }
     };
@@ -699,6 +716,49 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             };
             uint32_t msk[GROUPS * RGROUPS];
             uint32_t mine = 0;
+            uint32_t asked = ~0u, staged = 0, dropped = 0;               // EXACT: this lane's queries (16 bits), and its rows that are
+            if constexpr (EXACT) {                                       // staged and dropped whatever the accumulators say (8 bits a row block)
+                const int g4 = 4 * (fresh_lane() >> 4);
+                asked = (live >> g4 & 0xfu) | (live >> (g4 + 12) & 0xf0u);
+                asked |= asked << 8;
+                // An infinite inverse norm: zeros, or a norm below 2^-74 whose squares vanished, and such a row has a similarity.  (Not in
+                // fp16.)  So these rows are looked at, 16 KB by a wavefront at a time: with a row in five zero, 1M x 1024 bf16, four
+                // queries, 470 us a call, 398 without any (621 with eight rows and two steps of a loop over their pieces at a time).
+                if constexpr (DT != 2) {
+                    uint64_t todo = 0, solid = 0;                        // the wavefront's rows, 16 to a block
+#pragma unroll
+                    for (int b = 0; b < MR; ++b) todo |= (__builtin_amdgcn_ballot_w64((odd >> (8 + b) & 1u) != 0) & 0xffffull) << (16 * b);
+                    const int ln = fresh_lane(), nch = nkb * KB / (DT == 0 ? 4 : 8);
+                    const int64_t id0 = t * TILE_ROWS + wr_u * MR * 16;  // (past the bank's end: in the tile's storage, not valid below)
+                    int c0 = 0;
+                    while (todo != 0) {                                  // uniform
+                        constexpr int U = 16;
+                        u32x4_t x[U];
+                        int at[U];                                       // (past the last row: the last piece again)
+#pragma unroll
+                        for (int i = 0; i < U; ++i) {
+                            at[i] = todo != 0 ? __builtin_ctzll(todo) : at[i > 0 ? i - 1 : 0];
+                            const int c = c0 + ln < nch ? c0 + ln : nch - 1;
+                            if constexpr (DT == 0) x[i] = *reinterpret_cast<const u32x4_t*>(static_cast<const float*>(store_) + off32(id0 + at[i], c, nkb));
+                            else x[i] = *reinterpret_cast<const u32x4_t*>(static_cast<const uint16_t*>(store_) + off16(id0 + at[i], c, nkb));
+                            c0 += 64;
+                            if (c0 >= nch) { c0 = 0; todo &= todo - 1; }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);               // all of them requested before the first is used
+#pragma unroll
+                        for (int i = 0; i < U; ++i) {
+                            const uint32_t any = (x[i][0] | x[i][1] | x[i][2] | x[i][3]) & (DT == 0 ? 0x7fffffffu : 0x7fff7fffu);
+                            solid |= __builtin_amdgcn_ballot_w64(any != 0) != 0 ? 1ull << at[i] : 0ull;
+                        }
+                    }
+#pragma unroll
+                    for (int b = 0; b < MR; ++b)
+                        if (solid >> (16 * b + (ln & 15)) & 1ull) odd = (odd & ~(0x10u << b)) | 1u << b;
+                }
+                auto spread = [](uint32_t rows) __attribute__((always_inline)) { return ((rows & 0xfu) * 0x00204081u & 0x01010101u) * 0xffu; };   // bit b -> byte b
+                staged = spread(odd);
+                dropped = spread(odd >> 4);
+            }
 #pragma unroll
             for (int bg = 0; bg < RGROUPS; ++bg) {
                 uint32_t valid = 0;
@@ -711,7 +771,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     const AccGroup v = group(g, bg);
 #pragma unroll
                     for (int r = 15; r >= 0; --r) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(v.v[r]), 31);
-                    const uint32_t m = (EXACT ? ~neg | forced >> (4 * GB * BB * bg) : ~neg) & valid;
+                    const uint32_t m = (EXACT ? ((~neg & ~(dropped >> (16 * bg))) | staged >> (16 * bg)) & asked : ~neg) & valid;
                     msk[g * RGROUPS + bg] = m;
                     mine += __popc(m);
                 }
@@ -745,7 +805,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                         lkey[slot] = ((uint64_t)__float_as_uint(av) << 32) | (uint32_t)id;
                         lq[slot] = ok ? (uint32_t)ql : 0xffffu;          // the slot was reserved before the check
                     } else if constexpr (EXACT) {   // list full: the query is lost, and walks the bank
-                        if (q0 + ql < B) atomicMax(slot_counter(cnt, q0 + ql), (uint32_t)L.cap + 1u);
+                        atomicMax(slot_counter(cnt, q0 + ql), (uint32_t)L.cap + 1u);
                     } else if (ok) {   // list full (a very loose threshold): fall back to the direct path
                         uint32_t pos = atomicAdd(slot_counter(cnt, q0 + ql), 1u);
                         if (pos < (uint32_t)L.cap) surv[(int64_t)(q0 + ql) * L.cap + pos] = finish_key(av, ql, id, invnorm[id]);
@@ -845,6 +905,10 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     gload(gbA);
     if constexpr (Q_DIRECT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
+    if constexpr (EXACT) {
+        live = (uint32_t)__builtin_amdgcn_readfirstlane((int)total_s[1]);
+        if (live == 0) return;                          // uniform: all have read the same word
+    }
     load_invnorm(0);
     tile_prepare();
     for (int ti = 0; ti < my_tiles; ++ti) {

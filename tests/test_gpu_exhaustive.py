@@ -221,7 +221,7 @@ def test_masses_of_copies_pass_the_matrix_cores(orc, nq, copies):
 
 @pytest.mark.parametrize("dtype,nq,row_scale,query_scale", [
     ("f16", 7, 2.0 ** -14, 1.0), ("f16", 5, 3000.0, 1.0), ("f16", 8, 1.0, 2.0 ** -14), ("f16", 6, 1.0, 4000.0), ("bf16", 9, 1e-18, 1e3), ("f32", 6, 1e-17, 1.0),
-    ("f32", 5, 1.0, 1e17)])
+    ("f32", 5, 1.0, 1e17), ("bf16", 9, 1e-27, 1.0), ("f32", 6, 1e-27, 1.0), ("f32", 12, 1e18, 1.0)])
 def test_norms_beyond_the_threshold_operands(orc, dtype, nq, row_scale, query_scale):
     """Rows and queries whose norms a pair of 16-bit floats does not resolve: the fast scan leaves them to fp64."""
     rng = np.random.default_rng([37, nq])
@@ -241,3 +241,57 @@ def test_norms_beyond_the_threshold_operands(orc, dtype, nq, row_scale, query_sc
     stats = parity.check_retrieve(orc, stored, qr, qtab[0], k1, 8, 0.5, ex)
     assert stats["boundary_swaps"] == 0 and stats["final_swaps"] == 0
     bank.close()
+
+
+@pytest.mark.parametrize("what,dtype", [("run of zero rows", "bf16"), ("every sixth row zero", "bf16"), ("every sixth row zero", "f32"), ("every sixth row zero", "f16"),
+                                        ("small rows", "f16"), ("large queries", "f16"), ("zero queries", "bf16")])
+def test_rows_and_queries_without_a_usual_norm_lose_no_query(orc, what, dtype):
+    """A row without a norm is below every cut, and the norms that an fp16 bank can hold are no reason to leave the fast scan: the call
+    takes about as long as one over rows of unit norm (a call whose queries are lost and walk the bank takes five times as long)."""
+    rng = np.random.default_rng([38, len(what)])
+    N, d, nq, k1 = 150000, 512, 64, 64
+    rows = _unit(rng, N, d)
+    q = _unit(rng, nq, d)
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+
+    def timed(x, y):
+        bank = B.MemoryBank(d, dtype, N, max_B=nq, max_k1=k1)
+        bank.append(_dev(x), _dev(qtab[0]), _dev(qtab[1]))
+        y_dev, us = _dev(y), []
+        for i in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            bank.retrieve_exact(y_dev, 0, k1, 8, 0.5)
+            b.record()
+            torch.cuda.synchronize()
+            us.append(1e3 * a.elapsed_time(b))
+        ex = _exact(bank, y, 0, k1, 8, 0.5)
+        bank.close()
+        return sorted(us[2:])[3], ex
+
+    plain, _ = timed(rows, q)
+    rows, q, zero = rows.copy(), q.copy(), np.zeros(N, bool)
+    if what == "run of zero rows":
+        zero[70000:70500] = True
+    elif what == "every sixth row zero":
+        zero[::6] = True
+    elif what == "small rows":
+        rows *= np.float32(2.0 ** -10)
+    elif what == "large queries":
+        q *= np.float32(2.0 ** 17)
+    else:
+        q[1::2] = 0
+    rows[zero] = 0
+    us, ex = timed(rows, q)
+    print(f"exhaustive, {what} {dtype}: {us:.0f} us, {plain:.0f} without", flush=True)
+    some = np.array([0, 30, 62])
+    kept = np.flatnonzero(~zero)
+    to = np.full(N, -1, np.int32)
+    to[kept] = np.arange(kept.size, dtype=np.int32)
+    stored, qr = orc.round_to_store(rows[kept], DT[dtype]), orc.round_to_store(np.ascontiguousarray(q[some]), DT[dtype])
+    got = {k: v[some] for k, v in ex.items()}
+    assert not zero[got["cand_ids"]].any()
+    got["cand_ids"], got["ids"] = to[got["cand_ids"]], to[got["ids"]]
+    stats = parity.check_retrieve(orc, stored, qr, qtab[0][kept], k1, 8, 0.5, got)
+    assert stats["boundary_swaps"] == 0 and stats["final_swaps"] == 0
+    assert us < 2 * plain
