@@ -122,7 +122,7 @@ int mem_retrieve(evomem_t* h, const float* queries_dev, int B, int stage, int k1
  * The bank is read in the passes of the ordinary plan, once per group of up to eight or 32 queries, with cuts
  * that leave no rounding margin.  A query whose list overflows all the same (thousands of entries that beat
  * everything in the sparser passes) reads the whole bank again, in groups of four such queries, with lists
- * that cannot overflow.  1M x 1024 bf16 entries: four queries 0.39 ms, 64 queries 0.79 ms; one such query 0.5 ms
+ * that cannot overflow.  1M x 1024 bf16 entries: four queries 0.39 ms, 64 queries 0.67 ms; one such query 0.5 ms
  * on top, four of them with a pool of 2048 1 ms, 64 of them 7 ms.  It is the call for the queries that
  * mem_retrieve_flags reports, and an on-device cross-check of mem_retrieve.
  * Greedy selection only.  Errors: as mem_retrieve.

@@ -376,7 +376,7 @@ Plan plan_levels(int64_t N, int k1, int cap) {
 template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true, bool EXACT = false>
 int launch_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, int k1, const Mask& mask, int B) {
     constexpr int QT = 16 * MQ * WQ;
-    constexpr int lds = scan_mfma_lds_bytes<QT, MASKED>();
+    constexpr int lds = scan_mfma_lds_bytes<QT, MASKED, EXACT>();
     auto kern = k_scan_mfma<DT, MQ, WQ, MR, WR, MASKED, STREAM, EXACT>;
     static int resident[MAX_DEVICES] = {};          // workgroups of this kernel the whole device holds at once
     if (!resident[h->device]) {
@@ -407,7 +407,7 @@ int launch_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Leve
     hipLaunchKernelGGL(kern, grid, block, lds, st, (const void*)h->store, (const float*)h->invnorm,
                        (const uint16_t*)(ws + sc.w.qop), (const float*)(ws + sc.w.invq), (const float*)(ws + sc.w.thr),
                        (uint32_t*)(ws + sc.w.cnt), (uint64_t*)(ws + sc.w.surv), h->N, h->nkb, Bp, L, flush_every, mask, B,
-                       ExactPass{(const float*)(ws + sc.w.qf), (const double*)(ws + sc.w.invq64), (double*)(ws + sc.w.exact), sc.exact_stride});
+                       ExactPass{(const float*)(ws + sc.w.qf), (const double*)(ws + sc.w.invq64), (double*)(ws + sc.w.exact), sc.exact_stride, (int)(h->N / 500)});
     LAUNCHCHK();
     return MEM_OK;
 }
@@ -540,15 +540,15 @@ int launch_exact_scan(evomem* h, const Scratch& sc, hipStream_t st, int B, const
 
 // A denser pass of it on the matrix cores (32 queries to a tile): the ordinary scan finds the rows that may reach a query's cut,
 // and those few are scored in fp64.  Scoring every row in fp64 costs by the query, and a group of queries reads the bank once.
-// Whole calls, us, in fp64 and so: 1M x 1024 bf16, one query 394, 390; 2 430, 381; 4 485, 390; 8 682, 416; 16 1245, 444; 64 4552, 793;
-// 390,000 x 1024 fp32, 4 339, 341; 5 365, 341; 16 621, 400; 60,000 x 768 bf16 (220 tiles), 4 58.8, 60.7; 5 70.8, 62.4; 16 92.8, 67.4.
+// Whole calls, us, in fp64 and so: 1M x 1024 bf16, one query 394, 390; 2 430, 382; 4 485, 386; 8 682, 406; 16 1245, 415; 64 4552, 665;
+// 390,000 x 1024 fp32, 4 339, 341; 5 365, 340; 16 621, 353; 60,000 x 768 bf16 (220 tiles), 4 58.8, 60.7; 5 70.8, 62.4; 16 92.8, 67.4.
 // The fewer the queries the more fp64 waits for memory too, and the more the idle workgroups of a last round of tiles count: 300,000 x
-// 4096 fp16 (1098 tiles, 4.3 to a workgroup), 4 512, 549; 8 732, 611; 16 1310, 723; 100,000 (366, 1.4), 8 283, 336; 16 468, 413; 1M x 256
-// fp16 (3662, 14.3), 4 184, 138.  So two to four want many tiles and rounds of nine tenths, five to eight one round or rounds of four fifths.
-// A staged row costs 1.8 times what it costs in a pass that scores a group of eight, 2.6 times for four, and the scan itself half to
-// three quarters of such a pass, so what a pass is expected to stage (k1 * rho rows a query) may be a fifth or a seventeenth of the rows
+// 4096 fp16 (1098 tiles, 4.3 to a workgroup), 4 512, 549; 8 732, 554; 16 1310, 610; 100,000 (366, 1.4), 8 283, 336; 16 468, 299; 1M x 256
+// fp16 (3662, 14.3), 4 184, 146.  So two to four want many tiles and rounds of nine tenths, five to eight one round or rounds of four fifths.
+// A staged row cost 1.8 times what it costs in a pass that scores a group of eight, 2.6 times for four, when this was drawn (about as much
+// since a row is staged once for its queries), and the scan itself half to three quarters of such a pass, so what a pass is expected to stage (k1 * rho rows a query) may be a fifth or a seventeenth of the rows
 // times groups; large pools over short passes stay in fp64.  1024 bf16, all in fp64 and so, us: 500,000 rows, pool of 600, 5 queries 416, 346, 16
-// 661, 394; pool of 2048, 5 544, 490; 200,000 rows, pool of 600, 16 319, 263; 100,000 rows: the same, no pass qualifies.
+// 661, 377; pool of 2048, 5 544, 490; 200,000 rows, pool of 600, 16 319, 263; 100,000 rows: the same, no pass qualifies.
 bool use_exact_mfma(int dtype, const Level& L, int B, int k1) {
     const int64_t n = L.ntiles, places = (n + 255) / 256 * 256;
     if (L.rho == 0 || B == 1) return false;

@@ -15,7 +15,9 @@
 // queries, last pass: 0.41 ms for 2.0 GB, one query 0.33; fetching two steps ahead instead of one changed nothing) and costs by the
 // query.  Where it pays (use_exact_mfma in evomem.hip), such a pass runs on the matrix cores instead: their scan, with a
 // threshold below the query's cut by the margin of its rounding, finds the rows that may reach the cut, and only those are scored in
-// fp64, so lists and cuts are the same.  Whole call with 4 and 16 queries: 485 -> 390 us, 1245 -> 444 us.
+// fp64, so lists and cuts are the same.  Whole call with 4 and 16 queries: 485 -> 386 us, 1245 -> 415 us.  The masses of near-ties inside
+// the margin are scored too, 100,000 of them in 585 and 1260 us (526 and 1262 with every row scored); where most of them lie in a few tiles
+// the workgroups that have those score alone (20,000 in a run: 550 and 1528, 510 and 1239).
 #pragma once
 #include "k_ingest.h"
 #include "k_select.h"
@@ -37,11 +39,15 @@ struct ExactPass {
     const double* invq64;
     double* words;            // see exact_words
     int stride;
+    int most_rows;            // of a query that a workgroup scores, once it scores many
 };
 
 // Norms of rows and queries that the matrix cores' filter is good for: its thresholds are pairs of bf16, which have fp32's range and 2^-16
 // of precision; products of norms are kept from the ends.  All norms that fp16 rows can have fit; zero, infinity and NaN do not.
-__device__ __forceinline__ bool exact_norm_fits(float norm) { return norm >= 0x1p-50f && norm <= 0x1p50f; }
+// (2^-50 .. 2^50, so an inverse norm may be asked about as well.)
+__device__ __forceinline__ bool exact_norm_fits(float norm) {
+    return __float_as_uint(norm) - __float_as_uint(0x1p-50f) <= __float_as_uint(0x1p50f) - __float_as_uint(0x1p-50f);
+}
 
 // Products of four neighbouring rows r0 .. r0 + 3 of bank tile t with NB queries, accumulated in fp64 by a lane
 // group of 16: a lane takes one 16-byte chunk of each row per step (its offset within a k-block is fixed, so a
@@ -195,7 +201,7 @@ __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ su
     }
     store_kept(s, list);
     if (tid == 0) {
-        const bool filtered = exact_norm_fits(1.0f / invq[b]) && key_sim(s.cut) >= -1.5f;
+        const bool filtered = exact_norm_fits(invq[b]) && key_sim(s.cut) >= -1.5f;
         *slot_counter(cnt, b) = margin > 0.f && !filtered ? (uint32_t)SURV_CAP + 1u : s.kept;
         words[0] = s.cut;
         words[1] = 0ull;

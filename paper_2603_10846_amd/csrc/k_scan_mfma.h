@@ -32,8 +32,7 @@
 // The sparsest pass has no threshold and writes every row's key to the row's own position.
 //
 // EXACT: a denser pass of the exhaustive selection (k_exact.h).  The filter is the same, what it stages is scored in fp64 before it
-// goes to a list, and a query whose rows find no room to be staged is lost, as one whose list overflows is.  Padding queries and queries
-// that are lost stage nothing, and neither do zero rows, which are below every cut.
+// goes to a list.  Padding queries and queries that are lost stage nothing, and neither do zero rows, which are below every cut.
 #pragma once
 #include <type_traits>
 
@@ -142,9 +141,9 @@ constexpr int SCAN_LIST_CAP = 2048;     // survivor entries a workgroup can stag
 
 // LDS: two stages (bank tile + query tile); per-query threshold, inverse norm, survivor count and
 // list base; the workgroup's survivor list (8-byte key + 4-byte query index per entry); a counter.
-// (masked variant: the per-query type masks and excluded groups in addition)
-template <int QT, bool MASKED = false> constexpr int scan_mfma_lds_bytes() {
-    return 2 * (STAGE_BANK_BYTES + QT * 128) + QT * 16 + SCAN_LIST_CAP * 12 + 16 + (MASKED ? QT * 8 : 0);
+// (masked variant: the per-query type masks and excluded groups in addition; EXACT: cuts and inverse norms)
+template <int QT, bool MASKED = false, bool EXACT = false> constexpr int scan_mfma_lds_bytes() {
+    return 2 * (STAGE_BANK_BYTES + QT * 128) + QT * 16 + SCAN_LIST_CAP * 12 + 16 + (MASKED ? QT * 8 : EXACT ? QT * 16 : 0);
 }
 
 // DT: 0 fp32 store (bf16 split), 1 bf16, 2 f16.  Wave grid WQ x WR, each wave MQ x MR blocks of 16x16.
@@ -219,16 +218,15 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     uint32_t* total_s = lq + SCAN_LIST_CAP;
     uint32_t* allow_s = total_s + 4;                    // masked variant only
     uint32_t* exclude_s = allow_s + QT;
-    if constexpr (EXACT) {
-        // The queries of the tile that rows are looked for, a bit each: not the padding, not the lost, not those that no row can reach.
+    uint64_t* cut_s = reinterpret_cast<uint64_t*>(total_s + 4);                 // EXACT: cuts and inverse norms of the tile's queries
+    double* inv_s = reinterpret_cast<double*>(cut_s + QT);
+    uint32_t count = 0;
+    uint64_t cut = 0;
+    double inv64 = 0.0;
+    if constexpr (EXACT) {                              // (asked for together with the thresholds)
         static_assert(QT == 32 && MQ == 2 && MR == 4, "a bit per query, 16 bits per pair of row blocks");
-        if (wave == 0) {
-            const int b = q0 + (lane & 31), in = b < B ? b : 0;
-            const uint32_t count = *slot_counter(cnt, in);
-            const uint64_t cut = exact_words(exact.words, in, exact.stride)[0];
-            const uint64_t m = __builtin_amdgcn_ballot_w64(b < B && count <= (uint32_t)L.cap && cut != ~0ull);
-            if (lane == 0) total_s[1] = (uint32_t)m;
-        }
+        const int b = q0 + (lane & 31) < B ? q0 + (lane & 31) : 0;
+        if (wave == 0) { count = *slot_counter(cnt, b); cut = exact_words(exact.words, b, exact.stride)[0]; inv64 = exact.invq64[b]; }
     }
     for (int i = tid; i < QT; i += NT) {
         const float th = thr[q0 + i];
@@ -241,7 +239,15 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             exclude_s[i] = q0 + i < B ? mask.exclude[q0 + i] : 0u;
         }
     }
-    if (tid == 0) *total_s = 0;
+    if constexpr (EXACT) {
+        // The queries of the tile that rows are looked for, a bit each: not the padding, not the lost, not those that no row can reach.
+        if (wave == 0) {
+            const uint64_t m = __builtin_amdgcn_ballot_w64(q0 + (lane & 31) < B && count <= (uint32_t)L.cap && cut != ~0ull);
+            if (lane == 0) total_s[1] = (uint32_t)m;
+            if (lane < 32) { cut_s[lane] = cut; inv_s[lane] = inv64; base_s[lane] = 0; }
+        }
+    }
+    if (tid == 0) { total_s[0] = 0; total_s[2] = 0; total_s[3] = 0; }
     uint32_t live = ~0u;                                // EXACT: see there
 
     // Accumulators: (re)initialised at the start of every tile by MFMAs with a zero C operand.
@@ -570,60 +576,109 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         __syncthreads();
     };
 
-    // EXACT: the staged rows are scored again in fp64, 16 lanes to a row, and those whose key reaches the query's cut go to its list.
-    // About k1 * rho rows per query and pass come here, some 4 us for sixteen of 2 KB, and none is kept for the masses of near-ties
-    // that only the margin lets through (100,000 copies in 1M x 1024, four queries: 0.86 ms a call, 0.50 with the pass in fp64).
+    // EXACT: the staged rows are scored again in fp64, 16 lanes to a row and query, and a row whose key reaches the query's cut goes to its
+    // list.  About k1 * rho rows per query and pass come here.  A lane group takes the next row that none has taken, and scores it for its
+    // queries one after the other, 48 chunks to a step, the next step's on their way while one is used.  Where many queries are near the same rows
+    // (masses of near-ties, which only the margin lets through) the groups are at the same query most of the time, so that rows and
+    // queries are found in the compute unit's cache.  Against pairs staged
+    // one by one and scored one after the other (1M x 1024 bf16, whole call, us, four, 16 and 64 queries): 390, 455, 781 -> 386, 420, 665;
+    // 100,000 rows within the margin of all of them 841, 1625, 4559 -> 585, 1260, 3771; 20,000 such rows in a run, whose queries were lost for want
+    // of room, 647, 2823, 7417 -> 550, 1528, 2918.  Rows of 64 fp16 pay for the longer code: two queries over 1M, densest pass 53 -> 58.
+    // A workgroup that meets most of a query's rows (near-duplicates appended one after the other) would score them alone while the others
+    // have none: once it has scored more than 2048 pairs, a query with more than most_rows of them is lost, and walks the bank.
+    uint32_t* taken_s = total_s + 2;                           // rows taken; pairs scored; base_s: those of a query
     auto flush_exact = [&]() __attribute__((always_inline)) {
-        constexpr int EPC = DT == 0 ? 4 : 8, U = 8;            // elements per 16-byte chunk; chunks in flight
-        const uint32_t total = *total_s < (uint32_t)SCAN_LIST_CAP ? *total_s : (uint32_t)SCAN_LIST_CAP;
-        const int sub = tid & 15, nch = nkb * KB / EPC;
-        for (uint32_t e = (uint32_t)tid >> 4; e < total; e += NT / 16) {      // (uniform within a lane group)
-            const int32_t id = (int32_t)(uint32_t)lkey[e];
-            const int b = q0 + (int)lq[e];
-            const float4* y = reinterpret_cast<const float4*>(exact.qf + (int64_t)b * (nkb * KB));
-            const double inv = exact.invq64[b];                // (asked for with the row, not behind it)
-            const uint64_t cut = exact_words(exact.words, b, exact.stride)[0];
-            double dot = 0.0, ssq = 0.0;
-            for (int c0 = sub; c0 < nch; c0 += 16 * U) {
-                u32x4_t x[U];
-                float4 yv[U][EPC / 4];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int c = c0 + 16 * u < nch ? c0 + 16 * u : sub;      // past the end: loaded, not used
-                    if constexpr (DT == 0) x[u] = *reinterpret_cast<const u32x4_t*>(static_cast<const float*>(store_) + off32(id, c, nkb));
-                    else x[u] = *reinterpret_cast<const u32x4_t*>(static_cast<const uint16_t*>(store_) + off16(id, c, nkb));
-#pragma unroll
-                    for (int i = 0; i < EPC / 4; ++i) yv[u][i] = y[c * (EPC / 4) + i];
+        constexpr int EPC = DT == 0 ? 4 : 8, U = 3;            // elements per 16-byte chunk; chunks to a step
+        static_assert(!EXACT || WQ == 1, "a wavefront's number is that of its rows");
+        const int lane = fresh_lane(), sub = lane & 15, nch = nkb * KB / EPC;
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane((int)*total_s);      // (never more than the list holds)
+        // What a lane group fetches next; all that follows is uniform within it.
+        struct Step { u32x4_t x[U]; float4 y[U][EPC / 4]; int32_t id; int q, c; };       // c: first chunk; q < 0: none left
+        int32_t id = 0;
+        uint32_t left = 0;                                     // queries of the row
+        int at = 0;
+        auto next_pair = [&]() __attribute__((always_inline)) {
+            left &= left - 1;
+            for (;;) {
+                while (left == 0) {
+                    uint32_t row = 0;
+                    if (sub == 0) row = atomicAdd(taken_s, 1u);
+                    row = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)row, 0x150, 0xf, 0xf, true);       // of the first of 16 lanes
+                    if (row >= total) return;
+                    id = (int32_t)(uint32_t)lkey[row];
+                    left = (uint32_t)(lkey[row] >> 32) & live;
                 }
-                __builtin_amdgcn_sched_barrier(0);             // all of them requested before the first is used
+                const int q = __builtin_ctz(left);
+                if (taken_s[1] <= (uint32_t)SCAN_LIST_CAP || base_s[q] <= (uint32_t)exact.most_rows) return;
+                if (sub == 0) atomicMax(slot_counter(cnt, q0 + q), (uint32_t)L.cap + 1u);
+                left &= left - 1;
+            }
+        };
+        auto fetch = [&](Step& st) __attribute__((always_inline)) {
+            st.id = id;
+            st.q = left != 0 ? __builtin_ctz(left) : -1;
+            st.c = at;
+            const float4* y = reinterpret_cast<const float4*>(exact.qf + (int64_t)(q0 + (st.q < 0 ? 0 : st.q)) * (nkb * KB));    // (none left: loaded, not used)
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (c0 + 16 * u >= nch) break;
+            for (int u = 0; u < U; ++u) {
+                const int c = at + sub + 16 * u < nch ? at + sub + 16 * u : nch - 1;     // past the end: loaded, not used
+                if constexpr (DT == 0) st.x[u] = *reinterpret_cast<const u32x4_t*>(static_cast<const float*>(store_) + off32(id, c, nkb));
+                else st.x[u] = *reinterpret_cast<const u32x4_t*>(static_cast<const uint16_t*>(store_) + off16(id, c, nkb));
 #pragma unroll
-                    for (int k = 0; k < EPC; ++k) {
-                        double xd;
-                        if constexpr (DT == 0) xd = __uint_as_float(x[u][k]);
-                        else xd = DT == 1 ? bf16_to_f((uint16_t)(x[u][k >> 1] >> (16 * (k & 1)))) : f16_to_f((uint16_t)(x[u][k >> 1] >> (16 * (k & 1))));
-                        const float4 yk = yv[u][k >> 2];
-                        const double yd = (k & 3) == 0 ? yk.x : (k & 3) == 1 ? yk.y : (k & 3) == 2 ? yk.z : yk.w;
-                        dot += xd * yd;
-                        ssq += xd * xd;
-                    }
+                for (int i = 0; i < EPC / 4; ++i) st.y[u][i] = y[c * (EPC / 4) + i];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            at += 16 * U;
+            if (at >= nch) { at = 0; next_pair(); }
+        };
+        double dot = 0.0, ssq = 0.0;
+        auto use = [&](const Step& st) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (st.c + sub + 16 * u >= nch) break;
+#pragma unroll
+                for (int k = 0; k < EPC; ++k) {
+                    double xd;
+                    if constexpr (DT == 0) xd = __uint_as_float(st.x[u][k]);
+                    else xd = DT == 1 ? bf16_to_f((uint16_t)(st.x[u][k >> 1] >> (16 * (k & 1)))) : f16_to_f((uint16_t)(st.x[u][k >> 1] >> (16 * (k & 1))));
+                    const float4 yk = st.y[u][k >> 2];
+                    const double yd = (k & 3) == 0 ? yk.x : (k & 3) == 1 ? yk.y : (k & 3) == 2 ? yk.z : yk.w;
+                    dot += xd * yd;
+                    ssq += xd * xd;
                 }
             }
+            if (st.c + 16 * U < nch) return;
             dot = row16_sum(dot);
             ssq = row16_sum(ssq);
             if (sub == 0) {
-                const uint64_t key = exact_key(dot * inv * (1.0 / sqrt(ssq)), id);
-                if (key >= cut) {
-                    const uint32_t pos = atomicAdd(slot_counter(cnt, b), 1u);
-                    if (pos < (uint32_t)L.cap) surv[(int64_t)b * L.cap + pos] = key;
+                atomicAdd(taken_s + 1, 1u);
+                atomicAdd(base_s + st.q, 1u);
+                const uint64_t key = exact_key(dot * inv_s[st.q] * (1.0 / sqrt(ssq)), st.id);
+                if (key >= cut_s[st.q]) {
+                    const uint32_t pos = atomicAdd(slot_counter(cnt, q0 + st.q), 1u);
+                    if (pos < (uint32_t)L.cap) surv[(int64_t)(q0 + st.q) * L.cap + pos] = key;
                 }
+            }
+            dot = 0.0;
+            ssq = 0.0;
+        };
+        Step a, b;
+        next_pair();
+        if (left != 0) {
+            fetch(a);
+            for (;;) {
+                fetch(b);
+                use(a);
+                if (b.q < 0) break;
+                fetch(a);
+                use(b);
+                if (a.q < 0) break;
             }
         }
         __builtin_amdgcn_s_waitcnt(0x0f70);                    // vmcnt(0), as above
         __syncthreads();
-        if (tid == 0) *total_s = 0;
+        if (taken_s[1] > (uint32_t)SCAN_LIST_CAP) live &= ~(uint32_t)__builtin_amdgcn_ballot_w64(lane < 32 && base_s[lane & 31] > (uint32_t)exact.most_rows);
+        if (tid == 0) { total_s[0] = 0; taken_s[0] = 0; }
         __syncthreads();
     };
 
@@ -645,11 +700,18 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             const float norm = __builtin_amdgcn_rcpf(inv_n[b]);   // finish_key() forms it the same way
             const uint16_t nh = enc16(norm), nl = enc16(norm - dec16(nh));
             const uint32_t mh = nh ^ 0x8000u, ml = nl ^ 0x8000u;
-            if constexpr (EXACT) {
-                odd = (b == 0 ? 0u : odd) | (exact_norm_fits(norm) ? 0u : inv_n[b] == INFINITY ? 0x110u << b : 1u << b);
-            }
             bx[b] = none ? 0u : (mh | (ml << 16));
             by[b] = none ? 0u : mh;
+        }
+        if constexpr (EXACT) {
+            odd = 0;
+            bool all_fit = true;
+#pragma unroll
+            for (int b = 0; b < MR; ++b) all_fit = all_fit && exact_norm_fits(inv_n[b]);
+            if (__builtin_amdgcn_ballot_w64(!all_fit) != 0) {          // uniform, and seldom
+#pragma unroll
+                for (int b = 0; b < MR; ++b) odd |= exact_norm_fits(inv_n[b]) ? 0u : inv_n[b] == INFINITY ? 0x110u << b : 1u << b;
+            }
         }
     };
     auto tile_init = [&](int ti) __attribute__((always_inline)) {
@@ -755,9 +817,11 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     for (int b = 0; b < MR; ++b)
                         if (solid >> (16 * b + (ln & 15)) & 1ull) odd = (odd & ~(0x10u << b)) | 1u << b;
                 }
-                auto spread = [](uint32_t rows) __attribute__((always_inline)) { return ((rows & 0xfu) * 0x00204081u & 0x01010101u) * 0xffu; };   // bit b -> byte b
-                staged = spread(odd);
-                dropped = spread(odd >> 4);
+                if (__builtin_amdgcn_ballot_w64(odd != 0) != 0) {        // uniform
+                    auto spread = [](uint32_t rows) __attribute__((always_inline)) { return ((rows & 0xfu) * 0x00204081u & 0x01010101u) * 0xffu; };   // bit b -> byte b
+                    staged = spread(odd);
+                    dropped = spread(odd >> 4);
+                }
             }
 #pragma unroll
             for (int bg = 0; bg < RGROUPS; ++bg) {
@@ -777,8 +841,31 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
+            // EXACT: the list takes rows, each with the queries that it may reach; so there is room for every row of a tile, and the four
+            // lanes that hold a row's queries put them together.
+            if constexpr (EXACT) {
+                if (__builtin_amdgcn_ballot_w64(mine != 0) != 0) {      // uniform within the wavefront
+                    const int ln = fresh_lane(), g = ln >> 4;
+                    uint32_t queries = 0;                               // of row 16 * g + (ln & 15) of the wavefront's 64
+#pragma unroll
+                    for (int b = 0; b < MR; ++b) {
+                        const uint32_t m = msk[b / BB] >> (8 * (b % BB)) & 0xffu;       // this lane's of row block b
+                        uint32_t all = (m & 0xfu) << (4 * g) | (m >> 4) << (16 + 4 * g);
+                        const auto s16 = __builtin_amdgcn_permlane16_swap(all, all, false, false);
+                        all = s16[0] | s16[1];
+                        const auto s32 = __builtin_amdgcn_permlane32_swap(all, all, false, false);
+                        all = s32[0] | s32[1];
+                        queries = g == b ? all : queries;
+                    }
+                    const uint64_t rows = __builtin_amdgcn_ballot_w64(queries != 0);
+                    uint32_t at = 0;
+                    if (ln == 0) at = atomicAdd(total_s, (uint32_t)__popcll(rows));
+                    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(rows & ((1ull << ln) - 1ull));
+                    if (queries != 0) lkey[at] = (uint64_t)queries << 32 | (uint32_t)(t * TILE_ROWS + wr_u * MR * 16 + ln);
+                }
+            }
             // Slots: a prefix sum over the wavefront, one LDS atomic per wavefront for its total.
-            if (__builtin_amdgcn_ballot_w64(mine != 0) != 0) {          // uniform within the wavefront
+            else if (__builtin_amdgcn_ballot_w64(mine != 0) != 0) {     // uniform within the wavefront
                 const uint32_t incl = wave_inclusive_sum(mine);
                 uint32_t wave_base = 0;
                 if (fresh_lane() == 63) wave_base = atomicAdd(total_s, incl);
@@ -804,8 +891,6 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     if (slot < (uint32_t)SCAN_LIST_CAP) {
                         lkey[slot] = ((uint64_t)__float_as_uint(av) << 32) | (uint32_t)id;
                         lq[slot] = ok ? (uint32_t)ql : 0xffffu;          // the slot was reserved before the check
-                    } else if constexpr (EXACT) {   // list full: the query is lost, and walks the bank
-                        atomicMax(slot_counter(cnt, q0 + ql), (uint32_t)L.cap + 1u);
                     } else if (ok) {   // list full (a very loose threshold): fall back to the direct path
                         uint32_t pos = atomicAdd(slot_counter(cnt, q0 + ql), 1u);
                         if (pos < (uint32_t)L.cap) surv[(int64_t)(q0 + ql) * L.cap + pos] = finish_key(av, ql, id, invnorm[id]);
@@ -871,6 +956,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             // path above) and once at the end, so the device-wide round trip is paid every few tiles.
             if constexpr (EXACT) {                             // (no wavefront gets to the next tile's epilogue before all have looked)
                 __syncthreads();
+                static_assert(SCAN_LIST_CAP / 4 + TILE_ROWS <= SCAN_LIST_CAP, "room for the rows of another tile");
                 if (*total_s > (uint32_t)SCAN_LIST_CAP / 4 || ti == my_tiles - 1) flush_exact();      // uniform
             } else if (ti % flush_every == flush_every - 1 || ti == my_tiles - 1) {          // uniform
                 __syncthreads();
