@@ -360,7 +360,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         const uint32_t to = lds_at + (uint32_t)(QUERY_AT + s * QT * 128 + i * NT * 16) + (uint32_t)__builtin_amdgcn_readfirstlane(wave) * 1024u;
         const uint64_t from = (uint64_t)(qb + i * NT * 8);                 // (uniform; said so to the compiler)
         const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(from >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)from);
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(piece_at), "s"(base) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(piece_at), "s"(base) : "memory", "m0");
     };
     // Operand addresses.  Row (block*16 + l16) of an operand tile, logical chunk c = 4*h + grp of k-step h:
     // byte offset = block*2048 + l16*128 + ((c ^ f(l16)) * 16), the swizzle depending on l16 only.

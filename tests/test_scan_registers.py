@@ -1,6 +1,9 @@
 """The scan's matrix instructions are written as assembly that updates accumulators in place, so the compiler does not add the
 wait states that another instruction would need before it touches one.  Checked in the code it makes: between such an
-instruction and the settling wait nothing but matrix instructions names an accumulator's register."""
+instruction and the settling wait nothing but matrix instructions names an accumulator's register; and no vector instruction
+writes an operand of one in the two wait states before it.
+Query blocks go straight to LDS by assembly too, which sets M0 and counts on the order of the loads.  Checked: no value that the
+compiler put into M0 is used behind such a load, and enough loads follow the last of a step's before the wait that lets them through."""
 import os
 import re
 import subprocess
@@ -21,6 +24,7 @@ def test_nothing_touches_an_accumulator_in_flight(tmp_path):
     subprocess.check_call(["hipcc", *flags, "--cuda-device-only", "-S", "-o", str(out), binding.SRC], stderr=subprocess.DEVNULL)
     kernels = re.findall(r"^(_ZN3evk11k_scan_mfma\w+):(.*?)s_endpgm", out.read_text(), re.S | re.M)
     assert len(kernels) == 36
+    direct = 0
     for name, body in kernels:
         accumulators, lines, in_asm = set(), [], False
         for line in map(str.strip, body.splitlines()):
@@ -42,4 +46,29 @@ def test_nothing_touches_an_accumulator_in_flight(tmp_path):
                 flying = flying or asm
             elif flying:
                 assert not _registers(operands) & accumulators, f"{name}: {op} {operands}"
+
+        recent = []                                          # what vector instructions wrote in the last two wait states
+        for asm, op, operands in lines:
+            if asm and op.startswith("v_mfma"):
+                read = set().union(*(_registers(x) for x in operands.split(", ")[1:3]))
+                assert not any(read & written for written in recent), f"{name}: {op} {operands}"
+            states = int(operands) + 1 if op == "s_nop" else 1
+            written = _registers(operands.split(",")[0]) if op.startswith("v_") and not op.startswith(("v_mfma", "v_cmp", "v_readlane", "v_readfirstlane")) else set()
+            recent = (recent + [set()] * (states - 1) + [written])[-2:]
+
+        theirs = False                                       # what M0 holds is the compiler's
+        behind = None                                        # memory operations behind the last load to LDS
+        for asm, op, operands in lines:
+            if re.search(r"\bm0\b", operands):
+                if op.startswith("s_") and operands.startswith("m0"):
+                    theirs = not asm
+                else:
+                    assert not asm and theirs, f"{name}: {op} {operands}"
+            if asm and op.startswith("global_load_lds"):
+                behind, direct = 0, direct + 1
+            elif op.startswith(("global_", "buffer_", "scratch_", "flat_")) and behind is not None:
+                behind += 1
+            elif asm and op == "s_waitcnt" and behind is not None:
+                assert behind >= int(re.fullmatch(r"vmcnt\((\d+)\)", operands).group(1)), f"{name}: {operands} {behind} operations behind the loads"
+    assert direct > 0
     os.remove(out)
