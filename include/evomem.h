@@ -136,7 +136,7 @@ int mem_retrieve_exact(evomem_t* h, const float* queries_dev, int B, int stage, 
  * or ordered after it): copies B words to out_flags_dev (uint32[B]) on the stream, without synchronising.
  * Bit 0 (MEM_FLAG_OVERFLOW): during some scan pass more than 8192 rows of the bank reached the query's
  * running threshold (the k1-th best similarity seen so far, minus a rounding margin) -- a mass of
- * near-duplicates of the pool's last members.  The rows beyond 8192 were not kept, so the pool of such a
+ * near-duplicates of the pool's last members (16,384 where mem_plan_levels says that lists are that long).  The rows beyond were not kept, so the pool of such a
  * query may miss members whose similarity ties with its last ones; every other query of the call is
  * exact, and mem_retrieve_exact answers the flagged ones exactly.  Errors: MEM_EINVAL, MEM_ESTATE (no retrieve yet, or B larger than that call's), MEM_EHIP.
  */
@@ -306,8 +306,9 @@ int mem_profile_read(evomem_t* h, int capacity, int* n_out, float* ms_out, int64
  * so this launch's duration is the floor that the machine at hand sets for it. */
 int mem_read_probe(evomem_t* h, uint32_t* checksum_dev, int64_t* bytes_out, void* hip_stream);
 
-/* Host only, for tests of the scan plan: the passes a retrieve with pool size k1 makes over a bank of
- * N entries, sparsest first.  Pass i scans the 256-row tiles t = u * stride[i] (u = 0,1,...) below
+/* Host only, for tests of the scan plan: the passes that a retrieve with pool size k1 and a survivor list of
+ * 8192 entries to a query makes over a bank of N entries, sparsest first.  That is every retrieve except one with a pool of more than 256
+ * (other than mem_retrieve_exact) whose batch is at most a quarter of max_B rounded up to 256: it has lists of 16,384, and makes fewer.  Pass i scans the 256-row tiles t = u * stride[i] (u = 0,1,...) below
  * ceil(N/256), leaving out those with u % rho[i] == 0 when rho[i] > 0 (a sparser pass owns them);
  * ntiles[i] is their number.  Returns the number of passes (at most max_levels are written), or -1
  * on bad arguments. */

@@ -177,7 +177,7 @@ class MemoryBank:
         return ids, scores, cid, csim
 
     def retrieve_exact(self, queries: torch.Tensor, stage: int, k1: int, k2: int, lam: float, want_candidates: bool = False):
-        """mem_retrieve by exhaustive selection (every entry scored in fp64; no list can overflow)."""
+        """mem_retrieve by exhaustive selection: every entry that a fast scan with bounded rounding does not rule out is scored in fp64; no list can overflow."""
         assert queries.is_cuda and queries.dtype == torch.float32 and queries.is_contiguous()
         B = queries.shape[0]
         ids = torch.empty((B, k2), dtype=torch.int32, device=self.device)

@@ -447,7 +447,7 @@ int launch_gemv(evomem* h, const Scratch& sc, hipStream_t st, int B, const Level
     const float* qf = (const float*)(ws + sc.w.qf);
     uint32_t* cnt = (uint32_t*)(ws + sc.w.cnt);
     uint64_t* surv = (uint64_t*)(ws + sc.w.surv);
-    if (prep) {                                                     // the first pass: at most 32 tiles
+    if (prep) {                                                     // the first pass: at most 32 tiles, or 64 with two lists to a query
         hipLaunchKernelGGL((k_scan_gemv32<NB, 1, true>), dim3((unsigned)(16 * L.ntiles + prep->Bpad)), block, 0, st, (const float*)h->store,
                            (const float*)h->invnorm, qf, invq, thr, cnt, surv, h->N, h->nkb, B, L, mask, *prep);
         LAUNCHCHK();

@@ -14,8 +14,9 @@
 // fragments are read from LDS a few query blocks ahead, the LDS stores and global loads of the following
 // k-blocks issue between the MFMAs, and there is one workgroup barrier per k-block.
 //
-// What bounds it with 256 queries and more: power.  Under this load the shader clock falls to 1.6 - 2.0 GHz (2.4 without), so
-// what counts is the energy per k-block, and what the parts take adds up whether or not they overlap.  Fed from LDS alone, in a
+// What bounds it with 256 queries and more: no unit by itself.  Under this load the shader clock falls to 1.6 - 2.0 GHz (2.4 without);
+// with 256 queries at 1.98 GHz the matrix cores are busy for 54 % of the cycles and wavefronts wait for 44 % of theirs, so it is not the clock
+// alone, and what the parts take adds up although the loads are requested two k-blocks ahead.  Fed from LDS alone, in a
 // loop of its own, 256 x 256 x 64 takes 1.35 us with 32x32x16 instructions and 1.15 with 16x16x32 ones, which move half as many
 // accumulator bytes per product (1590 and 1820 TFLOP/s); 32 KB of queries from L2 add 0.1 us, 32 KB of bank rows from HBM 0.5.
 // Hence 16x16x32, queries loaded straight to LDS, and one rotation of the k-loop for workgroups that share bank tiles.  Whole
