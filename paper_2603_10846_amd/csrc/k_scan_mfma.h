@@ -15,8 +15,8 @@
 // k-blocks issue between the MFMAs, and there is one workgroup barrier per k-block.
 //
 // What bounds it with 256 queries and more: no unit by itself.  Under this load the shader clock falls to 1.6 - 2.0 GHz (2.4 without);
-// with 256 queries at 1.98 GHz the matrix cores are busy for 54 % of the cycles and wavefronts wait for 44 % of theirs, so it is not the clock
-// alone, and what the parts take adds up although the loads are requested two k-blocks ahead.  Fed from LDS alone, in a
+// the matrix cores are busy for 56 % of the cycles with 256 queries at 2.15 GHz and for 67 % with 1024 at 1.81, and wavefronts wait for 45 and
+// 48 % of theirs, so it is not the clock alone, and what the parts take adds up although the loads are requested two k-blocks ahead.  Fed from LDS alone, in a
 // loop of its own, 256 x 256 x 64 takes 1.35 us with 32x32x16 instructions and 1.15 with 16x16x32 ones, which move half as many
 // accumulator bytes per product (1590 and 1820 TFLOP/s); 32 KB of queries from L2 add 0.1 us, 32 KB of bank rows from HBM 0.5.
 // Hence 16x16x32, queries loaded straight to LDS, and one rotation of the k-loop for workgroups that share bank tiles.  Whole
@@ -267,7 +267,8 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     // matter for a dot product): workgroups run in near lock-step over tiles that are 2^n bytes
     // apart, and without the rotation they would all pull from the same few HBM channels at once.
     // Workgroups that share a walker's tiles start at the same one, so that each of them finds in L2 what the first
-    // one fetched (L2 misses of a pass over 1M x 1536 with 1024 queries: 104 M lines when they did not, 52 M; 2.52 -> 2.46 ms).
+    // one fetched (L2 misses of a pass over 1M x 1536 with 1024 queries: 104 M lines when they did not, 52 M, of which the bank is
+    // 25 M; 2.52 -> 2.46 ms).
     const int rot = (int)(((unsigned)first_j * 7u) % (unsigned)real_steps);
     auto rotated = [&](int step) __attribute__((always_inline)) {   // logical step -> k-step actually loaded
         if (step >= real_steps) return step;                          // the dummy step stays last

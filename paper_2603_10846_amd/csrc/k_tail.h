@@ -208,7 +208,7 @@ __device__ __forceinline__ TailArgsPtr tail_args_from_here() {
 }
 
 // K: keys of a query's list per lane (8 or 16).  With 16 there are not enough registers for them: 16 to 18 of a lane's are kept in
-// scratch memory (60 to 68 bytes), none with 8.  64 queries, a pool of 960 of 2 KB, four workgroups to a query: 61.6 us, 55 with 8 keys, which
+// scratch memory (60 to 68 bytes), none with 8.  64 queries, a pool of 960 of 2 KB, four workgroups to a query: 61 us, 55 with 8 keys, which
 // take twice the passes.
 template <int DT, bool BIG, int K = SURV_CAP / TAIL_T>
 __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
