@@ -376,7 +376,7 @@ Plan plan_levels(int64_t N, int k1, int cap) {
 template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true, bool EXACT = false>
 int launch_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, int k1, const Mask& mask, int B) {
     constexpr int QT = 16 * MQ * WQ;
-    constexpr int lds = scan_mfma_lds_bytes<QT, MASKED, EXACT>();
+    constexpr int lds = scan_mfma_lds_bytes<DT, QT, MASKED, EXACT>();
     auto kern = k_scan_mfma<DT, MQ, WQ, MR, WR, MASKED, STREAM, EXACT>;
     static int resident[MAX_DEVICES] = {};          // workgroups of this kernel the whole device holds at once
     if (!resident[h->device]) {
@@ -398,11 +398,11 @@ int launch_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Leve
     // as seldom as keeps the expected fill under 55 % of the list (a surplus takes the direct path).
     const double per_tile = L.rho ? (double)k1 * L.rho * QT / L.ntiles : 1.0;
     const int tiles_per_wg = (int)((L.ntiles + 8 * groups - 1) / (8 * groups));
-    int n_flush = (int)std::ceil(tiles_per_wg * (per_tile + 1.0) / (0.55 * SCAN_LIST_CAP));
+    int n_flush = (int)std::ceil(tiles_per_wg * (per_tile + 1.0) / (0.55 * scan_mfma_list_cap<DT, QT, MASKED, EXACT>()));
     if (n_flush < 1) n_flush = 1;
     int flush_every = (tiles_per_wg + n_flush - 1) / n_flush;
     if (flush_every < 1) flush_every = 1;
-    if (flush_every > 64) flush_every = 64;
+    if (flush_every > SCAN_LIST_TILES) flush_every = SCAN_LIST_TILES;
     unsigned char* ws = sc.base;
     hipLaunchKernelGGL(kern, grid, block, lds, st, (const void*)h->store, (const float*)h->invnorm,
                        (const uint16_t*)(ws + sc.w.qop), (const float*)(ws + sc.w.invq), (const float*)(ws + sc.w.thr),
@@ -648,7 +648,7 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
         return lqt;
     };
     auto direct = [&](const Level& L) { return !gemv && use_direct(L, B, Bp, tile_of(L)); };
-    const PrepArgs prep{queries_dev, qf, qop, invq, invq64, thr, cnt, flags, cnt0, B, Bp, h->d, h->nkb, ((uintptr_t)queries_dev & 15) == 0};
+    const PrepArgs prep{queries_dev, qf, qop, invq, invq64, thr, cnt, flags, cnt0, B, Bp, h->d, h->nkb, ((uintptr_t)queries_dev & 15) == 0, !gemv};
     // The queries are prepared in the launch of the first pass where that pass reads them as given: for few queries.  With more, what a
     // workgroup converts of them costs what the launch saves.  Whole calls, us, in a launch of their own and fused: one query,
     // 4096 x 768 fp32 22.1, 19.0; seven, 30,011 x 200 fp16 33.2, 30.7; one, 1M x 1024 bf16 359.9, 355.8; 32, 300,007 x 384 fp16

@@ -163,12 +163,9 @@ __global__ __launch_bounds__(256) void k_read_probe(const uint4* __restrict__ p,
 
 // Query preparation (Sec. 3.2, the query side of dense retrieval): round each query to the store's
 // element type, keep it widened (fp32, row-major, zero-padded to the k-block multiple) for the
-// GEMV scan and the fp64 re-score, and in the operand layout of the MFMA scan
-//   qop = [kb][Bpad][64 elements], 16-byte chunks swizzled like the bank rows, plus one all-zero
-//         k-block at kb = nkb                                                        (16-bit stores)
-//   qop = [kb][half h][Bpad][32 hi | 32 lo bf16], same swizzle                      (fp32 stores:
-//         the query is split as hi + lo in bf16 so that the scan can use bf16 MFMA)
-// plus its inverse norm (fp32 and fp64).  Also resets the per-query threshold and presets the
+// GEMV scan and the fp64 re-score, and as fragments for the matrix cores (qop_row in layout.h; for fp32
+// stores the query is split as hi + lo in bf16, so that the scan can use bf16 MFMA), with an all-zero
+// k-block behind the last one, plus its inverse norm (fp32 and fp64).  Also resets the per-query threshold and presets the
 // survivor count to the number of rows of the sparsest scan pass, which keeps every row.
 // One workgroup per padded query slot; slots >= B become all-zero queries that never pass a filter.
 //
@@ -187,6 +184,7 @@ struct PrepArgs {
     uint32_t cnt0;
     int B, Bpad, d, nkb;
     int aligned;                   // the queries lie at a multiple of 16 bytes (their rows are multiples of 32 bytes)
+    int operands;                  // qop is read (not by the VALU scan, whose Bpad need not be whole fragments)
 };
 // Eight consecutive elements of a query as given, from element e0 (a multiple of 8) on; zeros past its end.
 template <bool ALIGNED>
@@ -224,16 +222,16 @@ __device__ __forceinline__ void prep_query(const PrepArgs& A, int b, double* red
                 lo[i] = f2bf16_rne(v[i] - bf16_to_f(hi[i]));
                 ssq += (double)v[i] * (double)v[i];
             }
-            // half h = c / 4 of the k-block; inside it logical chunk (c % 4) is hi, 4 + (c % 4) is lo
-            int h = c >> 2, cc = c & 3;
-            uint16_t* base = qop + (((int64_t)kb * 2 + h) * Bpad + b) * KB;
+            const int64_t u = (kb * 2 + (c >> 2)) * 2;                  // heads; remainders in the row behind
             uint4 ph, pl;
             ph.x = hi[0] | ((uint32_t)hi[1] << 16); ph.y = hi[2] | ((uint32_t)hi[3] << 16);
             ph.z = hi[4] | ((uint32_t)hi[5] << 16); ph.w = hi[6] | ((uint32_t)hi[7] << 16);
             pl.x = lo[0] | ((uint32_t)lo[1] << 16); pl.y = lo[2] | ((uint32_t)lo[3] << 16);
             pl.z = lo[4] | ((uint32_t)lo[5] << 16); pl.w = lo[6] | ((uint32_t)lo[7] << 16);
-            *reinterpret_cast<uint4*>(base + swz16(cc, b & 255) * 8) = ph;
-            *reinterpret_cast<uint4*>(base + swz16(4 + cc, b & 255) * 8) = pl;
+            if (A.operands) {
+                *reinterpret_cast<uint4*>(qop + qop_row(u, Bpad) + qop_in_row(b, c & 3)) = ph;
+                *reinterpret_cast<uint4*>(qop + qop_row(u + 1, Bpad) + qop_in_row(b, c & 3)) = pl;
+            }
         } else {
             uint16_t h[8];
 #pragma unroll
@@ -245,7 +243,7 @@ __device__ __forceinline__ void prep_query(const PrepArgs& A, int b, double* red
             uint4 pk;
             pk.x = h[0] | ((uint32_t)h[1] << 16); pk.y = h[2] | ((uint32_t)h[3] << 16);
             pk.z = h[4] | ((uint32_t)h[5] << 16); pk.w = h[6] | ((uint32_t)h[7] << 16);
-            *reinterpret_cast<uint4*>(qop + ((int64_t)kb * Bpad + b) * KB + swz16(c, b & 255) * 8) = pk;
+            *reinterpret_cast<uint4*>(qop + qop_row(kb * 2 + (c >> 2), Bpad) + qop_in_row(b, c & 3)) = pk;
         }
         float* o = A.qf + (int64_t)b * dpad + c8 * 8;
         *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);

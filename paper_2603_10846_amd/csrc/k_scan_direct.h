@@ -83,18 +83,16 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_scan_direct(const void* _
                 for (int b = 0; b < MR; ++b)
 #pragma unroll
                     for (int i = 0; i < 2; ++i) x[u][b][i] = *reinterpret_cast<const u32x4_t*>(blk + b * 16 * KB + i * 4);
-                const uint16_t* qb = qop + (((int64_t)kb * 2 + h) * Bp + q0) * KB;
 #pragma unroll
                 for (int a = 0; a < MQ && !FIRST; ++a)
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) y[u][a][i] = *reinterpret_cast<const u32x4_t*>(qb + a * 16 * KB + (lane16 ^ (i * 32)));
+                    for (int i = 0; i < 2; ++i) y[u][a][i] = *reinterpret_cast<const u32x4_t*>(qop + qop_row(2 * su + i, Bp) + (q0 + a * 16) * 32 + lane * 8);
             } else {
                 const uint16_t* blk = static_cast<const uint16_t*>(store_) + (t * nkb + kb) * (int64_t)BLOCK_ELEMS + r0 * KB;
 #pragma unroll
                 for (int b = 0; b < MR; ++b) x[u][b][0] = *reinterpret_cast<const u32x4_t*>(blk + b * 16 * KB + (lane16 ^ (h * 32)));
-                const uint16_t* qb = qop + ((int64_t)kb * Bp + q0) * KB;
 #pragma unroll
-                for (int a = 0; a < MQ && !FIRST; ++a) y[u][a][0] = *reinterpret_cast<const u32x4_t*>(qb + a * 16 * KB + (lane16 ^ (h * 32)));
+                for (int a = 0; a < MQ && !FIRST; ++a) y[u][a][0] = *reinterpret_cast<const u32x4_t*>(qop + qop_row(su, Bp) + (q0 + a * 16) * 32 + lane * 8);
             }
             if constexpr (FIRST) {
                 const int e = su * 32 + grp * 8;

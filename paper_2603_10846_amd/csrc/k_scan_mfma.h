@@ -14,14 +14,18 @@
 // fragments are read from LDS a few query blocks ahead, the LDS stores and global loads of the following
 // k-blocks issue between the MFMAs, and there is one workgroup barrier per k-block.
 //
-// What bounds it with 256 queries and more: no unit by itself.  Under this load the shader clock falls to 1.6 - 2.0 GHz (2.4 without);
-// the matrix cores are busy for 56 % of the cycles with 256 queries at 2.15 GHz and for 67 % with 1024 at 1.81, and wavefronts wait for 45 and
-// 48 % of theirs, so it is not the clock alone, and what the parts take adds up although the loads are requested two k-blocks ahead.  Fed from LDS alone, in a
-// loop of its own, 256 x 256 x 64 takes 1.35 us with 32x32x16 instructions and 1.15 with 16x16x32 ones, which move half as many
-// accumulator bytes per product (1590 and 1820 TFLOP/s); 32 KB of queries from L2 add 0.1 us, 32 KB of bank rows from HBM 0.5.
-// Hence 16x16x32, queries loaded straight to LDS, and one rotation of the k-loop for workgroups that share bank tiles.  Whole
-// calls: 4M x 1536 bf16, 1024 queries 12.36 -> 11.21 ms, 1M x 1024 bf16, 256 queries 623 -> 603 us, 128 queries of 4096 fp16 over
-// 1.1M rows 1988 -> 1951 us; densest pass of 262,144 x 1024 fp32, 256 queries (registers no longer spilled) 354 -> 297 us.
+// 256 queries to a tile over 16-bit stores (RING): operands go from memory straight to LDS, through rings of three places, and the
+// two wavefronts of a SIMD take turns -- one feeds the matrix cores from registers while the other fetches its next fragments and asks for
+// what comes two or three blocks later (ring_step()).  Where all wavefronts do all of it side by side, as the smaller tiles do, each load
+// holds its wavefront up for some 50 cycles (the address path takes 16 for a 1 KB request) and the other one is no more likely to have
+// matrix instructions ready: parts switched off in turn, 1M x 1536 bf16 with 1024 queries, densest pass, 10^6 cycles: fragments and
+// matrix instructions alone 27.2, with queries loaded 30.4, with bank rows too 35.2, with the epilogue 37.6; taking turns 29.3, 29.9,
+// 31.2, 32.5.  The latency of the bank is hidden either way (rows from HBM, from L2 or none at all: the same cycles).
+// What bounds it now is the power limit: without the epilogue the same pass takes 4 % fewer cycles and as long, at a clock of
+// 1.79 instead of 1.87 GHz, and without loads of the bank it takes 12 % less, at 1.95.  Densest pass of 1M x 1536, 1024 queries 2470 ->
+// 2230 us (1390 TFLOP/s, on other cards up to 1450; the vendor's product of 16384 x 16384 x 8192 1540), 1M x 1024, 256 queries 460 -> 430.
+// One rotation of the k-loop for all workgroups of an XCD when several share its bank tiles: 2150 -> 2130 us.
+// Instructions: 16x16x32 move half as many accumulator bytes per product as 32x32x16 ones (256 x 256 x 64 from LDS alone 1.15 and 1.35 us).
 //
 // fp32 stores: each value is split on the fly into bf16 hi + bf16 lo and the product is
 // hi*hi + hi*lo + lo*hi (three MFMAs, relative error of a product about 2^-16); this only has to
@@ -138,14 +142,27 @@ __device__ __forceinline__ float only_non_negative(const AccGroup& g) {
 }
 
 constexpr int STAGE_BANK_BYTES = TILE_ROWS * 128;
-constexpr int SCAN_LIST_CAP = 2048;     // survivor entries a workgroup can stage per tile
+constexpr int SCAN_LDS = 160 * 1024;    // of a compute unit
+constexpr int SCAN_LIST_TILES = 64;     // a workgroup's list is written out after as many tiles at the latest
 
-// LDS: two stages (bank tile + query tile); per-query threshold, inverse norm, survivor count and
-// list base; the workgroup's survivor list (8-byte key + 4-byte query index per entry); a counter.
+// 16-bit stores with 256 queries to a tile: operands pass through rings in LDS (see ring_step()).
+template <int DT, int QT> constexpr bool scan_mfma_ring() { return DT != 0 && QT == 256; }
+// LDS: the operand stages -- two of a bank block and a query block, or, as rings, three of a bank block and three of half a query
+// block --; per-query threshold, inverse norm, survivor count and list base; tiles of the list; counters; the workgroup's survivor list (8 bytes an
+// entry), for which the rings leave less room.
 // (masked variant: the per-query type masks and excluded groups in addition; EXACT: cuts and inverse norms)
-template <int QT, bool MASKED = false, bool EXACT = false> constexpr int scan_mfma_lds_bytes() {
-    return 2 * (STAGE_BANK_BYTES + QT * 128) + QT * 16 + SCAN_LIST_CAP * 12 + 16 + (MASKED ? QT * 8 : EXACT ? QT * 16 : 0);
+template <int DT, int QT> constexpr int scan_mfma_stage_bytes() {
+    return scan_mfma_ring<DT, QT>() ? 3 * (STAGE_BANK_BYTES + QT * 64) : 2 * (STAGE_BANK_BYTES + QT * 128);
 }
+template <int DT, int QT, bool MASKED = false, bool EXACT = false> constexpr int scan_mfma_word_bytes() { return QT * 16 + SCAN_LIST_TILES * 4 + 16 + (MASKED ? QT * 8 : EXACT ? QT * 16 : 0); }
+// survivor entries a workgroup can stage
+template <int DT, int QT, bool MASKED = false, bool EXACT = false> constexpr int scan_mfma_list_cap() {
+    return scan_mfma_ring<DT, QT>() ? (SCAN_LDS - scan_mfma_stage_bytes<DT, QT>() - scan_mfma_word_bytes<DT, QT, MASKED, EXACT>()) / 8 : 2048;
+}
+template <int DT, int QT, bool MASKED = false, bool EXACT = false> constexpr int scan_mfma_lds_bytes() {
+    return scan_mfma_stage_bytes<DT, QT>() + scan_mfma_word_bytes<DT, QT, MASKED, EXACT>() + scan_mfma_list_cap<DT, QT, MASKED, EXACT>() * 8;
+}
+static_assert(scan_mfma_lds_bytes<1, 256, true>() <= SCAN_LDS && scan_mfma_lds_bytes<0, 256, true>() <= SCAN_LDS, "one workgroup to a compute unit");
 
 // DT: 0 fp32 store (bf16 split), 1 bf16, 2 f16.  Wave grid WQ x WR, each wave MQ x MR blocks of 16x16.
 // gridDim.x is a multiple of 8 * (Bp / QT).
@@ -166,17 +183,19 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     constexpr int QT = 16 * MQ * WQ;
     constexpr int BCH = 2048 / NT;                     // 16-byte bank chunks per lane per stage
     constexpr int QCH = QT * 8 / NT;                   // 16-byte query chunks per lane per stage
-    constexpr int QUERY_AT = 2 * STAGE_BANK_BYTES;     // the two stages of query blocks lie behind those of bank blocks
+    constexpr bool RING = scan_mfma_ring<DT, QT>();
+    constexpr int QUERY_AT = (RING ? 3 : 2) * STAGE_BANK_BYTES;        // the stages of queries lie behind those of bank blocks
+    constexpr int LIST_CAP = scan_mfma_list_cap<DT, QT, MASKED, EXACT>();
     // Query blocks go straight to LDS in the largest variant, whose registers are all taken; the few pieces of a smaller query tile
     // pass through registers, which look a step further ahead (whole masked call, 32 queries, 300,007 x 384 fp16: 94.8 us, 96.9
     // straight to LDS).
-    constexpr bool Q_DIRECT = QT == 256;
+    constexpr bool Q_DIRECT = QT == 256 && !RING;
     // an AccGroup: GB query blocks of BB row blocks, 16 registers (4 * (GB * row block + query block) + register)
     constexpr int GB = MQ < 4 ? MQ : 4, BB = 4 / GB, GROUPS = MQ / GB, RGROUPS = MR / BB;
     // 16-bit float type of the operands that carry thresholds and norms: the store's (bf16 also for fp32 stores, which are split into
     // bf16).  EXACT: always bf16, whose pairs are good to the margin over the whole range of norms that an fp16 row can have.
     constexpr int TT = DT == 2 && !EXACT ? 2 : 1;
-    auto enc16 = [](float x) __attribute__((always_inline)) { return TT == 2 ? f2f16_rne(x) : f2bf16_rne(x); };
+    auto enc16 = [](float x) __attribute__((always_inline)) { return TT == 2 ? f2f16_rne(x) : (uint16_t)cvt_pk_bf16(x, x); };
     auto dec16 = [](uint16_t h) __attribute__((always_inline)) { return TT == 2 ? f16_to_f(h) : bf16_to_f(h); };
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -209,14 +228,22 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
 
     auto sbank = [&](int s) __attribute__((always_inline)) { return smem + s * STAGE_BANK_BYTES; };
     auto sq = [&](int s) __attribute__((always_inline)) { return smem + QUERY_AT + s * QT * 128; };
-    uint32_t* thp_s = reinterpret_cast<uint32_t*>(smem + 2 * (STAGE_BANK_BYTES + QT * 128));   // thresholds as (hi | lo << 16), 16-bit floats
+    constexpr int WORDS_AT = scan_mfma_stage_bytes<DT, QT>();
+    uint32_t* thp_s = reinterpret_cast<uint32_t*>(smem + WORDS_AT);    // thresholds as (hi | lo << 16), 16-bit floats
     float* invq_s = reinterpret_cast<float*>(thp_s + QT);
     uint32_t* cnt_s = reinterpret_cast<uint32_t*>(invq_s + QT);
     uint32_t* base_s = cnt_s + QT;
-    constexpr uint32_t LKEY_OFF = 2 * (STAGE_BANK_BYTES + QT * 128) + QT * 16, LQ_OFF = LKEY_OFF + SCAN_LIST_CAP * 8;   // the list's two arrays
-    uint64_t* lkey = reinterpret_cast<uint64_t*>(smem + LKEY_OFF);
-    uint32_t* lq = reinterpret_cast<uint32_t*>(smem + LQ_OFF);
-    uint32_t* total_s = lq + SCAN_LIST_CAP;
+    constexpr uint32_t LIST_AT = WORDS_AT + scan_mfma_word_bytes<DT, QT, MASKED, EXACT>();
+    // An entry: accumulator value << 32 | refused << 24 | which of the tiles since the list was empty << 16 | row of the tile << 8 | register of the
+    // group, lane group << 4, group of query blocks << 6 (EXACT: queries << 32 | id).
+    uint64_t* list_s = reinterpret_cast<uint64_t*>(smem + LIST_AT);
+    constexpr uint32_t REFUSED = 1u << 24;
+    auto entry_query = [&](uint32_t m) __attribute__((always_inline)) {
+        return (int)(((m >> 6 & 3u) * GB + (m >> 2) % GB) * 16 + (m >> 4 & 3u) * 4 + (m & 3u));
+    };
+    auto entry_row = [&](uint32_t m) __attribute__((always_inline)) { return (m >> 8 & 0xffu) + (BB > 1 ? (m >> 3 & 1u) * 16 : 0u); };
+    uint32_t* tile_s = base_s + QT;                     // the tiles whose survivors the list holds
+    uint32_t* total_s = tile_s + SCAN_LIST_TILES;
     uint32_t* allow_s = total_s + 4;                    // masked variant only
     uint32_t* exclude_s = allow_s + QT;
     uint64_t* cut_s = reinterpret_cast<uint64_t*>(total_s + 4);                 // EXACT: cuts and inverse norms of the tile's queries
@@ -257,19 +284,19 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
 
     // Steps per tile, made even so that the two register sets / LDS stages are in the same phase at
     // every tile boundary: an odd count gets one dummy step that multiplies the tile's last bank
-    // block with an all-zero query block (the query operand holds one such block at index nkb).
+    // block with an all-zero query block (the query operand holds one such block at index nkb).  (Rings turn by themselves.)
     const int real_steps = DT == 0 ? nkb * 2 : nkb;
-    const int nsteps = real_steps + (real_steps & 1);
+    const int nsteps = RING ? real_steps : real_steps + (real_steps & 1);
     u32x4_t gbA[BCH], gbB[BCH], gqA[QCH], gqB[QCH];       // (gq: unless Q_DIRECT)
 
     // Bank and query loads run two steps ahead of the MFMAs.
     // Each tile walker starts its k-loop at a different k-block (the order of the k-blocks does not
     // matter for a dot product): workgroups run in near lock-step over tiles that are 2^n bytes
     // apart, and without the rotation they would all pull from the same few HBM channels at once.
-    // Workgroups that share a walker's tiles start at the same one, so that each of them finds in L2 what the first
+    // Workgroups that share a walker's tiles start at the same one (RING: all of an XCD, which share the queries too), so that each of them finds in L2 what the first
     // one fetched (L2 misses of a pass over 1M x 1536 with 1024 queries: 104 M lines when they did not, 52 M, of which the bank is
     // 25 M; 2.52 -> 2.46 ms).
-    const int rot = (int)(((unsigned)first_j * 7u) % (unsigned)real_steps);
+    const int rot = (int)((RING && nqt > 1 ? (unsigned)xcd * 3u : (unsigned)first_j * 7u) % (unsigned)real_steps);
     auto rotated = [&](int step) __attribute__((always_inline)) {   // logical step -> k-step actually loaded
         if (step >= real_steps) return step;                          // the dummy step stays last
         int k = step + rot;
@@ -279,12 +306,16 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     // (the cursor step and the loads themselves are separate, so that the loads can be issued one
     // at a time between MFMAs)
     auto gnext_q = [&]() __attribute__((always_inline)) {
-        const uint16_t* qb = qop + ((int64_t)rotated(ldq_step) * Bp + q0) * KB;
+        const uint16_t* qb = qop + qop_row(2 * rotated(ldq_step), Bp) + q0 * 32;
         if (++ldq_step == nsteps) ldq_step = 0;
         return qb;
     };
+    // A step's queries are two fragment rows (QT * 64 bytes each of this tile's), one behind the other in LDS.
+    constexpr int QROW = QT * 4;                       // 16-byte pieces of a row
+    const int64_t qrow_elems = qop_row(1, Bp);
     auto gpiece = [&](const uint16_t* base, int i) __attribute__((always_inline)) {
-        return *reinterpret_cast<const u32x4_t*>(base + (i * NT + tid) * 8);
+        if constexpr (NT <= QROW) return *reinterpret_cast<const u32x4_t*>(base + i * NT / QROW * qrow_elems + (i * NT % QROW + tid) * 8);
+        else return *reinterpret_cast<const u32x4_t*>(base + tid / QROW * qrow_elems + tid % QROW * 8);
     };
     auto gpiece_bank = [&](const uint16_t* base, int i) __attribute__((always_inline)) {
         if constexpr (STREAM) return __builtin_bit_cast(u32x4_t, stream_load16(base + (i * NT + tid) * 8));
@@ -360,18 +391,17 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     const uint32_t piece_at = (uint32_t)tid * 16u;
     auto qload_to_lds = [&](const uint16_t* qb, int s, int i) __attribute__((always_inline)) {
         const uint32_t to = lds_at + (uint32_t)(QUERY_AT + s * QT * 128 + i * NT * 16) + (uint32_t)__builtin_amdgcn_readfirstlane(wave) * 1024u;
-        const uint64_t from = (uint64_t)(qb + i * NT * 8);                 // (uniform; said so to the compiler)
+        const uint64_t from = (uint64_t)(qb + i * NT / QROW * qrow_elems + i * NT % QROW * 8);   // (uniform; said so to the compiler)
         const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(from >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)from);
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(piece_at), "s"(base) : "memory", "m0");
     };
-    // Operand addresses.  Row (block*16 + l16) of an operand tile, logical chunk c = 4*h + grp of k-step h:
-    // byte offset = block*2048 + l16*128 + ((c ^ f(l16)) * 16), the swizzle depending on l16 only.
+    // Operand addresses.  Queries: fragments of 1 KB, k-step h in row h of the stage.  Bank row (block*16 + l16), logical chunk
+    // c = 4*h + grp of k-step h: byte offset = block*2048 + l16*128 + ((c ^ f(l16)) * 16), the swizzle depending on l16 only.
     // The k-step enters through bit 6 only, so one per-lane offset per operand (the wave's first block folded in)
     // serves every block, both stages and both k-steps; the rest is a compile-time constant.
-    const uint32_t off0 = l16 * 128 + swz16(grp, l16) * 16;
-    const uint32_t offA0 = off0 + QUERY_AT + wq * MQ * 2048, offB0 = off0 + wr * MR * 2048;
-    auto frag_a = [&](int s, uint32_t off, int block) __attribute__((always_inline)) {
-        return *reinterpret_cast<const u32x4_t*>(smem + off + (s * QT * 128 + block * 2048));
+    const uint32_t offA0 = QUERY_AT + wq * MQ * 1024 + lane * 16, offB0 = l16 * 128 + swz16(grp, l16) * 16 + wr * MR * 2048;
+    auto frag_a = [&](int s, int h, int block) __attribute__((always_inline)) {
+        return *reinterpret_cast<const u32x4_t*>(smem + offA0 + (s * QT * 128 + h * QT * 64 + block * 1024));
     };
     auto frag_b = [&](int s, uint32_t off, int block) __attribute__((always_inline)) {
         return *reinterpret_cast<const u32x4_t*>(smem + off + (s * STAGE_BANK_BYTES + block * 2048));
@@ -384,7 +414,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     // no register to spare, and a value that gets spilled has to be waited for right after its
     // request, which drains every load in flight) and turned into MFMA operands (tile_prepare)
     // after that tile's epilogue, by when they have long arrived.  The rare epilogue paths that
-    // need an inverse norm of the current tile read it from memory again.
+    // need an inverse norm of the current tile read it from memory again.  (RING, which has registers left: behind the last step.)
     float inv_n[MR];
     int tile_now = 0;
     auto load_invnorm = [&](int ti) __attribute__((always_inline)) {
@@ -399,7 +429,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
 
     // Operand fragments of the 16-bit path, carried from step to step.  A step has 2 MQ slots (k-step h, query block a); the
     // query fragment of slot g lies in af[g % RA], requested RA slots ahead.
-    constexpr int RA = MQ < 4 ? MQ : 4, SLOTS = 2 * MQ, BARRIER = 3 * MQ / 2;
+    constexpr int RA = RING ? MQ : MQ < 4 ? MQ : 4, SLOTS = 2 * MQ, BARRIER = 3 * MQ / 2;
     u32x4_t af[RA], bfr[2][MR];
     auto compute = [&](int s, u32x4_t (&gb)[BCH], u32x4_t (&gq)[QCH], auto fetch_next) __attribute__((always_inline)) {
         if constexpr (DT == 0) {
@@ -411,23 +441,23 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 __builtin_amdgcn_sched_barrier(0);
             }
             u32x4_t bh[MR], bl[MR];
-            u32x4_t al = frag_a(s, offA0 ^ 64, 0);
+            u32x4_t al = frag_a(s, 1, 0);
 #pragma unroll
             for (int b = 0; b < MR; ++b) bh[b] = frag_b(s, offB0, b);
-            u32x4_t ah = frag_a(s, offA0, 0);
+            u32x4_t ah = frag_a(s, 0, 0);
 #pragma unroll
             for (int b = 0; b < MR; ++b) bl[b] = frag_b(s, offB0 ^ 64, b);
 #pragma unroll
             for (int a = 0; a < MQ; ++a) {
                 u32x4_t al1 = al, ah1 = ah;
-                if (MQ < 8 && a + 1 < MQ) { al1 = frag_a(s, offA0 ^ 64, a + 1); ah1 = frag_a(s, offA0, a + 1); }
+                if (MQ < 8 && a + 1 < MQ) { al1 = frag_a(s, 1, a + 1); ah1 = frag_a(s, 0, a + 1); }
 #pragma unroll
                 for (int b = 0; b < MR; ++b) mfma16_in_place<1>(acc[a][b], al, bh[b]);     // (MR of them apart: no one waits for the one before)
 #pragma unroll
                 for (int b = 0; b < MR; ++b) mfma16_in_place<1>(acc[a][b], ah, bl[b]);
 #pragma unroll
                 for (int b = 0; b < MR; ++b) mfma16_in_place<1>(acc[a][b], ah, bh[b]);
-                if (MQ == 8 && a + 1 < MQ) { al1 = frag_a(s, offA0 ^ 64, a + 1); ah1 = frag_a(s, offA0, a + 1); }   // (no registers to have them earlier)
+                if (MQ == 8 && a + 1 < MQ) { al1 = frag_a(s, 1, a + 1); ah1 = frag_a(s, 0, a + 1); }   // (no registers to have them earlier)
                 al = al1;
                 ah = ah1;
                 if (a == MQ / 2 - 1) {
@@ -456,17 +486,11 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             for (int g = 0; g < SLOTS; ++g) {
                 const int h = g / MQ, a = g % MQ;
                 // The step's only barrier: every wavefront has stored its share of stage s ^ 1 and has received all
-                // it reads from stage s.  The query block of the next step has arrived in LDS too: of what this
-                // wavefront requested in the previous step only the bank pieces came after it.  After the barrier
+                // it reads from stage s.  After the barrier
                 // the last quarter's slots still have their operands in registers or requested, and fetch the first
                 // fragments of the next step from stage s ^ 1, so the matrix pipe does not wait for LDS.
                 if (g == BARRIER) {
-                    if constexpr (Q_DIRECT) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(BCH) : "memory");
                     __syncthreads();
-                    if constexpr (Q_DIRECT) {                               // stage s is free: the query block two steps ahead
-#pragma unroll
-                        for (int i = 0; i < QCH; ++i) qload_to_lds(nq, s, i);
-                    }
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 // bank fragments: those of k-step 1 over the first slots, those of the next step behind the barrier
@@ -479,7 +503,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     // query fragments whose registers were free before stage s ^ 1 could be read
                     if (g == BARRIER) {
 #pragma unroll
-                        for (int f = SLOTS - RA; f < BARRIER; ++f) af[f % RA] = frag_a(s ^ 1, offA0, f + RA - SLOTS);
+                        for (int f = SLOTS - RA; f < BARRIER; ++f) af[f % RA] = frag_a(s ^ 1, 0, f + RA - SLOTS);
                     }
 #pragma unroll
                     for (int b = (g - BARRIER) * BPS; b < (g - BARRIER + 1) * BPS && b < MR; ++b) bfr[0][b] = frag_b(s ^ 1, offB0, b);
@@ -488,9 +512,9 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 for (int b = 0; b < MR; ++b) mfma16_in_place<DT>(acc[a][b], af[g % RA], bfr[h][b]);
                 if (g + RA < SLOTS) {
                     const int f = g + RA;
-                    af[g % RA] = frag_a(s, f >= MQ ? offA0 ^ 64 : offA0, f % MQ);
+                    af[g % RA] = frag_a(s, f / MQ, f % MQ);
                 } else if (FETCH && g >= BARRIER) {
-                    af[g % RA] = frag_a(s ^ 1, offA0, g + RA - SLOTS);
+                    af[g % RA] = frag_a(s ^ 1, 0, g + RA - SLOTS);
                 }
                 // the bank pieces: stored over the second and third quarter of the slots, reloaded over the last
                 constexpr int Q1 = MQ / 2;                                  // slots of a quarter
@@ -499,16 +523,15 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     for (int i = (g - Q1) * BCH / (2 * Q1); i < (g - Q1 + 1) * BCH / (2 * Q1); ++i)
                         *reinterpret_cast<u32x4_t*>(sbank(s ^ 1) + (i * NT + tid) * 16) = gb[i];
                 }
-                if constexpr (!Q_DIRECT) {                                  // stored over the second quarter, reloaded over the third
-                    if (g >= Q1 && g < MQ) {
+                // the query pieces: stored over the second quarter, reloaded over the third
+                if (g >= Q1 && g < MQ) {
 #pragma unroll
-                        for (int i = (g - Q1) * QCH / Q1; i < (g - Q1 + 1) * QCH / Q1; ++i)
-                            *reinterpret_cast<u32x4_t*>(sq(s ^ 1) + (i * NT + tid) * 16) = gq[i];
-                    }
-                    if (g >= MQ && g < BARRIER) {
+                    for (int i = (g - Q1) * QCH / Q1; i < (g - Q1 + 1) * QCH / Q1; ++i)
+                        *reinterpret_cast<u32x4_t*>(sq(s ^ 1) + (i * NT + tid) * 16) = gq[i];
+                }
+                if (g >= MQ && g < BARRIER) {
 #pragma unroll
-                        for (int i = (g - MQ) * QCH / Q1; i < (g - MQ + 1) * QCH / Q1; ++i) gq[i] = gpiece(nq, i);
-                    }
+                    for (int i = (g - MQ) * QCH / Q1; i < (g - MQ + 1) * QCH / Q1; ++i) gq[i] = gpiece(nq, i);
                 }
                 if (g >= BARRIER) {
 #pragma unroll
@@ -518,6 +541,79 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+    };
+
+    // RING: one step (a k-block) of the 16-bit path with 256 queries to a tile, in two halves of 32 k.  A half is two spells: fetch (12
+    // fragments from LDS to registers, four loads of 1 KB from memory to LDS) and multiply (32 matrix instructions).  A barrier ends
+    // every spell, and the last four wavefronts -- the second one of every SIMD -- are a spell behind the first four, so on each SIMD one
+    // multiplies while the other fetches.  The first four load queries, half a block a time, the others bank blocks, so that neither waits
+    // for the other's loads (a wavefront's loads are waited for in order).
+    //   queries: in the fetch of half i, half i + 2 goes to the place of half i - 1, which the second four have read a spell ago;
+    //            it is waited for before the barrier that ends the multiplication of half i + 1 (one load batch comes after it: vmcnt(4))
+    //   bank:    in the fetches of the two halves of block m, block m + 2 goes to the place of block m - 1; it is waited for
+    //            at the end of the fetch of the second half of block m + 1 (eight loads come after it), before the barrier behind which
+    //            the first four read it
+    // A tile begins with the first four a spell ahead and ends with both done, so the epilogue is everyone's at the same time and its
+    // barriers are met by all: both groups pass four barriers a step.
+    int wave_opaque = __builtin_amdgcn_readfirstlane(wave);
+    auto second = [&]() __attribute__((always_inline)) {       // one of the last four wavefronts?  Compared anew each time: a scalar
+        asm volatile("" : "+s"(wave_opaque));                  // compare and branch, not a lane mask kept
+        return wave_opaque >= 4;
+    };
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave) & 3;
+    uint32_t at_bank = 0, at_query = 0;                        // ring places of this step's bank block, of this half's queries
+    const char* src = nullptr;                                 // this lane's next piece, and where to
+    uint32_t dst = 0;
+    const uint32_t piece0 = (uint32_t)wave_u * 1024u + (uint32_t)lane * 16u;
+    // (per-lane addresses: a scalar one that a vector instruction has made would need five wait states, which nobody would add here)
+    auto ring_load = [&](bool bank) __attribute__((always_inline)) {
+        const uint32_t to = (uint32_t)__builtin_amdgcn_readfirstlane((int)dst);
+        if (STREAM && bank) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(to), "v"(src) : "memory", "m0");
+        else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(to), "v"(src) : "memory", "m0");
+        src += 4096;
+        dst += 4096;
+    };
+    auto ring_step = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (second()) __syncthreads();                       // a spell behind
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t a0 = offA0 + at_query, b0 = (h ? offB0 ^ 64 : offB0) + at_bank;
+#pragma unroll
+            for (int b = 0; b < MR; ++b) bfr[0][b] = *reinterpret_cast<const u32x4_t*>(smem + b0 + b * 2048);
+#pragma unroll
+            for (int a = 0; a < MQ; ++a) af[a] = *reinterpret_cast<const u32x4_t*>(smem + a0 + a * 1024);
+            __builtin_amdgcn_sched_barrier(0);
+            if (second()) {
+                if (h == 0) {
+                    src = reinterpret_cast<const char*>(gnext_b()) + piece0;
+                    dst = lds_at + (at_bank == 0 ? 2 * STAGE_BANK_BYTES : at_bank - STAGE_BANK_BYTES) + wave_u * 1024;
+                }
+#pragma unroll
+                for (int p = 0; p < 4; ++p) ring_load(true);
+                if (h == 1) __builtin_amdgcn_s_waitcnt(0x0f78);           // vmcnt(8)
+            } else {
+                if (h == 0) src = reinterpret_cast<const char*>(gnext_q()) + piece0;
+                else src += qrow_elems * 2 - 4 * 4096;
+                dst = lds_at + QUERY_AT + (at_query == 0 ? 2 * QT * 64 : at_query - QT * 64) + wave_u * 1024;
+#pragma unroll
+                for (int p = 0; p < 4; ++p) ring_load(false);
+            }
+            __syncthreads();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int a = 0; a < MQ; ++a)
+#pragma unroll
+                for (int b = 0; b < MR; ++b) mfma16_in_place<DT>(acc[a][b], af[a], bfr[0][b]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!second()) {
+                __builtin_amdgcn_s_waitcnt(0x0f74);                       // vmcnt(4)
+                __syncthreads();
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            at_query = at_query == 2 * QT * 64 ? 0u : at_query + QT * 64;
+        }
+        at_bank = at_bank == 2 * STAGE_BANK_BYTES ? 0u : at_bank + STAGE_BANK_BYTES;
     };
 
     // Key of a survivor from its accumulator value (score - threshold * norm, see tile_init): the
@@ -532,14 +628,13 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     };
 
     // Write the workgroup's staged survivors to the per-query lists (all lanes call it together):
-    // rank the entries of each query with LDS atomics, reserve that many slots with one device-wide
+    // count the entries of each query with LDS atomics, reserve that many slots with one device-wide
     // integer atomic per query that has any, copy.
     auto flush = [&]() __attribute__((always_inline)) {
-        const uint32_t total = *total_s < (uint32_t)SCAN_LIST_CAP ? *total_s : (uint32_t)SCAN_LIST_CAP;
+        const uint32_t total = *total_s < (uint32_t)LIST_CAP ? *total_s : (uint32_t)LIST_CAP;
         for (uint32_t e = tid; e < total; e += NT) {
-            uint32_t ql = lq[e];
-            if (MASKED && ql == 0xffffu) continue;            // a survivor its query does not accept
-            lq[e] = ql | (atomicAdd(cnt_s + ql, 1u) << 16);   // rank among the staged entries of ql
+            const uint32_t m = (uint32_t)list_s[e];
+            if (!(MASKED && (m & REFUSED))) atomicAdd(cnt_s + entry_query(m), 1u);
         }
         __syncthreads();
         for (int i = tid; i < QT; i += NT) {
@@ -552,21 +647,21 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         for (uint32_t e0 = tid; e0 < total; e0 += 4 * NT) {
             float inv[4];
             uint64_t ent[4];
+            int32_t id[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t e = e0 + k * NT;
-                ent[k] = lkey[e < total ? e : e0];
-                inv[k] = invnorm[(int32_t)(uint32_t)ent[k]];
+                ent[k] = list_s[e < total ? e : e0];
+                id[k] = (int32_t)(tile_s[(uint32_t)ent[k] >> 16 & 0xffu] * TILE_ROWS + entry_row((uint32_t)ent[k]));
+                inv[k] = invnorm[id[k]];
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t e = e0 + k * NT;
-                if (e < total && !(MASKED && (lq[e] & 0xffffu) == 0xffffu)) {
-                    const uint32_t ql = lq[e] & 0xffffu, rank = lq[e] >> 16;
-                    const uint32_t pos = base_s[ql] + rank;
-                    if (pos < (uint32_t)L.cap)
-                        surv[(int64_t)(q0 + ql) * L.cap + pos] =
-                            finish_key(__uint_as_float((uint32_t)(ent[k] >> 32)), (int)ql, (int32_t)(uint32_t)ent[k], inv[k]);
+                if (e < total && !(MASKED && ((uint32_t)ent[k] & REFUSED))) {
+                    const int ql = entry_query((uint32_t)ent[k]);
+                    const uint32_t pos = atomicAdd(base_s + ql, 1u);           // (the order in a list is of no account)
+                    if (pos < (uint32_t)L.cap) surv[(int64_t)(q0 + ql) * L.cap + pos] = finish_key(__uint_as_float((uint32_t)(ent[k] >> 32)), ql, id[k], inv[k]);
                 }
             }
         }
@@ -607,11 +702,11 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     if (sub == 0) row = atomicAdd(taken_s, 1u);
                     row = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)row, 0x150, 0xf, 0xf, true);       // of the first of 16 lanes
                     if (row >= total) return;
-                    id = (int32_t)(uint32_t)lkey[row];
-                    left = (uint32_t)(lkey[row] >> 32) & live;
+                    id = (int32_t)(uint32_t)list_s[row];
+                    left = (uint32_t)(list_s[row] >> 32) & live;
                 }
                 const int q = __builtin_ctz(left);
-                if (taken_s[1] <= (uint32_t)SCAN_LIST_CAP || base_s[q] <= (uint32_t)exact.most_rows) return;
+                if (taken_s[1] <= (uint32_t)LIST_CAP || base_s[q] <= (uint32_t)exact.most_rows) return;
                 if (sub == 0) atomicMax(slot_counter(cnt, q0 + q), (uint32_t)L.cap + 1u);
                 left &= left - 1;
             }
@@ -679,7 +774,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         }
         __builtin_amdgcn_s_waitcnt(0x0f70);                    // vmcnt(0), as above
         __syncthreads();
-        if (taken_s[1] > (uint32_t)SCAN_LIST_CAP) live &= ~(uint32_t)__builtin_amdgcn_ballot_w64(lane < 32 && base_s[lane & 31] > (uint32_t)exact.most_rows);
+        if (taken_s[1] > (uint32_t)LIST_CAP) live &= ~(uint32_t)__builtin_amdgcn_ballot_w64(lane < 32 && base_s[lane & 31] > (uint32_t)exact.most_rows);
         if (tid == 0) { total_s[0] = 0; taken_s[0] = 0; }
         __syncthreads();
     };
@@ -719,9 +814,12 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     auto tile_init = [&](int ti) __attribute__((always_inline)) {
         const bool use_thr = L.rho != 0;
         const int ln = fresh_lane();
+        uint32_t th[MQ];                                           // (all requested before the first is used)
+#pragma unroll
+        for (int a = 0; a < MQ; ++a) th[a] = thp_s[(wq_u * MQ + a) * 16 + (ln & 15)];
 #pragma unroll
         for (int a = 0; a < MQ; ++a) {
-            const uint32_t tp = use_thr && ln < 16 ? thp_s[(wq_u * MQ + a) * 16 + (ln & 15)] : 0u;
+            const uint32_t tp = use_thr && ln < 16 ? th[a] : 0u;
             const u32x4_t aext = {(tp & 0xffffu) | (tp << 16), tp >> 16, 0u, 0u};
 #pragma unroll
             for (int b = 0; b < MR; ++b) {
@@ -733,6 +831,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     };
 
     // ---- per-tile epilogue (all lanes of the workgroup call it together) ----
+    int since = 0;                                             // tiles whose survivors the list holds
     auto epilogue = [&](int ti) __attribute__((always_inline)) {
         const int j = first_j + ti * stride_j;
         const int64_t t = level_tile(L, j);
@@ -769,6 +868,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             // and all at the same time, instead of one dependent device-wide atomic per survivor.
             // The accumulators hold  score - threshold * norm  (see tile_init): survivors are the
             // non-negative values.
+            if constexpr (!EXACT) { if (threadIdx.x == 0) tile_s[since] = (uint32_t)t; }     // (a barrier comes before it is read)
             // Pass 1.  Per group and lane a 16-bit mask of the non-negative accumulators, built from the
             // sign bits with one funnel shift per register (no test for "no survivor here"
             // first: at the survivor rates of the dense passes nearly every wavefront has some).
@@ -780,6 +880,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             };
             uint32_t msk[GROUPS * RGROUPS];
             uint32_t mine = 0;
+            const int rows_here = N - t * TILE_ROWS < TILE_ROWS ? (int)(N - t * TILE_ROWS) : TILE_ROWS;
             uint32_t asked = ~0u, staged = 0, dropped = 0;               // EXACT: this lane's queries (16 bits), and its rows that are
             if constexpr (EXACT) {                                       // staged and dropped whatever the accumulators say (8 bits a row block)
                 const int g4 = 4 * (fresh_lane() >> 4);
@@ -830,7 +931,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 uint32_t valid = 0;
 #pragma unroll
                 for (int i = 0; i < BB; ++i)
-                    valid |= t * TILE_ROWS + (wr_u * MR + bg * BB + i) * 16 + (fresh_lane() & 15) < N ? ((1u << (4 * GB)) - 1u) << (4 * GB * i) : 0u;
+                    valid |= (wr_u * MR + bg * BB + i) * 16 + (fresh_lane() & 15) < rows_here ? ((1u << (4 * GB)) - 1u) << (4 * GB * i) : 0u;
 #pragma unroll
                 for (int g = 0; g < GROUPS; ++g) {
                     uint32_t neg = 0;                                    // sign bits, register 15 first
@@ -863,15 +964,20 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     uint32_t at = 0;
                     if (ln == 0) at = atomicAdd(total_s, (uint32_t)__popcll(rows));
                     at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(rows & ((1ull << ln) - 1ull));
-                    if (queries != 0) lkey[at] = (uint64_t)queries << 32 | (uint32_t)(t * TILE_ROWS + wr_u * MR * 16 + ln);
+                    if (queries != 0) list_s[at] = (uint64_t)queries << 32 | (uint32_t)(t * TILE_ROWS + wr_u * MR * 16 + ln);
                 }
             }
             // Slots: a prefix sum over the wavefront, one LDS atomic per wavefront for its total.
             else if (__builtin_amdgcn_ballot_w64(mine != 0) != 0) {     // uniform within the wavefront
                 const uint32_t incl = wave_inclusive_sum(mine);
+                const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
                 uint32_t wave_base = 0;
-                if (fresh_lane() == 63) wave_base = atomicAdd(total_s, incl);
-                uint32_t slot = (uint32_t)__builtin_amdgcn_readlane((int)wave_base, 63) + incl - mine;
+                if (fresh_lane() == 0) wave_base = atomicAdd(total_s, sum);
+                wave_base = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_base);
+                uint32_t slot = wave_base + incl - mine;
+                // what is the same in all of this lane's entries: tile, row in block 0, lane group
+                const int ln0 = fresh_lane();
+                const uint32_t where0 = (uint32_t)since << 16 | (uint32_t)(wr_u * MR * 16 + (ln0 & 15)) << 8 | (uint32_t)(wq_u * GROUPS << 6) | (uint32_t)(ln0 >> 4) << 4;
                 // Pass 2, survivors only, all lanes in parallel: each lane takes the first set bit of its
                 // own mask, fetches that accumulator register with a two-level select (registers cannot
                 // be indexed per lane) and stages (value, row id, query); the key is finished when the
@@ -886,13 +992,13 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 };
                 auto stage_one = [&](int g, int bg, int r, float av) __attribute__((always_inline)) {   // lanes with a survivor
                     const int ln = fresh_lane();
-                    const int32_t id = (int32_t)(t * TILE_ROWS + (wr_u * MR + bg * BB + ((r >> 2) & 3) / GB) * 16 + (ln & 15));
+                    const uint32_t rt = (uint32_t)((wr_u * MR + bg * BB + ((r >> 2) & 3) / GB) * 16 + (ln & 15));
+                    const int32_t id = (int32_t)(t * TILE_ROWS + rt);
                     const int ql = (wq_u * MQ + g * GB + ((r >> 2) & 3) % GB) * 16 + 4 * (ln >> 4) + (r & 3);
                     bool ok = true;
                     if constexpr (MASKED) ok = eligible(mask.tags[id], allow_s[ql], exclude_s[ql]);
-                    if (slot < (uint32_t)SCAN_LIST_CAP) {
-                        lkey[slot] = ((uint64_t)__float_as_uint(av) << 32) | (uint32_t)id;
-                        lq[slot] = ok ? (uint32_t)ql : 0xffffu;          // the slot was reserved before the check
+                    if (slot < (uint32_t)LIST_CAP) {
+                        list_s[slot] = (uint64_t)__float_as_uint(av) << 32 | where0 + (uint32_t)(bg * BB * 16 << 8 | g << 6 | r) | (ok ? 0u : REFUSED);   // the slot was reserved before the check
                     } else if (ok) {   // list full (a very loose threshold): fall back to the direct path
                         uint32_t pos = atomicAdd(slot_counter(cnt, q0 + ql), 1u);
                         if (pos < (uint32_t)L.cap) surv[(int64_t)(q0 + ql) * L.cap + pos] = finish_key(av, ql, id, invnorm[id]);
@@ -903,18 +1009,10 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 // a group stage it; lanes with more are left to the loop below, and so is everything when the
                 // wavefront's reservation does not fit the list (then no lane needs a room check here).
                 uint32_t rest = 0;
-                const bool fits = (uint32_t)__builtin_amdgcn_readlane((int)wave_base, 63) + (uint32_t)__builtin_amdgcn_readlane((int)incl, 63)
-                                  <= (uint32_t)SCAN_LIST_CAP;                                  // uniform
+                const bool fits = wave_base + sum <= (uint32_t)LIST_CAP;                       // uniform
                 // (a group of two row blocks: the rows past the bank's end must not be a group's maximum)
                 const bool whole = (t + 1) * TILE_ROWS <= N;                                   // uniform
-                const int ln0 = fresh_lane();
-                const int32_t id0 = (int32_t)(t * TILE_ROWS + wr_u * MR * 16 + (ln0 & 15));   // this lane's row in block b = 0
-                int qla[GROUPS];                                                               // this lane's first query in group g
-#pragma unroll
-                for (int g = 0; g < GROUPS; ++g) qla[g] = (wq_u * MQ + g * GB) * 16 + 4 * (ln0 >> 4);
-                // running LDS addresses of the lane's next list entry (key array, query array)
-                unsigned char* pk = smem + LKEY_OFF + slot * 8u;
-                unsigned char* pq = smem + LQ_OFF + slot * 4u;
+                unsigned char* pk = smem + LIST_AT + slot * 8u;                                // the lane's next list entry
 #pragma unroll
                 for (int bg = 0; bg < RGROUPS; ++bg)
 #pragma unroll
@@ -924,20 +1022,19 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                         if (take) {
                             const int r = __builtin_ctz(m);
                             const float av = only_non_negative(group(g, bg));
-                            const int32_t id = id0 + bg * BB * 16 + (BB > 1 ? (r >> 3) * 16 : 0);
-                            const int ql = qla[g] + (BB > 1 ? (r & 7) + 3 * (r & 4) : r + 3 * (r & 12));    // 16 * query block + register
-                            bool ok = true;
-                            if constexpr (MASKED) ok = eligible(mask.tags[id], allow_s[ql], exclude_s[ql]);
-                            *reinterpret_cast<uint64_t*>(pk) = ((uint64_t)__float_as_uint(av) << 32) | (uint32_t)id;
-                            *reinterpret_cast<uint32_t*>(pq) = ok ? (uint32_t)ql : 0xffffu;   // the slot was reserved before the check
+                            uint32_t where = where0 + (uint32_t)(bg * BB * 16 << 8 | g << 6) + (uint32_t)r;
+                            if constexpr (MASKED) {                                            // the slot was reserved before the check
+                                const int ql = entry_query(where);
+                                where |= eligible(mask.tags[t * TILE_ROWS + entry_row(where)], allow_s[ql], exclude_s[ql]) ? 0u : REFUSED;
+                            }
+                            *reinterpret_cast<uint64_t*>(pk) = (uint64_t)__float_as_uint(av) << 32 | where;
                             pk += 8;
-                            pq += 4;
                         }
                         const uint32_t left = take ? 0u : m;
                         msk[g * RGROUPS + bg] = left;
                         rest |= left;
                     }
-                slot = (uint32_t)(pq - (smem + LQ_OFF)) >> 2;
+                slot = (uint32_t)(pk - (smem + LIST_AT)) >> 3;
                 if (__builtin_amdgcn_ballot_w64(rest != 0) != 0) {
 #pragma unroll
                     for (int bg = 0; bg < RGROUPS; ++bg)
@@ -958,11 +1055,14 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             // path above) and once at the end, so the device-wide round trip is paid every few tiles.
             if constexpr (EXACT) {                             // (no wavefront gets to the next tile's epilogue before all have looked)
                 __syncthreads();
-                static_assert(SCAN_LIST_CAP / 4 + TILE_ROWS <= SCAN_LIST_CAP, "room for the rows of another tile");
-                if (*total_s > (uint32_t)SCAN_LIST_CAP / 4 || ti == my_tiles - 1) flush_exact();      // uniform
-            } else if (ti % flush_every == flush_every - 1 || ti == my_tiles - 1) {          // uniform
+                static_assert(LIST_CAP / 4 + TILE_ROWS <= LIST_CAP, "room for the rows of another tile");
+                if (*total_s > (uint32_t)LIST_CAP / 4 || ti == my_tiles - 1) flush_exact();      // uniform
+            } else if (since == flush_every - 1 || ti == my_tiles - 1) {          // uniform
                 __syncthreads();
                 flush();
+                since = 0;
+            } else {
+                ++since;
             }
         }
     };
@@ -975,13 +1075,43 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             __syncthreads();
         }
     };
-    if constexpr (Q_DIRECT) {
+    if constexpr (RING) {
+        static_assert(MQ == 8 && MR == 4 && NT == 512, "the slots' work");
+        if (second()) {
 #pragma unroll
-        for (int s = 0; s < (DT == 0 ? 1 : 2); ++s) {
-            const uint16_t* qb = gnext_q();
-#pragma unroll
-            for (int i = 0; i < QCH; ++i) qload_to_lds(qb, s, i);
+            for (int i = 0; i < 2; ++i) {
+                src = reinterpret_cast<const char*>(gnext_b()) + piece0;
+                dst = lds_at + i * STAGE_BANK_BYTES + wave_u * 1024;
+                for (int p = 0; p < 8; ++p) ring_load(true);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0f78);
+        } else {
+            src = reinterpret_cast<const char*>(gnext_q()) + piece0;
+            dst = lds_at + QUERY_AT + wave_u * 1024;
+            for (int p = 0; p < 4; ++p) ring_load(false);
+            src += qrow_elems * 2 - 4 * 4096;
+            for (int p = 0; p < 4; ++p) ring_load(false);
+            __builtin_amdgcn_s_waitcnt(0x0f74);
         }
+        __syncthreads();
+        load_invnorm(0);
+        tile_prepare();
+        for (int ti = 0; ti < my_tiles; ++ti) {
+            tile_init(ti);
+            int st = nsteps;
+            do ring_step(); while (--st > 0);
+            load_invnorm(ti + 1);
+            mfma_settle();
+            epilogue(ti);
+            tile_prepare();
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // blocks past the end still land in this workgroup's LDS
+        return;
+    }
+    if constexpr (Q_DIRECT) {
+        const uint16_t* qb = gnext_q();
+#pragma unroll
+        for (int i = 0; i < QCH; ++i) qload_to_lds(qb, 0, i);
     } else {
         gload_q(gqA);
     }
@@ -1005,7 +1135,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         if constexpr (DT == 0) load_invnorm(ti + 1);
         if constexpr (DT != 0) {
 #pragma unroll
-            for (int a = 0; a < RA; ++a) af[a] = frag_a(0, offA0, a);
+            for (int a = 0; a < RA; ++a) af[a] = frag_a(0, 0, a);
 #pragma unroll
             for (int b = 0; b < MR; ++b) bfr[0][b] = frag_b(0, offB0, b);
         }

@@ -37,6 +37,13 @@ __host__ __device__ __forceinline__ const uint32_t* slot_counter(const uint32_t*
 // physical 16-byte chunk index of logical chunk c (0..7) in row r (16-bit stores only)
 __host__ __device__ __forceinline__ int swz16(int c, int r) { return c ^ ((r >> 1) & 7); }
 
+// Prepared queries as matrix operands: fragments of 16 queries x 32 k, 1 KB each, a lane's 16 bytes after the other's --
+//   qop = [k-step of 32 elements][16-bit stores: 1 part; fp32 stores: bf16 head, remainder][Bpad / 16][64 lanes][8 elements]
+// with lane = 16 * (k / 8 % 4) + query % 16, as v_mfma_f32_16x16x32 takes them.  So a fragment is one contiguous piece wherever it is read from.
+// Two consecutive fragment rows (the halves of a k-block, or head and remainder) are what a step of the matrix-core scan stages.
+__host__ __device__ __forceinline__ int64_t qop_row(int64_t u, int Bpad) { return u * Bpad * 32; }                                // fragment row u
+__host__ __device__ __forceinline__ int qop_in_row(int q, int chunk) { return (q >> 4) * 512 + chunk * 128 + (q & 15) * 8; }      // query q's chunk of 8 in it
+
 // element offset of logical 8-element chunk c8 (k = 8*c8 ..) of entry id, 16-bit store
 __host__ __device__ __forceinline__ int64_t off16(int64_t id, int c8, int nkb) {
     int64_t t = id >> 8; int r = (int)(id & 255); int kb = c8 >> 3; int c = c8 & 7;
