@@ -189,8 +189,11 @@ __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ su
     uint64_t* words = exact_words(exact, b, exact_stride);
     const double inv64 = invq64[b];                 // (asked for with the list)
     Selected<SURV_CAP / 1024> s;
-    const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, sh, s);
-    if (!(inv64 > 0.0 && inv64 < (double)INFINITY)) {                       // uniform
+    const bool normed = inv64 > 0.0 && inv64 < (double)INFINITY;           // uniform
+    const uint32_t found = *slot_counter(cnt, b);
+    const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, false, sh, s,
+                                     [&](int i, uint32_t at) __attribute__((always_inline)) { if (normed && found <= (uint32_t)SURV_CAP) list[at] = s.key[i]; });
+    if (!normed) {
         for (int i = tid; i < k1; i += 1024) list[i] = pack_key(-INFINITY, i);  // (with more than one pass the bank holds more rows than a pool)
         if (tid == 0) { *slot_counter(cnt, b) = (uint32_t)k1; words[0] = ~0ull; words[1] = 0ull; }
         return;
@@ -199,7 +202,6 @@ __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ su
         if (tid == 0) words[0] = ~0ull;
         return;
     }
-    store_kept(s, list);
     if (tid == 0) {
         const bool filtered = exact_norm_fits(invq[b]) && key_sim(s.cut) >= -1.5f;
         *slot_counter(cnt, b) = margin > 0.f && !filtered ? (uint32_t)SURV_CAP + 1u : s.kept;

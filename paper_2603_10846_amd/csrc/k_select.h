@@ -67,12 +67,15 @@ __device__ __forceinline__ uint32_t group_prefix_u32(uint32_t x, uint32_t* part,
 // seed the next pass and, after the last pass, are the candidates that get re-scored in fp64.  Nothing is
 // sorted here -- slot order is irrelevant to every consumer.
 // Keys live in registers (8 per lane, 1024 lanes).  The kernel is a chain of barriers and LDS round trips
-// with one workgroup per query, so what counts is how many there are.  The first round uses 2048 bins of equal width in
+// with one workgroup per query, so what counts is how many there are.  The first round uses 1024 bins of equal width in
 // similarity: the pool is the thin upper tail of a list, so the pivot's bin nearly always holds no more than SEL_SMALL
 // keys and those few are ranked by counting.  (Digits of the bit pattern put most keys into a few bins, one per
-// exponent and leading bits; they remain for lists that equal widths cannot resolve.)  The keys that stay are placed by
-// prefix sums, not by one atomic each.  8192 keys of 64 queries: 8.5 us with digits of 11 bits, 6.3 now; 8192 keys of
-// one query 7.1, 6.2; lists of a filtering pass 5.1, 5.1.
+// exponent and leading bits; they remain for lists that equal widths cannot resolve.)  What every wavefront needs to know -- the
+// pivot's bin, the pivot -- every wavefront works out for itself from LDS, which takes less than handing it round behind a barrier:
+// four barriers, seven when one wavefront or lane found it for all.
+// 16 wavefronts share four SIMDs, so vector instructions count as well: places come from ballots and scalar sums, not from a prefix sum per lane.
+// Together, with the tail's: one query over 4096 rows, whole call 18.5 -> 17.9 us; seven over 30,011 (two selections) 30.2 -> 28.5; 32 over 300,007
+// (three) 91.2 -> 88.7; 64, pool of 960 193.9 -> 190.5.
 // A list that overflowed during the pass (more than SURV_CAP rows reached the threshold; the surplus was
 // dropped) is counted and the query is flagged: its pool may then miss members.
 // More than keep_max keys inside the margin ("crowded band"; near-duplicate entries do that):
@@ -83,13 +86,13 @@ __device__ __forceinline__ uint32_t group_prefix_u32(uint32_t x, uint32_t* part,
 //              fp32 resolution: the k1 best keys are kept, lower ids first among equal similarities.
 enum { SEL_PASS = 0, SEL_FINAL = 1, SEL_EXACT = 2 };
 constexpr int SEL_DIGIT = 11, SEL_BINS = 1 << SEL_DIGIT;
+constexpr int SEL_FIRST = 1024;          // bins of the first round
 constexpr int SEL_SMALL = 128;
 struct SelectLds {
-    uint32_t hist[SEL_BINS];
+    __align__(16) uint32_t hist[SEL_BINS];
     uint64_t small[SEL_SMALL];
-    uint64_t pivot;
     uint32_t most[16], least[16];
-    uint32_t part_a[16], part_b[16], digit, need, count, nsmall;
+    uint32_t part_a[16], part_b[16], count, nsmall, kept[2];
 };
 template <int K>         // keys per lane: 8 for a list of 8192, 16 for two
 struct Selected {
@@ -97,7 +100,7 @@ struct Selected {
     uint64_t cut;        // a key stays iff it is not 0 and not below this
     float tau;           // the threshold that this is (similarity units); meaningless with keep_all
     uint32_t kept;       // how many stay
-    uint32_t slot;       // this lane's first slot among them (its keys take consecutive slots)
+    uint32_t slot;       // the first place of this wavefront's among them
     bool keep_all;       // fewer keys than the pool has members: all stay and there is no threshold
     bool crowded;
 };
@@ -121,40 +124,55 @@ __device__ __forceinline__ uint32_t load_keys(const uint64_t* list, const uint32
     return raw;
 }
 
+// The bin in which the running count of the bins reaches `need` (PER bins to a lane), the rank that is left in it -> need, and how many keys it
+// has.  Every wavefront does the same.
+template <int PER>
+__device__ __forceinline__ uint32_t find_bin(const uint32_t* hist, int lane, uint32_t& need, uint32_t& in_bin) {
+    constexpr int Q = PER / 4;
+    uint32_t sum = 0;
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {                                            // (each lane from another quarter on: different banks)
+        const uint4 v = reinterpret_cast<const uint4*>(hist)[lane * Q + ((j + (lane >> 2)) & (Q - 1))];
+        sum += (v.x + v.y) + (v.z + v.w);
+    }
+    const uint32_t incl = wave_inclusive_sum(sum);
+    const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl >= need));
+    const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)incl, at) - (uint32_t)__builtin_amdgcn_readlane((int)sum, at);
+    const uint32_t c = lane < PER ? hist[at * PER + lane] : 0u;
+    const uint32_t upto = before + wave_inclusive_sum(c);
+    const int bin = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto >= need));
+    in_bin = (uint32_t)__builtin_amdgcn_readlane((int)c, bin);
+    need -= (uint32_t)__builtin_amdgcn_readlane((int)upto, bin) - in_bin;
+    return (uint32_t)(at * PER + bin);
+}
+
 // Selects among the keys in the registers (n of them, or fewer where some are empty; only the first `slots` places of the list
-// they were read from may hold one: what lies past them is skipped, a list is seldom full).
-template <int K>
-__device__ __forceinline__ void select_keys(int n, int slots, int k1, float margin, bool may_have_empty, int keep_max, int mode, SelectLds& sh,
-                                            Selected<K>& s) {
+// they were read from may hold one: what lies past them is skipped, a list is seldom full).  place(i, at) is called for this lane's
+// keys that stay, with their places (which may lie past keep_max: a crowded band, whose places are good for nothing unless the mode
+// says that it stays); a barrier follows.  `ordered`: the places follow from the list alone, not from which wavefront came first.
+template <int K, class Place>
+__device__ __forceinline__ void select_keys(int n, int slots, int k1, float margin, bool may_have_empty, int keep_max, int mode, bool ordered, SelectLds& sh,
+                                            Selected<K>& s, Place place) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const uint64_t (&key)[K] = s.key;
     for (int i = tid; i < SEL_BINS; i += 1024) sh.hist[i] = 0;
-    if (tid == 0) sh.nsmall = 0;
-    uint32_t used = 0;
-    uint32_t most = 0u, least = 0u;                   // largest similarity part of a key, and complement of the smallest
+    if (tid == 0) { sh.nsmall = 0; sh.kept[0] = 0; sh.kept[1] = 0; }
+    uint32_t used = 0;                                // keys of this wavefront
+    uint32_t most = 0u, least = 0xffffffffu;          // largest similarity part of a key, and the smallest less one (of no key: itself again)
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         if (i * 1024 >= slots) continue;                                 // uniform
-        if (key[i] != 0) {
-            const uint32_t o = (uint32_t)(key[i] >> 32);
-            most = o > most ? o : most;
-            least = ~o > least ? ~o : least;
-            ++used;
-        }
+        const uint32_t o = (uint32_t)(key[i] >> 32);
+        most = o > most ? o : most;
+        least = o - 1u < least ? o - 1u : least;
+        if (may_have_empty || n < k1) used += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[i] != 0));       // uniform
     }
     most = wave_max_u32(most);
-    least = wave_max_u32(least);
-    if (lane == 63) { sh.most[wave] = most; sh.least[wave] = least; }
+    least = wave_max_u32(~least);
+    if (lane == 63) { sh.most[wave] = most; sh.least[wave] = least; sh.part_b[wave] = used; }
     s.crowded = false;
     s.keep_all = false;
-    if (may_have_empty || n < k1) {                                       // uniform
-        uint32_t total;
-        const uint32_t first = group_prefix_u32(used, sh.part_a, wave, lane, total);      // (has the barrier)
-        s.keep_all = may_have_empty ? total < (uint32_t)k1 : true;
-        if (s.keep_all) { s.cut = 1ull; s.tau = 0.f; s.kept = total; s.slot = first; return; }
-    } else {
-        __syncthreads();
-    }
+    __syncthreads();
     most = 0u;
     least = 0u;
 #pragma unroll
@@ -162,48 +180,84 @@ __device__ __forceinline__ void select_keys(int n, int slots, int k1, float marg
         most = sh.most[w] > most ? sh.most[w] : most;
         least = sh.least[w] > least ? sh.least[w] : least;
     }
-    least = ~least;
+    least = ~least + 1u;
+    // Places of the keys that stay: a wavefront's lie together, in the order of i and lane.
+    auto place_all = [&](int again) __attribute__((always_inline)) {
+        uint64_t in[K];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            in[i] = i * 1024 < slots ? __builtin_amdgcn_ballot_w64(key[i] >= s.cut) : 0ull;
+            sum += (uint32_t)__popcll(in[i]);
+        }
+        if (ordered) {                                                       // uniform
+            uint32_t* part = again ? sh.part_b : sh.part_a;
+            if (lane == 0) part[wave] = sum;
+            __syncthreads();
+            s.slot = 0;
+            s.kept = 0;
+#pragma unroll
+            for (int w = 0; w < 16; ++w) {
+                const uint32_t p = part[w];
+                s.slot += w < wave ? p : 0u;
+                s.kept += p;
+            }
+            s.slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.slot);
+        } else {
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&sh.kept[again], sum);
+            s.slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        }
+        uint32_t at = s.slot;
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            if (in[i] == 0) continue;                                        // uniform within a wavefront
+            if (key[i] >= s.cut) place(i, at + __builtin_amdgcn_mbcnt_hi((uint32_t)(in[i] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in[i], 0u)));
+            at += (uint32_t)__popcll(in[i]);
+        }
+        __syncthreads();
+        if (!ordered) s.kept = sh.kept[again];
+    };
+    if (may_have_empty || n < k1) {                                       // uniform
+        uint32_t total = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) total += sh.part_b[w];
+        s.keep_all = total < (uint32_t)k1;
+        if (s.keep_all) {
+            s.cut = 1ull;
+            s.tau = 0.f;
+            place_all(0);
+            return;
+        }
+    }
     // The search for the k1-th key.  A round counts the keys per bin (bins in descending order, so that the pivot's bin is
     // found by a prefix sum); a bin of few keys is ranked by counting, else the next round looks into it.
     uint64_t pivot = 0;
     uint32_t need = (uint32_t)k1;
-    // the bin that holds the pivot, its rank there -> need, and how many keys it has; clears the bins for the next round
-    auto find_bin = [&](uint32_t& in_bin) __attribute__((always_inline)) {
-        __syncthreads();
-        const uint32_t c0 = sh.hist[2 * tid], c1 = sh.hist[2 * tid + 1];
-        sh.hist[2 * tid] = 0; sh.hist[2 * tid + 1] = 0;
-        uint32_t all;
-        const uint32_t run = group_prefix_u32(c0 + c1, sh.part_b, wave, lane, all);
-        if (run < need && run + c0 + c1 >= need) {                           // exactly one lane
-            const bool second = run + c0 < need;
-            sh.digit = (uint32_t)(2 * tid + second);
-            sh.need = need - run - (second ? c0 : 0u);
-            sh.count = second ? c1 : c0;
-        }
-        __syncthreads();
-        need = sh.need;
-        in_bin = sh.count;
-        return sh.digit;
-    };
     // ranks the in_bin keys that `in` names; the need-th of them is the pivot
     auto rank_few = [&](uint32_t in_bin, auto in) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < K; ++i)
             if (i * 1024 < slots && key[i] != 0 && in(i)) sh.small[atomicAdd(&sh.nsmall, 1u)] = key[i];
         __syncthreads();
-        if ((uint32_t)tid < in_bin) {
-            const uint64_t mine = sh.small[tid];
-            uint32_t rank = 0;
+        static_assert(SEL_SMALL == 128, "two keys to a lane");
+        uint64_t mine = sh.small[lane];
+        uint32_t rank = 0;
+        uint64_t at = 0;
+        for (int half = 0;; ++half) {                                        // uniform
 #pragma unroll 8
             for (uint32_t j = 0; j < in_bin; ++j) rank += sh.small[j] > mine;
-            if (rank == need - 1) sh.pivot = mine;                           // keys are distinct
+            at = __builtin_amdgcn_ballot_w64((uint32_t)(lane + 64 * half) < in_bin && rank == need - 1);           // keys are distinct
+            if (at != 0 || half == 1) break;
+            mine = sh.small[lane + 64];
+            rank = 0;
         }
-        __syncthreads();
-        return sh.pivot;
+        const int src = __builtin_ctzll(at | 1ull << 63);
+        return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), src) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, src);
     };
     // First round: bins of equal width in similarity between the largest and the smallest one (differences and
     // products round monotonically, so a better key never gets a later bin).  The upper tail, where the pivot lies, is thin.
-    const float top = ord2f(most), width = (float)SEL_BINS / (top - ord2f(least));
+    const float top = ord2f(most), width = (float)SEL_FIRST / (top - ord2f(least));
     bool found = false;
     if (width > 0.f && width < 1e30f && top - ord2f(least) < 1e30f) {        // uniform; not with infinities, NaN or equal similarities
         uint32_t bin[K];
@@ -212,16 +266,20 @@ __device__ __forceinline__ void select_keys(int n, int slots, int k1, float marg
             bin[i] = 0;
             if (i * 1024 >= slots) continue;                             // uniform
             const float x = (top - key_sim(key[i])) * width;
-            bin[i] = x < (float)(SEL_BINS - 1) ? (uint32_t)x : (uint32_t)(SEL_BINS - 1);
+            bin[i] = x < (float)(SEL_FIRST - 1) ? (uint32_t)x : (uint32_t)(SEL_FIRST - 1);
             if (key[i] != 0) atomicAdd(&sh.hist[bin[i]], 1u);
         }
+        __syncthreads();
         uint32_t in_bin;
-        const uint32_t at = find_bin(in_bin);
+        const uint32_t at = find_bin<SEL_FIRST / 64>(sh.hist, lane, need, in_bin);
         if (in_bin <= (uint32_t)SEL_SMALL) {                                 // uniform
             pivot = rank_few(in_bin, [&](int i) __attribute__((always_inline)) { return bin[i] == at; });
             found = true;
-        } else {
-            need = (uint32_t)k1;                                             // crowded: by digits, from the start
+        } else {                                                             // crowded: by digits, from the start
+            need = (uint32_t)k1;
+            __syncthreads();
+            for (int i = tid; i < SEL_FIRST; i += 1024) sh.hist[i] = 0;
+            __syncthreads();
         }
     }
     // By digits of 11 bits, from the highest bit on which two keys differ.
@@ -234,45 +292,37 @@ __device__ __forceinline__ void select_keys(int n, int slots, int k1, float marg
         for (int i = 0; i < K; ++i)
             if (i * 1024 < slots && key[i] != 0 && (hi == 63 || (key[i] >> (hi + 1)) == (prefix >> (hi + 1))))
                 atomicAdd(&sh.hist[SEL_BINS - 1 - ((uint32_t)(key[i] >> shift) & dmask)], 1u);
+        __syncthreads();
         uint32_t in_bin;
-        prefix |= (uint64_t)(SEL_BINS - 1 - find_bin(in_bin)) << shift;
+        prefix |= (uint64_t)(SEL_BINS - 1 - find_bin<SEL_BINS / 64>(sh.hist, lane, need, in_bin)) << shift;
         if (shift == 0) { pivot = prefix; break; }                           // all 64 bits are known
         if (in_bin <= (uint32_t)SEL_SMALL) {                                 // uniform
             pivot = rank_few(in_bin, [&](int i) __attribute__((always_inline)) { return (key[i] >> shift) == (prefix >> shift); });
             break;
         }
         hi = shift - 1;
+        __syncthreads();
+        for (int i = tid; i < SEL_BINS; i += 1024) sh.hist[i] = 0;
+        __syncthreads();
     }
     s.tau = key_sim(pivot) - margin;
-    s.cut = (uint64_t)f2ord(s.tau) << 32;           // every key with similarity >= tau compares >= cut
-    for (int again = 0;; ++again) {
-        uint32_t mine = 0;
-#pragma unroll
-        for (int i = 0; i < K; ++i)
-            if (i * 1024 < slots) mine += key[i] != 0 && key[i] >= s.cut;
-        s.slot = group_prefix_u32(mine, again ? sh.part_b : sh.part_a, wave, lane, s.kept);
-        if (again || s.kept <= (uint32_t)keep_max) break;                    // uniform
-        s.crowded = true;
-        if (mode != SEL_EXACT) break;
-        s.cut = pivot;                              // ties within fp32 resolution: exactly the k1 best
-    }
+    s.cut = (uint64_t)f2ord(s.tau) << 32 | 1u;      // every key with similarity >= tau compares >= cut (no id is 2^32 - 1), an empty one never
+    place_all(0);
+    if (s.kept <= (uint32_t)keep_max) return;                                // uniform
+    s.crowded = true;
+    if (mode != SEL_EXACT) return;
+    s.cut = pivot;                                  // ties within fp32 resolution: exactly the k1 best
+    __builtin_amdgcn_s_waitcnt(0x0f70);             // vmcnt(0): what place has stored comes before what it stores next
+    __syncthreads();
+    place_all(1);
 }
-template <int K>
+template <int K, class Place>
 __device__ __forceinline__ uint32_t select_keys(const uint64_t* list, const uint32_t* count, int k1, float margin, bool may_have_empty,
-                                                int keep_max, int mode, SelectLds& sh, Selected<K>& s) {
+                                                int keep_max, int mode, bool ordered, SelectLds& sh, Selected<K>& s, Place place) {
     const uint32_t raw = load_keys(list, count, s);
     const int n = raw > (uint32_t)(K * 1024) ? K * 1024 : (int)raw;
-    select_keys(n, n, k1, margin, may_have_empty, keep_max, mode, sh, s);
+    select_keys(n, n, k1, margin, may_have_empty, keep_max, mode, ordered, sh, s, place);
     return raw;
-}
-
-// The kept keys of a selection to the head of a list (the keys were read before a barrier inside the selection).
-template <int K>
-__device__ __forceinline__ void store_kept(const Selected<K>& s, uint64_t* list) {
-    uint32_t at = s.slot;
-#pragma unroll
-    for (int i = 0; i < K; ++i)
-        if (s.key[i] != 0 && s.key[i] >= s.cut) list[at++] = s.key[i];
 }
 
 // Between two scan passes: one workgroup per query.
@@ -285,9 +335,10 @@ __global__ __launch_bounds__(1024) void k_select(uint64_t* __restrict__ surv, ui
     const int b = (int)blockIdx.x, tid = threadIdx.x;
     uint64_t* list = surv + (int64_t)b * (K * 1024);
     Selected<K> s;
-    const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, margin, may_have_empty != 0, keep_max, SEL_PASS, sh, s);
+    // the keys that stay go to the list's head (they were all read before a barrier; the count too)
+    const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, margin, may_have_empty != 0, keep_max, SEL_PASS, false, sh, s,
+                                     [&](int i, uint32_t at) __attribute__((always_inline)) { list[at] = s.key[i]; });
     if (raw > (uint32_t)(K * 1024) && tid == 0) { atomicAdd(counters + 1, 1u); flags[b] |= 1u; }
-    store_kept(s, list);                            // (every lane has also read the count by now)
     if (tid == 0) {
         *slot_counter(cnt, b) = s.kept;
         thr[b] = (s.keep_all ? -2.0f : s.tau) / invq[b];      // no threshold: a finite floor, see k_prep_queries

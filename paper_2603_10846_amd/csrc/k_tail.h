@@ -74,17 +74,25 @@ __device__ __forceinline__ void rank_entries(const double* val, const int32_t* i
                                              double (*red)[16], Emit emit) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     if constexpr (!BIG) {
-        // four lanes share an entry: each counts over every fourth other entry
-        for (int i = tid / 4; i < n; i += TAIL_T / 4) {              // trip count uniform within a lane quad
-            const double v = val[i];
-            const int32_t id = ids[i];
-            int rank = 0;
+        // four lanes share an entry, or as many as there are: each counts over every fourth (8th, 16th) other entry
+        auto count = [&](auto lanes) __attribute__((always_inline)) {
+            constexpr int L = decltype(lanes)::value;
+            for (int i = tid / L; i < n; i += TAIL_T / L) {          // trip count uniform within the lanes that share
+                const double v = val[i];
+                const int32_t id = ids[i];
+                int rank = 0;
 #pragma unroll 8
-            for (int j = tid % 4; j < n; j += 4) rank += ranks_before(val[j], ids[j], v, id);
-            rank += __shfl_xor(rank, 1, 64);
-            rank += __shfl_xor(rank, 2, 64);
-            if (tid % 4 == 0) emit(i, rank);
-        }
+                for (int j = tid % L; j < n; j += L) rank += ranks_before(val[j], ids[j], v, id);
+                rank += __builtin_amdgcn_update_dpp(0, rank, 0xb1, 0xf, 0xf, true);             // quad_perm 1,0,3,2
+                rank += __builtin_amdgcn_update_dpp(0, rank, 0x4e, 0xf, 0xf, true);             // quad_perm 2,3,0,1
+                if constexpr (L >= 8) rank += __builtin_amdgcn_update_dpp(0, rank, 0x141, 0xf, 0xf, true);     // row_half_mirror
+                if constexpr (L >= 16) rank += __builtin_amdgcn_update_dpp(0, rank, 0x140, 0xf, 0xf, true);    // row_mirror
+                if (tid % L == 0) emit(i, rank);
+            }
+        };
+        if (n <= TAIL_T / 16) count(std::integral_constant<int, 16>{});
+        else if (n <= TAIL_T / 8) count(std::integral_constant<int, 8>{});
+        else count(std::integral_constant<int, 4>{});
     } else {
         constexpr int U = (BIG_K1_MAX + 256 + TAIL_T - 1) / TAIL_T;   // entries per lane
         // range of the finite values
@@ -233,7 +241,9 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     query_to_lds<DT>(yq, A.qf + (int64_t)b * A.nkb * KB, A.nkb, TAIL_T);                   // (barriers follow)
     // ---- selection ----
     Selected<K> s;
-    const uint32_t raw = select_keys(list, slot_counter(A.cnt, b), k1, A.margin, A.may_have_empty != 0, cap, A.mode, sh, s);
+    // (several workgroups each take a share of the same order)
+    const uint32_t raw = select_keys(list, slot_counter(A.cnt, b), k1, A.margin, A.may_have_empty != 0, cap, A.mode, parts > 1, sh, s,
+                                     [&](int i, uint32_t at) __attribute__((always_inline)) { if (at < (uint32_t)cap) i0[at] = key_id(s.key[i]); });
     const TailArgsPtr mid = tail_args_from_here();
     if (raw > (uint32_t)CAP && mid->mode == SEL_FINAL && part == 0 && tid == 0) { atomicAdd(mid->counters + 1, 1u); mid->flags[b] |= 1u; }
     // The last of the query's workgroups to come here?  All that one workgroup hands to another are the similarities
@@ -249,7 +259,7 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
         __syncthreads();
         return last_s != 0;
     };
-    auto stays = [&](int i) __attribute__((always_inline)) { return s.key[i] != 0 && s.key[i] >= s.cut; };
+    auto stays = [&](int i) __attribute__((always_inline)) { return s.key[i] >= s.cut; };
     // A crowded band (uniform, and the same for all of the query's workgroups): every key of it, up to the list's size, gets its
     // similarity accumulated in fp64 and the selection is made again with those, which are then the candidates' similarities.
     // The keys' ids stay in registers, so the similarities can take the place of the query's own list, or, if several
@@ -297,12 +307,6 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
 #pragma unroll
         for (int i = 0; i < K / 2; ++i) asm volatile("" : "+v"(places[i]));
         lay_out(0);
-    } else {
-        uint32_t at = s.slot;
-#pragma unroll
-        for (int i = 0; i < K; ++i)
-            if (stays(i)) ids[at++] = key_id(s.key[i]);
-        __syncthreads();
     }
     // the stage's values of all candidates: requested here, so that the z-scores need not wait for them
     constexpr int UC = ((BIG ? keep_of(BIG_K1_MAX) : KEEP_MAX) + TAIL_T - 1) / TAIL_T;
@@ -366,13 +370,9 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
         for (int i = 0; i < K; ++i) sim[i] = sim_at(mine[i] >= 0 ? places[i / 2] >> (16 * (i % 2)) & 0xffffu : 0u);
 #pragma unroll
         for (int i = 0; i < K; ++i) s.key[i] = mine[i] >= 0 ? exact_key(sim[i], mine[i]) : 0ull;
-        select_keys(kk, CAP, k1, EXACT_KEY_MARGIN, true, cap, SEL_EXACT, sh, s);
+        select_keys(kk, CAP, k1, EXACT_KEY_MARGIN, true, cap, SEL_EXACT, false, sh, s,
+                    [&](int i, uint32_t at) __attribute__((always_inline)) { if (at < (uint32_t)cap) { i0[at] = mine[i]; v0[at] = sim[i]; } });
         kk = (int)s.kept;
-        uint32_t at = s.slot;
-#pragma unroll
-        for (int i = 0; i < K; ++i)
-            if (stays(i)) { i0[at] = mine[i]; v0[at++] = sim[i]; }
-        __syncthreads();
         for (int i = tid; i < kk; i += TAIL_T) q0[i] = mid->qstage[i0[i]];
     } else {
         if (parts > 1)
