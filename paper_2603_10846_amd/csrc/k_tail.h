@@ -489,7 +489,8 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     // ---- epsilon-greedy slot filling (Sec. 3.3) ----
     // The whole pool is laid out in greedy order; every slot's draw is computed by its own lane (the draws
     // depend on the slot number only); then one wavefront fills the slots in order, because which members are
-    // still free depends on the slots before.  Lane w holds the free members 64 w .. 64 w + 63 as a bit mask.
+    // still free depends on the slots before.  Lane w holds the free members 64 w .. 64 w + 63 as a bit mask.  The slots between two that
+    // explore take the best free members in order, all at once (64 queries, a pool of 960, 32 slots, eps 0.1: whole call 190.5 us slot by slot, 185.9).
     int t = (int)threadIdx.x;                                          // (computed anew: what is kept for these lines is spilled by every call)
     asm volatile("" : "+v"(t));
     const int tl = t & 63;
@@ -505,19 +506,45 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     __syncthreads();
     if (t >= 64) return;                                               // uniform within a wavefront
     uint64_t is_free = k1e >= 64 * tl + 64 ? ~0ull : k1e <= 64 * tl ? 0ull : (1ull << (k1e - 64 * tl)) - 1ull;
-    for (int j = 0; j < k2e; ++j) {
-        const bool explore = (uint64_t)word0[j] < threshold;
-        const int want = explore ? (int)(((uint64_t)word1[j] * (uint32_t)(k1e - j)) >> 32) : 0;   // index among the free members
-        const int c = __popcll(is_free);
-        const int upto = (int)wave_inclusive_sum((uint32_t)c);
-        const int holder = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto > want));               // the first lane that reaches it
-        if (tl == holder) {
-            const int bit = nth_set_bit(is_free, want - (upto - c));
-            is_free &= ~(1ull << bit);
-            const int at = 64 * tl + bit;
-            out_ids[j] = i1[at];
-            out_scores[j] = (float)v1[at];
-            if (explored) explored[(int64_t)b * k2 + j] = explore ? 1 : 0;
+    auto emit = [&](int slot, int at, bool explore) __attribute__((always_inline)) {
+        out_ids[slot] = i1[at];
+        out_scores[slot] = (float)v1[at];
+        if (explored) explored[(int64_t)b * k2 + slot] = explore ? 1 : 0;
+    };
+    for (int c0 = 0; c0 < k2e; c0 += 64) {                             // a slot per lane
+        const int here = k2e - c0 < 64 ? k2e - c0 : 64;
+        const uint32_t w1 = tl < here ? word1[c0 + tl] : 0u;
+        const uint64_t explores = __builtin_amdgcn_ballot_w64(tl < here && (uint64_t)word0[c0 + (tl < here ? tl : 0)] < threshold);
+        for (int p = 0; p < here;) {                                   // uniform; every turn fills a slot at least
+            const int c = __popcll(is_free), upto = (int)wave_inclusive_sum((uint32_t)c), before = upto - c;
+            const uint64_t ahead = explores >> p;
+            const int run = ahead == 0 || __builtin_ctzll(ahead) > here - p ? here - p : __builtin_ctzll(ahead);
+            if (run > 0) {                                             // the run's t-th slot takes the t-th free member
+                const int t = tl - p;
+                int at = 0;
+                for (int done = 0; done < run;) {                      // (a turn for every lane that holds some of them)
+                    const int holder = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto > done));
+                    const uint64_t mask = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(is_free >> 32), holder) << 32
+                                        | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)is_free, holder);
+                    const int first = __builtin_amdgcn_readlane(before, holder), last = __builtin_amdgcn_readlane(upto, holder);
+                    if (t >= done && t < last) at = 64 * holder + nth_set_bit(mask, t - first);
+                    done = last;
+                }
+                if (t >= 0 && t < run) emit(c0 + tl, at, false);
+                if (upto <= run) is_free = 0;
+                else if (before < run) is_free &= ~((2ull << nth_set_bit(is_free, run - before - 1)) - 1ull);
+                p += run;
+            } else {
+                const int j = c0 + p;
+                const int want = (int)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)w1, p) * (uint32_t)(k1e - j)) >> 32);   // index among the free members
+                const int holder = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto > want));       // the first lane that reaches it
+                if (tl == holder) {
+                    const int bit = nth_set_bit(is_free, want - before);
+                    is_free &= ~(1ull << bit);
+                    emit(j, 64 * tl + bit, true);
+                }
+                ++p;
+            }
         }
     }
 }
