@@ -407,8 +407,8 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         return *reinterpret_cast<const u32x4_t*>(smem + off + (s * STAGE_BANK_BYTES + block * 2048));
     };
     // One step: the MFMAs on LDS stage s, and meanwhile the operands of the next step (registers gb, gq,
-    // loaded two steps ago) go to stage s ^ 1 and the same registers take the loads of the step three
-    // ahead, so two register sets are in flight at all times, tile epilogues included.
+    // loaded a step and a half ago) go to stage s ^ 1, and the loads of the step two ahead go to the registers stored in the step before
+    // (fp32 stores: of the step three ahead, to the registers just stored).
     // Inverse norms of this lane's MR bank rows of the next tile.  They are requested in the last
     // k-step of a tile (the fragment registers are free by then; across the whole k-loop there is
     // no register to spare, and a value that gets spilled has to be waited for right after its
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     // query fragment of slot g lies in af[g % RA], requested RA slots ahead.
     constexpr int RA = RING ? MQ : MQ < 4 ? MQ : 4, SLOTS = 2 * MQ, BARRIER = 3 * MQ / 2;
     u32x4_t af[RA], bfr[2][MR];
-    auto compute = [&](int s, u32x4_t (&gb)[BCH], u32x4_t (&gq)[QCH], auto fetch_next) __attribute__((always_inline)) {
+    auto compute = [&](int s, u32x4_t (&gb)[BCH], u32x4_t (&free)[BCH], u32x4_t (&gq)[QCH], auto fetch_next) __attribute__((always_inline)) {
         if constexpr (DT == 0) {
             // hi (chunks 0..3) and lo (4..7) of 32 elements: one k-step of three products
             if constexpr (Q_DIRECT) {
@@ -473,8 +473,10 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             // A software pipeline written out by hand, one slot per query block a of a k-step: the MFMAs of block a
             // (MR of them), then the LDS read of the fragment RA slots ahead into the registers those MFMAs have just
             // read, then one piece of the side work.  The bank fragments are used by every slot of a k-step and are
-            // double buffered instead.  The LDS stores (second and third quarter of the slots) and the global loads
-            // (last quarter) issue in the shadow of the MFMAs instead of forming a period without any.
+            // double buffered instead.  The global loads of bank pieces (first quarter of the slots) and the LDS stores (second and third)
+            // issue in the shadow of the MFMAs instead of forming a period without any.  (Behind the barrier, in the last quarter, the loads
+            // of all wavefronts met the first fragments' reads: 32 queries, 300,007 x 384 fp16, densest pass 44.6 us, 42.8 now; 64, 196,608 x
+            // 1024 bf16 69.3, 67.8.)
             // The scheduler is fenced per slot to keep this order (left alone it hoists the reads).
             // On entry af and bfr[0] hold the step's first fragments, fetched by the previous step or, for
             // the first step of a tile, by the tile loop (the last step of a tile fetches nothing: the
@@ -492,6 +494,12 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 if (g == BARRIER) {
                     __syncthreads();
                     __builtin_amdgcn_sched_barrier(0);
+                }
+                // the bank pieces two steps ahead, into the registers that the last step has stored
+                constexpr int Q1 = MQ / 2;                                  // slots of a quarter
+                if (g < Q1) {
+#pragma unroll
+                    for (int i = g * BCH / Q1; i < (g + 1) * BCH / Q1; ++i) free[i] = gpiece_bank(nb, i);
                 }
                 // bank fragments: those of k-step 1 over the first slots, those of the next step behind the barrier
                 constexpr int BPS = (2 * MR + MQ - 1) / MQ;               // per slot
@@ -516,8 +524,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 } else if (FETCH && g >= BARRIER) {
                     af[g % RA] = frag_a(s ^ 1, 0, g + RA - SLOTS);
                 }
-                // the bank pieces: stored over the second and third quarter of the slots, reloaded over the last
-                constexpr int Q1 = MQ / 2;                                  // slots of a quarter
+                // the bank pieces: stored over the second and third quarter of the slots
                 if (g >= Q1 && g < BARRIER) {
 #pragma unroll
                     for (int i = (g - Q1) * BCH / (2 * Q1); i < (g - Q1 + 1) * BCH / (2 * Q1); ++i)
@@ -533,11 +540,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
 #pragma unroll
                     for (int i = (g - MQ) * QCH / Q1; i < (g - MQ + 1) * QCH / Q1; ++i) gq[i] = gpiece(nq, i);
                 }
-                if (g >= BARRIER) {
-#pragma unroll
-                    for (int i = (g - BARRIER) * BCH / Q1; i < (g - BARRIER + 1) * BCH / Q1; ++i) gb[i] = gpiece_bank(nb, i);
-                    if (!FETCH && g == SLOTS - 1) load_invnorm(tile_now + 1);
-                }
+                if (!FETCH && g == SLOTS - 1) load_invnorm(tile_now + 1);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -1068,8 +1071,8 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     };
 
     // ---- pipeline over the flattened (tile, k-block) sequence; g counts steps over all tiles ----
-    auto phase = [&](int s, u32x4_t (&gb)[BCH], u32x4_t (&gq)[QCH], auto fetch_next) __attribute__((always_inline)) {
-        compute(s, gb, gq, fetch_next);
+    auto phase = [&](int s, u32x4_t (&gb)[BCH], u32x4_t (&free)[BCH], u32x4_t (&gq)[QCH], auto fetch_next) __attribute__((always_inline)) {
+        compute(s, gb, free, gq, fetch_next);
         if constexpr (DT == 0) {
             if constexpr (Q_DIRECT) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(BCH) : "memory");   // the query block: only the bank pieces came after it
             __syncthreads();
@@ -1120,7 +1123,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     gload(gbB);
     lstore(0, gbA, gqA);
     if constexpr (!Q_DIRECT) gload_q(gqA);
-    gload(gbA);
+    if constexpr (DT == 0) gload(gbA);
     if constexpr (Q_DIRECT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if constexpr (EXACT) {
@@ -1140,11 +1143,11 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             for (int b = 0; b < MR; ++b) bfr[0][b] = frag_b(0, offB0, b);
         }
         for (int st = 0; st < nsteps - 2; st += 2) {
-            phase(0, gbB, gqB, std::true_type{});
-            phase(1, gbA, gqA, std::true_type{});
+            phase(0, gbB, gbA, gqB, std::true_type{});
+            phase(1, gbA, gbB, gqA, std::true_type{});
         }
-        phase(0, gbB, gqB, std::true_type{});
-        phase(1, gbA, gqA, std::false_type{});
+        phase(0, gbB, gbA, gqB, std::true_type{});
+        phase(1, gbA, gbB, gqA, std::false_type{});
         mfma_settle();
         epilogue(ti);
         tile_prepare();
