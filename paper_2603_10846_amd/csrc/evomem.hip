@@ -268,9 +268,15 @@ int mem_shape_rewards(evomem_t* h, int stage, const unsigned char* feasible_dev,
     if (M == 0) return MEM_OK;
     if (!feasible_dev || !rewards_out_dev || (stage == 1 && (!latency_dev || !best_latency_dev))) return MEM_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    // (the chain's two words lie in the zero-initialised counter block, behind the statistics)
     RewardArgs A{feasible_dev, latency_dev, best_latency_dev, M, (double)sigma_min, (double)clip, reward_state(h, stage),
-                 reinterpret_cast<double*>(h->ws + h->w.surv), rewards_out_dev, stage, normalise};
-    if (M <= reward_one_launch(stage, normalise)) {
+                 reinterpret_cast<double*>(h->ws + h->w.surv), reinterpret_cast<uint64_t*>(h->ws + h->w.counters + 128), rewards_out_dev, stage, normalise};
+    if (normalise && M > REWARD_ONE && M <= (int64_t)REWARD_CHAIN * REWARD_T) {
+        hipLaunchKernelGGL(k_reward_chain, dim3((unsigned)((M + REWARD_T - 1) / REWARD_T)), dim3(REWARD_T), 0, st, A);
+        LAUNCHCHK();
+        return MEM_OK;
+    }
+    if (M <= REWARD_ONE) {
         hipLaunchKernelGGL(k_shape_rewards, dim3(1), dim3(REWARD_ONE), 0, st, A);
         LAUNCHCHK();
         return MEM_OK;

@@ -7,11 +7,11 @@
 //   (r_t - mu_{t-1}) / max(sigma_{t-1}, sigma_min), optionally clipped, with mu, sigma the running
 //   mean and population deviation of the raw rewards BEFORE it; the statistics (count, sum, sum of
 //   squares, fp64) persist in the handle's workspace.
-// The dependence of sample t on all earlier ones is a prefix sum.  A batch of little more than one workgroup's size is one
-// launch; a longer one is two: the first leaves every block's sums of (r, r^2), in the second a block adds
-// the sums of the blocks before it and scans its own samples.  The raw rewards are computed in both -- two fp64
-// logarithms and a tanh per sample are what bounds the kernel, and one workgroup walking the batch in
-// pieces of 1024 did them on one compute unit: 8192 samples 45.3 us, 3.3 + 4.2 us in two launches.
+// The dependence of sample t on all earlier ones is a prefix sum.  Up to 1024 samples are one workgroup's; up to 64 blocks of 256 are one
+// launch in which a block leaves its sums of (r, r^2) and waits for those of the blocks before it; longer batches are two launches, the
+// first for the sums, and in the second a block adds those of the blocks before it.  The raw rewards -- two fp64
+// logarithms and a tanh per sample -- are what bounds a block, and the launches (about 3 us each) the host.  us a call, one workgroup walking the batch in
+// pieces of 1024 up to 1536 samples (3072 in stage 0) and two launches beyond, and now: stage 1, 1025 samples 9.0, 7.2; 8192 8.9, 7.1; stage 0, 3072 9.6, 7.1.
 // All arithmetic in fp64; outputs fp32.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -21,12 +21,9 @@
 
 namespace evk {
 
-constexpr int REWARD_ONE = 1024;          // samples per piece of the one-launch form
-// Largest batch of the one-launch form.  A second launch costs the host about 3.5 us, a second piece what its samples cost
-// (one launch / two, us a call): stage 1, 1025 samples 10.1 / 11.5, 1536 11.0 / 11.7, 2000 12.8 / 11.5; stage 0 (no logarithms), 1025
-// 8.9 / 12.0, 3000 10.7 / 11.8, 4096 13.2 / 12.1; unnormalised rewards of a longer batch need one launch over all blocks in any case.
-__host__ constexpr int64_t reward_one_launch(int stage, int normalise) { return !normalise ? REWARD_ONE : stage == 0 ? 3 * REWARD_ONE : REWARD_ONE + REWARD_ONE / 2; }
-constexpr int REWARD_T = 256;             // samples per block of the two-launch form
+constexpr int REWARD_ONE = 1024;          // largest batch of one workgroup
+constexpr int REWARD_T = 256;             // samples per block of the other forms
+constexpr int REWARD_CHAIN = 64;          // blocks of the one-launch form, a bit each
 // Blocks of a pair of launches, at most: every block adds up the sums of all before it, so a pair's work has a part that
 // grows with the square of its blocks.  Normalised, 4 M samples 147 -> 133 us, 16.7 M 1267 -> 531, 67 M 17.5 -> 2.2 ms (a batch in one
 // pair before; pairs of 2048 blocks take 15 to 20 % longer than these).
@@ -48,7 +45,8 @@ struct RewardArgs {
     int64_t M;
     double sigma_min, clip;
     double* state;            // count, sum, sum of squares
-    double* sums;             // two-launch form: the statistics before the batch, then two sums per block
+    double* sums;             // the statistics before the batch (two launches), then two sums per block
+    uint64_t* chain;          // one launch: which blocks have left their sums, how many have read the others'; zero between calls
     float* out;
     int stage, normalise;
 };
@@ -88,28 +86,74 @@ __device__ __forceinline__ void block_prefix2(double (*part)[2], int wave, int l
     }
 }
 
-// One workgroup walks the batch in pieces of 1024 samples.
+// At most 1024 samples (more of them unnormalised are the last kernel's).
 __global__ __launch_bounds__(REWARD_ONE) void k_shape_rewards(RewardArgs A) {
-    __shared__ double part[2][REWARD_ONE / 64][2];
+    __shared__ double part[REWARD_ONE / 64][2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double n0 = 0.0, s0 = 0.0, q0 = 0.0;                             // the statistics before the piece
-    if (A.normalise) { n0 = A.state[0]; s0 = A.state[1]; q0 = A.state[2]; }
-    for (int64_t base = 0; base < A.M; base += REWARD_ONE) {
-        const int64_t j = base + tid;
-        const bool live = j < A.M;
-        const double raw = live ? raw_reward(A, j) : 0.0;
-        if (!A.normalise) {                                          // uniform
-            if (live) A.out[j] = (float)raw;
-            continue;
-        }
-        double bs, bq, as, aq;
-        block_prefix2<REWARD_ONE / 64>(part[(base / REWARD_ONE) & 1], wave, lane, raw, raw * raw, bs, bq, as, aq);    // (has a barrier)
-        if (live) A.out[j] = (float)normalised_reward(A, raw, n0 + tid, s0 + bs, q0 + bq);
-        n0 += (double)(A.M - base < REWARD_ONE ? A.M - base : REWARD_ONE);
-        s0 += as;
-        q0 += aq;
+    const bool live = tid < A.M;
+    const double raw = live ? raw_reward(A, tid) : 0.0;
+    if (!A.normalise) {                                              // uniform
+        if (live) A.out[tid] = (float)raw;
+        return;
     }
-    if (A.normalise && tid == 0) { A.state[0] = n0; A.state[1] = s0; A.state[2] = q0; }
+    const double n0 = A.state[0], s0 = A.state[1], q0 = A.state[2];  // the statistics before the batch
+    double bs, bq, as, aq;
+    block_prefix2<REWARD_ONE / 64>(part, wave, lane, raw, raw * raw, bs, bq, as, aq);    // (has a barrier)
+    if (live) A.out[tid] = (float)normalised_reward(A, raw, n0 + tid, s0 + bs, q0 + bq);
+    if (tid == 0) { A.state[0] = n0 + (double)A.M; A.state[1] = s0 + as; A.state[2] = q0 + aq; }
+}
+
+// Up to 64 blocks in one launch.  A block waits for those before it only.  All of the launch's blocks fit on the device many times
+// over, so each of them comes to run whatever the others do, and the wait ends; were there room for only a few they would come
+// in order, and the first of them waits for none.
+// What blocks hand to each other are their sums, stored and loaded as device-scope atomics, which pass by the caches that differ between
+// XCDs; a block's stores have been acknowledged before it says so.
+__global__ __launch_bounds__(REWARD_T) void k_reward_chain(RewardArgs A) {
+    __shared__ double total[REWARD_T / 64][2], part[REWARD_T / 64][2], earlier[2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, block = (int)blockIdx.x;
+    const int64_t j = (int64_t)block * REWARD_T + tid;
+    const bool live = j < A.M;
+    const double n_old = A.state[0], s_old = A.state[1], q_old = A.state[2];      // (replaced by the last block once all have said so)
+    const double raw = live ? raw_reward(A, j) : 0.0;
+    const double s = wave_total_d(raw), q = wave_total_d(raw * raw);
+    if (lane == 0) { total[wave][0] = s; total[wave][1] = q; }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (wave == 0) {                                                 // uniform within a wavefront
+        double* mine = A.sums + REWARD_HEAD;
+        if (lane < 2)
+            __hip_atomic_store(mine + 2 * block + lane, (total[0][lane] + total[1][lane]) + (total[2][lane] + total[3][lane]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) __hip_atomic_fetch_or(A.chain, 1ull << block, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t before = (1ull << block) - 1ull;
+        while ((__hip_atomic_load(A.chain, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & before) != before) __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
+        double es = 0.0, eq = 0.0;
+        if (lane < block) {
+            es = __hip_atomic_load(mine + 2 * lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            eq = __hip_atomic_load(mine + 2 * lane + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        es = wave_total_d(es);
+        eq = wave_total_d(eq);
+        if (lane == 0) {
+            earlier[0] = es;
+            earlier[1] = eq;
+            // the last block to get here leaves the words as it would find them
+            if (__hip_atomic_fetch_add(A.chain + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint64_t)gridDim.x - 1u) {
+                __hip_atomic_store(A.chain, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(A.chain + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+    double bs, bq, as, aq;
+    block_prefix2<REWARD_T / 64>(part, wave, lane, raw, raw * raw, bs, bq, as, aq);       // (has a barrier)
+    const double s0 = s_old + earlier[0], q0 = q_old + earlier[1];
+    if (live) A.out[j] = (float)normalised_reward(A, raw, n_old + (double)j, s0 + bs, q0 + bq);
+    if (block == (int)gridDim.x - 1 && tid == 0) {
+        A.state[0] = n_old + (double)A.M;
+        A.state[1] = s0 + as;
+        A.state[2] = q0 + aq;
+    }
 }
 
 // First launch of a longer batch: the blocks' sums, and a copy of the statistics (the second launch replaces them
