@@ -249,9 +249,12 @@ class MemoryBank:
                         exclude_group: torch.Tensor, want_candidates: bool = False):
         assert queries.is_cuda and queries.dtype == torch.float32 and queries.is_contiguous()
         B = queries.shape[0]
-        al = allow_types.to(device=self.device, dtype=torch.int64).to(torch.int32).contiguous()
-        ex = exclude_group.to(device=self.device, dtype=torch.int64).to(torch.int32).contiguous()
+        al = allow_types.to(device=self.device, dtype=torch.int64).contiguous().view(-1)
+        ex = exclude_group.to(device=self.device, dtype=torch.int64).contiguous().view(-1)
         assert al.numel() == B and ex.numel() == B
+        # the low words of both, in one launch (two conversions were 3 of 88 us of a call with 32 queries)
+        words = torch.cat((al.view(torch.int32).view(-1, 2)[:, 0], ex.view(torch.int32).view(-1, 2)[:, 0]))
+        al, ex = words[:B], words[B:]
         ids = torch.empty((B, k2), dtype=torch.int32, device=self.device)
         scores = torch.empty((B, k2), dtype=torch.float32, device=self.device)
         cid = torch.empty((B, k1), dtype=torch.int32, device=self.device) if want_candidates else None

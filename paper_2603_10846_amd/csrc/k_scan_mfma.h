@@ -170,7 +170,7 @@ static_assert(scan_mfma_lds_bytes<1, 256, true>() <= SCAN_LDS && scan_mfma_lds_b
 // MASKED: typed / masked retrieval -- a row is kept for a query only if the query accepts its tag.
 // STREAM: bank rows are loaded with the non-temporal hint (layout.h).  Right whenever a bank tile is read
 // by one workgroup only; with several query tiles per bank tile (more than 256 queries) the later readers
-// are meant to find the tile in L2, and the hint costs 7 % there (measured: 1185 -> 1105 TFLOP/s at 1024 queries).
+// are meant to find the tile in L2, and the hint costs 2 % there (measured: 1397 -> 1366 TFLOP/s at 1024 queries, the sparser passes 10 %).
 template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true, bool EXACT = false>
 __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __restrict__ store_, const float* __restrict__ invnorm,
                                                    const uint16_t* __restrict__ qop, const float* __restrict__ invq,
