@@ -14,7 +14,7 @@
 // fragments are read from LDS a few query blocks ahead, the LDS stores and global loads of the following
 // k-blocks issue between the MFMAs, and there is one workgroup barrier per k-block.
 //
-// 256 queries to a tile over 16-bit stores (RING): operands go from memory straight to LDS, through rings of three places, and the
+// 128 or 256 queries to a tile over 16-bit stores (RING): operands go from memory straight to LDS, through rings of three places, and the
 // two wavefronts of a SIMD take turns -- one feeds the matrix cores from registers while the other fetches its next fragments and asks for
 // what comes two or three blocks later (ring_step()).  Where all wavefronts do all of it side by side, as the smaller tiles do, each load
 // holds its wavefront up for some 50 cycles (the address path takes 16 for a 1 KB request) and the other one is no more likely to have
@@ -24,7 +24,8 @@
 // What bounds it now is the power limit: without the epilogue the same pass takes 4 % fewer cycles and as long, at a clock of
 // 1.79 instead of 1.87 GHz, and without loads of the bank it takes 12 % less, at 1.95.  Densest pass of 1M x 1536, 1024 queries 2470 ->
 // 2230 us (1390 TFLOP/s, on other cards up to 1450; the vendor's product of 16384 x 16384 x 8192 1540), 1M x 1024, 256 queries 460 -> 430.
-// One rotation of the k-loop for all workgroups of an XCD when several share its bank tiles: 2150 -> 2130 us.
+// One rotation of the k-loop for all workgroups of an XCD when several share its bank tiles: 2150 -> 2130 us.  128 queries (whole calls): 1.1M x 4096 fp16
+// 1592 -> 1546 us, 1M x 1024 bf16 391 -> 385, 200,000 x 768 134 -> 129, 1M x 64 100 -> 88, 300,007 x 384 92.0, 92.0.
 // Instructions: 16x16x32 move half as many accumulator bytes per product as 32x32x16 ones (256 x 256 x 64 from LDS alone 1.15 and 1.35 us).
 //
 // fp32 stores: each value is split on the fly into bf16 hi + bf16 lo and the product is
@@ -145,14 +146,15 @@ constexpr int STAGE_BANK_BYTES = TILE_ROWS * 128;
 constexpr int SCAN_LDS = 160 * 1024;    // of a compute unit
 constexpr int SCAN_LIST_TILES = 64;     // a workgroup's list is written out after as many tiles at the latest
 
-// 16-bit stores with 256 queries to a tile: operands pass through rings in LDS (see ring_step()).
-template <int DT, int QT> constexpr bool scan_mfma_ring() { return DT != 0 && QT == 256; }
+// 16-bit stores with 128 or 256 queries to a tile: operands pass through rings in LDS (see ring_step()).
+template <int DT, int QT> constexpr bool scan_mfma_ring() { return DT != 0 && QT >= 128; }
+constexpr int RING_PLACES = 3;          // (four of bank blocks with 128 queries: 1.1M x 4096 fp16 1546 -> 1557 us a call, 1M x 1024 385 -> 402)
 // LDS: the operand stages -- two of a bank block and a query block, or, as rings, three of a bank block and three of half a query
 // block --; per-query threshold, inverse norm, survivor count and list base; tiles of the list; counters; the workgroup's survivor list (8 bytes an
 // entry), for which the rings leave less room.
 // (masked variant: the per-query type masks and excluded groups in addition; EXACT: cuts and inverse norms)
 template <int DT, int QT> constexpr int scan_mfma_stage_bytes() {
-    return scan_mfma_ring<DT, QT>() ? 3 * (STAGE_BANK_BYTES + QT * 64) : 2 * (STAGE_BANK_BYTES + QT * 128);
+    return scan_mfma_ring<DT, QT>() ? RING_PLACES * (STAGE_BANK_BYTES + QT * 64) : 2 * (STAGE_BANK_BYTES + QT * 128);
 }
 template <int DT, int QT, bool MASKED = false, bool EXACT = false> constexpr int scan_mfma_word_bytes() { return QT * 16 + SCAN_LIST_TILES * 4 + 16 + (MASKED ? QT * 8 : EXACT ? QT * 16 : 0); }
 // survivor entries a workgroup can stage
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     constexpr int BCH = 2048 / NT;                     // 16-byte bank chunks per lane per stage
     constexpr int QCH = QT * 8 / NT;                   // 16-byte query chunks per lane per stage
     constexpr bool RING = scan_mfma_ring<DT, QT>();
-    constexpr int QUERY_AT = (RING ? 3 : 2) * STAGE_BANK_BYTES;        // the stages of queries lie behind those of bank blocks
+    constexpr int QUERY_AT = (RING ? RING_PLACES : 2) * STAGE_BANK_BYTES;        // the stages of queries lie behind those of bank blocks
     constexpr int LIST_CAP = scan_mfma_list_cap<DT, QT, MASKED, EXACT>();
     // Query blocks go straight to LDS in the largest variant, whose registers are all taken; the few pieces of a smaller query tile
     // pass through registers, which look a step further ahead (whole masked call, 32 queries, 300,007 x 384 fp16: 94.8 us, 96.9
@@ -546,13 +548,13 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         }
     };
 
-    // RING: one step (a k-block) of the 16-bit path with 256 queries to a tile, in two halves of 32 k.  A half is two spells: fetch (12
-    // fragments from LDS to registers, four loads of 1 KB from memory to LDS) and multiply (32 matrix instructions).  A barrier ends
+    // RING: one step (a k-block) of the 16-bit path with 128 or 256 queries to a tile, in two halves of 32 k.  A half is two spells: fetch (8 or
+    // 12 fragments from LDS to registers, two or four loads of 1 KB from memory to LDS) and multiply (16 or 32 matrix instructions).  A barrier ends
     // every spell, and the last four wavefronts -- the second one of every SIMD -- are a spell behind the first four, so on each SIMD one
     // multiplies while the other fetches.  The first four load queries, half a block a time, the others bank blocks, so that neither waits
     // for the other's loads (a wavefront's loads are waited for in order).
     //   queries: in the fetch of half i, half i + 2 goes to the place of half i - 1, which the second four have read a spell ago;
-    //            it is waited for before the barrier that ends the multiplication of half i + 1 (one load batch comes after it: vmcnt(4))
+    //            it is waited for before the barrier that ends the multiplication of half i + 1 (one batch of QL loads comes after it)
     //   bank:    in the fetches of the two halves of block m, block m + 2 goes to the place of block m - 1; it is waited for
     //            at the end of the fetch of the second half of block m + 1 (eight loads come after it), before the barrier behind which
     //            the first four read it
@@ -576,6 +578,8 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         src += 4096;
         dst += 4096;
     };
+    constexpr int QL = QT / 64;                                // loads of half a query block, of one of the four
+    constexpr auto wait_vm = [](int n) { return 0x0f70 | (n & 15) | (n >> 4) << 14; };       // s_waitcnt vmcnt(n)
     auto ring_step = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -590,17 +594,17 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             if (second()) {
                 if (h == 0) {
                     src = reinterpret_cast<const char*>(gnext_b()) + piece0;
-                    dst = lds_at + (at_bank == 0 ? 2 * STAGE_BANK_BYTES : at_bank - STAGE_BANK_BYTES) + wave_u * 1024;
+                    dst = lds_at + (at_bank == 0 ? (RING_PLACES - 1) * STAGE_BANK_BYTES : at_bank - STAGE_BANK_BYTES) + wave_u * 1024;
                 }
 #pragma unroll
                 for (int p = 0; p < 4; ++p) ring_load(true);
-                if (h == 1) __builtin_amdgcn_s_waitcnt(0x0f78);           // vmcnt(8)
+                if (h == 1) __builtin_amdgcn_s_waitcnt(wait_vm(8 * (RING_PLACES - 2)));
             } else {
                 if (h == 0) src = reinterpret_cast<const char*>(gnext_q()) + piece0;
-                else src += qrow_elems * 2 - 4 * 4096;
-                dst = lds_at + QUERY_AT + (at_query == 0 ? 2 * QT * 64 : at_query - QT * 64) + wave_u * 1024;
+                else src += qrow_elems * 2 - QL * 4096;
+                dst = lds_at + QUERY_AT + (at_query == 0 ? (RING_PLACES - 1) * QT * 64 : at_query - QT * 64) + wave_u * 1024;
 #pragma unroll
-                for (int p = 0; p < 4; ++p) ring_load(false);
+                for (int p = 0; p < QL; ++p) ring_load(false);
             }
             __syncthreads();
             __builtin_amdgcn_sched_barrier(0);
@@ -610,13 +614,13 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 for (int b = 0; b < MR; ++b) mfma16_in_place<DT>(acc[a][b], af[a], bfr[0][b]);
             __builtin_amdgcn_sched_barrier(0);
             if (!second()) {
-                __builtin_amdgcn_s_waitcnt(0x0f74);                       // vmcnt(4)
+                __builtin_amdgcn_s_waitcnt(wait_vm(QL));
                 __syncthreads();
             }
             __builtin_amdgcn_sched_barrier(0);
-            at_query = at_query == 2 * QT * 64 ? 0u : at_query + QT * 64;
+            at_query = at_query == (RING_PLACES - 1) * QT * 64 ? 0u : at_query + QT * 64;
         }
-        at_bank = at_bank == 2 * STAGE_BANK_BYTES ? 0u : at_bank + STAGE_BANK_BYTES;
+        at_bank = at_bank == (RING_PLACES - 1) * STAGE_BANK_BYTES ? 0u : at_bank + STAGE_BANK_BYTES;
     };
 
     // Key of a survivor from its accumulator value (score - threshold * norm, see tile_init): the
@@ -1079,22 +1083,22 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         }
     };
     if constexpr (RING) {
-        static_assert(MQ == 8 && MR == 4 && NT == 512, "the slots' work");
+        static_assert(NT == 512, "four wavefronts for the queries, four for the bank");
         if (second()) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
+            for (int i = 0; i < RING_PLACES - 1; ++i) {
                 src = reinterpret_cast<const char*>(gnext_b()) + piece0;
                 dst = lds_at + i * STAGE_BANK_BYTES + wave_u * 1024;
                 for (int p = 0; p < 8; ++p) ring_load(true);
             }
-            __builtin_amdgcn_s_waitcnt(0x0f78);
+            __builtin_amdgcn_s_waitcnt(wait_vm(8 * (RING_PLACES - 2)));
         } else {
             src = reinterpret_cast<const char*>(gnext_q()) + piece0;
             dst = lds_at + QUERY_AT + wave_u * 1024;
-            for (int p = 0; p < 4; ++p) ring_load(false);
-            src += qrow_elems * 2 - 4 * 4096;
-            for (int p = 0; p < 4; ++p) ring_load(false);
-            __builtin_amdgcn_s_waitcnt(0x0f74);
+            for (int p = 0; p < QL; ++p) ring_load(false);
+            src += qrow_elems * 2 - QL * 4096;
+            for (int p = 0; p < QL; ++p) ring_load(false);
+            __builtin_amdgcn_s_waitcnt(wait_vm(QL));
         }
         __syncthreads();
         load_invnorm(0);
