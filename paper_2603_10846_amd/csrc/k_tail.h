@@ -5,7 +5,7 @@
 // result, and at the same time), re-scores its share of the candidates, and the last one to finish orders the
 // pool.  Nothing waits for another workgroup.  Against separate launches: one query
 // over 4096 x 768 fp32 rows with a pool of 32 took 6.1 + 5.1 + 5.2 us in three launches, 10.7 in one.
-// What bounds it: about 4 us of barriers and LDS round trips in the selection, 1 us to lay out the candidates, 2 to 5 us in the
+// What bounds it: about 4 us of barriers and LDS round trips in the selection, which lays out the candidates too, 2 to 5 us in the
 // orderings and z-scores; in between the rows, which come at 6.8 TB/s when there are many (128 queries, a pool of 256 of 8 KB: 46 us).
 //
 // Re-scoring: 16 to 64 lanes per candidate row accumulate in fp64, so that the value filter, which divides by the
@@ -71,7 +71,7 @@ __device__ __forceinline__ void group_sum2(double (*red)[16], int wave, int lane
 // inputs were written before a barrier, and emit must not write them.
 template <bool BIG, class Emit>
 __device__ __forceinline__ void rank_entries(const double* val, const int32_t* ids, int n, uint32_t* order, SelectLds& sh,
-                                             double (*red)[16], Emit emit) {
+                                             Emit emit) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     if constexpr (!BIG) {
         // four lanes share an entry, or as many as there are: each counts over every fourth (8th, 16th) other entry
@@ -95,23 +95,28 @@ __device__ __forceinline__ void rank_entries(const double* val, const int32_t* i
         else count(std::integral_constant<int, 4>{});
     } else {
         constexpr int U = (BIG_K1_MAX + 256 + TAIL_T - 1) / TAIL_T;   // entries per lane
-        // range of the finite values
-        double hi = -INFINITY, lo = INFINITY;
+        // range of the finite values, rounded to fp32 (a value may lie half a step outside it)
+        uint32_t most = 0u, least = 0u;                              // complement of the smallest
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = tid + u * TAIL_T;
-            const double v = i < n ? val[i] : -INFINITY;
-            hi = fmax(hi, v);
-            if (v > -INFINITY) lo = fmin(lo, v);
+            const float v = i < n ? (float)val[i] : -INFINITY;
+            const uint32_t o = f2ord(v);
+            most = o > most ? o : most;
+            least = v > -INFINITY && ~o > least ? ~o : least;
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) { hi = fmax(hi, __shfl_xor(hi, o, 64)); lo = fmin(lo, __shfl_xor(lo, o, 64)); }
-        if (lane == 0) { red[0][wave] = hi; red[1][wave] = lo; }
+        most = wave_max_u32(most);
+        least = wave_max_u32(least);
+        if (lane == 63) { sh.most[wave] = most; sh.least[wave] = least; }
         for (int i = tid; i < SEL_BINS; i += TAIL_T) sh.hist[i] = 0;
         if (tid == 0) sh.count = 0;
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < 16; ++w) { hi = fmax(hi, red[0][w]); lo = fmin(lo, red[1][w]); }
+        for (int w = 0; w < 16; ++w) {
+            most = sh.most[w] > most ? sh.most[w] : most;
+            least = sh.least[w] > least ? sh.least[w] : least;
+        }
+        const double hi = ord2f(most), lo = ord2f(~least);
         const double scale = (double)SEL_BINS / (hi - lo);
         uint32_t bin[U], pos[U];
 #pragma unroll
@@ -119,7 +124,7 @@ __device__ __forceinline__ void rank_entries(const double* val, const int32_t* i
             const int i = tid + u * TAIL_T;
             if (i < n) {
                 const double x = (hi - val[i]) * scale;               // grows as the value falls; NaN (no range) goes to the last bucket
-                bin[u] = x < (double)(SEL_BINS - 1) ? (uint32_t)(int)x : (uint32_t)(SEL_BINS - 1);
+                bin[u] = x < 0.0 ? 0u : x < (double)(SEL_BINS - 1) ? (uint32_t)(int)x : (uint32_t)(SEL_BINS - 1);
                 pos[u] = atomicAdd(&sh.hist[bin[u]], 1u);
             }
         }
@@ -215,9 +220,9 @@ __device__ __forceinline__ TailArgsPtr tail_args_from_here() {
     return p;
 }
 
-// K: keys of a query's list per lane (8 or 16).  With 16 there are not enough registers for them: 16 to 18 of a lane's are kept in
-// scratch memory (60 to 68 bytes), none with 8.  64 queries, a pool of 960 of 2 KB, four workgroups to a query: 61 us, 55 with 8 keys, which
-// take twice the passes.
+// K: keys of a query's list per lane (8 or 16).  With 16 a lane keeps a few registers in scratch memory (16 to 32 bytes), none with 8.
+// 64 queries, a pool of 960 of 2 KB, four workgroups to a query: whole call 179.5 us (193.9 with 60 to 68 bytes, slots filled one by one and
+// the buckets' range found with shuffles of fp64 values: 61 us of it here).
 template <int DT, bool BIG, int K = SURV_CAP / TAIL_T>
 __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     constexpr int CAP = K * TAIL_T;
@@ -394,7 +399,7 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     unsigned char* explored = late->eg.explored;
     // ---- the pool: the k1e best by (similarity desc, id asc) -> (v1, i1, q1) ----
     const int k1e = kk < k1 ? kk : k1;
-    rank_entries<BIG>(v0, i0, kk, order, sh, red, [&](int i, int r) __attribute__((always_inline)) {
+    rank_entries<BIG>(v0, i0, kk, order, sh, [&](int i, int r) __attribute__((always_inline)) {
         if (r < k1e) { v1[r] = v0[i]; i1[r] = i0[i]; q1[r] = q0[i]; }
     });
     __syncthreads();
@@ -472,7 +477,7 @@ __global__ __launch_bounds__(TAIL_T) void k_tail(TailArgs A) {
     // ---- the k2 best by (score desc, id asc) ----
     const int k2e = k1e < k2 ? k1e : k2;
     const bool greedy = threshold == 0 && explored == nullptr;
-    rank_entries<BIG>(v0, i0, k1e, order, sh, red, [&](int i, int r) __attribute__((always_inline)) {
+    rank_entries<BIG>(v0, i0, k1e, order, sh, [&](int i, int r) __attribute__((always_inline)) {
         if (greedy) {
             if (r < k2e) { out_ids[r] = i0[i]; out_scores[r] = (float)v0[i]; }
         } else {
