@@ -236,6 +236,7 @@ int mem_read_q(evomem_t* h, int stage, int64_t first, int64_t n, float* dst_dev,
  * mu and sigma are the running mean and population deviation of all raw rewards of this stage seen
  * BEFORE sample j (in earlier calls and earlier in this batch; before the first sample mu = 0 and
  * sigma = 0).  The statistics are kept per stage in the workspace in fp64.
+ * Calls on a handle must be ordered (see above); two that overlap both end, with rewards and statistics of no meaning.
  * rewards_out_dev: float[M].  M = 0 is a no-op.
  * Errors: MEM_EINVAL (null pointers, stage, sigma_min <= 0 with normalise, clip < 0 or NaN), MEM_EHIP.
  */

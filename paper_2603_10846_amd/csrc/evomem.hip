@@ -97,6 +97,7 @@ struct evomem {
     uint32_t* tags = nullptr;   // per-entry tags of typed / masked retrieval (caller's buffer), or null
     const uint32_t* last_flags = nullptr;   // per-query status words of the latest retrieve (in the scratch it used)
     int last_B = 0;
+    uint32_t reward_calls = 0;  // number of the latest batch of rewards in one chained launch (after 2^32 - 1 of them: two launches)
     std::vector<hipEvent_t> ev;
     std::vector<int64_t> prof_rows;
 };
@@ -258,6 +259,14 @@ int mem_profile_read(evomem_t* h, int capacity, int* n_out, float* ms_out, int64
     return MEM_OK;
 }
 
+// Is the stream being recorded into a graph?  (Yes too where it can't be told: the default stream while another one records.)
+static bool recording(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // the normaliser's statistics live in the zero-initialised counter block: double[2 stages][3] at byte 64
 static double* reward_state(evomem_t* h, int stage) { return reinterpret_cast<double*>(h->ws + h->w.counters + 64) + 3 * stage; }
 
@@ -268,10 +277,12 @@ int mem_shape_rewards(evomem_t* h, int stage, const unsigned char* feasible_dev,
     if (M == 0) return MEM_OK;
     if (!feasible_dev || !rewards_out_dev || (stage == 1 && (!latency_dev || !best_latency_dev))) return MEM_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    // (the chain's two words lie in the zero-initialised counter block, behind the statistics)
+    // (the chain's two words lie in the zero-initialised counter block, behind the statistics; its calls are numbered from 1)
     RewardArgs A{feasible_dev, latency_dev, best_latency_dev, M, (double)sigma_min, (double)clip, reward_state(h, stage),
-                 reinterpret_cast<double*>(h->ws + h->w.surv), reinterpret_cast<uint64_t*>(h->ws + h->w.counters + 128), rewards_out_dev, stage, normalise};
-    if (normalise && M > REWARD_ONE && M <= (int64_t)REWARD_CHAIN * REWARD_T) {
+                 reinterpret_cast<double*>(h->ws + h->w.surv), reinterpret_cast<uint64_t*>(h->ws + h->w.counters + 128), h->reward_calls + 1,
+                 rewards_out_dev, stage, normalise};
+    if (normalise && M > REWARD_ONE && M <= (int64_t)REWARD_CHAIN * REWARD_T && A.call != 0 && !recording(st)) {
+        h->reward_calls = A.call;
         hipLaunchKernelGGL(k_reward_chain, dim3((unsigned)((M + REWARD_T - 1) / REWARD_T)), dim3(REWARD_T), 0, st, A);
         LAUNCHCHK();
         return MEM_OK;

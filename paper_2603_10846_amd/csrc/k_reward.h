@@ -46,7 +46,8 @@ struct RewardArgs {
     double sigma_min, clip;
     double* state;            // count, sum, sum of squares
     double* sums;             // the statistics before the batch (two launches), then two sums per block
-    uint64_t* chain;          // one launch: which blocks have left their sums, how many have read the others'; zero between calls
+    uint64_t* chain;          // one launch: which blocks have left their sums, 32 to a word: the latest call's number << 32 | a bit each
+    uint32_t call;            // one launch: its number, of this handle's; larger than any before, never 0
     float* out;
     int stage, normalise;
 };
@@ -104,8 +105,10 @@ __global__ __launch_bounds__(REWARD_ONE) void k_shape_rewards(RewardArgs A) {
 }
 
 // Up to 64 blocks in one launch.  A block waits for those before it only.  All of the launch's blocks fit on the device many times
-// over, so each of them comes to run whatever the others do, and the wait ends; were there room for only a few they would come
-// in order, and the first of them waits for none.
+// over, so each of them comes to run whatever the others do, and the wait ends.
+// No word is cleared, so no wait depends on when: a call raises the words to its own number, which drops the bits of earlier ones, and a later
+// number says as much as the bits do.  Were two calls on a handle to overlap, each might take the other's sums, but both would end and leave nothing
+// that a later call trips over.  The number comes from the host; a replayed graph would bring an old one, so recorded calls are two launches.
 // What blocks hand to each other are their sums, stored and loaded as device-scope atomics, which pass by the caches that differ between
 // XCDs; a block's stores have been acknowledged before it says so.
 __global__ __launch_bounds__(REWARD_T) void k_reward_chain(RewardArgs A) {
@@ -113,6 +116,7 @@ __global__ __launch_bounds__(REWARD_T) void k_reward_chain(RewardArgs A) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, block = (int)blockIdx.x;
     const int64_t j = (int64_t)block * REWARD_T + tid;
     const bool live = j < A.M;
+    if (tid == 0) (void)__hip_atomic_fetch_max(A.chain + (block >> 5), (uint64_t)A.call << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const double n_old = A.state[0], s_old = A.state[1], q_old = A.state[2];      // (replaced by the last block once all have said so)
     const double raw = live ? raw_reward(A, j) : 0.0;
     const double s = wave_total_d(raw), q = wave_total_d(raw * raw);
@@ -124,9 +128,19 @@ __global__ __launch_bounds__(REWARD_T) void k_reward_chain(RewardArgs A) {
         if (lane < 2)
             __hip_atomic_store(mine + 2 * block + lane, (total[0][lane] + total[1][lane]) + (total[2][lane] + total[3][lane]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (lane == 0) __hip_atomic_fetch_or(A.chain, 1ull << block, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint64_t before = (1ull << block) - 1ull;
-        while ((__hip_atomic_load(A.chain, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & before) != before) __builtin_amdgcn_s_sleep(1);
+        if (lane == 0) (void)__hip_atomic_fetch_or(A.chain + (block >> 5), 1ull << (block & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // lane 0 watches the word of blocks 0 to 31, lane 1 that of the others
+        const uint64_t before = ((1ull << block) - 1ull) >> (lane == 1 ? 32 : 0);
+        const uint32_t need = lane < 2 ? (uint32_t)before : 0u;
+        bool there = need == 0;
+        for (;;) {
+            if (!there) {
+                const uint64_t w = __hip_atomic_load(A.chain + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                there = (uint32_t)(w >> 32) > A.call || ((uint32_t)(w >> 32) == A.call && ((uint32_t)w & need) == need);
+            }
+            if (__builtin_amdgcn_ballot_w64(!there) == 0) break;     // uniform
+            __builtin_amdgcn_s_sleep(1);
+        }
         asm volatile("" ::: "memory");
         double es = 0.0, eq = 0.0;
         if (lane < block) {
@@ -135,15 +149,7 @@ __global__ __launch_bounds__(REWARD_T) void k_reward_chain(RewardArgs A) {
         }
         es = wave_total_d(es);
         eq = wave_total_d(eq);
-        if (lane == 0) {
-            earlier[0] = es;
-            earlier[1] = eq;
-            // the last block to get here leaves the words as it would find them
-            if (__hip_atomic_fetch_add(A.chain + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint64_t)gridDim.x - 1u) {
-                __hip_atomic_store(A.chain, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(A.chain + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
+        if (lane == 0) { earlier[0] = es; earlier[1] = eq; }
     }
     double bs, bq, as, aq;
     block_prefix2<REWARD_T / 64>(part, wave, lane, raw, raw * raw, bs, bq, as, aq);       // (has a barrier)
