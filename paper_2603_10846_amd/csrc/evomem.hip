@@ -390,11 +390,11 @@ Plan plan_levels(int64_t N, int k1, int cap) {
     return p;
 }
 
-template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true, bool EXACT = false>
+template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true, bool EXACT = false, bool BUSY = false>
 int launch_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Level& L, int k1, const Mask& mask, int B) {
     constexpr int QT = 16 * MQ * WQ;
     constexpr int lds = scan_mfma_lds_bytes<DT, QT, MASKED, EXACT>();
-    auto kern = k_scan_mfma<DT, MQ, WQ, MR, WR, MASKED, STREAM, EXACT>;
+    auto kern = k_scan_mfma<DT, MQ, WQ, MR, WR, MASKED, STREAM, EXACT, BUSY>;
     static int resident[MAX_DEVICES] = {};          // workgroups of this kernel the whole device holds at once
     if (!resident[h->device]) {
         HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
@@ -420,6 +420,9 @@ int launch_mfma(evomem* h, const Scratch& sc, hipStream_t st, int Bp, const Leve
     int flush_every = (tiles_per_wg + n_flush - 1) / n_flush;
     if (flush_every < 1) flush_every = 1;
     if (flush_every > SCAN_LIST_TILES) flush_every = SCAN_LIST_TILES;
+    if constexpr (scan_mfma_busy<DT, QT, MASKED>() && !BUSY) {        // (an expected tile fills more than half of the list, or there is only one)
+        if (flush_every == 1 && L.rho != 0) return launch_mfma<DT, MQ, WQ, MR, WR, MASKED, STREAM, EXACT, true>(h, sc, st, Bp, L, k1, mask, B);
+    }
     unsigned char* ws = sc.base;
     hipLaunchKernelGGL(kern, grid, block, lds, st, (const void*)h->store, (const float*)h->invnorm,
                        (const uint16_t*)(ws + sc.w.qop), (const float*)(ws + sc.w.invq), (const float*)(ws + sc.w.thr),

@@ -164,6 +164,14 @@ template <int DT, int QT, bool MASKED = false, bool EXACT = false> constexpr int
 template <int DT, int QT, bool MASKED = false, bool EXACT = false> constexpr int scan_mfma_lds_bytes() {
     return scan_mfma_stage_bytes<DT, QT>() + scan_mfma_word_bytes<DT, QT, MASKED, EXACT>() + scan_mfma_list_cap<DT, QT, MASKED, EXACT>() * 8;
 }
+// ... and with BUSY, where the list is written out after every tile.  A list that runs full costs a device-wide atomic per surplus survivor, so many
+// survivors to a tile (wide pools, small banks, masks) need room, and what the rings leave is less than that of the smaller tiles.  The place of
+// the tile's last bank block is free from the end of the k-loop to the next tile's first loads.  Whole calls, us, lists of 2048 entries / what the
+// rings leave / the place: 65,536 x 256 bf16, 256 queries, pool of 256 84, 86, 71; 100,000 x 256 masked, 1024 queries, pool of 128 238, 254, 221.
+// (128 queries to a tile: the rings leave more than that, 4830 entries.)
+constexpr int BUSY_LIST = STAGE_BANK_BYTES / 8;
+template <int DT, int QT, bool MASKED> constexpr bool scan_mfma_busy() { return scan_mfma_ring<DT, QT>() && scan_mfma_list_cap<DT, QT, MASKED>() < BUSY_LIST; }
+static_assert(BUSY_LIST >= 2048 && scan_mfma_list_cap<1, 128, true>() >= BUSY_LIST, "rings leave a busy tile's list no less room than two stages did");
 static_assert(scan_mfma_lds_bytes<1, 256, true>() <= SCAN_LDS && scan_mfma_lds_bytes<0, 256, true>() <= SCAN_LDS, "one workgroup to a compute unit");
 
 // DT: 0 fp32 store (bf16 split), 1 bf16, 2 f16.  Wave grid WQ x WR, each wave MQ x MR blocks of 16x16.
@@ -173,7 +181,9 @@ static_assert(scan_mfma_lds_bytes<1, 256, true>() <= SCAN_LDS && scan_mfma_lds_b
 // STREAM: bank rows are loaded with the non-temporal hint (layout.h).  Right whenever a bank tile is read
 // by one workgroup only; with several query tiles per bank tile (more than 256 queries) the later readers
 // are meant to find the tile in L2, and the hint costs 2 % there (measured: 1397 -> 1366 TFLOP/s at 1024 queries, the sparser passes 10 %).
-template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true, bool EXACT = false>
+// BUSY: the list is written out after every tile and lies in a ring's free place.  (A variant of its own: chosen at run time, the kernel for seldom
+// written lists took 2 % longer, 2M x 1536, 1024 queries 4960 -> 5100 us, though its k-loop was the same.)
+template <int DT, int MQ, int WQ, int MR, int WR, bool MASKED, bool STREAM = true, bool EXACT = false, bool BUSY = false>
 __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __restrict__ store_, const float* __restrict__ invnorm,
                                                    const uint16_t* __restrict__ qop, const float* __restrict__ invq,
                                                    const float* __restrict__ thr, uint32_t* __restrict__ cnt,
@@ -239,6 +249,8 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     // An entry: accumulator value << 32 | refused << 24 | which of the tiles since the list was empty << 16 | row of the tile << 8 | register of the
     // group, lane group << 4, group of query blocks << 6 (EXACT: queries << 32 | id).
     uint64_t* list_s = reinterpret_cast<uint64_t*>(smem + LIST_AT);
+    static_assert(!BUSY || RING, "a place of a ring");
+    constexpr uint32_t LIST_ROOM = BUSY ? BUSY_LIST : LIST_CAP;
     constexpr uint32_t REFUSED = 1u << 24;
     auto entry_query = [&](uint32_t m) __attribute__((always_inline)) {
         return (int)(((m >> 6 & 3u) * GB + (m >> 2) % GB) * 16 + (m >> 4 & 3u) * 4 + (m & 3u));
@@ -637,10 +649,11 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
     // Write the workgroup's staged survivors to the per-query lists (all lanes call it together):
     // count the entries of each query with LDS atomics, reserve that many slots with one device-wide
     // integer atomic per query that has any, copy.
-    auto flush = [&]() __attribute__((always_inline)) {
-        const uint32_t total = *total_s < (uint32_t)LIST_CAP ? *total_s : (uint32_t)LIST_CAP;
+    auto flush = [&](uint32_t list_at) __attribute__((always_inline)) {
+        const uint64_t* list = reinterpret_cast<const uint64_t*>(smem + list_at);
+        const uint32_t total = *total_s < LIST_ROOM ? *total_s : LIST_ROOM;
         for (uint32_t e = tid; e < total; e += NT) {
-            const uint32_t m = (uint32_t)list_s[e];
+            const uint32_t m = (uint32_t)list[e];
             if (!(MASKED && (m & REFUSED))) atomicAdd(cnt_s + entry_query(m), 1u);
         }
         __syncthreads();
@@ -658,7 +671,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t e = e0 + k * NT;
-                ent[k] = list_s[e < total ? e : e0];
+                ent[k] = list[e < total ? e : e0];
                 id[k] = (int32_t)(tile_s[(uint32_t)ent[k] >> 16 & 0xffu] * TILE_ROWS + entry_row((uint32_t)ent[k]));
                 inv[k] = invnorm[id[k]];
             }
@@ -839,7 +852,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
 
     // ---- per-tile epilogue (all lanes of the workgroup call it together) ----
     int since = 0;                                             // tiles whose survivors the list holds
-    auto epilogue = [&](int ti) __attribute__((always_inline)) {
+    auto epilogue = [&](int ti, uint32_t list_at) __attribute__((always_inline)) {
         const int j = first_j + ti * stride_j;
         const int64_t t = level_tile(L, j);
         if (L.rho == 0) {
@@ -1004,8 +1017,8 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                     const int ql = (wq_u * MQ + g * GB + ((r >> 2) & 3) % GB) * 16 + 4 * (ln >> 4) + (r & 3);
                     bool ok = true;
                     if constexpr (MASKED) ok = eligible(mask.tags[id], allow_s[ql], exclude_s[ql]);
-                    if (slot < (uint32_t)LIST_CAP) {
-                        list_s[slot] = (uint64_t)__float_as_uint(av) << 32 | where0 + (uint32_t)(bg * BB * 16 << 8 | g << 6 | r) | (ok ? 0u : REFUSED);   // the slot was reserved before the check
+                    if (slot < LIST_ROOM) {
+                        *reinterpret_cast<uint64_t*>(smem + list_at + slot * 8u) = (uint64_t)__float_as_uint(av) << 32 | where0 + (uint32_t)(bg * BB * 16 << 8 | g << 6 | r) | (ok ? 0u : REFUSED);   // the slot was reserved before the check
                     } else if (ok) {   // list full (a very loose threshold): fall back to the direct path
                         uint32_t pos = atomicAdd(slot_counter(cnt, q0 + ql), 1u);
                         if (pos < (uint32_t)L.cap) surv[(int64_t)(q0 + ql) * L.cap + pos] = finish_key(av, ql, id, invnorm[id]);
@@ -1016,10 +1029,10 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 // a group stage it; lanes with more are left to the loop below, and so is everything when the
                 // wavefront's reservation does not fit the list (then no lane needs a room check here).
                 uint32_t rest = 0;
-                const bool fits = wave_base + sum <= (uint32_t)LIST_CAP;                       // uniform
+                const bool fits = wave_base + sum <= LIST_ROOM;                                // uniform
                 // (a group of two row blocks: the rows past the bank's end must not be a group's maximum)
                 const bool whole = (t + 1) * TILE_ROWS <= N;                                   // uniform
-                unsigned char* pk = smem + LIST_AT + slot * 8u;                                // the lane's next list entry
+                unsigned char* pk = smem + list_at + slot * 8u;                                // the lane's next list entry
 #pragma unroll
                 for (int bg = 0; bg < RGROUPS; ++bg)
 #pragma unroll
@@ -1041,7 +1054,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                         msk[g * RGROUPS + bg] = left;
                         rest |= left;
                     }
-                slot = (uint32_t)(pk - (smem + LIST_AT)) >> 3;
+                slot = ((uint32_t)(pk - smem) - list_at) >> 3;
                 if (__builtin_amdgcn_ballot_w64(rest != 0) != 0) {
 #pragma unroll
                     for (int bg = 0; bg < RGROUPS; ++bg)
@@ -1064,9 +1077,9 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
                 __syncthreads();
                 static_assert(LIST_CAP / 4 + TILE_ROWS <= LIST_CAP, "room for the rows of another tile");
                 if (*total_s > (uint32_t)LIST_CAP / 4 || ti == my_tiles - 1) flush_exact();      // uniform
-            } else if (since == flush_every - 1 || ti == my_tiles - 1) {          // uniform
+            } else if (BUSY || since == flush_every - 1 || ti == my_tiles - 1) {  // uniform
                 __syncthreads();
-                flush();
+                flush(list_at);
                 since = 0;
             } else {
                 ++since;
@@ -1109,7 +1122,9 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             do ring_step(); while (--st > 0);
             load_invnorm(ti + 1);
             mfma_settle();
-            epilogue(ti);
+            // All have read the tile's last bank block: the second four before the barrier that ended their last fetch.  What they load to its place
+            // next they ask for behind the next tile's first barrier, which nobody reaches before it has left the epilogue.
+            epilogue(ti, !BUSY ? LIST_AT : at_bank == 0 ? (uint32_t)((RING_PLACES - 1) * STAGE_BANK_BYTES) : at_bank - (uint32_t)STAGE_BANK_BYTES);
             tile_prepare();
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // blocks past the end still land in this workgroup's LDS
@@ -1153,7 +1168,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
         phase(0, gbB, gbA, gqB, std::true_type{});
         phase(1, gbA, gbB, gqA, std::false_type{});
         mfma_settle();
-        epilogue(ti);
+        epilogue(ti, LIST_AT);
         tile_prepare();
     }
     if constexpr (Q_DIRECT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // query blocks past the end still land in this workgroup's LDS
