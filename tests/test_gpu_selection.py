@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from tests import parity
-from tests.test_gpu_parity import DT, _make_bank, _unit
+from tests.test_gpu_parity import DT, _dev, _make_bank, _unit
 
 pytestmark = pytest.mark.gpu
 
@@ -44,4 +44,23 @@ def test_lists_of_any_spread(orc, dtype, N, nq, k1, kind):
     if kind in ("equal", "steps"):
         assert stats["boundary_swaps"] == 0
     assert not bank.retrieve_flags(nq).cpu().numpy().any() and bank.counters() == (0, 0)
+    bank.close()
+
+
+@pytest.mark.parametrize("kind", ["outlier", "steps", "equal"])
+@pytest.mark.parametrize("dtype,N,nq,k1", [("bf16", 20000, 3, 200), ("f32", 9000, 2, 1), ("f16", 17000, 9, 64)])
+def test_exhaustive_lists_of_any_spread(orc, dtype, N, nq, k1, kind):
+    """The same in the exhaustive call, whose selections cut a crowded list back to the pool before any of its places are given out."""
+    rng = np.random.default_rng([67, N, k1])
+    v = _unit(rng, 1, 64)
+    rows = _rows(kind, rng, N, 64, v)
+    q = np.concatenate([v, _unit(rng, nq, 64)])[:nq]
+    qtab = rng.uniform(-1, 1, (2, N)).astype(np.float32)
+    print(f"exhaustive selection {kind} {dtype} N={N} B={nq} k1={k1}", flush=True)
+    bank = _make_bank(dtype, rows, qtab, max_B=nq, max_k1=k1)
+    ids, scores, cid, csim = bank.retrieve_exact(_dev(q), 0, k1, min(8, k1), 0.5, want_candidates=True)
+    got = {"ids": ids.cpu().numpy(), "scores": scores.cpu().numpy(), "cand_ids": cid.cpu().numpy(), "cand_sims": csim.cpu().numpy()}
+    stats = parity.check_retrieve(orc, orc.round_to_store(rows, DT[dtype]), orc.round_to_store(q, DT[dtype]), qtab[0], k1, min(8, k1), 0.5, got)
+    if kind in ("equal", "steps"):
+        assert stats["boundary_swaps"] == 0
     bank.close()
