@@ -675,7 +675,11 @@ static int retrieve_impl(evomem_t* h, const float* queries_dev, int B, int stage
     // masked 92.6, 92.7; 64, 65,536 x 1024 fp32 83.5, 84.0; 64, 262,144 x 1024 bf16 235.6, 238.1.
     const bool fused = plan.n > 0 && !exhaustive && prep.aligned && (gemv || (B <= 16 && direct(plan.lv[0])));
     if (!fused) {
-        with_store_type(h->dtype, [&](auto dt) { hipLaunchKernelGGL(k_prep_queries<decltype(dt)::value>, dim3(Bp), dim3(256), 0, st, prep); });
+        with_store_type(h->dtype, [&](auto dt) {
+            constexpr int DT = decltype(dt)::value;
+            if (!gemv && prep_by_fragments(DT == 0, Bp, h->nkb)) hipLaunchKernelGGL(k_prep_fragments<DT>, dim3((unsigned)prep_fragment_workgroups(Bp, h->nkb)), dim3(256), 0, st, prep);
+            else hipLaunchKernelGGL(k_prep_queries<DT>, dim3(Bp), dim3(256), 0, st, prep);
+        });
         LAUNCHCHK();
     }
 

@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void k_read_probe(const uint4* __restrict__ p,
 // stores the query is split as hi + lo in bf16, so that the scan can use bf16 MFMA), with an all-zero
 // k-block behind the last one, plus its inverse norm (fp32 and fp64).  Also resets the per-query threshold and presets the
 // survivor count to the number of rows of the sparsest scan pass, which keeps every row.
-// One workgroup per padded query slot; slots >= B become all-zero queries that never pass a filter.
+// Slots >= B become all-zero queries that never pass a filter.
 //
 // It takes as long as a launch does (3 to 5 us), and the first scan pass needs of it only what a workgroup can make of the
 // queries itself.  So where that pass has variants that read the queries as given (FIRST in k_scan_direct.h and k_scan_gemv.h)
@@ -201,81 +201,125 @@ __device__ __forceinline__ void load_query8(const float* row, int e0, int d, flo
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = in ? v[i] : 0.f;
 }
-// All NT lanes of a workgroup call it; red has a word per wavefront.
-template <int DT, int NT>
-__device__ __forceinline__ void prep_query(const PrepArgs& A, int b, double* red) {
-    const int tid = threadIdx.x, dpad = A.nkb * KB, nkb = A.nkb, Bpad = A.Bpad, B = A.B;
-    uint16_t* qop = A.qop;
-    double ssq = 0.0;
-    for (int c8 = tid; c8 < nkb * 8; c8 += NT) {
-        float v[8];
-        const float* row = A.q + (int64_t)(b < B ? b : 0) * A.d;
-        if (A.aligned) load_query8<true>(row, c8 * 8, b < B ? A.d : 0, v);
-        else load_query8<false>(row, c8 * 8, b < B ? A.d : 0, v);
-        int kb = c8 >> 3, c = c8 & 7;
-        if (DT == 0) {
-            // fp32 store: keep the value; operand = bf16 hi + bf16 lo
-            uint16_t hi[8], lo[8];
+// Chunk c8 (eight consecutive elements) of query b, rounded to the store's type (h: 16-bit types, two to a word) and widened again; slots >= B are all-zero.
+template <int DT>
+__device__ __forceinline__ void prep_values(const PrepArgs& A, int b, int c8, float (&v)[8], uint32_t (&h)[4]) {
+    const float* row = A.q + (int64_t)(b < A.B ? b : 0) * A.d;
+    if (A.aligned) load_query8<true>(row, c8 * 8, b < A.B ? A.d : 0, v);
+    else load_query8<false>(row, c8 * 8, b < A.B ? A.d : 0, v);
+    if constexpr (DT != 0) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                hi[i] = f2bf16_rne(v[i]);
-                lo[i] = f2bf16_rne(v[i] - bf16_to_f(hi[i]));
-                ssq += (double)v[i] * (double)v[i];
+        for (int i = 0; i < 4; ++i) {
+            h[i] = DT == 1 ? cvt_pk_bf16(v[2 * i], v[2 * i + 1]) : f2f16_rne(v[2 * i]) | (uint32_t)f2f16_rne(v[2 * i + 1]) << 16;
+            const uint16_t lo = (uint16_t)h[i], hi = (uint16_t)(h[i] >> 16);
+            v[2 * i] = DT == 1 ? bf16_to_f(lo) : f16_to_f(lo);
+            v[2 * i + 1] = DT == 1 ? bf16_to_f(hi) : f16_to_f(hi);
+        }
+    }
+}
+__device__ __forceinline__ double prep_squares(const float (&v)[8]) {
+    double ssq = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ssq += (double)v[i] * (double)v[i];
+    return ssq;
+}
+template <int DT>
+__device__ __forceinline__ void prep_store(const PrepArgs& A, int b, int c8, const float (&v)[8], const uint32_t (&h)[4]) {
+    const int kb = c8 >> 3, c = c8 & 7, Bpad = A.Bpad;
+    if constexpr (DT == 0) {
+        // fp32 store: operand = bf16 hi + bf16 lo
+        if (A.operands) {
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                hi[i] = cvt_pk_bf16(v[2 * i], v[2 * i + 1]);
+                lo[i] = cvt_pk_bf16(v[2 * i] - bf16_to_f((uint16_t)hi[i]), v[2 * i + 1] - bf16_to_f((uint16_t)(hi[i] >> 16)));
             }
             const int64_t u = (kb * 2 + (c >> 2)) * 2;                  // heads; remainders in the row behind
-            uint4 ph, pl;
-            ph.x = hi[0] | ((uint32_t)hi[1] << 16); ph.y = hi[2] | ((uint32_t)hi[3] << 16);
-            ph.z = hi[4] | ((uint32_t)hi[5] << 16); ph.w = hi[6] | ((uint32_t)hi[7] << 16);
-            pl.x = lo[0] | ((uint32_t)lo[1] << 16); pl.y = lo[2] | ((uint32_t)lo[3] << 16);
-            pl.z = lo[4] | ((uint32_t)lo[5] << 16); pl.w = lo[6] | ((uint32_t)lo[7] << 16);
-            if (A.operands) {
-                *reinterpret_cast<uint4*>(qop + qop_row(u, Bpad) + qop_in_row(b, c & 3)) = ph;
-                *reinterpret_cast<uint4*>(qop + qop_row(u + 1, Bpad) + qop_in_row(b, c & 3)) = pl;
-            }
-        } else {
-            uint16_t h[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                h[i] = DT == 1 ? f2bf16_rne(v[i]) : f2f16_rne(v[i]);
-                v[i] = DT == 1 ? bf16_to_f(h[i]) : f16_to_f(h[i]);
-                ssq += (double)v[i] * (double)v[i];
-            }
-            uint4 pk;
-            pk.x = h[0] | ((uint32_t)h[1] << 16); pk.y = h[2] | ((uint32_t)h[3] << 16);
-            pk.z = h[4] | ((uint32_t)h[5] << 16); pk.w = h[6] | ((uint32_t)h[7] << 16);
-            *reinterpret_cast<uint4*>(qop + qop_row(kb * 2 + (c >> 2), Bpad) + qop_in_row(b, c & 3)) = pk;
+            *reinterpret_cast<uint4*>(A.qop + qop_row(u, Bpad) + qop_in_row(b, c & 3)) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            *reinterpret_cast<uint4*>(A.qop + qop_row(u + 1, Bpad) + qop_in_row(b, c & 3)) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
         }
-        float* o = A.qf + (int64_t)b * dpad + c8 * 8;
-        *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
-        *reinterpret_cast<float4*>(o + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    } else {
+        *reinterpret_cast<uint4*>(A.qop + qop_row(kb * 2 + (c >> 2), Bpad) + qop_in_row(b, c & 3)) = make_uint4(h[0], h[1], h[2], h[3]);
     }
-    // one all-zero k-block behind the last one: the MFMA scan pairs it with a repeated bank block
-    // when it pads an odd number of k-steps to an even one, and after the last pass its words count the
-    // workgroups of the tail
-    if (tid < 8) *reinterpret_cast<uint4*>(qop + ((int64_t)(DT == 0 ? 2 * nkb : nkb) * Bpad + b) * KB + tid * 8) = make_uint4(0, 0, 0, 0);
+    float* o = A.qf + (int64_t)b * A.nkb * KB + c8 * 8;
+    *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<float4*>(o + 4) = make_float4(v[4], v[5], v[6], v[7]);
+}
+// one all-zero k-block behind the last one: the MFMA scan pairs it with a repeated bank block
+// when it pads an odd number of k-steps to an even one, and after the last pass its words count the
+// workgroups of the tail.  Eight lanes to a query.
+template <int DT>
+__device__ __forceinline__ void prep_zero_block(const PrepArgs& A, int b, int lane) {
+    *reinterpret_cast<uint4*>(A.qop + ((int64_t)(DT == 0 ? 2 * A.nkb : A.nkb) * A.Bpad + b) * KB + lane * 8) = make_uint4(0, 0, 0, 0);
+}
+__device__ __forceinline__ void prep_words(const PrepArgs& A, int b, double ssq) {
+    const bool live = b < A.B;
+    const double inv = live ? 1.0 / sqrt(ssq) : 0.0;
+    A.invq64[b] = inv;
+    A.invq[b] = (float)inv;
+    // "No threshold yet" is a finite floor below every reachable value (the scan compares
+    // dot * invnorm, which lies in [-|q|, |q|]); empty slots get a threshold their all-zero query
+    // can never reach.  Finite values keep the scan's arithmetic free of inf - inf.
+    A.thr[b] = live ? (float)(-2.0 / inv) : 1.0f;
+    *slot_counter(A.cnt, b) = live ? A.cnt0 : 0u;     // rows the sparsest pass will write without counting
+    A.flags[b] = 0u;                 // per-query status of this retrieve (bit 0: a survivor list overflowed)
+}
+// One query, by all NT lanes of a workgroup; red has a word per wavefront.  Without STORE only its norm and its words.
+template <int DT, int NT, bool STORE = true>
+__device__ __forceinline__ void prep_query(const PrepArgs& A, int b, double* red) {
+    const int tid = threadIdx.x;
+    double ssq = 0.0;
+    for (int c8 = tid; c8 < A.nkb * 8; c8 += NT) {
+        float v[8];
+        uint32_t h[4];
+        prep_values<DT>(A, b, c8, v, h);
+        ssq += prep_squares(v);
+        if constexpr (STORE) prep_store<DT>(A, b, c8, v, h);
+    }
+    if (tid < 8) prep_zero_block<DT>(A, b, tid);
     ssq = wave_total_d(ssq);
     if ((tid & 63) == 0) red[tid >> 6] = ssq;
     __syncthreads();
     if (tid == 0) {
-        bool live = b < B;
         ssq = 0.0;
 #pragma unroll
         for (int w = 0; w < NT / 64; ++w) ssq += red[w];
-        double inv = live ? 1.0 / sqrt(ssq) : 0.0;
-        A.invq64[b] = inv;
-        A.invq[b] = (float)inv;
-        // "No threshold yet" is a finite floor below every reachable value (the scan compares
-        // dot * invnorm, which lies in [-|q|, |q|]); empty slots get a threshold their all-zero query
-        // can never reach.  Finite values keep the scan's arithmetic free of inf - inf.
-        A.thr[b] = live ? (float)(-2.0 / inv) : 1.0f;
-        *slot_counter(A.cnt, b) = live ? A.cnt0 : 0u;     // rows the sparsest pass will write without counting
-        A.flags[b] = 0u;                 // per-query status of this retrieve (bit 0: a survivor list overflowed)
+        prep_words(A, b, ssq);
     }
 }
+// A query to a workgroup.
 template <int DT>
 __global__ __launch_bounds__(256) void k_prep_queries(PrepArgs A) {
     __shared__ double red[4];
     prep_query<DT, 256>(A, (int)blockIdx.x, red);
+}
+// The first Bpad workgroups take a query each, for its norm and its words, and the others 16 queries' part of the k dimension each, which they
+// write as whole fragments.  (A query's own pieces of a fragment are 16 bytes, 256 apart.)  Both read the queries, so with whole rounds of
+// groups they are on the same XCD.
+constexpr int PREP_SLICE = 16;           // chunks of 16 queries to a workgroup
+inline int prep_fragment_workgroups(int Bpad, int nkb) { return Bpad + Bpad / 16 * ((nkb * 8 + PREP_SLICE - 1) / PREP_SLICE); }
+// Which of the two, in us, a query to a workgroup / this: fp32, 64 queries of 1024 2.9, 2.6; 256 of 1024 4.3, 3.7; 512 of 4096 9.4, 6.7; 1024 of
+// 2048 9.7, 6.9, of 4096 17.7, 10.0 (9.5 when a query's operands lay together).  16 bits, whose queries are rounded twice so: 256 of 4096 5.8, 6.8; 1024 of
+// 1024 5.9, 6.3, of 2048 7.0, 7.1, of 4096 11.6, 9.3 (8.2).
+inline bool prep_by_fragments(bool f32, int Bpad, int nkb) { return f32 || (int64_t)Bpad * nkb >= 1024 * 48; }
+template <int DT>
+__global__ __launch_bounds__(256) void k_prep_fragments(PrepArgs A) {
+    __shared__ double red[4];
+    const int i = (int)blockIdx.x, j = i >> 3, tid = threadIdx.x;
+    if (i < A.Bpad) {                                                   // uniform
+        prep_query<DT, 256, false>(A, A.Bpad % 128 == 0 ? ((i & 7) + 8 * (j >> 4)) * 16 + (j & 15) : i, red);
+        return;
+    }
+    static_assert(16 * PREP_SLICE == 256, "a chunk to a lane");
+    const uint32_t groups = (uint32_t)A.Bpad / 16, k = (uint32_t)(i - A.Bpad);
+    const int b = (int)(k % groups) * 16 + (tid & 15), c8 = (int)(k / groups) * PREP_SLICE + (tid >> 4);
+    if (c8 < A.nkb * 8) {
+        float v[8];
+        uint32_t h[4];
+        prep_values<DT>(A, b, c8, v, h);
+        prep_store<DT>(A, b, c8, v, h);
+    }
 }
 
 }  // namespace evk

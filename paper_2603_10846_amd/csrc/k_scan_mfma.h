@@ -75,13 +75,6 @@ __device__ __forceinline__ void mfma_settle() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Two fp32 values rounded to bf16 (round to nearest even) and packed, a first: one v_cvt_pk_bf16_f32.
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b) {
-    typedef __attribute__((ext_vector_type(2))) float f32x2_t;
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-    const f32x2_t v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
 
 // hi/lo split of two fp32 values for the matrix cores: returns the packed bf16 heads and leaves the
 // (exactly representable) remainders a - head(a), b - head(b) in ra, rb.
