@@ -3,7 +3,10 @@ wait states that another instruction would need before it touches one.  Checked 
 instruction and the settling wait nothing but matrix instructions names an accumulator's register; and no vector instruction
 writes an operand of one in the two wait states before it.
 Query blocks go straight to LDS by assembly too, which sets M0 and counts on the order of the loads.  Checked: no value that the
-compiler put into M0 is used behind such a load, and enough loads follow the last of a step's before the wait that lets them through."""
+compiler put into M0 is used behind such a load, and enough loads follow the last of a step's before the wait that lets them through.
+Where operands pass through rings (16-bit stores, 128 or 256 queries to a tile) the waits count on how many loads follow, each group of wavefronts
+for itself.  Checked: the k-loop has the reads, loads, waits and barriers that its schedule rests on, in their order, and no other memory
+operation and no other wait for one."""
 import os
 import re
 import subprocess
@@ -16,6 +19,40 @@ def _registers(operands):
     for kind, lo, hi, one_kind, one in re.findall(r"\b([va])\[(\d+):(\d+)\]|\b([va])(\d+)\b", operands):
         out |= {(kind, i) for i in range(int(lo), int(hi) + 1)} if kind else {(one_kind, int(one))}
     return out
+
+
+def _memory_events(body):
+    """Runs of: r LDS reads, L loads to LDS, g other memory operations, M matrix instructions; Wn waits for memory, B barriers (behind a wait for all LDS
+    reads)."""
+    events, reads_pending = [], False
+    for line in map(str.strip, body.splitlines()):
+        if not line or line[0] in ";.":
+            continue
+        op = line.split()[0]
+        if op.startswith("global_load_lds"):
+            e = "L"
+        elif op.startswith(("global_", "buffer_", "scratch_", "flat_")):
+            e = "g"
+        elif op.startswith("v_mfma"):
+            e = "M"
+        elif op.startswith("ds_read"):
+            e, reads_pending = "r", True
+        elif op == "s_barrier":
+            e = "B?" if reads_pending else "B"
+        elif op == "s_waitcnt":
+            if "lgkmcnt(0)" in line:
+                reads_pending = False
+            vm = re.search(r"vmcnt\((\d+)\)", line)
+            if not vm:
+                continue
+            e = f"W{vm.group(1)}"
+        else:
+            continue
+        if events and events[-1][0] == e and e in "rLgM":
+            events[-1][1] += 1
+        else:
+            events.append([e, 1])
+    return " ".join(e if n == 1 else f"{e}x{n}" for e, n in events)
 
 
 def test_nothing_touches_an_accumulator_in_flight(tmp_path):
@@ -71,4 +108,20 @@ def test_nothing_touches_an_accumulator_in_flight(tmp_path):
             elif asm and op == "s_waitcnt" and behind is not None:
                 assert behind >= int(re.fullmatch(r"vmcnt\((\d+)\)", operands).group(1)), f"{name}: {operands} {behind} operations behind the loads"
     assert direct > 0
+
+    rings = 0
+    for name, body in kernels:
+        dt, mq, wq = map(int, re.match(r"_ZN3evk11k_scan_mfmaILi(\d)ELi(\d)ELi(\d)E", name).groups())
+        if dt == 0 or mq * wq < 8:
+            continue
+        rings += 1
+        # Half a query block is 16 * mq * wq fragments' rows of 64 bytes, loaded by four wavefronts, 1 KB at a time; a bank block is 32 KB: eight loads.
+        # The query group waits, at the end of half i + 1, until only the loads of half i + 3 are left: q of them.  The bank group waits, in the second
+        # half of block m + 1, until only those of block m + 2 are: eight.  At the start two halves and two blocks are asked for.
+        q, fetch, multiply = mq * wq // 4, f"rx{mq + 4} Lx{mq * wq // 4 + 4}", f"B Mx{4 * mq} W{mq * wq // 4} B"
+        events = _memory_events(body)
+        assert events.count(f"Lx{2 * q} W{q} Lx16 W8 B ") == 1, f"{name}: {events}"
+        assert events.count(f" B {fetch} {multiply} B {fetch} W8 {multiply} ") == 1, f"{name}: {events}"
+        assert events.count("L") == 4, f"{name}: {events}"
+    assert rings == 20
     os.remove(out)
