@@ -191,7 +191,7 @@ __global__ __launch_bounds__(1024) void k_exact_select(uint64_t* __restrict__ su
     Selected<SURV_CAP / 1024> s;
     const bool normed = inv64 > 0.0 && inv64 < (double)INFINITY;           // uniform
     const uint32_t found = *slot_counter(cnt, b);
-    const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, true, sh, s,
+    const uint32_t raw = select_keys(list, slot_counter(cnt, b), k1, EXACT_KEY_MARGIN, false, keep_max, SEL_EXACT, false, sh, s,
                                      [&](int i, uint32_t at) __attribute__((always_inline)) { if (normed && found <= (uint32_t)SURV_CAP) list[at] = s.key[i]; });
     if (!normed) {
         for (int i = tid; i < k1; i += 1024) list[i] = pack_key(-INFINITY, i);  // (with more than one pass the bank holds more rows than a pool)

@@ -87,10 +87,10 @@ __device__ __forceinline__ uint32_t group_prefix_u32(uint32_t x, uint32_t* part,
 enum { SEL_PASS = 0, SEL_FINAL = 1, SEL_EXACT = 2 };
 constexpr int SEL_DIGIT = 11, SEL_BINS = 1 << SEL_DIGIT;
 constexpr int SEL_FIRST = 1024;          // bins of the first round
-constexpr int SEL_SMALL = 128;
+constexpr int SEL_SMALL = 128, SEL_FEW = 32;
 struct SelectLds {
     __align__(16) uint32_t hist[SEL_BINS];
-    uint64_t small[SEL_SMALL];
+    uint64_t small[SEL_SMALL], pivot;
     uint32_t most[16], least[16];
     uint32_t part_a[16], part_b[16], count, nsmall, kept[2], digit, need;
 };
@@ -240,19 +240,25 @@ __device__ __forceinline__ void select_keys(int n, int slots, int k1, float marg
         for (int i = 0; i < K; ++i)
             if (i * 1024 < slots && key[i] != 0 && in(i)) sh.small[atomicAdd(&sh.nsmall, 1u)] = key[i];
         __syncthreads();
-        static_assert(SEL_SMALL == 128, "two keys to a lane");
-        uint64_t mine = sh.small[lane];
-        uint32_t rank = 0;
-        uint64_t at = 0;
-        for (int half = 0;; ++half) {                                        // uniform
-#pragma unroll 8
-            for (uint32_t j = 0; j < in_bin; ++j) rank += sh.small[j] > mine;
-            at = __builtin_amdgcn_ballot_w64((uint32_t)(lane + 64 * half) < in_bin && rank == need - 1);           // keys are distinct
-            if (at != 0 || half == 1) break;
-            mine = sh.small[lane + 64];
-            rank = 0;
+        // A few of them every wavefront ranks for itself; many (near-duplicates) are ranked once, eight lanes to a key, and the pivot is handed round.
+        // (All 16 wavefronts over 96 copies of a row: the exhaustive call's first selection 11.6 us, 8.6 so.)
+        if (in_bin > (uint32_t)SEL_FEW) {                                    // uniform
+            static_assert(SEL_SMALL * 8 == 1024, "eight lanes to a key");
+            const uint64_t mine = sh.small[tid >> 3];
+            uint32_t rank = 0;
+            for (uint32_t j = tid & 7; j < in_bin; j += 8) rank += sh.small[j] > mine;
+            rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, 0xb1, 0xf, 0xf, true);             // quad_perm 1,0,3,2
+            rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, 0x4e, 0xf, 0xf, true);             // quad_perm 2,3,0,1
+            rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, 0x141, 0xf, 0xf, true);            // row_half_mirror
+            if ((uint32_t)(tid >> 3) < in_bin && rank == need - 1) sh.pivot = mine;                        // keys are distinct
+            __syncthreads();
+            return sh.pivot;
         }
-        const int src = __builtin_ctzll(at | 1ull << 63);
+        const uint64_t mine = sh.small[lane];
+        uint32_t rank = 0;
+#pragma unroll 8
+        for (uint32_t j = 0; j < in_bin; ++j) rank += sh.small[j] > mine;
+        const int src = __builtin_ctzll(__builtin_amdgcn_ballot_w64((uint32_t)lane < in_bin && rank == need - 1) | 1ull << 63);
         return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), src) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, src);
     };
     // First round: bins of equal width in similarity between the largest and the smallest one (differences and
@@ -283,8 +289,8 @@ __device__ __forceinline__ void select_keys(int n, int slots, int k1, float marg
         }
     }
     // By digits of 11 bits, from the highest bit on which two keys differ.  Here one lane finds the bin for all: 16 wavefronts that each read 2048
-    // bins take longer than two barriers (7000 near-duplicates among 40,000 rows, one query, the selection after the first pass 17.6 -> 14.9 us,
-    // of the exhaustive call 19.0 -> 16.2).  It clears the bins for the next round.
+    // bins take longer than two barriers (7000 near-duplicates among 40,000 rows, one query, the selection after the first pass 17.6 -> 14.9 us; 14.1
+    // with many keys ranked once, that of the exhaustive call 19.0 -> 14.9).  It clears the bins for the next round.
     auto find_digit = [&](uint32_t& in_bin) __attribute__((always_inline)) {
         __syncthreads();
         const uint2 c = reinterpret_cast<const uint2*>(sh.hist)[tid];
