@@ -21,8 +21,9 @@
 // matrix instructions ready: parts switched off in turn, 1M x 1536 bf16 with 1024 queries, densest pass, 10^6 cycles: fragments and
 // matrix instructions alone 27.2, with queries loaded 30.4, with bank rows too 35.2, with the epilogue 37.6; taking turns 29.3, 29.9,
 // 31.2, 32.5.  The latency of the bank is hidden either way (rows from HBM, from L2 or none at all: the same cycles).
-// What bounds it now is the power limit: without the epilogue the same pass takes 4 % fewer cycles and as long, at a clock of
-// 1.79 instead of 1.87 GHz, and without loads of the bank it takes 12 % less, at 1.95.  Densest pass of 1M x 1536, 1024 queries 2470 ->
+// What bounds it with 1024 queries is the power limit: without the epilogue that pass takes 4 % fewer cycles and as long, at a clock of
+// 1.79 instead of 1.87 GHz, and without loads of the bank, too, it takes 12 % less, at 1.95.  With 256 queries the same parts take time: 1M x 1024
+// 420 us, 386 without the epilogue, 327 without bank loads too, the matrix cores busy for 62, 69 and 76 % of the cycles.  Densest pass of 1M x 1536, 1024 queries 2470 ->
 // 2230 us (1390 TFLOP/s, on other cards up to 1450; the vendor's product of 16384 x 16384 x 8192 1540), 1M x 1024, 256 queries 460 -> 430.
 // One rotation of the k-loop for all workgroups of an XCD when several share its bank tiles: 2150 -> 2130 us.  128 queries (whole calls): 1.1M x 4096 fp16
 // 1592 -> 1546 us, 1M x 1024 bf16 391 -> 385, 200,000 x 768 134 -> 129, 1M x 64 100 -> 88, 300,007 x 384 92.0, 92.0.
