@@ -484,7 +484,7 @@ __global__ __launch_bounds__(64 * WQ * WR, 2) void k_scan_mfma(const void* __res
             // double buffered instead.  The global loads of bank pieces (first quarter of the slots) and the LDS stores (second and third)
             // issue in the shadow of the MFMAs instead of forming a period without any.  (Behind the barrier, in the last quarter, the loads
             // of all wavefronts met the first fragments' reads: 32 queries, 300,007 x 384 fp16, densest pass 44.6 us, 42.8 now; 64, 196,608 x
-            // 1024 bf16 69.3, 67.8.)
+            // 1024 bf16 69.3, 67.8.  In kernel traces of whole calls the first of them takes 41 us, masked 46.)
             // The scheduler is fenced per slot to keep this order (left alone it hoists the reads).
             // On entry af and bfr[0] hold the step's first fragments, fetched by the previous step or, for
             // the first step of a tile, by the tile loop (the last step of a tile fetches nothing: the
